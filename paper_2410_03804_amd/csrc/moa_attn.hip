@@ -4,6 +4,7 @@
 //
 //   k_attn_generic   any dtype / head_dim <= 256: one wavefront per (sequence, query, head),
 //                    64 keys per step, exact online softmax with wavefront shuffles.
+//   k_attn_f32       fp32, head_dim 64 / 128: 16 query rows per workgroup on the fp32 matrix instructions.
 //   k_attn_fused     bf16, head_dim 64 / 128, short key ranges: a workgroup owns 32 query rows and the
 //                    whole key range (its waves split the keys and are combined through LDS), so there
 //                    are no partial results and no second launch.  Described at the kernel.
@@ -642,6 +643,147 @@ __global__ __launch_bounds__(64 * NW) void k_attn_fused(AttnGroup grp, int nrb)
         atomicOr(a.dev_status, MOA_DEV_EMPTY_KEYS);
 }
 
+// ------------------------------------------------------------------ fp32, whole key range in one workgroup
+// One workgroup owns 16 query rows of one (sequence, KV head) -- heads of the group times tree tokens, as above -- and
+// all of its keys; wavefront w takes the 16-key tiles w, w + 8, ... and the eight (max, sum, accumulator) triples are
+// combined through LDS in wavefront order.  Everything is v_mfma_f32_16x16x4 (fp32 products and sums): S^T = K Q^T puts a
+// query in each lane column, and its result layout (lane (li, kg) holds keys 4 kg .. 4 kg + 3 of query li) is the operand
+// layout of O^T += V^T P^T with key 4 kg + j in slot j, so the probabilities never leave their registers.  K and V come
+// straight from global memory, the next tile's behind this tile's arithmetic.  At the sizes fp32 is used at it is bound by
+// latency: one workgroup's chain is the launch.  It replaced k_attn_generic there (a serial dot product per lane and a
+// shuffle per key: 20 us per core at 16 rows x 72 keys x 64).
+constexpr int F32_NW = 8;
+
+template <int DH>
+constexpr size_t attn_f32_lds() { return ((size_t)F32_NW * (DH / 4) * 64 + 2 * F32_NW * 16) * sizeof(float); }
+
+template <int DH>
+__global__ __launch_bounds__(64 * F32_NW) void k_attn_f32(AttnGroup grp, int nrb)
+{
+    constexpr int NW = F32_NW, NKS = DH / 16, NDB = DH / 16, NV = 4 * NDB, VPW = NV / NW;
+    extern __shared__ __attribute__((aligned(16))) float fsm[];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, kg = lane >> 4;
+    const int u = (int)blockIdx.x / nrb, rb = (int)blockIdx.x - u * nrb;
+    const int call = u / grp.nbg, bg = u - call * grp.nbg;
+    const AttnArgs &a = grp.a[call];
+    const int b = bg / a.Hkv, g = bg - b * a.Hkv;
+    const int G = a.H / a.Hkv, RG = G * a.Mq, W = (a.mask_rows + 63) >> 6;
+    const float scale = 1.0f / sqrtf((float)DH);
+
+    int rho = rb * 16 + li;                          // this lane's query column
+    const bool row_ok = rho < RG;
+    if (!row_ok) rho = RG - 1;
+    const int mrow = rho / G, hh = rho - mrow * G;
+    const int64_t qoff = (((int64_t)b * a.Mq + mrow) * a.H + g * G + hh) * DH;
+    f32x4 qf[NKS];
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const f32x4 *)((const float *)a.q + qoff + 16 * ks + 4 * kg);
+
+    const int len = clamp_len(a.len[b], a.P_cap, tid == 0 ? a.dev_status : nullptr);
+    const int Mt = a.mask ? a.Mt : 0;
+    const int ntc = (len + 15) / 16, nt = ntc + (Mt + 15) / 16;
+    const float *kc = (const float *)a.kcache + (int64_t)bg * a.P_cap * DH, *vc = (const float *)a.vcache + (int64_t)bg * a.P_cap * DH;
+    const float *ktp = (const float *)a.ktree + (int64_t)bg * a.tree_cap * DH, *vtp = (const float *)a.vtree + (int64_t)bg * a.tree_cap * DH;
+    const uint64_t *mbits = a.mask ? a.mask + ((int64_t)b * a.mask_rows + a.mask_row0 + mrow) * W : nullptr;
+
+    f32x4 kf[2][NKS];
+    float vf[2][NDB][4];
+    auto fetch = [&](int set, int i) {
+        const bool tree = i >= ntc;
+        const int base = 16 * (tree ? i - ntc : i), last = (tree ? Mt : len) - 1;
+        const float *ks_ = tree ? ktp : kc, *vs_ = tree ? vtp : vc;
+        const float *kp = ks_ + (int64_t)min(base + li, last) * DH + 4 * kg;      // rows past the end repeat the last one
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) kf[set][ks] = *(const f32x4 *)(kp + 16 * ks);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float *vp = vs_ + (int64_t)min(base + 4 * kg + j, last) * DH + li;
+#pragma unroll
+            for (int d = 0; d < NDB; ++d) vf[set][d][j] = vp[16 * d];
+        }
+    };
+    f32x4 acc[NDB];
+#pragma unroll
+    for (int d = 0; d < NDB; ++d) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float mrun = -INFINITY, lrun = 0.f;
+    auto tile = [&](int set, int i) {
+        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[set][ks][j], qf[ks][j], s, 0, 0, 0);
+        const bool tree = i >= ntc;
+        const int base = 16 * (tree ? i - ntc : i), nvalid = (tree ? Mt : len) - base;     // >= 1
+        uint32_t vis = 0xffffu;
+        if (tree) vis &= (uint32_t)(mbits[base >> 6] >> (base & 63));
+        if (nvalid < 16) vis &= (1u << nvalid) - 1u;
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            s[v] = ((vis >> (4 * kg + v)) & 1u) ? s[v] * scale : -INFINITY;
+            tmax = fmaxf(tmax, s[v]);
+        }
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+        const float mnew = fmaxf(mrun, tmax), msafe = (mnew == -INFINITY) ? 0.f : mnew;
+        const float corr = expf(mrun - msafe);
+        float psum = 0.f;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) { s[v] = expf(s[v] - msafe); psum += s[v]; }
+        psum += __shfl_xor(psum, 16);
+        psum += __shfl_xor(psum, 32);
+        lrun = lrun * corr + psum;
+        mrun = mnew;
+#pragma unroll
+        for (int d = 0; d < NDB; ++d) {
+            acc[d] *= corr;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[set][d][j], s[j], acc[d], 0, 0, 0);
+        }
+    };
+    if (wave < nt) {
+        fetch(0, wave);
+        for (int i = wave; i < nt; i += 2 * NW) {
+            if (i + NW < nt) fetch(1, i + NW);
+            tile(0, i);
+            if (i + NW >= nt) break;
+            if (i + 2 * NW < nt) fetch(0, i + 2 * NW);
+            tile(1, i + NW);
+        }
+    }
+
+    float *red = fsm, *msh = red + NW * NV * 64, *lsh = msh + NW * 16;       // [NW][NV][64], [NW][16] twice
+    if (kg == 0) {
+        msh[wave * 16 + li] = mrun;
+        lsh[wave * 16 + li] = lrun;
+    }
+#pragma unroll
+    for (int d = 0; d < NDB; ++d)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[(wave * NV + 4 * d + v) * 64 + lane] = acc[d][v];
+    __syncthreads();
+    float wgt[NW], mstar = -INFINITY, lsum = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { wgt[w] = msh[w * 16 + li]; mstar = fmaxf(mstar, wgt[w]); }
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        wgt[w] = (wgt[w] == -INFINITY) ? 0.f : expf(wgt[w] - mstar);
+        lsum += wgt[w] * lsh[w * 16 + li];
+    }
+    const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
+    float *orow = (float *)a.out + qoff;
+#pragma unroll
+    for (int t = 0; t < VPW; ++t) {
+        const int v = wave * VPW + t;               // accumulator value v: head_dim 16 (v / 4) + 4 kg + v % 4
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) sum += wgt[w] * red[(w * NV + v) * 64 + lane];
+        if (row_ok) orow[16 * (v >> 2) + 4 * kg + (v & 3)] = sum * inv;
+    }
+    if (wave == 0 && kg == 0 && row_ok && lsum == 0.f && a.empty_is_error && a.dev_status)
+        atomicOr(a.dev_status, MOA_DEV_EMPTY_KEYS);
+}
+
 // DH/8 lanes per (sequence, query, head) row, 8 head_dim values (one 16-byte load per slice) per lane; a
 // workgroup of 256 threads folds 2048/DH rows
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
@@ -754,6 +896,40 @@ static hipError_t launch_attn_generic(const AttnArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
+static bool attn_f32_ok(const AttnArgs &a)
+{
+    auto al = [](const void *p) { return (((uintptr_t)p) & 15) == 0; };
+    return a.dtype == DT_F32 && (a.dh == 64 || a.dh == 128) && al(a.q) && al(a.kcache) && al(a.ktree);
+}
+
+template <int DH>
+static hipError_t launch_f32_as(const AttnGroup &grp, int nrb, unsigned grid, hipStream_t stream)
+{
+    constexpr size_t lds = attn_f32_lds<DH>();
+    static bool raised[16] = {};
+    hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_f32<DH>, lds);
+    if (e != hipSuccess) return e;
+    prof_begin(K_ATTN_F32, stream);
+    MOA_KLAUNCH((k_attn_f32<DH>), dim3(grid), dim3(64 * F32_NW), lds, stream, grp, nrb);
+    prof_end(stream);
+    return hipGetLastError();
+}
+
+// n = 1 or 2 calls of identical shape (B, Mq, H, Hkv, dh)
+static hipError_t launch_attn_f32(const AttnArgs *calls, int n, hipStream_t stream)
+{
+    const AttnArgs &a = calls[0];
+    AttnGroup grp;
+    grp.a[0] = calls[0];
+    grp.a[1] = calls[n - 1];
+    grp.nbg = a.B * a.Hkv;
+    grp.ncalls = n;
+    const int nrb = ((a.H / a.Hkv) * a.Mq + 15) / 16;
+    const int64_t grid = (int64_t)n * grp.nbg * nrb;
+    if (grid > 0x7fffffff) return hipErrorInvalidValue;
+    return a.dh == 128 ? launch_f32_as<128>(grp, nrb, (unsigned)grid, stream) : launch_f32_as<64>(grp, nrb, (unsigned)grid, stream);
+}
+
 static bool attn_split_ok(const AttnArgs &a, int P_cap_geo)
 {
     return mfma_ok(a.dtype, a.dh, &a) && a.ws && (((uintptr_t)a.ws) & 15) == 0 &&
@@ -848,6 +1024,7 @@ hipError_t launch_attn(const AttnArgs &a_in, hipStream_t stream)
     if (!tree_window(a)) return hipErrorInvalidValue;
     if (mfma_ok(a.dtype, a.dh, &a) && want_fused(a)) return launch_attn_fused(&a, 1, stream);
     if (attn_split_ok(a, a.P_cap)) return launch_attn_split(&a, 1, stream);
+    if (attn_f32_ok(a)) return launch_attn_f32(&a, 1, stream);
     return launch_attn_generic(a, stream);
 }
 
@@ -863,6 +1040,7 @@ hipError_t launch_attn_pair(const AttnArgs &a0_in, const AttnArgs &a1_in, hipStr
         if (!want_fused(a0) && !want_fused(a1) && attn_split_ok(a0, cap) && attn_split_ok(a1, cap))
             return launch_attn_split(both, 2, stream);
     }
+    if (same && attn_f32_ok(a0) && attn_f32_ok(a1)) return launch_attn_f32(both, 2, stream);
     hipError_t e = launch_attn(a0, stream);
     if (e != hipSuccess) return e;
     return launch_attn(a1, stream);

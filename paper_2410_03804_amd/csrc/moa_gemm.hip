@@ -1,6 +1,6 @@
 // Projections Y = X W^T (W row-major [N, K]) for the Q/K/V/O projections of LSA, CA and
-// tree verification.  Three kernels:
-//   k_linear_generic     any dtype / shape, fp32 FMA, LDS-tiled 64x64 (fp32 path and odd shapes)
+// tree verification.  The kernels of this file (fp32 tensors and bf16 shapes outside their tiles: moa_gemm_f32.hip):
+//   k_linear_generic     any dtype / shape / alignment, fp32 FMA, LDS-tiled 64x64 (what no other kernel can read)
 //   k_linear_skinny_bf16 <=64 rows per tile: weight streaming, HBM-bound.  Operands go straight
 //                        from global memory into MFMA 16x16x32 fragments (both are K-contiguous,
 //                        which is exactly the fragment layout), the four waves of a workgroup
@@ -755,7 +755,7 @@ static bool aligned16(const void *p) { return (((uintptr_t)p) & 15) == 0; }
 
 // which kernel a call gets; decided from shapes and alignment alone, so that launch_linear knows beforehand whether
 // the launch can carry what LinArgs::carry_sum names
-enum LinPath { P_TILED, P_SPLITK, P_SKINNY, P_EACH, P_GENERIC };
+enum LinPath { P_TILED, P_SPLITK, P_SKINNY, P_F32, P_EACH, P_GENERIC };
 
 static LinPath linear_path(int dtype, const LinArgs &a, int *nq_out)
 {
@@ -770,7 +770,7 @@ static LinPath linear_path(int dtype, const LinArgs &a, int *nq_out)
         fast = a.seg[s].N % 32 == 0 && aligned16(a.seg[s].W) && aligned16(st.dst) &&
                (st.mode == StoreSpec::ROW ? st.ld % 8 == 0 : st.dh % 8 == 0);
     }
-    if (!fast) return own_x ? P_EACH : P_GENERIC;
+    if (!fast) return linear_f32_ok(dtype, a) ? P_F32 : own_x ? P_EACH : P_GENERIC;
     bool all128 = true, all64 = true;
     int ntot = 0;
     for (int s = 0; s < a.nseg; ++s) {
@@ -985,6 +985,10 @@ static hipError_t launch_linear_impl(int dtype, const LinArgs &a, hipStream_t st
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         return finish_splitk(a, ka, ntot, stream, fused);
+    }
+    if (path == P_F32) {
+        *rode = a.rider_units > 0;
+        return launch_linear_f32(dtype, a, stream);
     }
     if (path == P_EACH) return launch_linear_each(dtype, a, stream);
     if (path == P_SKINNY) {
