@@ -102,13 +102,9 @@ size_t lsa_ws_bytes(const moa_shape_t *s, int64_t T)
 {
     const int64_t tc = T < LSA_CHUNK ? T : LSA_CHUNK, ob = T < LSA_OBLOCK ? T : LSA_OBLOCK;
     const size_t eq = (size_t)s->lsa_q_heads * s->head_dim, ekv = (size_t)s->lsa_kv_heads * s->head_dim;
-    // the projections of a short chunk (the first and the last one can be) stream the weights and keep partial sums
-    const int64_t tail = T % LSA_CHUNK;
     // the output projection may carry the memory's folded K/V projections as two more segments (draft step)
     size_t lin = linear_workspace_bytes(s->dtype, ob, (int)eq, (int)(eq + 2 * (size_t)s->n_kv_heads * s->head_dim));
     lin = max2(lin, linear_workspace_bytes(s->dtype, ob, (int)eq, (int)eq));
-    lin = max2(lin, linear_workspace_bytes(s->dtype, tc * s->n_layers, s->d_lsa_in, (int)(eq + 2 * ekv)));
-    if (tail) lin = max2(lin, linear_workspace_bytes(s->dtype, tail * s->n_layers, s->d_lsa_in, (int)(eq + 2 * ekv)));
     return align256((size_t)tc * s->n_layers * (eq + 2 * ekv) * esize(s->dtype)) + align256((size_t)ob * eq * esize(s->dtype)) +
            align256(lin);
 }
@@ -345,8 +341,7 @@ static void lsa_chunk_args(const moa_shape_t *shape, const void *hs, int64_t t0,
     la->R = tc * L;
     la->K = d_in;
     la->ldx = d_in;
-    la->ws = b.lin_ws;
-    la->ws_bytes = b.lin_ws_bytes;
+    la->in_order = true;                 // the same Q/K/V bits as the one-kernel form
     *aa = LsaAttnArgs{};
     aa->dtype = shape->dtype;
     auto add = [&](const void *w, int n, int col, const void **ptr, int64_t *ldp) {
@@ -1385,8 +1380,8 @@ static int32_t piece_lsa_append(const moa_step_args_t *a, const StepBufs &bf, vo
 // The step's first projections and an LSA chain that is one pass (at most LSA_CHUNK tokens, or an output-projection
 // block of them in the one-kernel form), with the small kernels riding in launches that do not depend on them:
 //   1. CA query + verification Q/K/V projections  + the step's integer work
-//   2. LSA in one kernel (or its Q/K/V projection) + the pass that adds up launch 1's K slices (the one-kernel form and
-//                                                    the tiled kernel carry it; else that pass is a launch of its own)
+//   2. LSA in one kernel (or its Q/K/V projection) + the pass that adds up launch 1's K slices, if it has any (the
+//                                                    one-kernel form carries it; else that pass is a launch of its own)
 //   3. (attention over the layers, when apart)     4. LSA W_o (+ the memory's folded K/V)
 // scr2 is the second scratch region: launch 1's partial sums live there while the LSA chain uses the first.
 static int32_t piece_lsa_interleaved(const moa_step_args_t *a, const StepBufs &bf, char *scr, size_t scr_bytes, char *scr2,
@@ -1411,14 +1406,10 @@ static int32_t piece_lsa_interleaved(const moa_step_args_t *a, const StepBufs &b
         LinArgs la;
         LsaAttnArgs aa;
         lsa_chunk_args(sh, a->lsa_hs, 0, T, a->lsa_wq, a->lsa_wk, a->lsa_wv, abar, b, &la, &aa);
-        if (la.nseg) {
-            la.carry_sum = &sum_pair;
-            prof_set_site(S_LSA_QKV);
-            MOA_TRY_HIP(launch_linear(dt, la, st), "lsa: projection");
-        } else {
-            prof_set_site(S_PAIR_QKV);
-            MOA_TRY_HIP(launch_splitk_sum(sum_pair, st), "draft_step: projections");
-        }
+        prof_set_site(S_PAIR_QKV);
+        MOA_TRY_HIP(launch_splitk_sum(sum_pair, st), "draft_step: projections");
+        prof_set_site(S_LSA_QKV);
+        if (la.nseg) MOA_TRY_HIP(launch_linear(dt, la, st), "lsa: projection");
         prof_set_site(S_LSA_ATTN);
         MOA_TRY_HIP(launch_lsa_attn(aa, st), "lsa: attention over layers");
     }
@@ -1644,7 +1635,6 @@ static int32_t two_stream_main(const moa_step_args_t *a, const StepBufs &bf, cha
 
 static int32_t draft_step_concurrent(const moa_step_args_t *a, SideStream *ss)
 {
-    const LinearLeaveRoom share_the_compute_units;
     hipStream_t main = (hipStream_t)a->stream, side = ss->stream;
     const GroupLayout L = group_layout(a->shape, a->B, a->M, a->P_cap, a->ca_P_cap, a->T_lsa);
     char *scr_main = nullptr;
@@ -1746,7 +1736,6 @@ static int32_t two_stream_sa_side_verify(const moa_step_args_t *a, const StepBuf
 // launch started only after the chain, 59 us late).
 static int32_t draft_step_concurrent_sa(const moa_step_args_t *args, const moa_step_args_t *a, SideStream *ss)
 {
-    const LinearLeaveRoom share_the_compute_units;
     hipStream_t main = (hipStream_t)a->stream, side = ss->stream;
     const GroupLayout L = group_layout(a->shape, a->B, a->M, a->P_cap, a->ca_P_cap, a->T_lsa);
     char *scr_main = nullptr;

@@ -119,10 +119,10 @@ __device__ __forceinline__ int64_t store_offset(const StoreSpec &s, int64_t r, i
 
 // ---- optional per-launch timing (hipEvents around single kernels), used by the benchmark only
 enum KernelId {
-    K_TREE_BUILD = 0, K_TREE_ACCEPT, K_APPEND_LEN, K_LIN_GENERIC, K_LIN_SKINNY, K_LIN_SPLITK, K_LIN_REDUCE, K_LIN_TILED, K_SCATTER,
+    K_TREE_BUILD = 0, K_TREE_ACCEPT, K_APPEND_LEN, K_LIN_GENERIC, K_LIN_REDUCE, K_SCATTER,
     K_ATTN_GENERIC, K_ATTN_MFMA, K_ATTN_MERGE, K_LSA_ATTN, K_LSA_ATTN_MFMA, K_STEP_SMALL, K_ATTN_FUSED, K_PROBE_READ, K_PROBE_MFMA,
     K_RMSNORM, K_ROPE, K_SWIGLU, K_ADD_OUT, K_TREE_EXPAND, K_TREE_FINALIZE, K_TOPK_LOGPROB,
-    K_LM_HEAD, K_LM_HEAD_REDUCE, K_TOPK_MERGE, K_MSG_TREE, K_MSG_ACCEPT, K_LIN_SPLITK_CHUNKED, K_LSA_FUSED, K_LSA_FUSED_PK, K_LSA_PACK, K_LSA_FUSED_PK_LEAN, K_LIN_SPLITK_XRES, K_LIN_F32_LATENCY, K_LIN_F32_TILE, K_ATTN_F32, K_COUNT
+    K_LM_HEAD, K_LM_HEAD_REDUCE, K_TOPK_MERGE, K_MSG_TREE, K_MSG_ACCEPT, K_LSA_FUSED, K_LSA_FUSED_PK, K_LSA_PACK, K_LSA_FUSED_PK_LEAN, K_LIN_F32_LATENCY, K_LIN_F32_TILE, K_ATTN_F32, K_LIN_BF16, K_COUNT
 };
 enum SiteId {
     S_NONE = 0, S_TREE_BUILD, S_LSA_QKV, S_LSA_ATTN, S_LSA_OPROJ, S_APPEND_KV, S_APPEND_LEN, S_CA_QPROJ, S_CA_CORE,
@@ -180,9 +180,8 @@ struct LsaAttnArgs {
     void *abar;              // [T, Hq*dh]
 };
 
-// The pass that adds up the K slices of a weight-streaming projection, as data: what launch_linear leaves behind
-// when asked not to launch it (LinArgs::sum_out), what another launch can carry (LinArgs::carry_sum) and what
-// launch_splitk_sum runs.
+// The pass that adds up the K slices of a projection, as data: what launch_linear leaves behind when asked not to launch
+// it (LinArgs::sum_out), what the LSA kernel can carry (LsaFusedCall::carry_sum) and what launch_splitk_sum runs.
 // Rotary position embedding of a decoder layer's queries and draft keys (position = clamped prefix length + depth of
 // the node; the pair (c, c + dh/2) of every head is rotated by position * theta^(-2c/dh), the angle in double
 // precision): everything launch_rope needs, so that a projection can apply it on the way out.
@@ -236,7 +235,7 @@ struct LinArgs {
     int64_t ldx;
     int nseg;
     LinSeg seg[4];
-    void *ws;          // optional scratch for the split-K kernel (linear_workspace_bytes)
+    void *ws;          // optional scratch for the sums of K slices (linear_workspace_bytes); without it K is not cut
     size_t ws_bytes;
     StepSmallArgs rider;   // optional: integer work carried in rider_units spare workgroups of the projection's grid
     int rider_units;       // 0 = none; the work is done when the projection kernel has finished
@@ -255,30 +254,22 @@ struct LinArgs {
     void *epi_out;
     RopeArgs rope;
     NormArgs norm;
-    // The summing pass of an earlier weight-streaming projection, carried in spare workgroups at the front of this
-    // launch's grid: it is done when this launch has finished, and must neither feed this projection nor depend on
-    // it.  Only the tiled kernel carries; on the other paths the pass is launched apart, first.  A host pointer, read
-    // during the call; NULL or blocks == 0 = nothing.
-    const SumArgs *carry_sum;
-    // Weight-streaming path only: do not launch the pass that adds up the K slices but describe it here (blocks = 0
-    // when another kernel ran and nothing is left to do).  The caller has it carried by a later launch or runs
-    // launch_splitk_sum; the partial sums (ws) must stay untouched until then.
+    bool in_order;     // sum along K in one chain of matrix instructions, as the one-kernel LSA does (same bits)
+    // Where K is cut into slices: do not launch the pass that adds them up but describe it here (blocks = 0 when nothing
+    // is left to do).  The caller has it carried by a later launch or runs launch_splitk_sum;
+    // the partial sums (ws) must stay untouched until then.
     SumArgs *sum_out;
 };
 
 // Y_s = X_s W_s^T for up to four weight matrices (one launch on the fast paths; segments usually share X).
 hipError_t launch_linear(int dtype, const LinArgs &a, hipStream_t stream);
-// While an object of this type lives, this thread's projections keep to kernels that leave LDS and registers for a
-// second kernel on the same compute units (the two-stream schedule runs its branches side by side).
-struct LinearLeaveRoom {
-    LinearLeaveRoom();
-    ~LinearLeaveRoom();
-    bool before;
-};
+// the bf16 kernel behind launch_linear (moa_gemm_bf16.hip) and its name by profiling variant
+hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused, int *splits);
+const char *linear_bf16_name(int variant);
 // the single-precision kernels behind launch_linear (moa_gemm_f32.hip): operands they can read, and the launch
 bool linear_f32_ok(int dtype, const LinArgs &a);
 hipError_t launch_linear_f32(int dtype, const LinArgs &a, hipStream_t stream);
-// scratch the fast weight-streaming path wants for R rows and ntot output features in total (0 = not used)
+// scratch for the sums of K slices of a projection of R rows and ntot output features in total (0 = K is not cut)
 size_t linear_workspace_bytes(int dtype, int64_t R, int K, int ntot);
 
 // dst(store spec) = X, element by element (NULL-weight projections that still change layout)
@@ -333,8 +324,8 @@ hipError_t launch_swiglu(int dtype, const void *gu, int64_t R, int d_ff, void *a
 hipError_t launch_add_out(int dtype, const float *h, const void *t, int64_t n, void *out, hipStream_t stream);
 
 // ---- LSA in one kernel: projection of a token's layer rows, attention over the layers, mean; writes the mean-folded
-// heads abar [T, Hq*dh] (the output projection is a launch of its own, on one row per token).  rider / carry_sum as in
-// LinArgs: work of other calls carried in spare workgroups at the front of the grid.
+// heads abar [T, Hq*dh] (the output projection is a launch of its own, on one row per token).  rider as in LinArgs;
+// carry_sum: the pass over an earlier projection's K slices; both in spare workgroups at the front of the grid.
 struct LsaFusedCall {
     int dtype;
     const void *hs, *wq, *wk, *wv;

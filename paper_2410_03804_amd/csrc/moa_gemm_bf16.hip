@@ -1,0 +1,447 @@
+// Projections Y = X W^T of bf16 tensors on the matrix cores (MFMA 32x32x16), for any number of rows: one kernel,
+// instantiated for the tiles that the path's row counts and widths ask for, and the rule that picks one.
+//
+// A workgroup owns a tile of rows x features and, as a rule, all of K: no partial sums, no second launch.  It walks K in
+// tiles of 64; both operands come from global memory straight into LDS (128-byte row pieces, no registers, no LDS store
+// instructions) through rings of several stages, so that loads of the next SX - 1 and SW - 1 k tiles are in flight
+// behind the current one.  One barrier per k tile: it stands three quarters into the tile's MFMAs, when the last operands
+// of the tile have been read, so that the first operands of the next one arrive behind the last quarter.  With WK > 1 the
+// wavefronts form groups that take every WK-th k tile each, with rings of their own, and add up through LDS at the end:
+// for few rows, where one group's chain of barrier, operand read and MFMA is longer than the memory needs.
+//
+// What bounds it: for few rows the weights (60 x 4096 x 8192: 17.9 us = 3.7 TB/s and no summing pass, where K slices with
+// fp32 partial sums took 21.0 + 4.0; 8 x 4096 x 128256: 162 us = 6.5 TB/s against 196 + 5), for many the way from L2 to
+// LDS, which one compute unit fills at 50 - 60 GB/s here (loads alone 61 us, MFMAs alone 58, both 79 at 1024 x 4096 x
+// 10240, where 128 x 128 tiles with everything waited for at each barrier took 135; 19200 x 2048 x 4096: 302 against 388).
+#include "moa_common.h"
+#include "moa_tree_device.h"
+
+#include <math.h>
+
+namespace moa {
+
+struct GemmArgs {
+    LinArgs a;
+    int tile_begin[5];   // first feature tile of each segment; [nseg] = all
+    int tiles_per_xcd;   // feature tiles owned by one XCD
+    int lead_blocks;     // workgroups in front of the projection's own (LinArgs::rider, padded to the XCD count)
+    int row_tiles;
+    int splits;          // slices of K; with more than one the sums go to `part` for a second pass
+    float *part;         // [64-row tiles][splits][64][ntot]
+    int ntot;            // features of all segments
+    int gated;           // EPI_SWIGLU inside the kernel: 32-feature blocks alternate between the two matrices
+};
+
+// 64 lanes x 16 bytes from base + off (each lane its own) to 1 KB of LDS at `lds`.  Written out because the compiler, which
+// knows what the builtin writes, waits for every such load in flight in front of any LDS read that might alias it: the
+// loads of later k tiles would be waited for with the current one's.  base must be the product of scalar arithmetic (a
+// scalar written by a vector instruction may be read too early by this one, and nobody inserts the wait states here).
+__device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t off, const void *base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base));
+}
+template <int N>
+__device__ __forceinline__ void wait_loads_and_barrier()
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+template <int WR, int WF, int MR, int NF, int SX, int SW, int WK>
+__global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(GemmArgs ga)
+{
+    constexpr int BM = 32 * MR * WR, BN = 32 * NF * WF, BK = 64, NWV = WR * WF;   // NWV: wavefronts of one K group
+    constexpr int NXI = BM / 8 / NWV, NWI = (BN / 8 + NWV - 1) / NWV;             // load instructions per wavefront and k tile
+    constexpr uint32_t XST = BM * BK * 2, WST = BN * BK * 2;                      // bytes per stage
+    constexpr int ALLOW = (SX - 2) * (NXI + NWI) + (SW > SX ? NWI : 0);
+    static_assert(BM % (8 * NWV) == 0 && SW >= SX && SX >= 2, "");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+
+    const LinArgs &a = ga.a;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = (tid >> 6) % NWV, kgrp = __builtin_amdgcn_readfirstlane((tid >> 6) / NWV);
+    if ((int)blockIdx.x < ga.lead_blocks) {
+        if ((int)blockIdx.x < a.rider_units && tid < 64)
+            step_small_unit(a.rider, (int)blockIdx.x, (int32_t *)smem, (int32_t *)smem + MOA_MAX_TREE);
+        return;
+    }
+    // Workgroups are dealt to the 8 XCDs round-robin, and each XCD has its own L2: an XCD gets a contiguous group of
+    // feature tiles for all row tiles, so that its slice of W is fetched into its L2 once.
+    const int bx = (int)blockIdx.x - ga.lead_blocks, xcd = bx & 7, j = bx >> 3;
+    const int ftile = xcd * ga.tiles_per_xcd + j % ga.tiles_per_xcd;
+    if (ftile >= ga.tile_begin[a.nseg]) return;
+    const int rest = j / ga.tiles_per_xcd, rt = rest % ga.row_tiles, split = rest / ga.row_tiles;
+    int s = 0;
+    while (s + 1 < a.nseg && ftile >= ga.tile_begin[s + 1]) ++s;
+    const int tile_features = ga.gated ? BN / 2 : BN;
+    const int n0 = (ftile - ga.tile_begin[s]) * tile_features, N = a.seg[s].N, K = a.K;
+    const int64_t r0 = (int64_t)rt * BM;
+    const int wfi = wave % WF, wri = wave / WF;
+    const int64_t ldx = a.seg[s].X ? a.seg[s].ldx : a.ldx;
+    const int nk = K / (BK * WK * ga.splits);      // k tiles of this K group in this slice: every WK-th one
+    const int64_t kbyte0 = ((int64_t)split * nk * WK + kgrp) * (BK * 2);
+    const char *xbase = (const char *)(a.seg[s].X ? a.seg[s].X : a.X) + r0 * ldx * 2 + kbyte0;
+
+    // This lane's 16-byte pieces as offsets from the bases, for the first k tile.  An instruction moves eight tile rows of
+    // 128 bytes into 1 KB of LDS; piece c of row r lives at position c ^ (r / 2 & 7) of its row, which spreads the operand
+    // reads of 16 rows over all banks.  W rows are permuted inside blocks of 32 so that the 16 results a lane gets from
+    // a block are 16 consecutive features.
+    uint32_t xoff[NXI], woff[NWI], xdst[NXI], wdst[NWI];
+    const char *wbase[NWI];
+    const int lrow = lane >> 3, lpos = lane & 7;
+#pragma unroll
+    for (int i = 0; i < NXI; ++i) {
+        const int g = __builtin_amdgcn_readfirstlane(wave) + NWV * i, row = 8 * g + lrow;
+        const int64_t rmax = a.R - 1 - r0;                       // rows past the end repeat the last one; never stored
+        const int rr = row < rmax ? row : (int)rmax;
+        xoff[i] = (uint32_t)(rr * ldx * 2 + 16 * (lpos ^ ((row >> 1) & 7)));
+        xdst[i] = (uint32_t)(g * 1024);
+    }
+#pragma unroll
+    for (int i = 0; i < NWI; ++i) {
+        int g = __builtin_amdgcn_readfirstlane(wave) + NWV * i;
+        if (g > BN / 8 - 1) g = BN / 8 - 1;                      // the same rows once more into the same place
+        const int row = 8 * g + lrow, p = row & 31;
+        int blk = g >> 2, sel = s;
+        if (ga.gated) { sel = blk & 1; blk >>= 1; }
+        int f = 32 * blk + 16 * ((p >> 2) & 1) + 4 * (p >> 3) + (p & 3);
+        if (n0 + f > N - 1) f = N - 1 - n0;
+        wbase[i] = (const char *)a.seg[sel].W + (int64_t)n0 * K * 2 + kbyte0;
+        woff[i] = (uint32_t)f * (uint32_t)K * 2u + (uint32_t)(16 * (lpos ^ ((row >> 1) & 7)));
+        wdst[i] = SX * XST + (uint32_t)(g * 1024);
+    }
+    const uint32_t ring = (uint32_t)kgrp * (SX * XST + SW * WST);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem + ring;
+    uint32_t xfill = 0, wfill = 0;                 // stage (byte offset) the next load goes to
+    auto issue_x = [&](int kt) {                   // tiles past the last repeat it (nobody reads them)
+        const int64_t ko = (int64_t)(kt < nk ? kt : nk - 1) * (WK * BK * 2);
+#pragma unroll
+        for (int i = 0; i < NXI; ++i) lds_dma16(lds0 + xdst[i] + xfill, xoff[i], xbase + ko);
+        xfill = xfill + XST == SX * XST ? 0 : xfill + XST;
+    };
+    auto issue_w = [&](int kt) {
+        const int64_t ko = (int64_t)(kt < nk ? kt : nk - 1) * (WK * BK * 2);
+#pragma unroll
+        for (int i = 0; i < NWI; ++i) lds_dma16(lds0 + wdst[i] + wfill, woff[i], wbase[i] + ko);
+        wfill = wfill + WST == SW * WST ? 0 : wfill + WST;
+    };
+#pragma unroll
+    for (int i = 0; i < SW; ++i) {
+        if (i >= SW - SX) issue_x(i - (SW - SX));
+        issue_w(i);
+    }
+
+    f32x16 acc[NF][MR];
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+        for (int jj = 0; jj < MR; ++jj)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][jj][e] = 0.f;
+
+    uint32_t koff[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) koff[ks] = (uint32_t)(l32 * 128 + 16 * ((2 * ks + half) ^ ((l32 >> 1) & 7)));
+    const uint32_t xrd = ring + (uint32_t)(wri * (32 * MR) * 128), wrd = ring + (uint32_t)(SX * XST + wfi * (32 * NF) * 128);
+    uint32_t xcur = 0, wcur = 0;                   // stages being read
+    bf16x8 af[2][NF], bf[2][MR];
+    auto read = [&](int set, int ks) {
+        const char *wp = smem + (wrd + wcur + koff[ks]), *xp = smem + (xrd + xcur + koff[ks]);
+#pragma unroll
+        for (int i = 0; i < NF; ++i) af[set][i] = *(const bf16x8 *)(wp + 4096 * i);
+#pragma unroll
+        for (int i = 0; i < MR; ++i) bf[set][i] = *(const bf16x8 *)(xp + 4096 * i);
+    };
+    auto multiply = [&](int set) {
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+#pragma unroll
+            for (int jj = 0; jj < MR; ++jj)
+                acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[set][i], bf[set][jj], acc[i][jj], 0, 0, 0);
+    };
+    auto advance = [&] {
+        xcur = xcur + XST == SX * XST ? 0 : xcur + XST;
+        wcur = wcur + WST == SW * WST ? 0 : wcur + WST;
+    };
+    wait_loads_and_barrier<ALLOW>();
+    read(0, 0);
+    int kt = 0;
+    for (; kt < nk - SX; ++kt) {
+        read(1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(0);
+        read(0, 2);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(1);
+        read(1, 3);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(0);
+        if (NF * MR >= 8) __builtin_amdgcn_sched_barrier(0);
+        wait_loads_and_barrier<ALLOW>();           // tile kt + 1 is in LDS for everybody, nobody reads tile kt any more
+        advance();
+        read(0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(1);
+        issue_x(kt + SX);
+        issue_w(kt + SW);
+    }
+    for (; kt < nk; ++kt) {
+        read(1, 1);
+        multiply(0);
+        read(0, 2);
+        multiply(1);
+        read(1, 3);
+        multiply(0);
+        if (kt + 1 < nk) {
+            wait_loads_and_barrier<0>();
+            advance();
+            read(0, 0);
+        }
+        multiply(1);
+    }
+
+    if (WK > 1) {                                  // the K groups' sums, added up in group order
+        constexpr int PER = NF * MR * 16 * 64;
+        float *red = (float *)smem;
+        wait_loads_and_barrier<0>();
+        if (kgrp > 0) {
+#pragma unroll
+            for (int i = 0; i < NF; ++i)
+#pragma unroll
+                for (int jj = 0; jj < MR; ++jj)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        red[((kgrp - 1) * NWV + wave) * PER + ((i * MR + jj) * 16 + e) * 64 + lane] = acc[i][jj][e];
+        }
+        __syncthreads();
+        if (kgrp > 0) return;
+#pragma unroll
+        for (int g = 0; g < WK - 1; ++g)
+#pragma unroll
+            for (int i = 0; i < NF; ++i)
+#pragma unroll
+                for (int jj = 0; jj < MR; ++jj)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        acc[i][jj][e] += red[(g * NWV + wave) * PER + ((i * MR + jj) * 16 + e) * 64 + lane];
+    }
+
+    // acc[i][jj][v]: feature 32 i + 16 half + v of the wavefront's, row 32 jj + l32
+#pragma unroll
+    for (int jj = 0; jj < MR; ++jj) {
+        const int64_t r = r0 + wri * (32 * MR) + 32 * jj + l32;
+        if (r >= a.R) continue;
+        if (ga.splits > 1) {
+            float *p = ga.part + (((r >> 6) * ga.splits + split) * 64 + (r & 63)) * ga.ntot;
+            int col = 0;
+            for (int q = 0; q < s; ++q) col += a.seg[q].N;
+#pragma unroll
+            for (int i = 0; i < NF; ++i) {
+                const int n = n0 + wfi * (32 * NF) + 32 * i + 16 * half;
+                if (n >= N) continue;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *(f32x4 *)(p + col + n + 4 * q) = f32x4{acc[i][jj][4 * q], acc[i][jj][4 * q + 1], acc[i][jj][4 * q + 2], acc[i][jj][4 * q + 3]};
+            }
+            continue;
+        }
+        auto store16 = [&](bf16_t *d, const float (&v)[16]) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                u32x4 pk;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) pk[e] = pack_bf16x2(v[8 * q + 2 * e], v[8 * q + 2 * e + 1]);
+                *(u32x4 *)(d + 8 * q) = pk;
+            }
+        };
+        if (NF % 2 == 0 && ga.gated) {             // silu(gate) * up, both through the storage type first
+#pragma unroll
+            for (int i = 0; i + 1 < NF; i += 2) {
+                const int n = n0 + wfi * (16 * NF) + 16 * i + 16 * half;
+                if (n >= N) continue;
+                float v[16];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float g = bf2f(f2bf(acc[i][jj][e]));
+                    v[e] = g / (1.0f + __expf(-g)) * bf2f(f2bf(acc[i + (NF > 1)][jj][e]));
+                }
+                store16((bf16_t *)a.epi_out + r * N + n, v);
+            }
+            continue;
+        }
+        const int64_t rp = store_row_part(a.seg[s].st, r);
+        if (rp < 0) continue;
+#pragma unroll
+        for (int i = 0; i < NF; ++i) {
+            const int n = n0 + wfi * (32 * NF) + 32 * i + 16 * half;
+            if (n >= N) continue;
+            float v[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = acc[i][jj][e];
+            if (a.epi == LinArgs::EPI_ADD_F32) {
+                const float *h = a.epi_res + r * N + n;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) v[e] = h[e] + bf2f(f2bf(v[e]));
+                store16((bf16_t *)a.epi_out + r * N + n, v);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {       // eight features never straddle a head
+                    u32x4 pk;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) pk[e] = pack_bf16x2(v[8 * q + 2 * e], v[8 * q + 2 * e + 1]);
+                    *(u32x4 *)((bf16_t *)a.seg[s].st.dst + rp + store_feat_part(a.seg[s].st, n + 8 * q)) = pk;
+                }
+            }
+        }
+    }
+}
+
+// The instantiated tiles: wavefronts along rows and features, 32-wide blocks per wavefront along rows and features, stages
+// of the activation and the weight ring, K groups; then microseconds per k tile of the workgroup's (64 WK columns) with
+// one workgroup on a compute unit, with a second one on up to half of them, and with two on all (0: its LDS holds one),
+// measured over 1 .. 4096 rows, K 2048 .. 14336 and 4096 .. 128256 features.
+#define MOA_GEMM_TILES(T)                                     \
+    T(0, 1, 1, 1, 1, 5, 5, 2, 0.25f, 0.40f, 0.40f)            \
+    T(1, 1, 1, 1, 1, 2, 3, 4, 0.55f, 0.66f, 0.66f)            \
+    T(2, 1, 1, 1, 2, 3, 3, 2, 0.45f, 0.74f, 0.74f)            \
+    T(3, 2, 1, 1, 1, 3, 4, 2, 0.42f, 0.75f, 0.75f)            \
+    T(4, 2, 2, 1, 1, 4, 6, 1, 0.27f, 0.33f, 0.46f)            \
+    T(5, 2, 2, 1, 2, 3, 3, 2, 0.88f, 0.f, 0.f)                \
+    T(6, 4, 2, 1, 2, 4, 4, 1, 0.55f, 0.f, 0.f)                \
+    T(7, 4, 1, 1, 5, 4, 4, 1, 0.72f, 0.f, 0.f)                \
+    T(8, 4, 2, 2, 2, 3, 4, 1, 0.90f, 0.f, 0.f)                \
+    T(9, 8, 1, 1, 5, 3, 3, 1, 1.12f, 0.f, 0.f)                \
+    T(10, 4, 2, 2, 4, 2, 2, 1, 1.55f, 0.f, 0.f)               \
+    T(11, 4, 2, 1, 1, 3, 4, 2, 0.82f, 0.f, 0.f)               \
+    T(12, 4, 2, 2, 3, 2, 3, 1, 1.25f, 0.f, 0.f)
+
+struct GemmTile {
+    int bm, bn, threads, wk;
+    size_t lds;
+    bool gated;          // pairs of feature blocks in one wavefront: can apply a gated activation
+    float us1, us_mid, us2;
+};
+#define MOA_GEMM_INFO(id, WR, WF, MR, NF, SX, SW, WK, US1, USM, US2)                                                            \
+    {32 * MR * WR, 32 * NF * WF, 64 * WR * WF * WK, WK, (size_t)(SX * 32 * MR * WR + SW * 32 * NF * WF) * 128 * WK, NF % 2 == 0, US1, USM, US2},
+static const GemmTile kTiles[] = {MOA_GEMM_TILES(MOA_GEMM_INFO)};
+
+struct GemmPlan { int tile, splits; };
+
+// The tile, and into how many slices K is cut, by an estimate of the time: rounds of workgroups over 256 compute units at
+// the measured time per k tile, or the weights at 5.8 TB/s, whichever is longer; slices cost a pass over their sums.
+// Against the best tile of each of 191 measured shapes the choice is 1 % slower on average.  What it comes to: up to 32
+// rows the 32-row tiles; up to some hundred the 64-row ones; with more, the largest tile that still gives every compute
+// unit one (1024 x 4096: 256 x 160 for 10240 features, 77.6 us against 98 - 108 with the tiles next to it, 256 x 128 for
+// 8192); slices only for a long K with few features (60 x 14336 x 4096: four, 30 us against 68).  A pass of its own behind
+// an unsplit projection (`pass_us`) counts against not splitting, since the sum over slices does that work on the way.
+static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi, bool in_order)
+{
+    GemmPlan best = {0, 1};
+    int ntot = 0;
+    for (int s = 0; s < nseg; ++s) ntot += n_seg[s];
+    float best_us = 3.4e38f;
+    const float stream_us = 6.f + 2.f * (float)K * (float)ntot / 5.8e6f;
+    for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
+        const GemmTile &t = kTiles[i];
+        if (in_order ? t.wk > 1 : ((t.bm == 32) != (R <= 32) || K % (64 * t.wk) != 0)) continue;
+        int64_t tiles = 0;
+        for (int s = 0; s < nseg; ++s) tiles += (n_seg[s] + t.bn - 1) / t.bn;
+        tiles *= (R + t.bm - 1) / t.bm;
+        for (int splits = 1; splits <= 4; splits *= 2) {
+            if (splits > 1 && (in_order || R > 192 || ntot % 64 || K % (64 * t.wk * splits) || K / (64 * t.wk * splits) < 8)) break;
+            const int64_t n = tiles * splits;
+            float per;                             // k-tile times of one compute unit
+            if (t.us2 > 0.f) {
+                const int64_t rest = n % 512;
+                per = (float)(n / 512) * t.us2;
+                if (rest) per += rest <= 256 ? t.us1 : rest <= 384 ? t.us_mid : t.us2;
+            } else {
+                per = (float)((n + 255) / 256) * t.us1;
+            }
+            const float busy_us = 5.f + per * (float)(K / (64 * t.wk * splits));
+            float us = busy_us > stream_us ? busy_us + 0.1f * stream_us : stream_us + 0.1f * busy_us;
+            if (splits > 1) us += (epi == LinArgs::EPI_ROPE ? 8.f : 5.f) + (float)R * (float)ntot * (float)splits * 8.f / 3.5e6f;
+            else if (epi == LinArgs::EPI_ROPE || epi == LinArgs::EPI_ADD_NORM || (epi == LinArgs::EPI_SWIGLU && !t.gated)) us += 5.f;
+            if (us < best_us) {
+                best_us = us;
+                best = {i, splits};
+            }
+        }
+    }
+    return best;
+}
+
+static size_t partial_bytes(int64_t R, int ntot, int splits)
+{
+    return splits > 1 ? (size_t)((R + 63) / 64) * splits * 64 * (size_t)ntot * sizeof(float) : 0;
+}
+
+// (for one segment; several make about the same plan, and one that needs more room than there is is not cut)
+size_t linear_workspace_bytes(int dtype, int64_t R, int K, int ntot)
+{
+    if (dtype != DT_BF16 || R < 1 || R > 192 || K % 128 || ntot % 64) return 0;
+    size_t most = 0;
+    for (int epi : {(int)LinArgs::EPI_NONE, (int)LinArgs::EPI_ADD_NORM, (int)LinArgs::EPI_SWIGLU}) {
+        const size_t n = partial_bytes(R, ntot, plan_gemm(R, K, &ntot, 1, epi, false).splits);
+        if (n > most) most = n;
+    }
+    return most;
+}
+
+// One launch.  *fused: it applied a.epi; *splits > 1: the sums of that many K slices are in a.ws, to be added up.
+hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused, int *splits)
+{
+    int ntot = 0, n_seg[4] = {};
+    bool all64 = true;
+    for (int s = 0; s < a.nseg; ++s) {
+        n_seg[s] = a.seg[s].N;
+        ntot += a.seg[s].N;
+        all64 = all64 && a.seg[s].N % 64 == 0;
+    }
+    GemmPlan p = plan_gemm(a.R, a.K, n_seg, a.nseg, a.epi, a.in_order);
+    if (p.splits > 1 && !(all64 && a.ws && a.ws_bytes >= partial_bytes(a.R, ntot, p.splits) && (((uintptr_t)a.ws) & 15) == 0)) p.splits = 1;
+    const GemmTile &t = kTiles[p.tile];
+    GemmArgs ga;
+    ga.a = a;
+    ga.splits = *splits = p.splits;
+    ga.part = (float *)a.ws;
+    ga.ntot = ntot;
+    ga.gated = a.epi == LinArgs::EPI_SWIGLU && t.gated && p.splits == 1;
+    *fused = ga.gated || (a.epi == LinArgs::EPI_ADD_F32 && p.splits == 1);
+    int ft = 0;
+    for (int s = 0; s < a.nseg; ++s) {
+        ga.tile_begin[s] = ft;
+        if (!ga.gated) ft += (a.seg[s].N + t.bn - 1) / t.bn;
+        else if (s == 0) ft = (2 * a.seg[0].N + t.bn - 1) / t.bn;
+    }
+    for (int s = a.nseg; s < 5; ++s) ga.tile_begin[s] = ft;
+    ga.tiles_per_xcd = (ft + 7) / 8;
+    ga.row_tiles = (int)((a.R + t.bm - 1) / t.bm);
+    ga.lead_blocks = (a.rider_units + 7) & ~7;      // a multiple of the XCD count: the tile mapping keeps its phase
+    const int64_t blocks = ga.lead_blocks + (int64_t)8 * ga.tiles_per_xcd * ga.row_tiles * ga.splits;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    hipError_t e = hipSuccess;
+    static bool raised[sizeof(kTiles) / sizeof(kTiles[0])][16] = {};
+    switch (p.tile) {
+#define MOA_GEMM_LAUNCH(id, WR, WF, MR, NF, SX, SW, WK, US1, USM, US2)                                                              \
+    case id:                                                                                                                   \
+        e = raise_lds_limit_once(raised[id], (const void *)k_linear_bf16<WR, WF, MR, NF, SX, SW, WK>, t.lds);                  \
+        if (e != hipSuccess) return e;                                                                                         \
+        prof_begin(K_LIN_BF16 + 64 * (id + 1), stream);                                                                        \
+        MOA_KLAUNCH((k_linear_bf16<WR, WF, MR, NF, SX, SW, WK>), dim3((unsigned)blocks), dim3(t.threads), t.lds, stream, ga);  \
+        break;
+        MOA_GEMM_TILES(MOA_GEMM_LAUNCH)
+    }
+    prof_end(stream);
+    return hipGetLastError();
+}
+
+// the kernel's name as a profiler prints it
+const char *linear_bf16_name(int variant)
+{
+    static const char *const names[] = {
+#define MOA_GEMM_NAME(id, WR, WF, MR, NF, SX, SW, WK, US1, USM, US2) "k_linear_bf16<" #WR ", " #WF ", " #MR ", " #NF ", " #SX ", " #SW ", " #WK ">",
+        MOA_GEMM_TILES(MOA_GEMM_NAME)};
+    return variant >= 1 && variant <= (int)(sizeof(names) / sizeof(names[0])) ? names[variant - 1] : "k_linear_bf16";
+}
+
+}  // namespace moa

@@ -1,0 +1,81 @@
+"""GPU parity of the bf16 projection kernel at the edges of its tiles: row counts around each tile height, feature counts
+that leave part of the last tile empty, fewer k tiles than the load rings have stages, K cut into slices, and the gated
+activation and the residual applied inside the kernel (moa_mlp_block) on ragged sizes."""
+import numpy as np
+import pytest
+import torch
+
+import moa_inputs as mi
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def G():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util
+    return gpu_util
+
+
+@pytest.fixture(scope="module")
+def moa(G):
+    import paper_2410_03804_amd as m
+    return m
+
+
+CASES = [
+    (1, 128, 32),            # two k tiles, fewer than any ring's stages
+    (32, 256, 4128),         # 32-row tiles, ragged last feature tile
+    (7, 384, 16416),         # K groups of two only, many tiles
+    (16, 512, 20000),        # four K groups (K in 256s), two workgroups per compute unit
+    (32, 640, 31904),        # pairs of feature blocks, half a tile at the end
+    (33, 128, 4096),
+    (64, 1152, 10272),       # 64 x 64 tiles, half a tile at the end
+    (61, 2048, 28704),       # 64 x 128
+    (65, 384, 8192),
+    (64, 12288, 2048),       # K in slices
+    (129, 12288, 1024),      # the same, three 64-row pieces
+    (192, 640, 4128),
+    (193, 256, 8224),
+    (300, 896, 6176),
+    (257, 1024, 18464),      # two row tiles of 256, one row in the second
+    (1000, 640, 10272),      # 256-row tiles, ragged everywhere
+    (2049, 512, 8224),
+]
+
+
+@pytest.mark.parametrize("R,K,N", CASES)
+def test_gemm_tile_edges(G, moa, R, K, N):
+    print(f"[case] linear bf16 R={R} K={K} N={N}", flush=True)
+    g = torch.Generator().manual_seed(R + K + N)
+    x = torch.randn(R, K, generator=g).bfloat16()
+    w = (torch.randn(N, K, generator=g) / K ** 0.5).bfloat16()
+    y = torch.full((R + 1, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(max(moa.linear_workspace_bytes(moa.BF16, R, K, N), 256), dtype=torch.uint8, device="cuda")
+    moa.linear(x.cuda(), w.cuda(), y[:R], ws)
+    torch.cuda.synchronize()
+    assert torch.isnan(y[R]).all(), "rows past the end are not written"
+    # fp32 on the GPU by the library routine: sums of K exact products, error K eps of order-1 results; one bf16 rounding
+    # of a value up to 5 sigma (2^-9 of it = 1e-2) bounds the difference, and its rms is 2^-9 / sqrt(3)
+    want = x.cuda().float() @ w.cuda().float().t()
+    diff = (y[:R].float() - want).abs()
+    assert diff.max().item() <= 2.0 ** -8 * want.abs().max().item()
+    assert (diff.norm() / want.norm()).item() <= 2.0 ** -9
+
+
+@pytest.mark.parametrize("R,d,d_ff", [(7, 512, 96), (33, 256, 2080), (64, 1024, 7200), (100, 512, 608), (260, 384, 1056)])
+def test_mlp_block_ragged_sizes(G, moa, oracle, R, d, d_ff):
+    rng = np.random.default_rng(R + d + d_ff)
+    q = lambda a: mi.quantize(a.astype(np.float32), "bf16")
+    x, res = q(rng.standard_normal((R, d))), q(0.5 * rng.standard_normal((R, d)))
+    g = q(1.0 + 0.1 * rng.standard_normal(d))
+    wg, wu, wd = (q(rng.standard_normal(s) / np.sqrt(s[1])) for s in ((d_ff, d), (d_ff, d), (d, d_ff)))
+    print(f"[case] mlp_block R={R} d={d} d_ff={d_ff}", flush=True)
+    out = torch.full((R, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(max(moa.mlp_block_workspace_bytes(moa.BF16, R, d, d_ff), 256), dtype=torch.uint8, device="cuda")
+    dev = [G.dev(a, "bf16") for a in (x, res, g, wg, wu, wd)]
+    moa.mlp_block(moa.BF16, dev[0], dev[1], *dev[2:], 1e-5, out, ws)
+    torch.cuda.synchronize()
+    want = oracle.mlp_block(x, res, g, wg, wu, wd, 1e-5)
+    G.check_close(G.host(out), want, "bf16", f"mlp_block[{R}x{d}x{d_ff}]", residual_stream=True)
