@@ -14,6 +14,7 @@
 // LDS, which one compute unit fills at 50 - 60 GB/s here (loads alone 61 us, MFMAs alone 58, both 79 at 1024 x 4096 x
 // 10240, where 128 x 128 tiles with everything waited for at each barrier took 135; 19200 x 2048 x 4096: 302 against 388).
 #include "moa_common.h"
+#include "moa_gemm_device.h"
 #include "moa_tree_device.h"
 
 #include <math.h>
@@ -32,33 +33,14 @@ struct GemmArgs {
     int gated;           // EPI_SWIGLU inside the kernel: 32-feature blocks alternate between the two matrices
 };
 
-// 64 lanes x 16 bytes from base + off (each lane its own) to 1 KB of LDS at `lds`.  Written out because the compiler, which
-// knows what the builtin writes, waits for every such load in flight in front of any LDS read that might alias it: the
-// loads of later k tiles would be waited for with the current one's.  base must be the product of scalar arithmetic (a
-// scalar written by a vector instruction may be read too early by this one, and nobody inserts the wait states here).
-__device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t off, const void *base)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base));
-}
-template <int N>
-__device__ __forceinline__ void wait_loads_and_barrier()
-{
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
-
 template <int WR, int WF, int MR, int NF, int SX, int SW, int WK>
 __global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(GemmArgs ga)
 {
-    constexpr int BM = 32 * MR * WR, BN = 32 * NF * WF, BK = 64, NWV = WR * WF;   // NWV: wavefronts of one K group
-    constexpr int NXI = BM / 8 / NWV, NWI = (BN / 8 + NWV - 1) / NWV;             // load instructions per wavefront and k tile
-    constexpr uint32_t XST = BM * BK * 2, WST = BN * BK * 2;                      // bytes per stage
-    constexpr int ALLOW = (SX - 2) * (NXI + NWI) + (SW > SX ? NWI : 0);
-    static_assert(BM % (8 * NWV) == 0 && SW >= SX && SX >= 2, "");
+    using Loop = GemmLoop<WR, WF, MR, NF, SX, SW, WK>;
+    constexpr int BM = Loop::BM, BN = Loop::BN;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-
     const LinArgs &a = ga.a;
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
-    const int wave = (tid >> 6) % NWV, kgrp = __builtin_amdgcn_readfirstlane((tid >> 6) / NWV);
+    const int tid = threadIdx.x;
     if ((int)blockIdx.x < ga.lead_blocks) {
         if ((int)blockIdx.x < a.rider_units && tid < 64)
             step_small_unit(a.rider, (int)blockIdx.x, (int32_t *)smem, (int32_t *)smem + MOA_MAX_TREE);
@@ -72,163 +54,25 @@ __global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(GemmArgs ga)
     const int rest = j / ga.tiles_per_xcd, rt = rest % ga.row_tiles, split = rest / ga.row_tiles;
     int s = 0;
     while (s + 1 < a.nseg && ftile >= ga.tile_begin[s + 1]) ++s;
-    const int tile_features = ga.gated ? BN / 2 : BN;
-    const int n0 = (ftile - ga.tile_begin[s]) * tile_features, N = a.seg[s].N, K = a.K;
+    const int n0 = (ftile - ga.tile_begin[s]) * (ga.gated ? BN / 2 : BN), N = a.seg[s].N, K = a.K;
     const int64_t r0 = (int64_t)rt * BM;
-    const int wfi = wave % WF, wri = wave / WF;
     const int64_t ldx = a.seg[s].X ? a.seg[s].ldx : a.ldx;
-    const int nk = K / (BK * WK * ga.splits);      // k tiles of this K group in this slice: every WK-th one
-    const int64_t kbyte0 = ((int64_t)split * nk * WK + kgrp) * (BK * 2);
-    const char *xbase = (const char *)(a.seg[s].X ? a.seg[s].X : a.X) + r0 * ldx * 2 + kbyte0;
-
-    // This lane's 16-byte pieces as offsets from the bases, for the first k tile.  An instruction moves eight tile rows of
-    // 128 bytes into 1 KB of LDS; piece c of row r lives at position c ^ (r / 2 & 7) of its row, which spreads the operand
-    // reads of 16 rows over all banks.  W rows are permuted inside blocks of 32 so that the 16 results a lane gets from
-    // a block are 16 consecutive features.
-    uint32_t xoff[NXI], woff[NWI], xdst[NXI], wdst[NWI];
-    const char *wbase[NWI];
-    const int lrow = lane >> 3, lpos = lane & 7;
-#pragma unroll
-    for (int i = 0; i < NXI; ++i) {
-        const int g = __builtin_amdgcn_readfirstlane(wave) + NWV * i, row = 8 * g + lrow;
-        const int64_t rmax = a.R - 1 - r0;                       // rows past the end repeat the last one; never stored
-        const int rr = row < rmax ? row : (int)rmax;
-        xoff[i] = (uint32_t)(rr * ldx * 2 + 16 * (lpos ^ ((row >> 1) & 7)));
-        xdst[i] = (uint32_t)(g * 1024);
-    }
-#pragma unroll
-    for (int i = 0; i < NWI; ++i) {
-        int g = __builtin_amdgcn_readfirstlane(wave) + NWV * i;
-        if (g > BN / 8 - 1) g = BN / 8 - 1;                      // the same rows once more into the same place
-        const int row = 8 * g + lrow, p = row & 31;
-        int blk = g >> 2, sel = s;
-        if (ga.gated) { sel = blk & 1; blk >>= 1; }
-        int f = 32 * blk + 16 * ((p >> 2) & 1) + 4 * (p >> 3) + (p & 3);
-        if (n0 + f > N - 1) f = N - 1 - n0;
-        wbase[i] = (const char *)a.seg[sel].W + (int64_t)n0 * K * 2 + kbyte0;
-        woff[i] = (uint32_t)f * (uint32_t)K * 2u + (uint32_t)(16 * (lpos ^ ((row >> 1) & 7)));
-        wdst[i] = SX * XST + (uint32_t)(g * 1024);
-    }
-    const uint32_t ring = (uint32_t)kgrp * (SX * XST + SW * WST);
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem + ring;
-    uint32_t xfill = 0, wfill = 0;                 // stage (byte offset) the next load goes to
-    auto issue_x = [&](int kt) {                   // tiles past the last repeat it (nobody reads them)
-        const int64_t ko = (int64_t)(kt < nk ? kt : nk - 1) * (WK * BK * 2);
-#pragma unroll
-        for (int i = 0; i < NXI; ++i) lds_dma16(lds0 + xdst[i] + xfill, xoff[i], xbase + ko);
-        xfill = xfill + XST == SX * XST ? 0 : xfill + XST;
-    };
-    auto issue_w = [&](int kt) {
-        const int64_t ko = (int64_t)(kt < nk ? kt : nk - 1) * (WK * BK * 2);
-#pragma unroll
-        for (int i = 0; i < NWI; ++i) lds_dma16(lds0 + wdst[i] + wfill, woff[i], wbase[i] + ko);
-        wfill = wfill + WST == SW * WST ? 0 : wfill + WST;
-    };
-#pragma unroll
-    for (int i = 0; i < SW; ++i) {
-        if (i >= SW - SX) issue_x(i - (SW - SX));
-        issue_w(i);
-    }
-
-    f32x16 acc[NF][MR];
-#pragma unroll
-    for (int i = 0; i < NF; ++i)
-#pragma unroll
-        for (int jj = 0; jj < MR; ++jj)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][jj][e] = 0.f;
-
-    uint32_t koff[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) koff[ks] = (uint32_t)(l32 * 128 + 16 * ((2 * ks + half) ^ ((l32 >> 1) & 7)));
-    const uint32_t xrd = ring + (uint32_t)(wri * (32 * MR) * 128), wrd = ring + (uint32_t)(SX * XST + wfi * (32 * NF) * 128);
-    uint32_t xcur = 0, wcur = 0;                   // stages being read
-    bf16x8 af[2][NF], bf[2][MR];
-    auto read = [&](int set, int ks) {
-        const char *wp = smem + (wrd + wcur + koff[ks]), *xp = smem + (xrd + xcur + koff[ks]);
-#pragma unroll
-        for (int i = 0; i < NF; ++i) af[set][i] = *(const bf16x8 *)(wp + 4096 * i);
-#pragma unroll
-        for (int i = 0; i < MR; ++i) bf[set][i] = *(const bf16x8 *)(xp + 4096 * i);
-    };
-    auto multiply = [&](int set) {
-#pragma unroll
-        for (int i = 0; i < NF; ++i)
-#pragma unroll
-            for (int jj = 0; jj < MR; ++jj)
-                acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[set][i], bf[set][jj], acc[i][jj], 0, 0, 0);
-    };
-    auto advance = [&] {
-        xcur = xcur + XST == SX * XST ? 0 : xcur + XST;
-        wcur = wcur + WST == SW * WST ? 0 : wcur + WST;
-    };
-    wait_loads_and_barrier<ALLOW>();
-    read(0, 0);
-    int kt = 0;
-    for (; kt < nk - SX; ++kt) {
-        read(1, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(0);
-        read(0, 2);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(1);
-        read(1, 3);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(0);
-        if (NF * MR >= 8) __builtin_amdgcn_sched_barrier(0);
-        wait_loads_and_barrier<ALLOW>();           // tile kt + 1 is in LDS for everybody, nobody reads tile kt any more
-        advance();
-        read(0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(1);
-        issue_x(kt + SX);
-        issue_w(kt + SW);
-    }
-    for (; kt < nk; ++kt) {
-        read(1, 1);
-        multiply(0);
-        read(0, 2);
-        multiply(1);
-        read(1, 3);
-        multiply(0);
-        if (kt + 1 < nk) {
-            wait_loads_and_barrier<0>();
-            advance();
-            read(0, 0);
-        }
-        multiply(1);
-    }
-
-    if (WK > 1) {                                  // the K groups' sums, added up in group order
-        constexpr int PER = NF * MR * 16 * 64;
-        float *red = (float *)smem;
-        wait_loads_and_barrier<0>();
-        if (kgrp > 0) {
-#pragma unroll
-            for (int i = 0; i < NF; ++i)
-#pragma unroll
-                for (int jj = 0; jj < MR; ++jj)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e)
-                        red[((kgrp - 1) * NWV + wave) * PER + ((i * MR + jj) * 16 + e) * 64 + lane] = acc[i][jj][e];
-        }
-        __syncthreads();
-        if (kgrp > 0) return;
-#pragma unroll
-        for (int g = 0; g < WK - 1; ++g)
-#pragma unroll
-            for (int i = 0; i < NF; ++i)
-#pragma unroll
-                for (int jj = 0; jj < MR; ++jj)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e)
-                        acc[i][jj][e] += red[(g * NWV + wave) * PER + ((i * MR + jj) * 16 + e) * 64 + lane];
-    }
+    const int nk = K / (Loop::BK * WK * ga.splits);
+    Loop g;
+    g.set_x((const char *)(a.seg[s].X ? a.seg[s].X : a.X) + r0 * ldx * 2, ldx, a.R - r0);
+    g.set_w(K, N - n0, [&](int blk, int *first) {
+        const int sel = ga.gated ? blk & 1 : s;
+        *first = 32 * (ga.gated ? blk >> 1 : blk);
+        return (const char *)a.seg[sel].W + (int64_t)n0 * K * 2;
+    });
+    if (!g.run(smem, split * nk, nk)) return;
+    f32x16 (&acc)[NF][MR] = g.acc;
+    const int l32 = g.lane & 31, half = g.lane >> 5, wfi = g.wave % WF;
 
     // acc[i][jj][v]: feature 32 i + 16 half + v of the wavefront's, row 32 jj + l32
 #pragma unroll
     for (int jj = 0; jj < MR; ++jj) {
-        const int64_t r = r0 + wri * (32 * MR) + 32 * jj + l32;
+        const int64_t r = r0 + g.wave_row() + 32 * jj + l32;
         if (r >= a.R) continue;
         if (ga.splits > 1) {
             float *p = ga.part + (((r >> 6) * ga.splits + split) * 64 + (r & 63)) * ga.ntot;
@@ -261,8 +105,8 @@ __global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(GemmArgs ga)
                 float v[16];
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    const float g = bf2f(f2bf(acc[i][jj][e]));
-                    v[e] = g / (1.0f + __expf(-g)) * bf2f(f2bf(acc[i + (NF > 1)][jj][e]));
+                    const float t = bf2f(f2bf(acc[i][jj][e]));
+                    v[e] = t / (1.0f + __expf(-t)) * bf2f(f2bf(acc[i + (NF > 1)][jj][e]));
                 }
                 store16((bf16_t *)a.epi_out + r * N + n, v);
             }

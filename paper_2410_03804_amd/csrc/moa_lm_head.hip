@@ -1,11 +1,13 @@
 // Greedy token of the LLM at every tree node: tgt[r] = argmax_v x[r] . W[v] over the vocabulary (Sec. 2.1,
 // y ~ Softmax(LM_head(o)); greedy verification takes the arg max).  The logits are never stored: the head is one
 // pass over its weights ([V, d], 1 GiB at the Llama-3 shape, the largest single read of a decoding cycle), each
-// workgroup reduces its 128 tokens to one (logit, id) pair per row and a second small kernel reduces the pairs.
-// Weight streaming as in the split-K projections (64 contiguous bytes per lane straight into MFMA operands, the
-// next K chunk requested before this one is used), but a workgroup walks the whole K range, so there are no
-// partial sums to write: with V/128 = 1002 workgroups the grid is deep enough without splitting K.
+// workgroup reduces its tile of tokens to one (logit, id) pair per row and a second small kernel reduces the pairs.
+// The product is the projections' (GemmLoop): HBM-bound up to about 128 rows, by the matrix cores and the way from L2
+// to LDS above.  128256 tokens x 4096: 8 rows 173 us (6.1 TB/s), 60 rows 184 (5.7 TB/s; 204 with weights in registers and
+// the activation chunk staged behind two barriers), 256 rows in one pass 256 us where passes of 64 rows took 4 x 204.
+// That an XCD walks a contiguous range of the head is worth a tenth (tiles dealt round-robin: 211 us at 60 rows).
 #include "moa_common.h"
+#include "moa_gemm_device.h"
 #include "../../include/moa.h"
 
 namespace moa {
@@ -14,130 +16,66 @@ struct LmHeadArgs {
     const bf16_t *X;      // [R, K]
     const bf16_t *W;      // [V, K]
     int R, K, V;
-    float *pval;          // [tiles, 64]
-    int32_t *pid;         // [tiles, 64]
+    int tiles, tiles_per_xcd;
+    float *pval;          // [R, tiles]
+    int32_t *pid;         // [R, tiles]
 };
 
 __device__ __forceinline__ bool better(float a, int ia, float b, int ib) { return a > b || (a == b && ia < ib); }
 
-// TG groups of 16 tokens per wavefront: a workgroup's tile is 64 TG tokens, and the activation chunk it stages per K
-// chunk serves that many -- with TG = 1 the workgroups pull as many activation bytes out of the L2 as weight bytes out
-// of HBM (one 480 KB pass over X per 64 tokens).
-template <int NQ, int TG, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void k_lm_head_argmax(LmHeadArgs a)
+template <int WR, int WF, int MR, int NF, int SX, int SW, int WK>
+__global__ __launch_bounds__(64 * WR * WF * WK) void k_lm_head_argmax(LmHeadArgs a)
 {
-    constexpr int KS = 128 * NQ, LDK = KS + 8, CPR = KS / 8, NT = 64 * NW, XL = (64 * CPR) / NT;
-    extern __shared__ __attribute__((aligned(16))) bf16_t Xs[];   // [64][LDK]; reused for the per-wave bests at the end
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, kg = lane >> 4;
-    const int tile = blockIdx.x;
-    const int n0 = (tile * NW + wave) * 16 * TG;
-    const bf16_t *wp[TG];
+    using Loop = GemmLoop<WR, WF, MR, NF, SX, SW, WK>;
+    constexpr int BM = Loop::BM, BN = Loop::BN;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    // an XCD's workgroups (every eighth) walk a contiguous range of the head
+    const int tile = (int)(blockIdx.x & 7) * a.tiles_per_xcd + (int)(blockIdx.x >> 3), n0 = tile * BN;
+    if (tile >= a.tiles) return;
+    Loop g;
+    g.set_x(a.X, a.K, a.R);
+    g.set_w(a.K, a.V - n0, [&](int blk, int *first) {          // tokens past the end repeat the last one; masked below
+        *first = 32 * blk;
+        return (const char *)a.W + (int64_t)n0 * a.K * 2;
+    });
+    const bool mine = g.run(smem, 0, a.K / (Loop::BK * WK));
+    // best of the wavefront's tokens per row, then of the wavefronts along the tokens
+    wait_loads_and_barrier<0>();                               // the rings are dead; their memory is reused
+    float *wv = (float *)smem;                                 // [WF][BM]
+    int32_t *wi = (int32_t *)(wv + WF * BM);
+    const int l32 = g.lane & 31, half = g.lane >> 5;
+    if (mine) {
 #pragma unroll
-    for (int t = 0; t < TG; ++t) {
-        int wrow = n0 + 16 * t + li;
-        if (wrow > a.V - 1) wrow = a.V - 1;                 // tokens past the end repeat the last one; masked below
-        wp[t] = a.W + (int64_t)wrow * a.K + 8 * kg;         // k slot (q, j, kg) is k = 128 q + 32 j + 8 kg
-    }
-    const int nchunk = a.K / KS;
-
-    // Piece c = tid + NT i of the slice is row c / CPR, 16-byte column c % CPR: the column and the row's remainder
-    // are the same for every i, so one 32-bit lane offset serves all loads and the per-i part of the address is
-    // uniform (a scalar base): sixteen 64-bit lane addresses kept alive across the chunk loop would not fit the
-    // register budget of two workgroups per CU, and reloading spilled ones waits for every load in flight.
-    static_assert(NT % CPR == 0, "rows advance by a whole number per NT pieces");
-    constexpr int RSTEP = NT / CPR;                         // rows between piece i and piece i + 1
-    const uint32_t xoff = (uint32_t)(((tid / CPR) * a.K + 8 * (tid % CPR)) * (int)sizeof(bf16_t));
-    u32x4 xr[XL];
+        for (int jj = 0; jj < MR; ++jj) {
+            float bv = -INFINITY;
+            int bi = 0x7fffffff;
 #pragma unroll
-    for (int i = 0; i < XL; ++i) xr[i] = u32x4{0u, 0u, 0u, 0u};   // rows past the end stay zero; never used
-    auto load_x = [&](int kc) {
-        const char *xb = (const char *)(a.X + (int64_t)kc * KS);
+            for (int i = 0; i < NF; ++i)
 #pragma unroll
-        for (int i = 0; i < XL; ++i)
-            if (tid / CPR + RSTEP * i < a.R)
-                xr[i] = *(const u32x4 *)(xb + (int64_t)i * RSTEP * a.K * (int64_t)sizeof(bf16_t) + xoff);
-    };
-    bf16x8 wf[2][TG][NQ][4];
-    auto load_w = [&](int set, int kc) {
-#pragma unroll
-        for (int t = 0; t < TG; ++t)
-#pragma unroll
-            for (int q = 0; q < NQ; ++q)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) wf[set][t][q][j] = *(const bf16x8 *)(wp[t] + (int64_t)kc * KS + 128 * q + 32 * j);
-    };
-    load_x(0);
-    load_w(0, 0);
-    f32x4 acc[TG][4];
-#pragma unroll
-    for (int t = 0; t < TG; ++t)
-#pragma unroll
-        for (int rb = 0; rb < 4; ++rb) acc[t][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    auto chunk = [&](int set, int kc) {
-        if (kc + 1 < nchunk) load_w(set ^ 1, kc + 1);       // the next chunk's weights are on their way
-        // Bare barriers (LDS traffic drained, then s_barrier): __syncthreads() also waits for every outstanding
-        // global load, which would hold each chunk until the weights just requested for the next one have arrived.
-        if (kc > 0) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // every wave is done reading the previous slice
-#pragma unroll
-        for (int i = 0; i < XL; ++i) {
-            const int c = tid + NT * i;
-            *(u32x4 *)&Xs[(c / CPR) * LDK + 8 * (c % CPR)] = xr[i];
-        }
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (kc + 1 < nchunk) load_x(kc + 1);
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                bf16x8 xf[4];
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb) xf[rb] = *(const bf16x8 *)&Xs[(16 * rb + li) * LDK + 128 * q + 32 * j + 8 * kg];
-#pragma unroll
-                for (int t = 0; t < TG; ++t)
-#pragma unroll
-                    for (int rb = 0; rb < 4; ++rb)
-                        acc[t][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[set][t][q][j], xf[rb], acc[t][rb], 0, 0, 0);
-            }
-    };
-    for (int kc = 0; kc < nchunk; kc += 2) {                // two chunks per trip: the register sets alternate statically
-        chunk(0, kc);
-        if (kc + 1 < nchunk) chunk(1, kc + 1);
-    }
-
-    // lane holds tokens n0 + 16 t + 4 kg .. + 3 for row 16 rb + li: best of the workgroup's tokens per row
-    __syncthreads();
-    float *wv = (float *)Xs;                                 // [NW waves][64 rows]
-    int32_t *wi = (int32_t *)(wv + 64 * NW);
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
-        float bv = -INFINITY;
-        int bi = 0x7fffffff;
-#pragma unroll
-        for (int t = 0; t < TG; ++t)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int id = n0 + 16 * t + 4 * kg + e;
-                const float v = acc[t][rb][e];
-                if (id < a.V && better(v, id, bv, bi)) { bv = v; bi = id; }
-            }
-#pragma unroll
-        for (int o = 16; o <= 32; o <<= 1) {
-            const float ov = __shfl_xor(bv, o);
-            const int oi = __shfl_xor(bi, o);
+                for (int e = 0; e < 16; ++e) {
+                    const int id = n0 + g.wave_feature() + 32 * i + 16 * half + e;
+                    const float v = g.acc[i][jj][e];
+                    if (id < a.V && better(v, id, bv, bi)) { bv = v; bi = id; }
+                }
+            const float ov = __shfl_xor(bv, 32);
+            const int oi = __shfl_xor(bi, 32);
             if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+            if (half == 0) {
+                const int at = (g.wave % WF) * BM + g.wave_row() + 32 * jj + l32;
+                wv[at] = bv;
+                wi[at] = bi;
+            }
         }
-        if (kg == 0) { wv[wave * 64 + 16 * rb + li] = bv; wi[wave * 64 + 16 * rb + li] = bi; }
     }
     __syncthreads();
-    if (tid < 64) {
-        float bv = wv[tid];
-        int bi = wi[tid];
+    for (int r = threadIdx.x; r < BM && r < a.R; r += 64 * WR * WF * WK) {
+        float bv = wv[r];
+        int bi = wi[r];
 #pragma unroll
-        for (int w = 1; w < NW; ++w)
-            if (better(wv[w * 64 + tid], wi[w * 64 + tid], bv, bi)) { bv = wv[w * 64 + tid]; bi = wi[w * 64 + tid]; }
-        a.pval[(int64_t)tile * 64 + tid] = bv;
-        a.pid[(int64_t)tile * 64 + tid] = bi;
+        for (int w = 1; w < WF; ++w)
+            if (better(wv[w * BM + r], wi[w * BM + r], bv, bi)) { bv = wv[w * BM + r]; bi = wi[w * BM + r]; }
+        a.pval[(int64_t)r * a.tiles + tile] = bv;
+        a.pid[(int64_t)r * a.tiles + tile] = bi;
     }
 }
 
@@ -148,13 +86,12 @@ __global__ __launch_bounds__(256) void k_lm_head_reduce(const float *__restrict_
     __shared__ float sv[4];
     __shared__ int si[4];
     const int r = blockIdx.x, t = threadIdx.x;
+    const float *pv = pval + (int64_t)r * tiles;
+    const int32_t *pi = pid + (int64_t)r * tiles;
     float bv = -INFINITY;
     int bi = 0x7fffffff;
-    for (int k = t; k < tiles; k += 256) {
-        const float v = pval[(int64_t)k * 64 + r];
-        const int i = pid[(int64_t)k * 64 + r];
-        if (better(v, i, bv, bi)) { bv = v; bi = i; }
-    }
+    for (int k = t; k < tiles; k += 256)
+        if (better(pv[k], pi[k], bv, bi)) { bv = pv[k]; bi = pi[k]; }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         const float ov = __shfl_xor(bv, o);
@@ -170,6 +107,26 @@ __global__ __launch_bounds__(256) void k_lm_head_reduce(const float *__restrict_
         tgt[r] = bi;
         if (best) best[r] = bv;
     }
+}
+
+// one pass: the most rows (at most pa->R on entry) whose pairs fit `pairs`
+template <int WR, int WF, int MR, int NF, int SX, int SW, int WK>
+static hipError_t launch_head(LmHeadArgs *pa, int64_t pairs, hipStream_t st)
+{
+    using Loop = GemmLoop<WR, WF, MR, NF, SX, SW, WK>;
+    static_assert(Loop::BN >= Loop::BM, "");        // so that a pass takes (nearly) all the rows its tile has
+    LmHeadArgs &a = *pa;
+    a.tiles = (a.V + Loop::BN - 1) / Loop::BN;
+    a.tiles_per_xcd = (a.tiles + 7) / 8;
+    if (a.R > pairs / a.tiles) a.R = (int)(pairs / a.tiles);
+    a.pid = (int32_t *)(a.pval + (size_t)a.tiles * a.R);
+    static bool raised[16] = {};
+    hipError_t e = raise_lds_limit_once(raised, (const void *)k_lm_head_argmax<WR, WF, MR, NF, SX, SW, WK>, Loop::LDS_BYTES);
+    if (e != hipSuccess) return e;
+    prof_begin(K_LM_HEAD, st);
+    MOA_KLAUNCH((k_lm_head_argmax<WR, WF, MR, NF, SX, SW, WK>), dim3(8 * a.tiles_per_xcd), dim3(64 * WR * WF * WK), Loop::LDS_BYTES, st, a);
+    prof_end(st);
+    return hipGetLastError();
 }
 
 }  // namespace moa
@@ -193,34 +150,32 @@ int32_t moa_lm_head_argmax(int32_t dtype, const void *x, int32_t R, int32_t d, c
     if (dtype != MOA_BF16) return api_fail(MOA_ERR_DTYPE, "lm_head_argmax: bf16 only");
     if (R < 1 || V < 1 || d < 128 || d % 128) return api_fail(MOA_ERR_SHAPE, "lm_head_argmax: R >= 1, V >= 1, d a multiple of 128");
     if ((((uintptr_t)x) | ((uintptr_t)w)) & 15) return api_fail(MOA_ERR_SHAPE, "lm_head_argmax: x and w must be 16-byte aligned");
-    constexpr int TG = 2, NW = 4;               // 128 tokens per workgroup (eight wavefronts, 256 tokens: 223 against 214 us)
-    const int tiles = (V + 16 * TG * NW - 1) / (16 * TG * NW);
-    const size_t need = (size_t)tiles * 64 * (sizeof(float) + sizeof(int32_t));
+    size_t need = 0;
+    (void)moa_lm_head_workspace_bytes(V, &need);
     if (!ws || (((uintptr_t)ws) & 255) || ws_bytes < need) return api_fail(MOA_ERR_WORKSPACE, "lm_head_argmax: workspace NULL, misaligned or smaller than moa_lm_head_workspace_bytes");
     hipStream_t st = (hipStream_t)stream;
-    // 256-wide K chunks: with 512-wide ones the two weight sets and the staged activations no longer fit the registers
-    // of two workgroups per CU, and every reload of a spilled value waits for all loads in flight (measured 319 us
-    // against 241 us at 60 x 4096 x 128256)
-    const int nq = d % 256 == 0 ? 2 : 1;
-    const size_t lds = (size_t)64 * (128 * nq + 8) * sizeof(bf16_t);
-    // 64 rows per pass (the weights are streamed once per pass; a tree has at most 256 nodes)
-    for (int r0 = 0; r0 < R; r0 += 64) {
-        LmHeadArgs a;
+    // Up to 256 rows per pass over the weights, in the tile that the row count calls for.
+    const int64_t pairs = (int64_t)(need / (sizeof(float) + sizeof(int32_t)));     // a pair per token in 64s
+    LmHeadArgs a = {};
+    for (int r0 = 0; r0 < R; r0 += a.R) {
         a.X = (const bf16_t *)x + (int64_t)r0 * d;
         a.W = (const bf16_t *)w;
-        a.R = R - r0 < 64 ? R - r0 : 64;
+        a.R = R - r0 < 256 ? R - r0 : 256;
         a.K = d;
         a.V = V;
         a.pval = (float *)ws;
-        a.pid = (int32_t *)((float *)ws + (size_t)tiles * 64);
         prof_set_site(S_LM_HEAD);
-        prof_begin(K_LM_HEAD, st);
-        if (nq == 2) MOA_KLAUNCH((k_lm_head_argmax<2, TG, NW>), dim3(tiles), dim3(64 * NW), lds, st, a);
-        else MOA_KLAUNCH((k_lm_head_argmax<1, TG, NW>), dim3(tiles), dim3(64 * NW), lds, st, a);
-        prof_end(st);
-        if (hipGetLastError() != hipSuccess) return api_fail(MOA_ERR_HIP, "lm_head_argmax: launch failed");
+        // Wide tiles keep the activations' share of what goes through a compute unit small; with fewer of them than two
+        // per compute unit the narrow ones fill the chip better (40 x 4096 x 32000: 50 against 58 us).
+        const bool wide = V >= 2 * 256 * 128;
+        hipError_t e;
+        if (a.R <= 32) e = launch_head<1, 1, 1, 2, 3, 3, 2>(&a, pairs, st);
+        else if (a.R <= 64) e = wide ? launch_head<2, 2, 1, 2, 3, 3, 1>(&a, pairs, st) : launch_head<2, 2, 1, 1, 4, 6, 1>(&a, pairs, st);
+        else if (a.R <= 128) e = wide ? launch_head<2, 2, 2, 2, 2, 3, 1>(&a, pairs, st) : launch_head<4, 2, 1, 2, 4, 4, 1>(&a, pairs, st);
+        else e = launch_head<4, 2, 2, 4, 2, 2, 1>(&a, pairs, st);
+        if (e != hipSuccess) return api_fail(MOA_ERR_HIP, "lm_head_argmax: launch failed");
         prof_begin(K_LM_HEAD_REDUCE, st);
-        MOA_KLAUNCH(k_lm_head_reduce, dim3(a.R), dim3(256), 0, st, a.pval, a.pid, tiles, tgt + r0, best ? best + r0 : nullptr);
+        MOA_KLAUNCH(k_lm_head_reduce, dim3(a.R), dim3(256), 0, st, a.pval, a.pid, a.tiles, tgt + r0, best ? best + r0 : nullptr);
         prof_end(st);
         if (hipGetLastError() != hipSuccess) return api_fail(MOA_ERR_HIP, "lm_head_argmax: launch failed");
     }

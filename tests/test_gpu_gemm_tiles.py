@@ -79,3 +79,21 @@ def test_mlp_block_ragged_sizes(G, moa, oracle, R, d, d_ff):
     torch.cuda.synchronize()
     want = oracle.mlp_block(x, res, g, wg, wu, wd, 1e-5)
     G.check_close(G.host(out), want, "bf16", f"mlp_block[{R}x{d}x{d_ff}]", residual_stream=True)
+
+
+@pytest.mark.parametrize("R,d,V", [(32, 256, 4130), (33, 512, 65600), (64, 128, 300), (65, 256, 66000), (128, 384, 1000), (129, 256, 4099),
+                                   (256, 128, 257), (300, 256, 65601), (3, 128, 1)])
+def test_lm_head_tiles(G, moa, R, d, V):
+    """The LM head's arg-max in each of its tiles, with ragged vocabularies and more rows than one pass takes.  Inputs are
+    small integers, so every logit is exact in fp32 whatever the order of the sum: ids (ties to the lower one) and winning
+    logits must be exactly those of the fp64 product."""
+    print(f"[case] lm_head R={R} d={d} V={V}", flush=True)
+    g = torch.Generator().manual_seed(R + d + V)
+    x, w = torch.randint(-3, 4, (R, d), generator=g), torch.randint(-3, 4, (V, d), generator=g)
+    tgt, best = torch.full((R,), -1, dtype=torch.int32, device="cuda"), torch.zeros(R, device="cuda")
+    ws = torch.empty(max(moa.lm_head_workspace_bytes(V), 256), dtype=torch.uint8, device="cuda")
+    moa.lm_head_argmax(x.bfloat16().cuda(), w.bfloat16().cuda(), tgt, ws, best)
+    torch.cuda.synchronize()
+    logits = (x.double() @ w.double().t()).numpy()
+    assert np.array_equal(tgt.cpu().numpy(), np.argmax(logits, axis=1))
+    assert np.array_equal(best.cpu().numpy().astype(np.float64), logits.max(axis=1))
