@@ -593,6 +593,7 @@ static int32_t attn_stage_project(const char *who, const moa_shape_t *shape, con
     la.ldx = d;
     la.ws = bf.scratch_p;
     la.ws_bytes = bf.scratch_p_bytes;
+    la.same_sums = tree && !t_sites;          // verification: a step may launch this layer together with others
     *q_out = x;
     if (wq) {
         la.seg[la.nseg].W = wq;
@@ -1264,6 +1265,7 @@ static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, v
     la.ldx = d;
     la.ws = scr;
     la.ws_bytes = scr_bytes;
+    la.same_sums = true;
     if (which & 1) {
         LinSeg &q = la.seg[la.nseg++];
         q.W = a->ca_wq;

@@ -255,6 +255,8 @@ struct LinArgs {
     RopeArgs rope;
     NormArgs norm;
     bool in_order;     // sum along K in one chain of matrix instructions, as the one-kernel LSA does (same bits)
+    bool same_sums;    // the order of the sums along K depends on R and K alone, not on what else is in the launch (a step's
+                       // schedules group the same projections differently and give the same bits)
     // Where K is cut into slices: do not launch the pass that adds them up but describe it here (blocks = 0 when nothing
     // is left to do).  The caller has it carried by a later launch or runs launch_splitk_sum;
     // the partial sums (ws) must stay untouched until then.

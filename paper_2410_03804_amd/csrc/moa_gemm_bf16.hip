@@ -177,8 +177,12 @@ struct GemmPlan { int tile, splits; };
 // unit one (1024 x 4096: 256 x 160 for 10240 features, 77.6 us against 98 - 108 with the tiles next to it, 256 x 128 for
 // 8192); slices only for a long K with few features (60 x 14336 x 4096: four, 30 us against 68).  A pass of its own behind
 // an unsplit projection (`pass_us`) counts against not splitting, since the sum over slices does that work on the way.
-static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi, bool in_order)
+//
+// same_sums: pairs of K groups up to 32 rows, one group above, no slices, whatever the features (60 x 4096: 64 x 64 tiles
+// in one group are what the grouped launch of 10240 features takes anyway; 6144 alone would be 19 us instead of 22).
+static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi, bool in_order, bool same_sums)
 {
+    if (same_sums && (R > 32 || K % 128)) in_order = true;
     GemmPlan best = {0, 1};
     int ntot = 0;
     for (int s = 0; s < nseg; ++s) ntot += n_seg[s];
@@ -186,12 +190,12 @@ static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi,
     const float stream_us = 6.f + 2.f * (float)K * (float)ntot / 5.8e6f;
     for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
         const GemmTile &t = kTiles[i];
-        if (in_order ? t.wk > 1 : ((t.bm == 32) != (R <= 32) || K % (64 * t.wk) != 0)) continue;
+        if (in_order ? t.wk > 1 : ((t.bm == 32) != (R <= 32) || K % (64 * t.wk) != 0 || (same_sums && t.wk != 2))) continue;
         int64_t tiles = 0;
         for (int s = 0; s < nseg; ++s) tiles += (n_seg[s] + t.bn - 1) / t.bn;
         tiles *= (R + t.bm - 1) / t.bm;
         for (int splits = 1; splits <= 4; splits *= 2) {
-            if (splits > 1 && (in_order || R > 192 || ntot % 64 || K % (64 * t.wk * splits) || K / (64 * t.wk * splits) < 8)) break;
+            if (splits > 1 && (in_order || same_sums || R > 192 || ntot % 64 || K % (64 * t.wk * splits) || K / (64 * t.wk * splits) < 8)) break;
             const int64_t n = tiles * splits;
             float per;                             // k-tile times of one compute unit
             if (t.us2 > 0.f) {
@@ -225,7 +229,7 @@ size_t linear_workspace_bytes(int dtype, int64_t R, int K, int ntot)
     if (dtype != DT_BF16 || R < 1 || R > 192 || K % 128 || ntot % 64) return 0;
     size_t most = 0;
     for (int epi : {(int)LinArgs::EPI_NONE, (int)LinArgs::EPI_ADD_NORM, (int)LinArgs::EPI_SWIGLU}) {
-        const size_t n = partial_bytes(R, ntot, plan_gemm(R, K, &ntot, 1, epi, false).splits);
+        const size_t n = partial_bytes(R, ntot, plan_gemm(R, K, &ntot, 1, epi, false, false).splits);
         if (n > most) most = n;
     }
     return most;
@@ -241,7 +245,7 @@ hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused,
         ntot += a.seg[s].N;
         all64 = all64 && a.seg[s].N % 64 == 0;
     }
-    GemmPlan p = plan_gemm(a.R, a.K, n_seg, a.nseg, a.epi, a.in_order);
+    GemmPlan p = plan_gemm(a.R, a.K, n_seg, a.nseg, a.epi, a.in_order, a.same_sums);
     if (p.splits > 1 && !(all64 && a.ws && a.ws_bytes >= partial_bytes(a.R, ntot, p.splits) && (((uintptr_t)a.ws) & 15) == 0)) p.splits = 1;
     const GemmTile &t = kTiles[p.tile];
     GemmArgs ga;
