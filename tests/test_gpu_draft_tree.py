@@ -136,6 +136,53 @@ def test_topk_logprob_parity(G, moa, oracle, dtype, F, V, Bw):
     assert np.max(np.abs(logp.cpu().numpy().astype(np.float64) - wl)) < 1e-5 * max(1.0, np.abs(wl).max())
 
 
+@pytest.mark.parametrize("dtype,F,V,Bw,offset", [("bf16", 2, 8 * 257, 16, 0), ("bf16", 2, 8 * 257, 16, 1), ("f32", 1, 131072, 16, 0),
+                                                 ("bf16", 1, 131080, 16, 0), ("f32", 1, 131081, 3, 0), ("bf16", 5, 16, 16, 0), ("f32", 3, 9, 1, 1)])
+def test_topk_logprob_ties_and_alignment(G, moa, oracle, dtype, F, V, Bw, offset):
+    """Whole rows of one value (every id of a slice reaches the bound), a few values that all tie, one thread's run holding
+    all the best, and logits that start off a 16-byte boundary."""
+    rng = np.random.default_rng(V + Bw + offset)
+    logits = rng.integers(-2, 3, (F, V)).astype(np.float32)
+    logits[0] = -1.5
+    if F > 1:
+        logits[1, max(0, V - 8):] = 7.0
+    print(f"[case] topk ties {dtype} F={F} V={V} breadth={Bw} offset={offset}", flush=True)
+    d = torch.empty(F * V + offset, dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+    dl = d[offset:].view(F, V)
+    dl.copy_(torch.from_numpy(logits))
+    tok = torch.zeros((F, Bw), dtype=torch.int32, device="cuda")
+    logp = torch.zeros((F, Bw), dtype=torch.float32, device="cuda")
+    ws = torch.empty(max(moa.topk_workspace_bytes(F, V, Bw), 256), dtype=torch.uint8, device="cuda")
+    moa.topk_logprob(dl, Bw, tok, logp, ws)
+    torch.cuda.synchronize()
+    wt, wl = oracle.topk_logprob(logits, Bw)
+    assert np.array_equal(tok.cpu().numpy(), wt)
+    assert np.max(np.abs(logp.cpu().numpy().astype(np.float64) - wl)) < 1e-5 * max(1.0, np.abs(wl).max())
+
+
+@pytest.mark.parametrize("n,m", [(1, 1), (63, 20), (64, 64), (65, 30), (1024, 255), (1025, 200), (2500, 255), (4096, 250)])
+def test_tree_finalize_ties(G, moa, oracle, n, m):
+    """Few distinct values: which candidates are kept is decided by their indices, across groups of 64 and of 1024."""
+    rng = np.random.default_rng(n)
+    parent = np.array([-1 if c < 4 else rng.integers(0, c) for c in range(n)], dtype=np.int32)
+    lp = np.zeros(n, np.float32)
+    for c in range(n):                                          # a child is never more likely than its parent
+        lp[c] = (0.0 if parent[c] < 0 else lp[parent[c]]) - float(rng.integers(0, 2))
+    lp[n // 2:][lp[n // 2:] < -3] = -np.inf
+    for c in range(n):
+        if parent[c] >= 0:
+            lp[c] = min(lp[c], lp[parent[c]])
+    tk = rng.integers(0, 128256, n).astype(np.int32)
+    print(f"[case] finalize ties n={n} m={m}", flush=True)
+    out = [torch.full((1, 1 + m), -7, dtype=torch.int32, device="cuda") for _ in range(3)]
+    st = G.status_word()
+    moa.tree_finalize(n, m, G.dev(np.array([9], np.int32)), G.dev(lp[None]), G.dev(tk[None]), G.dev(parent[None]), *out, st)
+    torch.cuda.synchronize()
+    assert st.item() == 0
+    for got, want in zip(out, oracle.tree_finalize(n, m, np.int32(9), lp, tk, parent)):
+        assert np.array_equal(got[0, :len(want)].cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("R,d,V", [(60, 4096, 128256), (64, 512, 1000), (7, 256, 70), (130, 384, 5000), (1, 128, 64)])
 def test_lm_head_argmax_parity(G, moa, oracle, R, d, V):
     """The greedy token per row.  The device accumulates bf16 products in fp32, the oracle in fp64, so where two logits

@@ -82,3 +82,31 @@ def test_accept_message_bit_exact(G, moa, oracle, dtype, A, n_vec, n):
     assert np.array_equal(y.cpu().numpy().view(np.uint32), wy.view(np.uint32))
     scale = np.abs(x).max(axis=2, keepdims=True) / np.float32(127)
     assert np.all(np.abs(y.cpu().numpy() - x) <= scale * (0.5 + 2e-5) + 1e-30)
+
+
+@pytest.mark.parametrize("dtype,n,offset", [("bf16", 8, 0), ("bf16", 2048, 1), ("f32", 2056, 0), ("f32", 4104, 1), ("bf16", 6144, 0)])
+def test_accept_message_runs_and_alignment(G, moa, oracle, dtype, n, offset):
+    """Vectors of one run of eight, one run past the 256 threads, several passes; activations off a 16-byte boundary."""
+    A, n_vec = 3, 2
+    rng = np.random.default_rng(n + offset)
+    x = mi.quantize(rng.standard_normal((A, n_vec, n)).astype(np.float32), dtype)
+    x[0, 0, n - 1] = 9.0
+    tok = rng.integers(0, 128256, A).astype(np.int32)
+    print(f"[case] msg_accept runs {dtype} n={n} offset={offset}", flush=True)
+    d = torch.empty(x.size + offset, dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+    dx = d[offset:].view(x.shape)
+    dx.copy_(torch.from_numpy(x))
+    msg = torch.zeros(moa.msg_accept_bytes(A, n_vec, n), dtype=torch.uint8, device="cuda")
+    st = G.status_word()
+    moa.msg_pack_accept(G.dev(tok), dx, msg, st)
+    t2 = torch.full((A,), -9, dtype=torch.int32, device="cuda")
+    dy = torch.zeros(x.size + offset, dtype=torch.float32, device="cuda")
+    y = dy[offset:].view(x.shape)
+    moa.msg_unpack_accept(msg, t2, y)
+    torch.cuda.synchronize()
+    assert st.item() == 0
+    want = oracle.msg_pack_accept(tok, x)
+    assert np.array_equal(msg.cpu().numpy().reshape(want.shape), want)
+    wt, wy = oracle.msg_unpack_accept(want, n_vec, n)
+    assert np.array_equal(t2.cpu().numpy(), wt)
+    assert np.array_equal(y.cpu().numpy().view(np.uint32), wy.view(np.uint32))
