@@ -1,0 +1,74 @@
+"""GPU parity of the attention kernel for more than 128 query rows per (sequence, KV head) at the edges of its tiles: row
+counts around 128 and 256 and in several row tiles, key ranges around the 64-key tiles and the two 32-key halves of one,
+an empty prefix, slices of the key range that hold no key, one slice (no merge pass), trees of one to three mask words, and
+scores that move the reference of the exponent between tiles."""
+import numpy as np
+import pytest
+import torch
+
+import moa_inputs as mi
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def G():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util
+    return gpu_util
+
+
+@pytest.fixture(scope="module")
+def moa(G):
+    import paper_2410_03804_amd as m
+    m.debug_force_attn_kernel("split")
+    yield m
+    m.debug_force_attn_kernel("auto")
+
+
+CASES = [
+    # M, H, Hkv, prefix lengths, cache rows per sequence, factor on the queries
+    (43, 3, 1, [0, 1, 31, 64], 70, 1.0),             # 129 rows: one 256-row tile, half of it empty
+    (64, 4, 1, [65, 128, 129], 400, 1.0),            # 256 rows exactly; slices without a key
+    (65, 4, 1, [191, 33], 1024, 1.0),                # 260 rows: two row tiles, a tree of two tiles
+    (130, 2, 1, [300, 97], 640, 4.0),                # a tree of three tiles, peaked scores
+    (173, 6, 2, [5, 1000], 2100, 1.0),               # 519 rows: three row tiles, two KV heads
+    (130, 4, 2, [257] * 32, 260, 1.0),               # 64 (sequence, head) pairs of two row tiles: two slices
+    (65, 64, 16, [40] * 16, 100, 1.0),               # 256 pairs of two row tiles: one slice, no merge pass
+    (70, 8, 2, [999], 1000, 30.0),                   # scores of order 100: the reference moves at most tiles
+]
+
+
+@pytest.mark.parametrize("M,H,Hkv,plen,P_cap,factor", CASES)
+def test_attn_long_tile_edges(G, moa, oracle, M, H, Hkv, plen, P_cap, factor):
+    cfg = mi.Config(name="long", index=13, dtype="bf16", B=len(plen), P_min=1, P_max=max(max(plen), 1), M=M, D=7, max_branch=5, L=2,
+                    d=256, H=H, Hkv=Hkv, dh=128, d_lsa_in=256, rms_norm=True)
+    plen = np.array(plen, dtype=np.int32)
+    w, x = mi.verify_weights(cfg), mi.verify_inputs(cfg)
+    w["wq"] = mi.quantize(w["wq"] * factor, "bf16")
+    kc, vc = mi.kv_cache(cfg, which=0, P_cap=P_cap)
+    for b, n in enumerate(plen):                     # rows past a sequence's length are never used
+        kc[b, :, n:], vc[b, :, n:] = np.nan, np.nan
+    mask_np, _ = oracle.tree_build(mi.trees(cfg))
+    print(f"[case] tree_verify M={M} H={H}/{Hkv} B={cfg.B} P_cap={P_cap} factor={factor}", flush=True)
+    shape = G.shape_of(cfg)
+    out = torch.full((cfg.B, M, cfg.d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    kt = torch.empty((cfg.B, Hkv, M, 128), dtype=torch.bfloat16, device="cuda")
+    vt, st = torch.empty_like(kt), G.status_word()
+    moa.tree_verify_attn(shape, G.dev(x, "bf16"), *(G.dev(w[k], "bf16") for k in ("wq", "wk", "wv", "wo")), G.dev(kc, "bf16"),
+                         G.dev(vc, "bf16"), G.dev(plen), P_cap, G.dev(mask_np.view(np.int64)), out, kt, vt,
+                         G.workspace(shape, cfg.B, P_cap, M, 0), st)
+    torch.cuda.synchronize()
+    assert st.item() == 0
+    want, _, _ = oracle.tree_verify_attn(x, w["wq"], w["wk"], w["wv"], w["wo"], kc, vc, plen, mask_np, H, Hkv, 128)
+    if factor == 1.0:
+        G.check_close(G.host(out), want, "bf16", f"tree_verify[{M}x{H}/{Hkv}]")
+        return
+    # queries of size `factor` are rounded to 2^-9 of that, so a score is off by up to factor * 2^-9 rms and a weight by as much
+    # relative to itself; 2^-8 for the roundings of the rest.  The largest element of 10^5 at six times the rms
+    got = G.host(out)
+    assert np.all(np.isfinite(got))
+    bound = factor * 2.0 ** -9 + 2.0 ** -8
+    assert np.linalg.norm(got - want) <= bound * np.linalg.norm(want)
+    assert np.abs(got - want).max() <= 6 * bound * np.sqrt(np.mean(want ** 2))
