@@ -16,6 +16,8 @@
 //                    lane owns one query column and the softmax max/sum need a single cross-lane
 //                    exchange; P^T feeds the second MFMA straight from registers and V^T comes out of
 //                    the LDS transpose read.
+//   k_attn_long      the same split with 256 query rows per workgroup, for more than 128 rows per (sequence, KV
+//                    head) at head_dim 128.  Described at the kernel.
 //   k_attn_merge     combines the per-slice (max, sum, accumulator) triples.
 #include "moa_common.h"
 #include "moa_gemm_device.h"
@@ -391,7 +393,8 @@ __global__ __launch_bounds__(256, NBLK == 1 ? 2 : 1) void k_attn_mfma(AttnGroup 
 // eight rows of 64 bytes); one barrier per tile, two tiles in flight behind the current one.
 // The reference of the exponent follows the running maximum only when a score exceeds it by more than 2^8: sums and
 // accumulators hold the same relative precision, and the rescale is rare.
-// 8 x 32768 keys x 128 tree tokens, both cores: 1555 us (0.71 PFLOP/s) with 32 rows per wavefront.
+// What bounds it is the matrix pipe and the softmax arithmetic together.  8 x 32768 keys x 128 tree tokens, both cores:
+// 1290 us (0.85 PFLOP/s), where 32 rows per wavefront took 1555.
 constexpr int LK = 64;            // keys per tile
 constexpr int LRING = 4;
 constexpr float RESCALE_AT = 8.f; // log2
@@ -1148,6 +1151,8 @@ static bool mfma_ok(int dtype, int dh, const AttnArgs *a)
 // 25 % faster than two blocks per wave at RG = 512 even though K/V are then read by twice as many row tiles
 constexpr int ATTN_NBLK = 1;
 
+// More rows than one 128-row tile holds (measured whole steps: 256 rows per KV head, 16 sequences 734 -> 730 us; 480 rows,
+// 70B shape 680 -> 671; 512 rows, 32768 keys 2114 -> 1855); up to 128 the 256-row tile would be half empty or worse.
 static bool long_form(int RG, int dh) { return dh == 128 && RG > 128; }
 
 static SplitGeom split_geometry(int B, int Mq, int H, int Hkv, int dh, int P_cap)
@@ -1239,8 +1244,8 @@ static bool attn_split_ok(const AttnArgs &a, int P_cap_geo)
 // Which MFMA kernel.  The whole-key-range form needs one launch, writes no partial results and has the shorter
 // fixed part, but re-reads K/V once per 32 query rows and runs one workgroup per CU: it wins while the call is
 // latency-bound, i.e. while its workgroups fit the chip in one round and the key range is short (C1: 14.5 us
-// against 17.8 + 6.8 us).  With more work the split form (128 rows per workgroup, two workgroups per CU, then the
-// merge) is ahead (B = 16, prefixes up to 2048: 122 against 166 us).  moa_debug_force_attn_kernel overrides the
+// against 17.8 + 6.8 us).  With more work the split form (128 rows per workgroup and two workgroups per CU, or 256
+// rows and one, see long_form; then the merge) is ahead (B = 16, prefixes up to 2048: 122 against 166 us).  moa_debug_force_attn_kernel overrides the
 // choice (the parity tests run every case through both forms).
 constexpr int FUSED_MAX_KEYS = 8192;
 constexpr int FUSED_MAX_WORKGROUPS = 256;

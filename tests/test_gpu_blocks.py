@@ -92,6 +92,23 @@ def test_mlp_block_in_place_and_empty(G, moa, oracle):
     assert moa.mlp_block_workspace_bytes(moa.BF16, 0, 512, 768) >= 0
 
 
+@pytest.mark.parametrize("R", [60, 240])
+def test_mlp_block_output_off_alignment(G, moa, R):
+    """An output row that starts off a 16-byte boundary gets the bits an aligned one gets."""
+    x, res, w = block_inputs("bf16", R, 512, 768, R, True)
+    wd = [G.dev(w[k], "bf16") for k in ("g", "w_gate", "w_up", "w_down")]
+    ws = torch.empty(moa.mlp_block_workspace_bytes(moa.BF16, R, 512, 768), dtype=torch.uint8, device="cuda")
+    xd, rd = G.dev(x, "bf16"), G.dev(res, "bf16")
+    want = torch.empty_like(xd)
+    flat = torch.full((R * 512 + 16,), -7.0, dtype=torch.bfloat16, device="cuda")
+    got = flat[1:1 + R * 512].view(R, 512)
+    print(f"[case] mlp_block R={R} out + 2 bytes", flush=True)
+    moa.mlp_block(moa.BF16, xd, rd, *wd, EPS, want, ws)
+    moa.mlp_block(moa.BF16, xd, rd, *wd, EPS, got, ws)
+    assert torch.equal(got, want)
+    assert flat[0] == -7.0 and (flat[1 + R * 512:] == -7.0).all()
+
+
 def test_block_entry_points_reject_bad_arguments(G, moa):
     x, res, w = block_inputs("bf16", 4, 256, 512, 1, False)
     xd = G.dev(x, "bf16")
