@@ -168,7 +168,7 @@ def _check(rc: int):
 
 
 def _dev(t, dtype, numel, name):
-    """Device pointer of tensor t after checking it can hold what the call touches."""
+    """Device pointer (a number: the argument types make the pointer) of tensor t after checking it can hold what the call touches."""
     if t is None:
         return None
     if not isinstance(t, torch.Tensor):
@@ -179,12 +179,12 @@ def _dev(t, dtype, numel, name):
         raise ValueError(f"{name}: dtype {t.dtype}, expected {dtype}")
     if t.numel() < numel:
         raise ValueError(f"{name}: {t.numel()} elements, the call touches {numel}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    # the current stream's handle without a Stream object around it, which is made anew on each call
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
 
 
 def _ws(ws):
@@ -192,7 +192,7 @@ def _ws(ws):
         return None, 0
     if not ws.is_cuda or not ws.is_contiguous():
         raise ValueError("ws: must be a contiguous CUDA tensor")
-    return C.c_void_p(ws.data_ptr()), ws.numel() * ws.element_size()
+    return ws.data_ptr(), ws.numel() * ws.element_size()
 
 
 def workspace_bytes(shape: Shape, B: int, P_cap: int, M: int, T_lsa: int) -> int:
@@ -546,8 +546,7 @@ def fold_projection(w_outer, w_inner, out=None, stream=None):
 def _ptr_array(tensors, dtype, numel, name):
     arr = (C.c_void_p * len(tensors))()
     for i, t in enumerate(tensors):
-        p = _dev(t, dtype, numel, f"{name}[{i}]")
-        arr[i] = None if p is None else p.value
+        arr[i] = _dev(t, dtype, numel, f"{name}[{i}]")
     return arr
 
 
@@ -652,8 +651,7 @@ class StepPlan:
         self._ref = C.byref(args)
 
     def run(self, stream=None):
-        s = torch.cuda.current_stream() if stream is None else stream
-        self._args.stream = s.cuda_stream
+        self._args.stream = _stream(stream)
         rc = _lib.moa_draft_step(self._ref)
         if rc != 0:
             raise MoaError(rc, last_error())
