@@ -156,7 +156,8 @@ __global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(GemmArgs ga)
     T(9, 8, 1, 1, 5, 3, 3, 1, 1.12f, 0.f, 0.f)                \
     T(10, 4, 2, 2, 4, 2, 2, 1, 1.55f, 0.f, 0.f)               \
     T(11, 4, 2, 1, 1, 3, 4, 2, 0.82f, 0.f, 0.f)               \
-    T(12, 4, 2, 2, 3, 2, 3, 1, 1.25f, 0.f, 0.f)
+    T(12, 4, 2, 2, 3, 2, 3, 1, 1.25f, 0.f, 0.f)               \
+    T(13, 2, 2, 1, 1, 4, 5, 2, 0.66f, 0.f, 0.f)
 
 struct GemmTile {
     int bm, bn, threads, wk;
@@ -178,11 +179,13 @@ struct GemmPlan { int tile, splits; };
 // 8192); slices only for a long K with few features (60 x 14336 x 4096: four, 30 us against 68).  A pass of its own behind
 // an unsplit projection (`pass_us`) counts against not splitting, since the sum over slices does that work on the way.
 //
-// same_sums: pairs of K groups up to 32 rows, one group above, no slices, whatever the features (60 x 4096: 64 x 64 tiles
-// in one group are what the grouped launch of 10240 features takes anyway; 6144 alone would be 19 us instead of 22).
+// same_sums: pairs of K groups up to 32 rows, and up to 64 where K is at most 4096; one group else; no slices, whatever
+// the features.  60 x 4096: 6144 features, a verification layer of its own, 18.7 us against 23.6 with one group (96 tiles
+// of 64 x 64), a step with 32 such layers 1845 -> 1733; the grouped launch of 10240 26.7 against 25.2.  Beyond K = 4096
+// a tile of 64 x 64 pairs per compute unit runs out of compute units first (18432 features at K = 8192).
 static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi, bool in_order, bool same_sums)
 {
-    if (same_sums && (R > 32 || K % 128)) in_order = true;
+    if (same_sums && (R > 64 || (R > 32 && K > 4096) || K % 128)) in_order = true;
     GemmPlan best = {0, 1};
     int ntot = 0;
     for (int s = 0; s < nseg; ++s) ntot += n_seg[s];
