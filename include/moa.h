@@ -171,9 +171,9 @@ int32_t moa_tree_verify_attn(const moa_shape_t *shape, const void *x, int32_t B,
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments without ws / ws_bytes, same
  * kernels, same results bit for bit.  The scratch (projected queries, heads, partial sums, partial attention results)
  * is a fixed 32 MiB array in the library's own device memory, one copy per GPU, held until the process ends; the call
- * itself allocates and frees nothing.  MOA_ERR_WORKSPACE when the call would need more than that (what
- * moa_workspace_bytes(shape, B, P_cap, M, 0) reports; the Llama-3-8B shape with one sequence, a tree of 64 and 4096
- * cached tokens needs about 12 MiB) -- use moa_tree_verify_attn then.  Every call on a GPU shares that GPU's array:
+ * itself allocates and frees nothing.  MOA_ERR_WORKSPACE when the call would need more than that (at most
+ * what moa_workspace_bytes(shape, B, P_cap, M, 0) reports; the Llama-3-8B shape with one sequence, a tree of 64 and 4096
+ * cached tokens needs 17.5 MiB) -- use moa_tree_verify_attn then.  Every call on a GPU shares that GPU's array:
  * calls that overlap in time on one GPU (different streams, different host threads) race; calls on one stream do not.
  * The array keeps the previous call's contents and nothing in it has to start at zero. */
 int32_t moa_tree_verify_attn_noalloc(const moa_shape_t *shape, const void *x, int32_t B, int32_t M,

@@ -98,41 +98,43 @@ constexpr int64_t LSA_OBLOCK = 4096;  // tokens per output-projection pass (one 
 
 size_t max2(size_t a, size_t b) { return a > b ? a : b; }
 
-size_t lsa_ws_bytes(const moa_shape_t *s, int64_t T)
+// Scratch sizes.  A call checks its workspace against what it uses itself; a query (upto) reports what suffices for every
+// call with sizes up to the queried ones: fewer rows can be cut into more slices and then need more than many.
+size_t lsa_ws_bytes(const moa_shape_t *s, int64_t T, bool upto = false)
 {
     const int64_t tc = T < LSA_CHUNK ? T : LSA_CHUNK, ob = T < LSA_OBLOCK ? T : LSA_OBLOCK;
     const size_t eq = (size_t)s->lsa_q_heads * s->head_dim, ekv = (size_t)s->lsa_kv_heads * s->head_dim;
     // the output projection may carry the memory's folded K/V projections as two more segments (draft step)
-    size_t lin = linear_workspace_bytes(s->dtype, ob, (int)eq, (int)(eq + 2 * (size_t)s->n_kv_heads * s->head_dim));
-    lin = max2(lin, linear_workspace_bytes(s->dtype, ob, (int)eq, (int)eq));
+    size_t lin = linear_workspace_bytes(s->dtype, ob, (int)eq, (int)(eq + 2 * (size_t)s->n_kv_heads * s->head_dim), upto);
+    lin = max2(lin, linear_workspace_bytes(s->dtype, ob, (int)eq, (int)eq, upto));
     return align256((size_t)tc * s->n_layers * (eq + 2 * ekv) * esize(s->dtype)) + align256((size_t)ob * eq * esize(s->dtype)) +
            align256(lin);
 }
 
 // scratch shared by the projections' split-K partials and the attention core's split-KV partials
-size_t attn_scratch_bytes(const moa_shape_t *s, int B, int Mq, int P_cap, bool tree)
+size_t attn_scratch_bytes(const moa_shape_t *s, int B, int Mq, int P_cap, bool tree, bool upto)
 {
     const int e = s->n_q_heads * s->head_dim, ekv = s->n_kv_heads * s->head_dim;
     const int64_t R = (int64_t)B * Mq;
-    size_t n = attn_workspace_bytes(s->dtype, B, Mq, s->n_q_heads, s->n_kv_heads, s->head_dim, P_cap);
-    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, e + (tree ? 2 * ekv : 0)));
-    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, e));
-    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, 2 * ekv));
-    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, ekv));
-    n = max2(n, linear_workspace_bytes(s->dtype, R, e, s->d_model));
+    size_t n = attn_workspace_bytes(s->dtype, B, Mq, s->n_q_heads, s->n_kv_heads, s->head_dim, P_cap, upto);
+    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, e + (tree ? 2 * ekv : 0), upto));
+    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, e, upto));
+    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, 2 * ekv, upto));
+    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, ekv, upto));
+    n = max2(n, linear_workspace_bytes(s->dtype, R, e, s->d_model, upto));
     return align256(n);
 }
 
-size_t attn_ws_bytes(const moa_shape_t *s, int B, int Mq, int P_cap)
+size_t attn_ws_bytes(const moa_shape_t *s, int B, int Mq, int P_cap, bool upto = false)
 {
     const size_t e = (size_t)s->n_q_heads * s->head_dim;
-    return 2 * align256((size_t)B * Mq * e * esize(s->dtype)) + attn_scratch_bytes(s, B, Mq, P_cap, true);
+    return 2 * align256((size_t)B * Mq * e * esize(s->dtype)) + attn_scratch_bytes(s, B, Mq, P_cap, true, upto);
 }
 
-size_t append_ws_bytes(const moa_shape_t *s, int64_t T, int d_mem)
+size_t append_ws_bytes(const moa_shape_t *s, int64_t T, int d_mem, bool upto = false)
 {
     const int ekv = s->n_kv_heads * s->head_dim;
-    return align256(max2(linear_workspace_bytes(s->dtype, T, d_mem, 2 * ekv), linear_workspace_bytes(s->dtype, T, d_mem, ekv)));
+    return align256(max2(linear_workspace_bytes(s->dtype, T, d_mem, 2 * ekv, upto), linear_workspace_bytes(s->dtype, T, d_mem, ekv, upto)));
 }
 
 // workspace split of the grouped step:
@@ -142,7 +144,7 @@ struct GroupLayout {
     size_t total() const { return len_bytes + 4 * qa + scratch; }
 };
 
-GroupLayout group_layout(const moa_shape_t *s, int B, int M, int P_cap, int ca_P_cap, int64_t T)
+GroupLayout group_layout(const moa_shape_t *s, int B, int M, int P_cap, int ca_P_cap, int64_t T, bool upto = false)
 {
     GroupLayout L;
     const int e = s->n_q_heads * s->head_dim, ekv = s->n_kv_heads * s->head_dim;
@@ -150,15 +152,15 @@ GroupLayout group_layout(const moa_shape_t *s, int B, int M, int P_cap, int ca_P
     L.len_bytes = align256((size_t)B * sizeof(int32_t));
     L.qa = align256((size_t)R * e * esize(s->dtype));
     const int cap = P_cap > ca_P_cap ? P_cap : ca_P_cap;
-    L.attn_each = align256(attn_workspace_bytes(s->dtype, B, M, s->n_q_heads, s->n_kv_heads, s->head_dim, cap));
+    L.attn_each = align256(attn_workspace_bytes(s->dtype, B, M, s->n_q_heads, s->n_kv_heads, s->head_dim, cap, upto));
     size_t n = 2 * L.attn_each;
-    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, 2 * e + 2 * ekv));
-    n = max2(n, linear_workspace_bytes(s->dtype, R, e, 2 * s->d_model));
-    n = max2(n, attn_ws_bytes(s, B, M, P_cap));                       // verification layers after the first
-    n = max2(n, attn_ws_bytes(s, B, M, ca_P_cap));
+    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, 2 * e + 2 * ekv, upto));
+    n = max2(n, linear_workspace_bytes(s->dtype, R, e, 2 * s->d_model, upto));
+    n = max2(n, attn_ws_bytes(s, B, M, P_cap, upto));                       // verification layers after the first
+    n = max2(n, attn_ws_bytes(s, B, M, ca_P_cap, upto));
     if (T > 0) {
-        n = max2(n, lsa_ws_bytes(s, T));
-        n = max2(n, append_ws_bytes(s, T, s->lsa_q_heads * s->head_dim));
+        n = max2(n, lsa_ws_bytes(s, T, upto));
+        n = max2(n, append_ws_bytes(s, T, s->lsa_q_heads * s->head_dim, upto));
     }
     L.scratch = align256(n);
     return L;
@@ -201,15 +203,15 @@ int32_t moa_workspace_bytes(const moa_shape_t *shape, int32_t B, int32_t P_cap, 
     int32_t rc = check_shape(shape, false);
     if (rc) return rc;
     if (B < 1 || M < 1 || P_cap < 0 || T_lsa < 0) return fail(MOA_ERR_SHAPE, "B=%d M=%d P_cap=%d T_lsa=%lld", B, M, P_cap, (long long)T_lsa);
-    size_t need = attn_ws_bytes(shape, B, M, P_cap);
+    size_t need = attn_ws_bytes(shape, B, M, P_cap, true);
     if (T_lsa > 0) {
         rc = check_shape(shape, true);
         if (rc) return rc;
-        need = max2(need, lsa_ws_bytes(shape, T_lsa));
-        need = max2(need, append_ws_bytes(shape, T_lsa, shape->lsa_q_heads * shape->head_dim));
-        need = max2(need, append_ws_bytes(shape, T_lsa, shape->d_model));
+        need = max2(need, lsa_ws_bytes(shape, T_lsa, true));
+        need = max2(need, append_ws_bytes(shape, T_lsa, shape->lsa_q_heads * shape->head_dim, true));
+        need = max2(need, append_ws_bytes(shape, T_lsa, shape->d_model, true));
         // moa_draft_step: grouped buffers, plus a second scratch region when it runs two branches side by side
-        const GroupLayout L = group_layout(shape, B, M, P_cap, P_cap, T_lsa);
+        const GroupLayout L = group_layout(shape, B, M, P_cap, P_cap, T_lsa, true);
         need = max2(need, L.total() + L.scratch);
     }
     *bytes_host = need;
@@ -941,7 +943,7 @@ struct TliBufs {
     size_t attn_bytes, lin_bytes, total;
 };
 
-static TliBufs tli_carve(const moa_shape_t *s, int32_t d_ff, int32_t B, int32_t Mn, int32_t P_cap, void *ws)
+static TliBufs tli_carve(const moa_shape_t *s, int32_t d_ff, int32_t B, int32_t Mn, int32_t P_cap, void *ws, bool upto = false)
 {
     const int64_t R = (int64_t)B * Mn;
     const size_t es = esize(s->dtype), d = (size_t)s->d_model;
@@ -949,10 +951,10 @@ static TliBufs tli_carve(const moa_shape_t *s, int32_t d_ff, int32_t B, int32_t 
     size_t off = 0;
     // (sizes are measured with ws == NULL: no pointer arithmetic on a null base)
     auto take = [&](size_t bytes) { char *p = ws ? (char *)ws + off : nullptr; off += align256(bytes); return p; };
-    t.attn_bytes = align256(attn_ws_bytes(s, B, Mn, P_cap));
+    t.attn_bytes = align256(attn_ws_bytes(s, B, Mn, P_cap, upto));
     t.attn = take(t.attn_bytes);
-    t.lin_bytes = align256(max2(linear_workspace_bytes(s->dtype, R, s->d_model, 2 * d_ff),
-                                linear_workspace_bytes(s->dtype, R, d_ff, s->d_model)));
+    t.lin_bytes = align256(max2(linear_workspace_bytes(s->dtype, R, s->d_model, 2 * d_ff, upto),
+                                linear_workspace_bytes(s->dtype, R, d_ff, s->d_model, upto)));
     t.lin = take(t.lin_bytes);
     t.n = take((size_t)R * d * es);
     t.tmp = take((size_t)R * d * es);
@@ -970,7 +972,7 @@ int32_t moa_tli_workspace_bytes(const moa_shape_t *shape, const moa_decoder_cfg_
     int32_t rc = check_shape(shape, false);
     if (rc) return rc;
     if (B < 1 || M < 1 || P_cap < 0 || cfg->d_ff < 1) return fail(MOA_ERR_SHAPE, "B=%d M=%d P_cap=%d d_ff=%d", B, M, P_cap, cfg->d_ff);
-    *bytes_host = tli_carve(shape, cfg->d_ff, B, M, P_cap, nullptr).total;
+    *bytes_host = tli_carve(shape, cfg->d_ff, B, M, P_cap, nullptr, true).total;
     return MOA_OK;
 }
 
@@ -1052,13 +1054,13 @@ int32_t moa_tli_decoder_layer(const moa_shape_t *shape, const moa_decoder_cfg_t 
 }
 
 // ---- the drafter's own layers: pre-norm in front of an attention sub-layer, MLP sub-block behind it
-static MlpBufs mlp_carve(int dtype, int64_t R, int d, int d_ff, void *ws, size_t *total)
+static MlpBufs mlp_carve(int dtype, int64_t R, int d, int d_ff, void *ws, size_t *total, bool upto = false)
 {
     const size_t es = esize(dtype);
     MlpBufs b;
     size_t off = 0;
     auto take = [&](size_t bytes) { char *p = ws ? (char *)ws + off : nullptr; off += align256(bytes); return p; };
-    b.lin_bytes = align256(max2(linear_workspace_bytes(dtype, R, d, 2 * d_ff), linear_workspace_bytes(dtype, R, d_ff, d)));
+    b.lin_bytes = align256(max2(linear_workspace_bytes(dtype, R, d, 2 * d_ff, upto), linear_workspace_bytes(dtype, R, d_ff, d, upto)));
     b.lin = take(b.lin_bytes);
     b.n = take((size_t)R * d * es);
     b.tmp = take((size_t)R * d * es);
@@ -1084,7 +1086,7 @@ int32_t moa_mlp_block_workspace_bytes(int32_t dtype, int64_t R, int32_t d, int32
     if (!bytes_host) return fail(MOA_ERR_NULL, "mlp_block_workspace_bytes: NULL pointer");
     int32_t rc = mlp_check("mlp_block_workspace_bytes", dtype, R, d, d_ff, 0.f);
     if (rc) return rc;
-    mlp_carve(dtype, R, d, d_ff, nullptr, bytes_host);
+    mlp_carve(dtype, R, d, d_ff, nullptr, bytes_host, true);
     return MOA_OK;
 }
 
@@ -1131,7 +1133,7 @@ int32_t moa_linear_workspace_bytes(int32_t dtype, int64_t R, int32_t K, int32_t 
     if (!bytes_host) return fail(MOA_ERR_NULL, "linear_workspace_bytes: bytes_host is NULL");
     if (dtype != MOA_F32 && dtype != MOA_BF16) return fail(MOA_ERR_DTYPE, "dtype %d", dtype);
     if (R < 0 || K < 1 || N < 1) return fail(MOA_ERR_SHAPE, "linear_workspace_bytes: R=%lld K=%d N=%d", (long long)R, K, N);
-    *bytes_host = align256(linear_workspace_bytes(dtype, R, K, N));
+    *bytes_host = align256(linear_workspace_bytes(dtype, R, K, N, true));
     return MOA_OK;
 }
 

@@ -1183,13 +1183,26 @@ static SplitGeom split_geometry(int B, int Mq, int H, int Hkv, int dh, int P_cap
     return g;
 }
 
-size_t attn_workspace_bytes(int dtype, int B, int Mq, int H, int Hkv, int dh, int P_cap)
+size_t attn_workspace_bytes(int dtype, int B, int Mq, int H, int Hkv, int dh, int P_cap, bool upto)
 {
     if (!mfma_ok(dtype, dh, nullptr)) return 0;
+    const size_t row_bytes = (size_t)dh * sizeof(f16_t) + 2 * sizeof(float);
+    if (upto) {
+        // Neither fewer rows nor fewer sequences always need less (they leave room for more key slices), so this is a bound
+        // that grows with every size.  `units` row tiles of 128 take at most max(units, min(512, units * most)) slices; the
+        // 256-row form never takes more rows than those and none for one slice, which leaves its sizes the one-tile calls.
+        const int RG = (H / Hkv) * Mq;
+        const int64_t units = (int64_t)B * Hkv * ((RG + 127) / 128), alone = long_form(RG, dh) ? (int64_t)B * Hkv : units;
+        int64_t most = ((P_cap + KT - 1) / KT) / 2;
+        most = most < 1 ? 1 : most > 64 ? 64 : most;
+        int64_t slices = units * most < 512 ? units * most : 512;
+        if (slices < alone) slices = alone;
+        return (size_t)slices * 128 * ATTN_NBLK * row_bytes + 256;
+    }
     const SplitGeom g = split_geometry(B, Mq, H, Hkv, dh, P_cap);
     if (g.nsplit == 1 && long_form((H / Hkv) * Mq, dh)) return 256;
     const size_t rows = (size_t)B * Hkv * g.nsplit * g.rows_pad;
-    return rows * ((size_t)dh * sizeof(f16_t) + 2 * sizeof(float)) + 256;
+    return rows * row_bytes + 256;
 }
 
 static hipError_t launch_attn_generic(const AttnArgs &a, hipStream_t stream)

@@ -271,8 +271,9 @@ const char *linear_bf16_name(int variant);
 // the single-precision kernels behind launch_linear (moa_gemm_f32.hip): operands they can read, and the launch
 bool linear_f32_ok(int dtype, const LinArgs &a);
 hipError_t launch_linear_f32(int dtype, const LinArgs &a, hipStream_t stream);
-// scratch for the sums of K slices of a projection of R rows and ntot output features in total (0 = K is not cut)
-size_t linear_workspace_bytes(int dtype, int64_t R, int K, int ntot);
+// scratch for the sums of K slices of a projection of R rows and ntot output features in total (0 = K is not cut);
+// upto: the most that any row count from 1 to R asks for
+size_t linear_workspace_bytes(int dtype, int64_t R, int K, int ntot, bool upto = false);
 
 // dst(store spec) = X, element by element (NULL-weight projections that still change layout)
 hipError_t launch_scatter_copy(int dtype, const void *X, int64_t R, int N, int64_t ldx, const StoreSpec &st,
@@ -310,7 +311,8 @@ struct AttnArgs {
     void *ws;
     size_t ws_bytes;
 };
-size_t attn_workspace_bytes(int dtype, int B, int Mq, int H, int Hkv, int dh, int P_cap);
+// scratch for the partial results of a split key range; upto: at least what any call with sizes up to these asks for
+size_t attn_workspace_bytes(int dtype, int B, int Mq, int H, int Hkv, int dh, int P_cap, bool upto = false);
 hipError_t launch_attn(const AttnArgs &a, hipStream_t stream);
 // Two independent cores of the same shape (cross-attention and one verification layer) in one launch; P_cap may
 // differ, each call's ws must hold attn_workspace_bytes for the larger one.  Falls back to two launches.

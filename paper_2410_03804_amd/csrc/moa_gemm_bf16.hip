@@ -227,14 +227,22 @@ static size_t partial_bytes(int64_t R, int ntot, int splits)
 }
 
 // (for one segment; several make about the same plan, and one that needs more room than there is is not cut)
-size_t linear_workspace_bytes(int dtype, int64_t R, int K, int ntot)
+size_t linear_workspace_bytes(int dtype, int64_t R, int K, int ntot, bool upto)
 {
-    if (dtype != DT_BF16 || R < 1 || R > 192 || K % 128 || ntot % 64) return 0;
+    if (dtype != DT_BF16 || R < 1 || K % 128 || ntot % 64) return 0;
     size_t most = 0;
-    for (int epi : {(int)LinArgs::EPI_NONE, (int)LinArgs::EPI_ADD_NORM, (int)LinArgs::EPI_SWIGLU}) {
-        const size_t n = partial_bytes(R, ntot, plan_gemm(R, K, &ntot, 1, epi, false, false).splits);
+    auto ask = [&](int64_t r) {
+        if (r > 192 || r > R) return;
+        // (of all epilogues EPI_ADD_NORM counts most against not splitting, and none changes which split is the best one)
+        const size_t n = partial_bytes(r, ntot, plan_gemm(r, K, &ntot, 1, LinArgs::EPI_ADD_NORM, false, false).splits);
         if (n > most) most = n;
-    }
+    };
+    ask(R);
+    // Between the row counts where some tile needs one more of itself, all that grows with the rows is the price of a
+    // slice, so the fewest rows are cut into the most slices, and all have as many 64-row tiles of sums (those of 129 rows
+    // or more: three).
+    if (upto)
+        for (int64_t r : {1, 33, 65, 129}) ask(r);
     return most;
 }
 
