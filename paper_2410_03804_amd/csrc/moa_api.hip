@@ -595,7 +595,7 @@ static int32_t attn_stage_project(const char *who, const moa_shape_t *shape, con
     la.ldx = d;
     la.ws = bf.scratch_p;
     la.ws_bytes = bf.scratch_p_bytes;
-    la.same_sums = tree && !t_sites;          // verification: a step may launch this layer together with others
+    la.same_sums = t_sites ? 0 : LinArgs::SAME_SUMS_IN;      // cross-attention, verification: a step may group them
     *q_out = x;
     if (wq) {
         la.seg[la.nseg].W = wq;
@@ -701,6 +701,7 @@ static int32_t attn_stage_core(const char *who, const moa_shape_t *shape, const 
         lo.seg[0].ldx = 0;
         lo.ws = bf.scratch_c;
         lo.ws_bytes = bf.scratch_c_bytes;
+        lo.same_sums = t_sites ? 0 : LinArgs::SAME_SUMS_OUT;
         if (norm) {                          // the block's residual and next norm on the way out (a reused decoder layer)
             lo.epi = LinArgs::EPI_ADD_NORM;
             lo.norm = *norm;
@@ -1267,7 +1268,7 @@ static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, v
     la.ldx = d;
     la.ws = scr;
     la.ws_bytes = scr_bytes;
-    la.same_sums = true;
+    la.same_sums = LinArgs::SAME_SUMS_IN;
     if (which & 1) {
         LinSeg &q = la.seg[la.nseg++];
         q.W = a->ca_wq;
@@ -1452,6 +1453,7 @@ static int32_t piece_oproj(const moa_step_args_t *a, const StepBufs &bf, int whi
     lo.ldx = e;
     lo.ws = scr;
     lo.ws_bytes = scr_bytes;
+    lo.same_sums = LinArgs::SAME_SUMS_OUT;
     if (which & 1) lo.seg[lo.nseg++] = oproj_seg(sh, bf.h_ca, a->ca_wo, a->ca_out);
     if (which & 2) lo.seg[lo.nseg++] = oproj_seg(sh, bf.h_v, a->v_wo_host[0], a->v_out_host[0]);
     lo.X = lo.seg[0].X;

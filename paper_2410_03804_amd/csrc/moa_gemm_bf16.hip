@@ -179,13 +179,10 @@ struct GemmPlan { int tile, splits; };
 // 8192); slices only for a long K with few features (60 x 14336 x 4096: four, 30 us against 68).  A pass of its own behind
 // an unsplit projection (`pass_us`) counts against not splitting, since the sum over slices does that work on the way.
 //
-// same_sums: pairs of K groups up to 32 rows, and up to 64 where K is at most 4096; one group else; no slices, whatever
-// the features.  60 x 4096: 6144 features, a verification layer of its own, 18.7 us against 23.6 with one group (96 tiles
-// of 64 x 64), a step with 32 such layers 1845 -> 1733; the grouped launch of 10240 26.7 against 25.2.  Beyond K = 4096
-// a tile of 64 x 64 pairs per compute unit runs out of compute units first (18432 features at K = 8192).
-static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi, bool in_order, bool same_sums)
+// same_sums: pairs of K groups up to that many rows, one group beyond; no slices, whatever the features.
+static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi, bool in_order, int same_sums)
 {
-    if (same_sums && (R > 64 || (R > 32 && K > 4096) || K % 128)) in_order = true;
+    if (same_sums && R > same_sums) in_order = true;
     GemmPlan best = {0, 1};
     int ntot = 0;
     for (int s = 0; s < nseg; ++s) ntot += n_seg[s];
@@ -234,7 +231,7 @@ size_t linear_workspace_bytes(int dtype, int64_t R, int K, int ntot, bool upto)
     auto ask = [&](int64_t r) {
         if (r > 192 || r > R) return;
         // (of all epilogues EPI_ADD_NORM counts most against not splitting, and none changes which split is the best one)
-        const size_t n = partial_bytes(r, ntot, plan_gemm(r, K, &ntot, 1, LinArgs::EPI_ADD_NORM, false, false).splits);
+        const size_t n = partial_bytes(r, ntot, plan_gemm(r, K, &ntot, 1, LinArgs::EPI_ADD_NORM, false, 0).splits);
         if (n > most) most = n;
     };
     ask(R);

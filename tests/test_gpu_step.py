@@ -143,6 +143,33 @@ def test_schedules_agree(G, case):
                 assert torch.equal(a, b), name
 
 
+def _wide(rows, **kw):
+    return mi.Config(**dict(dict(name=f"W{rows}", index=17, dtype="bf16", B=1, P_min=140, P_max=140, M=rows, D=5, max_branch=4, L=2,
+                                 d=4096, H=32, Hkv=8, dh=128, d_lsa_in=2048, rms_norm=True), **kw))
+
+
+@pytest.mark.parametrize("cfg", [
+    # row counts on both sides of where the projections' sums change their order, at widths where a launch of one matrix
+    # and one of several would choose differently if they were free to
+    _wide(9), _wide(60), _wide(111), _wide(130), _wide(33, d=8192, H=64)], ids=lambda c: f"{c.dtype}-{c.B}x{c.M}x{c.d}")
+def test_schedules_give_the_same_bits(G, cfg):
+    """Where every schedule runs the attention cores over the whole key range, nothing is left that could differ: the sums
+    along K are in one order however a schedule groups the projections."""
+    from paper_2410_03804_amd.workload import DeviceStep
+    work = mi.step_workload(cfg, n_verify_layers=2)
+    ref = None
+    for name in ("sequential", "grouped", "two_stream"):
+        print(f"[case] same bits {cfg.name} {cfg.dtype} {name}", flush=True)
+        step = DeviceStep(work, fold=False)
+        step.run(schedule=SCHEDULES[name])
+        torch.cuda.synchronize()
+        assert step.dev_status.item() == 0
+        out = [t for group in _step_outputs(step) for t in group]
+        ref = ref or out
+        for i, (a, b) in enumerate(zip(ref, out)):
+            assert torch.equal(a, b), (name, i)
+
+
 @pytest.mark.parametrize("case", ["small_bf16", "C1_bf16", "C0_f32"])
 def test_folded_memory_projection_agrees_with_the_two_projections(G, case):
     """With ca_wk lsa_wo and ca_wv lsa_wo folded once, the memory's new rows come straight from LSA's mean-folded heads
