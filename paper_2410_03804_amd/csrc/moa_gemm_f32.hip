@@ -216,7 +216,8 @@ bool linear_f32_ok(int dtype, const LinArgs &a)
 }
 
 // 64 x 64 tiles once there are enough of them to keep the chip's matrix pipes busy; below that a workgroup's own chain
-// of k tiles is what a launch costs, and 16 x 16 tiles spread it over sixteen times as many workgroups.
+// of k tiles is what a launch costs, and 16 x 16 tiles spread it over sixteen times as many workgroups.  Launches that a
+// step groups in one way or another (LinArgs::same_sums) count twice their widest segment: a layer's Q/K/V.
 constexpr int64_t F32_TILE_MIN_WORKGROUPS = 128;
 
 hipError_t launch_linear_f32(int dtype, const LinArgs &a, hipStream_t stream)
@@ -224,12 +225,15 @@ hipError_t launch_linear_f32(int dtype, const LinArgs &a, hipStream_t stream)
     F32Args fa;
     fa.a = a;
     const size_t piece = dtype == DT_BF16 ? 8 : 16;
-    int64_t t64 = 0;
+    int64_t t64 = 0, widest = 0;
     for (int s = 0; s < a.nseg; ++s) {
         const StoreSpec &st = a.seg[s].st;
         fa.vec[s] = aligned_to(st.dst, piece) && (st.mode == StoreSpec::ROW ? st.ld % 4 == 0 : st.dh % 4 == 0);
-        t64 += (a.seg[s].N + 63) / 64;
+        const int64_t n = (a.seg[s].N + 63) / 64;
+        t64 += n;
+        if (n > widest) widest = n;
     }
+    if (a.same_sums) t64 = 2 * widest;
     const bool big = t64 * ((a.R + 63) / 64) >= F32_TILE_MIN_WORKGROUPS;
     const int edge = big ? 64 : 16;
     int t = 0;
