@@ -104,9 +104,10 @@ size_t lsa_ws_bytes(const moa_shape_t *s, int64_t T, bool upto = false)
 {
     const int64_t tc = T < LSA_CHUNK ? T : LSA_CHUNK, ob = T < LSA_OBLOCK ? T : LSA_OBLOCK;
     const size_t eq = (size_t)s->lsa_q_heads * s->head_dim, ekv = (size_t)s->lsa_kv_heads * s->head_dim;
+    const int ekv_ca = s->n_kv_heads * s->head_dim;
     // the output projection may carry the memory's folded K/V projections as two more segments (draft step)
-    size_t lin = linear_workspace_bytes(s->dtype, ob, (int)eq, (int)(eq + 2 * (size_t)s->n_kv_heads * s->head_dim), upto);
-    lin = max2(lin, linear_workspace_bytes(s->dtype, ob, (int)eq, (int)eq, upto));
+    size_t lin = linear_workspace_bytes(s->dtype, ob, (int)eq, {(int)eq, ekv_ca, ekv_ca}, upto);
+    lin = max2(lin, linear_workspace_bytes(s->dtype, ob, (int)eq, {(int)eq}, upto));
     return align256((size_t)tc * s->n_layers * (eq + 2 * ekv) * esize(s->dtype)) + align256((size_t)ob * eq * esize(s->dtype)) +
            align256(lin);
 }
@@ -117,11 +118,16 @@ size_t attn_scratch_bytes(const moa_shape_t *s, int B, int Mq, int P_cap, bool t
     const int e = s->n_q_heads * s->head_dim, ekv = s->n_kv_heads * s->head_dim;
     const int64_t R = (int64_t)B * Mq;
     size_t n = attn_workspace_bytes(s->dtype, B, Mq, s->n_q_heads, s->n_kv_heads, s->head_dim, P_cap, upto);
-    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, e + (tree ? 2 * ekv : 0), upto));
-    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, e, upto));
-    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, 2 * ekv, upto));
-    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, ekv, upto));
-    n = max2(n, linear_workspace_bytes(s->dtype, R, e, s->d_model, upto));
+    // (any of the projections may be missing: a NULL weight)
+    auto room = [&](int K, std::initializer_list<int> seg) { n = max2(n, linear_workspace_bytes(s->dtype, R, K, seg, upto)); };
+    room(s->d_model, {e});
+    if (tree) {
+        room(s->d_model, {e, ekv, ekv});
+        room(s->d_model, {e, ekv});
+        room(s->d_model, {ekv, ekv});
+        room(s->d_model, {ekv});
+    }
+    room(e, {s->d_model});
     return align256(n);
 }
 
@@ -134,7 +140,7 @@ size_t attn_ws_bytes(const moa_shape_t *s, int B, int Mq, int P_cap, bool upto =
 size_t append_ws_bytes(const moa_shape_t *s, int64_t T, int d_mem, bool upto = false)
 {
     const int ekv = s->n_kv_heads * s->head_dim;
-    return align256(max2(linear_workspace_bytes(s->dtype, T, d_mem, 2 * ekv, upto), linear_workspace_bytes(s->dtype, T, d_mem, ekv, upto)));
+    return align256(max2(linear_workspace_bytes(s->dtype, T, d_mem, {ekv, ekv}, upto), linear_workspace_bytes(s->dtype, T, d_mem, {ekv}, upto)));
 }
 
 // workspace split of the grouped step:
@@ -154,8 +160,8 @@ GroupLayout group_layout(const moa_shape_t *s, int B, int M, int P_cap, int ca_P
     const int cap = P_cap > ca_P_cap ? P_cap : ca_P_cap;
     L.attn_each = align256(attn_workspace_bytes(s->dtype, B, M, s->n_q_heads, s->n_kv_heads, s->head_dim, cap, upto));
     size_t n = 2 * L.attn_each;
-    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, 2 * e + 2 * ekv, upto));
-    n = max2(n, linear_workspace_bytes(s->dtype, R, e, 2 * s->d_model, upto));
+    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, {e, e, ekv, ekv}, upto));
+    n = max2(n, linear_workspace_bytes(s->dtype, R, e, {s->d_model, s->d_model}, upto));
     n = max2(n, attn_ws_bytes(s, B, M, P_cap, upto));                       // verification layers after the first
     n = max2(n, attn_ws_bytes(s, B, M, ca_P_cap, upto));
     if (T > 0) {
@@ -954,8 +960,8 @@ static TliBufs tli_carve(const moa_shape_t *s, int32_t d_ff, int32_t B, int32_t 
     auto take = [&](size_t bytes) { char *p = ws ? (char *)ws + off : nullptr; off += align256(bytes); return p; };
     t.attn_bytes = align256(attn_ws_bytes(s, B, Mn, P_cap, upto));
     t.attn = take(t.attn_bytes);
-    t.lin_bytes = align256(max2(linear_workspace_bytes(s->dtype, R, s->d_model, 2 * d_ff, upto),
-                                linear_workspace_bytes(s->dtype, R, d_ff, s->d_model, upto)));
+    t.lin_bytes = align256(max2(linear_workspace_bytes(s->dtype, R, s->d_model, {d_ff, d_ff}, upto),
+                                linear_workspace_bytes(s->dtype, R, d_ff, {s->d_model}, upto)));
     t.lin = take(t.lin_bytes);
     t.n = take((size_t)R * d * es);
     t.tmp = take((size_t)R * d * es);
@@ -1061,7 +1067,7 @@ static MlpBufs mlp_carve(int dtype, int64_t R, int d, int d_ff, void *ws, size_t
     MlpBufs b;
     size_t off = 0;
     auto take = [&](size_t bytes) { char *p = ws ? (char *)ws + off : nullptr; off += align256(bytes); return p; };
-    b.lin_bytes = align256(max2(linear_workspace_bytes(dtype, R, d, 2 * d_ff, upto), linear_workspace_bytes(dtype, R, d_ff, d, upto)));
+    b.lin_bytes = align256(max2(linear_workspace_bytes(dtype, R, d, {d_ff, d_ff}, upto), linear_workspace_bytes(dtype, R, d_ff, {d}, upto)));
     b.lin = take(b.lin_bytes);
     b.n = take((size_t)R * d * es);
     b.tmp = take((size_t)R * d * es);
@@ -1134,7 +1140,7 @@ int32_t moa_linear_workspace_bytes(int32_t dtype, int64_t R, int32_t K, int32_t 
     if (!bytes_host) return fail(MOA_ERR_NULL, "linear_workspace_bytes: bytes_host is NULL");
     if (dtype != MOA_F32 && dtype != MOA_BF16) return fail(MOA_ERR_DTYPE, "dtype %d", dtype);
     if (R < 0 || K < 1 || N < 1) return fail(MOA_ERR_SHAPE, "linear_workspace_bytes: R=%lld K=%d N=%d", (long long)R, K, N);
-    *bytes_host = align256(linear_workspace_bytes(dtype, R, K, N, true));
+    *bytes_host = align256(linear_workspace_bytes(dtype, R, K, {N}, true));
     return MOA_OK;
 }
 

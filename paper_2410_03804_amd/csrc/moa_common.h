@@ -5,6 +5,8 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 namespace moa {
 
 typedef uint16_t bf16_t;
@@ -278,9 +280,9 @@ const char *linear_bf16_name(int variant);
 // the single-precision kernels behind launch_linear (moa_gemm_f32.hip): operands they can read, and the launch
 bool linear_f32_ok(int dtype, const LinArgs &a);
 hipError_t launch_linear_f32(int dtype, const LinArgs &a, hipStream_t stream);
-// scratch for the sums of K slices of a projection of R rows and ntot output features in total (0 = K is not cut);
+// scratch for the sums of K slices of a launch of R rows on matrices of n output features each (0 = K is not cut);
 // upto: the most that any row count from 1 to R asks for
-size_t linear_workspace_bytes(int dtype, int64_t R, int K, int ntot, bool upto = false);
+size_t linear_workspace_bytes(int dtype, int64_t R, int K, std::initializer_list<int> n, bool upto = false);
 
 // dst(store spec) = X, element by element (NULL-weight projections that still change layout)
 hipError_t launch_scatter_copy(int dtype, const void *X, int64_t R, int N, int64_t ldx, const StoreSpec &st,

@@ -180,12 +180,16 @@ struct GemmPlan { int tile, splits; };
 // an unsplit projection (`pass_us`) counts against not splitting, since the sum over slices does that work on the way.
 //
 // same_sums: pairs of K groups up to that many rows, one group beyond; no slices, whatever the features.
-static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi, bool in_order, int same_sums)
+static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi, bool in_order, int same_sums, int most_splits = 4)
 {
     if (same_sums && R > same_sums) in_order = true;
     GemmPlan best = {0, 1};
     int ntot = 0;
-    for (int s = 0; s < nseg; ++s) ntot += n_seg[s];
+    for (int s = 0; s < nseg; ++s) {
+        ntot += n_seg[s];
+        if (n_seg[s] % 64) most_splits = 1;        // the pass over the sums takes features in 64s
+    }
+    if (in_order || same_sums || R > 192) most_splits = 1;
     float best_us = 3.4e38f;
     const float stream_us = 6.f + 2.f * (float)K * (float)ntot / 5.8e6f;
     for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
@@ -194,8 +198,8 @@ static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi,
         int64_t tiles = 0;
         for (int s = 0; s < nseg; ++s) tiles += (n_seg[s] + t.bn - 1) / t.bn;
         tiles *= (R + t.bm - 1) / t.bm;
-        for (int splits = 1; splits <= 4; splits *= 2) {
-            if (splits > 1 && (in_order || same_sums || R > 192 || ntot % 64 || K % (64 * t.wk * splits) || K / (64 * t.wk * splits) < 8)) break;
+        for (int splits = 1; splits <= most_splits; splits *= 2) {
+            if (splits > 1 && (K % (64 * t.wk * splits) || K / (64 * t.wk * splits) < 8)) break;
             const int64_t n = tiles * splits;
             float per;                             // k-tile times of one compute unit
             if (t.us2 > 0.f) {
@@ -223,15 +227,16 @@ static size_t partial_bytes(int64_t R, int ntot, int splits)
     return splits > 1 ? (size_t)((R + 63) / 64) * splits * 64 * (size_t)ntot * sizeof(float) : 0;
 }
 
-// (for one segment; several make about the same plan, and one that needs more room than there is is not cut)
-size_t linear_workspace_bytes(int dtype, int64_t R, int K, int ntot, bool upto)
+size_t linear_workspace_bytes(int dtype, int64_t R, int K, std::initializer_list<int> n_seg, bool upto)
 {
-    if (dtype != DT_BF16 || R < 1 || K % 128 || ntot % 64) return 0;
+    if (dtype != DT_BF16 || R < 1 || K % 128) return 0;
+    int ntot = 0;
+    for (int n : n_seg) ntot += n;
     size_t most = 0;
     auto ask = [&](int64_t r) {
         if (r > 192 || r > R) return;
         // (of all epilogues EPI_ADD_NORM counts most against not splitting, and none changes which split is the best one)
-        const size_t n = partial_bytes(r, ntot, plan_gemm(r, K, &ntot, 1, LinArgs::EPI_ADD_NORM, false, 0).splits);
+        const size_t n = partial_bytes(r, ntot, plan_gemm(r, K, n_seg.begin(), (int)n_seg.size(), LinArgs::EPI_ADD_NORM, false, 0).splits);
         if (n > most) most = n;
     };
     ask(R);
@@ -247,14 +252,15 @@ size_t linear_workspace_bytes(int dtype, int64_t R, int K, int ntot, bool upto)
 hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused, int *splits)
 {
     int ntot = 0, n_seg[4] = {};
-    bool all64 = true;
     for (int s = 0; s < a.nseg; ++s) {
         n_seg[s] = a.seg[s].N;
         ntot += a.seg[s].N;
-        all64 = all64 && a.seg[s].N % 64 == 0;
     }
     GemmPlan p = plan_gemm(a.R, a.K, n_seg, a.nseg, a.epi, a.in_order, a.same_sums);
-    if (p.splits > 1 && !(all64 && a.ws && a.ws_bytes >= partial_bytes(a.R, ntot, p.splits) && (((uintptr_t)a.ws) & 15) == 0)) p.splits = 1;
+    // without room for the sums of slices another tile may be the best one (64 x 14336 x 4096: 52 us in 64 x 32 against
+    // 71 in the 64 x 64 of four slices)
+    if (p.splits > 1 && !(a.ws && a.ws_bytes >= partial_bytes(a.R, ntot, p.splits) && (((uintptr_t)a.ws) & 15) == 0))
+        p = plan_gemm(a.R, a.K, n_seg, a.nseg, a.epi, a.in_order, a.same_sums, 1);
     const GemmTile &t = kTiles[p.tile];
     GemmArgs ga;
     ga.a = a;

@@ -64,6 +64,31 @@ def test_gemm_tile_edges(G, moa, R, K, N):
     assert (diff.norm() / want.norm()).item() <= 2.0 ** -9
 
 
+@pytest.mark.parametrize("R,K,N", [(64, 14336, 4096), (129, 12288, 1024)])
+def test_without_a_workspace_the_plan_is_made_for_whole_k(G, moa, R, K, N):
+    """The tile that is best for several K slices leaves most of the chip idle when there is no room for their sums: without
+    a workspace another kernel runs, with the same result."""
+    g = torch.Generator().manual_seed(R)
+    x, w = torch.randn(R, K, generator=g).bfloat16().cuda(), (torch.randn(N, K, generator=g) / K ** 0.5).bfloat16().cuda()
+    ws = torch.empty(moa.linear_workspace_bytes(moa.BF16, R, K, N), dtype=torch.uint8, device="cuda")
+    assert ws.numel() > 0                                     # K is cut
+    out, kernels = [], []
+    for room in (ws, None):
+        print(f"[case] linear bf16 R={R} K={K} N={N} workspace={room is not None}", flush=True)
+        y = torch.full((R, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        moa.profile_enable(True)
+        try:
+            moa.linear(x, w, y, room)
+            torch.cuda.synchronize()
+            kernels.append({k for _, k, _, _ in moa.profile_collect()})
+        finally:
+            moa.profile_enable(False)
+        out.append(y.float())
+    assert len(kernels[0]) == 2 and len(kernels[1]) == 1 and not kernels[1] <= kernels[0], kernels
+    # each within one bf16 rounding of the product (see above)
+    assert (out[0] - out[1]).abs().max().item() <= 2.0 ** -7 * out[0].abs().max().item()
+
+
 @pytest.mark.parametrize("R,d,d_ff", [(7, 512, 96), (33, 256, 2080), (64, 1024, 7200), (100, 512, 608), (260, 384, 1056)])
 def test_mlp_block_ragged_sizes(G, moa, oracle, R, d, d_ff):
     rng = np.random.default_rng(R + d + d_ff)
