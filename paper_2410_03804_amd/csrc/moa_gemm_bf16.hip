@@ -144,13 +144,13 @@ __global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(GemmArgs ga)
 // one workgroup on a compute unit, with a second one on up to half of them, and with two on all (0: its LDS holds one),
 // measured over 1 .. 4096 rows, K 2048 .. 14336 and 4096 .. 128256 features.
 #define MOA_GEMM_TILES(T)                                     \
-    T(0, 1, 1, 1, 1, 5, 5, 2, 0.25f, 0.40f, 0.40f)            \
+    T(0, 1, 1, 1, 1, 5, 5, 2, 0.25f, 0.34f, 0.34f)            \
     T(1, 1, 1, 1, 1, 2, 3, 4, 0.55f, 0.66f, 0.66f)            \
     T(2, 1, 1, 1, 2, 3, 3, 2, 0.45f, 0.74f, 0.74f)            \
-    T(3, 2, 1, 1, 1, 3, 4, 2, 0.42f, 0.75f, 0.75f)            \
+    T(3, 2, 1, 1, 1, 3, 4, 2, 0.44f, 0.75f, 0.75f)            \
     T(4, 2, 2, 1, 1, 4, 6, 1, 0.27f, 0.33f, 0.46f)            \
     T(5, 2, 2, 1, 2, 3, 3, 2, 0.88f, 0.f, 0.f)                \
-    T(6, 4, 2, 1, 2, 4, 4, 1, 0.55f, 0.f, 0.f)                \
+    T(6, 4, 2, 1, 2, 4, 4, 1, 0.57f, 0.f, 0.f)                \
     T(7, 4, 1, 1, 5, 4, 4, 1, 0.72f, 0.f, 0.f)                \
     T(8, 4, 2, 2, 2, 3, 4, 1, 0.90f, 0.f, 0.f)                \
     T(9, 8, 1, 1, 5, 3, 3, 1, 1.12f, 0.f, 0.f)                \
@@ -172,15 +172,17 @@ static const GemmTile kTiles[] = {MOA_GEMM_TILES(MOA_GEMM_INFO)};
 struct GemmPlan { int tile, splits; };
 
 // The tile, and into how many slices K is cut, by an estimate of the time: rounds of workgroups over 256 compute units at
-// the measured time per k tile, or the weights at 5.8 TB/s, whichever is longer; slices cost a pass over their sums.
-// Against the best tile of each of 191 measured shapes the choice is 1 % slower on average.  What it comes to: up to 32
+// the measured time per k tile, or the weights at 5.8 TB/s, whichever is longer; slices cost a pass over their sums.  An XCD
+// gets whole feature tiles, so a round is full when its share of them fills its 32 compute units (1600 x 8192 x 9216 in
+// 256 x 256: 252 workgroups, 35 of them on seven XCDs each, 355 us against 232 in 256 x 128).  Against the best tile of each
+// of 693 measured calls (33 shapes, weights from memory) the choice is 1.3 % slower on average.  What it comes to: up to 32
 // rows the 32-row tiles; up to some hundred the 64-row ones; with more, the largest tile that still gives every compute
 // unit one (1024 x 4096: 256 x 160 for 10240 features, 77.6 us against 98 - 108 with the tiles next to it, 256 x 128 for
-// 8192); slices only for a long K with few features (60 x 14336 x 4096: four, 30 us against 68).  A pass of its own behind
-// an unsplit projection (`pass_us`) counts against not splitting, since the sum over slices does that work on the way.
+// 8192); slices only for a long K with few features (60 x 14336 x 4096: four, 30 us against 52).  A pass of its own behind
+// an unsplit projection counts against not splitting, since the sum over slices does that work on the way.
 //
 // same_sums: pairs of K groups up to that many rows, one group beyond; no slices, whatever the features.
-static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi, bool in_order, int same_sums, int most_splits = 4)
+static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi, bool in_order, int same_sums, int most_splits = 8)
 {
     if (same_sums && R > same_sums) in_order = true;
     GemmPlan best = {0, 1};
@@ -190,22 +192,28 @@ static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi,
         if (n_seg[s] % 64) most_splits = 1;        // the pass over the sums takes features in 64s
     }
     if (in_order || same_sums || R > 192) most_splits = 1;
+    else if (R > 64 && most_splits > 4) most_splits = 4;       // eight pay off where the sums are few (64 x 4096 x 1024: 9.7 against 10.5 us)
     float best_us = 3.4e38f;
     const float stream_us = 6.f + 2.f * (float)K * (float)ntot / 5.8e6f;
     for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
         const GemmTile &t = kTiles[i];
         if (in_order ? t.wk > 1 : ((t.bm == 32) != (R <= 32) || K % (64 * t.wk) != 0 || (same_sums && t.wk != 2))) continue;
+        const int64_t row_tiles = (R + t.bm - 1) / t.bm;
         int64_t tiles = 0;
         for (int s = 0; s < nseg; ++s) tiles += (n_seg[s] + t.bn - 1) / t.bn;
-        tiles *= (R + t.bm - 1) / t.bm;
+        tiles = (tiles + 7) / 8 * 8 * row_tiles;
+        // two 64 x 64 workgroups of one row tile share nothing, and take as long as one after the other (60 x 8192 x 18432:
+        // 0.63 us per k tile where two row tiles of the same weights take 0.38)
+        const bool apart = t.bm == 64 && t.bn == 64 && row_tiles == 1;
+        const float us_mid = apart ? 0.60f : t.us_mid, us2 = apart ? 0.65f : t.us2;
         for (int splits = 1; splits <= most_splits; splits *= 2) {
-            if (splits > 1 && (K % (64 * t.wk * splits) || K / (64 * t.wk * splits) < 8)) break;
+            if (splits > 1 && (K % (64 * t.wk * splits) || K / (64 * t.wk * splits) < 4)) break;
             const int64_t n = tiles * splits;
             float per;                             // k-tile times of one compute unit
             if (t.us2 > 0.f) {
                 const int64_t rest = n % 512;
-                per = (float)(n / 512) * t.us2;
-                if (rest) per += rest <= 256 ? t.us1 : rest <= 384 ? t.us_mid : t.us2;
+                per = (float)(n / 512) * us2;
+                if (rest) per += rest <= 256 ? t.us1 : rest <= 384 ? us_mid : us2;
             } else {
                 per = (float)((n + 255) / 256) * t.us1;
             }
