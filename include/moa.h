@@ -382,8 +382,8 @@ int32_t moa_fold_projection(int32_t dtype, const void *w_outer, const void *w_in
  *    per stage, exactly as the single entry points would.
  * Integer results are identical under all three; floating-point results of 0 and 1 are
  * bit-identical (without the Self-Attention layer), those of 2, and of 1 with that layer, differ from
- * them only where the two attention cores end up with a different number of key slices (partials
- * merged in another order). */
+ * them only where the two attention cores end up with a different number of key slices or row tiles of
+ * another height (partials merged in another order). */
 enum { MOA_SCHED_GROUPED = 0, MOA_SCHED_TWO_STREAM = 1, MOA_SCHED_SEQUENTIAL = 2 };
 
 typedef struct {
@@ -453,13 +453,14 @@ const char *moa_profile_site_name(int32_t site);
 /* Testing aid (not part of the method).  The attention core of moa_cross_attn_draft, moa_tree_verify_attn,
  * moa_self_attn_draft, moa_tli_decoder_layer and moa_draft_step has two matrix-core forms for bf16 with head_dim 64
  * or 128 and picks one from the call's shape: one workgroup per 32 query rows walking the whole key range (short key
- * ranges, few workgroups) or the key range split over workgroups with a merging pass (everything else).  Both compute
- * the attention of Sec. 2.2 / 3.1.2; they differ in the order partial sums are merged.  This call forces one of them
+ * ranges, few workgroups) or the key range split over workgroups with a merging pass (everything else), these with
+ * 128 or 256 query rows each.  All compute the attention of Sec. 2.2 / 3.1.2; they differ in the order partial sums
+ * are merged.  MOA_ATTN_KERNEL_SPLIT_WIDE forces 256 rows where there are more than 128 at head_dim 128.  This call forces one of them
  * for every later call of the process (MOA_ATTN_KERNEL_AUTO restores the choice by shape) so that a parity test can
  * run each case through both.  A forced form that a call cannot take (fp32, other head_dim, workspace too small for
  * the split form) falls back as the automatic choice would.  Host only, launches nothing; MOA_ERR_SHAPE for another
  * value.  Not thread-safe against calls in flight on other host threads (they see either value). */
-enum { MOA_ATTN_KERNEL_AUTO = 0, MOA_ATTN_KERNEL_WHOLE = 1, MOA_ATTN_KERNEL_SPLIT = 2 };
+enum { MOA_ATTN_KERNEL_AUTO = 0, MOA_ATTN_KERNEL_WHOLE = 1, MOA_ATTN_KERNEL_SPLIT = 2, MOA_ATTN_KERNEL_SPLIT_WIDE = 3 };
 int32_t moa_debug_force_attn_kernel(int32_t form);
 
 /* The same for the Layer Self-Attention (moa_lsa, moa_draft_step): for bf16 with head_dim 128, at most 96 layers, an

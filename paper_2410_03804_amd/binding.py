@@ -679,7 +679,7 @@ def profile_enable(on: bool, only_kernel: str | None = None, every: int = 1):
     _check(_lib.moa_profile_enable(1 if on else 0, -1 if only_kernel is None else profile_kernel_id(only_kernel)))
 
 
-ATTN_KERNEL = {"auto": 0, "whole": 1, "split": 2}
+ATTN_KERNEL = {"auto": 0, "whole": 1, "split": 2, "split_wide": 3}
 
 
 def debug_force_attn_kernel(form: str = "auto"):

@@ -16,8 +16,8 @@
 //                    lane owns one query column and the softmax max/sum need a single cross-lane
 //                    exchange; P^T feeds the second MFMA straight from registers and V^T comes out of
 //                    the LDS transpose read.
-//   k_attn_long      the same split with 256 query rows per workgroup, for more than 128 rows per (sequence, KV
-//                    head) at head_dim 128.  Described at the kernel.
+//   k_attn_long      the same split with 256 query rows per workgroup at head_dim 128, where that is faster (see
+//                    split_geometry).  Described at the kernel.
 //   k_attn_merge     combines the per-slice (max, sum, accumulator) triples.
 #include "moa_common.h"
 #include "moa_gemm_device.h"
@@ -25,13 +25,14 @@
 
 #include <math.h>
 
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
 namespace moa {
 
 // which MFMA form the attention core takes: 0 = chosen from the call's shape, 1 = whole key range per workgroup,
-// 2 = split-KV + merge (moa_debug_force_attn_kernel; process-wide, read once per launch)
+// 2 = split-KV + merge, 3 = that in 256-row tiles (moa_debug_force_attn_kernel; process-wide, read once per launch)
 static std::atomic<int> g_attn_form{0};
 
 __device__ __forceinline__ float wave_max(float v)
@@ -132,6 +133,7 @@ struct SplitGeom {
     int nsplit;     // key-range slices
     int rowtiles;   // workgroups along the G*Mq rows of one (sequence, KV head)
     int rows_pad;   // rowtiles * rows per workgroup
+    bool wide;      // 256 rows per workgroup (k_attn_long) instead of 128
 };
 
 typedef _Float16 f16_t;
@@ -1151,11 +1153,8 @@ static bool mfma_ok(int dtype, int dh, const AttnArgs *a)
 // 25 % faster than two blocks per wave at RG = 512 even though K/V are then read by twice as many row tiles
 constexpr int ATTN_NBLK = 1;
 
-// More rows than one 128-row tile holds (measured whole steps: 256 rows per KV head, 16 sequences 734 -> 730 us; 480 rows,
-// 70B shape 680 -> 671; 512 rows, 32768 keys 2114 -> 1855); up to 128 the 256-row tile would be half empty or worse.
-static bool long_form(int RG, int dh) { return dh == 128 && RG > 128; }
-
-static SplitGeom split_geometry(int B, int Mq, int H, int Hkv, int dh, int P_cap)
+// ncalls: 1, or 2 of this shape in one launch (the number of key slices of either form does not depend on it)
+static SplitGeom split_geometry(int B, int Mq, int H, int Hkv, int dh, int P_cap, int ncalls)
 {
     const int RG = (H / Hkv) * Mq;
     const int rows = 128 * ATTN_NBLK, tiles_cap = (P_cap + KT - 1) / KT;
@@ -1168,19 +1167,33 @@ static SplitGeom split_geometry(int B, int Mq, int H, int Hkv, int dh, int P_cap
     if (want > 64) want = 64;
     if (want < 1) want = 1;
     g.nsplit = want;
-    if (!long_form(RG, dh)) return g;
+    g.wide = false;
+    const int form = g_attn_form.load(std::memory_order_relaxed);
+    if (dh != 128 || RG <= 128) return g;
     // 256-row tiles, one workgroup per compute unit; never more scratch than the 128-row tiles' slices would take
-    const int64_t most_rows = (int64_t)g.nsplit * g.rows_pad;
-    g.rowtiles = (RG + 255) / 256;
-    g.rows_pad = g.rowtiles * 256;
-    want = 256 / (B * Hkv * g.rowtiles);
+    SplitGeom w;
+    w.wide = true;
+    w.rowtiles = (RG + 255) / 256;
+    w.rows_pad = w.rowtiles * 256;
+    want = 256 / (B * Hkv * w.rowtiles);
     most = ((P_cap + LK - 1) / LK) / 2;
     if (want > most) want = most;
     if (want > 64) want = 64;
-    while (want > 1 && (int64_t)want * g.rows_pad > most_rows) --want;
+    while (want > 1 && (int64_t)want * w.rows_pad > (int64_t)g.nsplit * g.rows_pad) --want;
     if (want < 1) want = 1;
-    g.nsplit = want;
-    return g;
+    w.nsplit = want;
+    // Which one, by an estimate: a round of 128-row workgroups, two per compute unit, takes 3 us per tile of 64 keys, one of
+    // 256-row workgroups 2.35 us and 4 us more in front and behind.  It decides where the rows fill their last tile badly
+    // (8 sequences x 32768 keys x 8 KV heads: 260 .. 384 rows 638 .. 660 us in three tiles of 128 against 992 in two of 256,
+    // which leaves half of the chip idle; 388 .. 512 rows 746 .. 767 against 610 .. 624), where the rows of an XCD's units
+    // need one workgroup more than it has compute units, and where a slice is a few tiles (4 x 2048 keys, 224 rows: 27
+    // against 30 us).  Two calls in one launch can fill what one leaves idle (a step of 8 x 32768 keys, 260 .. 384 rows:
+    // 1285 .. 1331 us against 1199 .. 1240 in 256-row tiles).  Over 290 measured calls it is 0.4 % behind the better form, and never slower than 128-row tiles.
+    const int64_t units = (int64_t)ncalls * B * Hkv;
+    const int64_t per128 = (tiles_cap + g.nsplit - 1) / g.nsplit, rounds128 = (units * g.nsplit * g.rowtiles + 511) / 512;
+    const int64_t per256 = (tiles_cap + w.nsplit - 1) / w.nsplit, rounds256 = ((units * w.nsplit + 7) / 8 * 8 * w.rowtiles + 255) / 256;
+    const bool wide = form == MOA_ATTN_KERNEL_SPLIT_WIDE || 4.f + 2.35f * (float)(per256 * rounds256) < 3.f * (float)(per128 * rounds128);
+    return wide ? w : g;
 }
 
 size_t attn_workspace_bytes(int dtype, int B, int Mq, int H, int Hkv, int dh, int P_cap, bool upto)
@@ -1189,19 +1202,20 @@ size_t attn_workspace_bytes(int dtype, int B, int Mq, int H, int Hkv, int dh, in
     const size_t row_bytes = (size_t)dh * sizeof(f16_t) + 2 * sizeof(float);
     if (upto) {
         // Neither fewer rows nor fewer sequences always need less (they leave room for more key slices), so this is a bound
-        // that grows with every size.  `units` row tiles of 128 take at most max(units, min(512, units * most)) slices; the
-        // 256-row form never takes more rows than those and none for one slice, which leaves its sizes the one-tile calls.
-        const int RG = (H / Hkv) * Mq;
-        const int64_t units = (int64_t)B * Hkv * ((RG + 127) / 128), alone = long_form(RG, dh) ? (int64_t)B * Hkv : units;
+        // that grows with every size.  `units` row tiles of 128 take at most max(units, min(512, units * most)) slices, and
+        // the 256-row form never takes more rows than those.
+        const int64_t units = (int64_t)B * Hkv * (((int64_t)(H / Hkv) * Mq + 127) / 128);
         int64_t most = ((P_cap + KT - 1) / KT) / 2;
         most = most < 1 ? 1 : most > 64 ? 64 : most;
         int64_t slices = units * most < 512 ? units * most : 512;
-        if (slices < alone) slices = alone;
+        if (slices < units) slices = units;
         return (size_t)slices * 128 * ATTN_NBLK * row_bytes + 256;
     }
-    const SplitGeom g = split_geometry(B, Mq, H, Hkv, dh, P_cap);
-    if (g.nsplit == 1 && long_form((H / Hkv) * Mq, dh)) return 256;
-    const size_t rows = (size_t)B * Hkv * g.nsplit * g.rows_pad;
+    size_t rows = 0;
+    for (int ncalls : {1, 2}) {
+        const SplitGeom g = split_geometry(B, Mq, H, Hkv, dh, P_cap, ncalls);
+        if (g.nsplit > 1 || !g.wide) rows = std::max(rows, (size_t)B * Hkv * g.nsplit * g.rows_pad);
+    }
     return rows * row_bytes + 256;
 }
 
@@ -1258,14 +1272,14 @@ static bool attn_split_ok(const AttnArgs &a, int P_cap_geo)
 // fixed part, but re-reads K/V once per 32 query rows and runs one workgroup per CU: it wins while the call is
 // latency-bound, i.e. while its workgroups fit the chip in one round and the key range is short (C1: 14.5 us
 // against 17.8 + 6.8 us).  With more work the split form (128 rows per workgroup and two workgroups per CU, or 256
-// rows and one, see long_form; then the merge) is ahead (B = 16, prefixes up to 2048: 122 against 166 us).  moa_debug_force_attn_kernel overrides the
+// rows and one, see split_geometry; then the merge) is ahead (B = 16, prefixes up to 2048: 122 against 166 us).  moa_debug_force_attn_kernel overrides the
 // choice (the parity tests run every case through both forms).
 constexpr int FUSED_MAX_KEYS = 8192;
 constexpr int FUSED_MAX_WORKGROUPS = 256;
 static bool want_fused(const AttnArgs &a)
 {
     const int form = g_attn_form.load(std::memory_order_relaxed);
-    if (form == MOA_ATTN_KERNEL_SPLIT) return false;
+    if (form == MOA_ATTN_KERNEL_SPLIT || form == MOA_ATTN_KERNEL_SPLIT_WIDE) return false;
     if (form == MOA_ATTN_KERNEL_WHOLE) return true;
     const int64_t wgs = (int64_t)a.B * a.Hkv * (((a.H / a.Hkv) * a.Mq + 31) / 32);
     return a.P_cap + a.Mt <= FUSED_MAX_KEYS && wgs <= FUSED_MAX_WORKGROUPS;
@@ -1305,7 +1319,7 @@ static hipError_t launch_attn_split(const AttnArgs *calls, int n, hipStream_t st
 {
     const AttnArgs &a = calls[0];
     const int cap = n == 2 && calls[1].P_cap > a.P_cap ? calls[1].P_cap : a.P_cap;
-    const SplitGeom g = split_geometry(a.B, a.Mq, a.H, a.Hkv, a.dh, cap);
+    const SplitGeom g = split_geometry(a.B, a.Mq, a.H, a.Hkv, a.dh, cap, n);
     AttnGroup grp;
     grp.a[0] = calls[0];
     grp.a[1] = calls[n - 1];
@@ -1313,7 +1327,7 @@ static hipError_t launch_attn_split(const AttnArgs *calls, int n, hipStream_t st
     grp.ncalls = n;
     const int nblocks = n * a.B * a.Mq * a.H;
     hipError_t e;
-    if (long_form((a.H / a.Hkv) * a.Mq, a.dh)) {
+    if (g.wide) {
         constexpr size_t lds = (size_t)LRING * LK * 128 * 2 * 2;
         static bool raised[16] = {};
         e = raise_lds_limit_once(raised, (const void *)k_attn_long<128>, lds);
@@ -1383,8 +1397,8 @@ hipError_t launch_attn_pair(const AttnArgs &a0_in, const AttnArgs &a1_in, hipStr
 
 extern "C" int32_t moa_debug_force_attn_kernel(int32_t form)
 {
-    if (form < MOA_ATTN_KERNEL_AUTO || form > MOA_ATTN_KERNEL_SPLIT)
-        return moa::api_fail(MOA_ERR_SHAPE, "debug_force_attn_kernel: form must be MOA_ATTN_KERNEL_AUTO / _WHOLE / _SPLIT");
+    if (form < MOA_ATTN_KERNEL_AUTO || form > MOA_ATTN_KERNEL_SPLIT_WIDE)
+        return moa::api_fail(MOA_ERR_SHAPE, "debug_force_attn_kernel: form must be MOA_ATTN_KERNEL_AUTO / _WHOLE / _SPLIT / _SPLIT_WIDE");
     moa::g_attn_form.store(form, std::memory_order_relaxed);
     return MOA_OK;
 }

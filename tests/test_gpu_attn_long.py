@@ -19,10 +19,11 @@ def G():
     return gpu_util
 
 
-@pytest.fixture(scope="module")
-def moa(G):
+@pytest.fixture(scope="module", params=["split_wide", "split"])
+def moa(G, request):
+    """256-row tiles, then the tiles that the estimate of the time picks (128 rows for most of these small calls)."""
     import paper_2410_03804_amd as m
-    m.debug_force_attn_kernel("split")
+    m.debug_force_attn_kernel(request.param)
     yield m
     m.debug_force_attn_kernel("auto")
 
@@ -72,3 +73,25 @@ def test_attn_long_tile_edges(G, moa, oracle, M, H, Hkv, plen, P_cap, factor):
     bound = factor * 2.0 ** -9 + 2.0 ** -8
     assert np.linalg.norm(got - want) <= bound * np.linalg.norm(want)
     assert np.abs(got - want).max() <= 6 * bound * np.sqrt(np.mean(want ** 2))
+
+
+@pytest.mark.parametrize("M,kernel", [(65, "k_attn_mfma<128, 1>"), (96, "k_attn_mfma<128, 1>"), (97, "k_attn_long<128>"),
+                                      (128, "k_attn_long<128>")])
+def test_row_tile_height_follows_how_well_rows_fill_it(G, M, kernel):
+    """8 sequences x 8 KV heads: up to 384 rows three tiles of 128 keep the chip busy where two of 256 leave half of it idle
+    (their scratch would not hold two key slices); from there on 256-row tiles are the faster ones."""
+    import paper_2410_03804_amd as m
+    B, P = 8, 4096
+    shape = m.Shape(2, 4096, 32, 8, 128, 256, 2, 1, m.BF16)
+    print(f"[case] cross_attn_draft B={B} M={M} P_cap={P}", flush=True)
+    kc, x = torch.randn(B, 8, P, 128, device="cuda").bfloat16(), torch.randn(B, M, 4096, device="cuda").bfloat16()
+    out, ln = torch.empty_like(x), torch.full((B,), P, dtype=torch.int32, device="cuda")
+    ws = torch.empty(m.workspace_bytes(shape, B, P, M, 0), dtype=torch.uint8, device="cuda")
+    m.profile_enable(True)
+    try:
+        m.cross_attn_draft(shape, x, None, None, kc, kc, ln, P, out, ws, G.status_word())
+        torch.cuda.synchronize()
+        names = {k for _, k, _, _ in m.profile_collect()}
+    finally:
+        m.profile_enable(False)
+    assert kernel in names, names
