@@ -257,14 +257,18 @@ struct LinArgs {
     RopeArgs rope;
     NormArgs norm;
     bool in_order;     // sum along K in one chain of matrix instructions, as the one-kernel LSA does (same bits)
-    // > 0: the order of the sums along K depends on R alone, not on what else is in the launch (a step's schedules group
-    // the same projections differently and give the same bits).  bf16: two K groups up to this many rows, one beyond.
-    // Measured at 8 .. 240 rows and K = 4096 .. 8192, the launches of a step grouped and alone: up to 64 rows two groups
-    // are as fast where one fills the chip and a quarter faster where it does not (60 x 4096: W_o 16.2 against 21.5 us,
-    // 60 x 8192 x 18432: 70.9 against 85.6); beyond, the grouped Q/K/V launch is faster in one (128 x 4096 x 10240: 29.4
-    // against 33.4; 128 x 8192 x 18432: 87 against 115), while the output projections, half as wide, gain by two up to
-    // 128 rows (4096 x 4096 16.8 against 21.8 us, a pair of them the same; 8192 x 16384: 69.5 against 87.5).
-    enum { SAME_SUMS_IN = 64, SAME_SUMS_OUT = 128 };      // query / key / value projections, output projections
+    // not 0: the order of the sums along K depends on R and K alone, not on what else is in the launch (a step's schedules
+    // group the same projections differently and give the same bits).  bf16: no slices of K, and two K groups up to a row
+    // count, one chain beyond.  Measured at 8 .. 1024 rows and K = 4096 .. 8192, grouped launches and single ones:
+    //   IN (query / key / value projections): 64 rows.  Up to there two groups are as fast where one fills the chip and a
+    //     quarter faster where it does not (60 x 4096 x 6144: 17.7 against 22.6 us, 60 x 8192 x 18432: 70.9 against 85.6);
+    //     beyond, the grouped launch is faster in one chain (128 x 4096 x 10240: 29.4 against 33.4; 128 x 8192 x 18432: 87
+    //     against 115).
+    //   OUT (output projections): as long as a pair of them, 2 K features wide, is one round of 64 x 128 tiles.  256 x 4096
+    //     x 8192 32.7 against 36.1 us, 180 x 5120 x 10240 43.4 against 51.8, 128 x 8192 x 16384 69.5 against 87.5; beyond,
+    //     300 x 4096 x 8192 49.0 against 34.5, 144 x 8192 x 16384 113 against 72.
+    enum { SAME_SUMS_IN = 1, SAME_SUMS_OUT };
+    static int pair_rows(int same_sums, int K) { return same_sums == SAME_SUMS_IN ? 64 : 16384 / K * 64; }
     int same_sums;
     // Where K is cut into slices: do not launch the pass that adds them up but describe it here (blocks = 0 when nothing
     // is left to do).  The caller has it carried by a later launch or runs launch_splitk_sum;

@@ -181,10 +181,10 @@ struct GemmPlan { int tile, splits; };
 // 8192); slices only for a long K with few features (60 x 14336 x 4096: four, 30 us against 52).  A pass of its own behind
 // an unsplit projection counts against not splitting, since the sum over slices does that work on the way.
 //
-// same_sums: pairs of K groups up to that many rows, one group beyond; no slices, whatever the features.
+// same_sums: pairs of K groups or one chain, no slices, whatever the features (see LinArgs).
 static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi, bool in_order, int same_sums, int most_splits = 8)
 {
-    if (same_sums && R > same_sums) in_order = true;
+    if (same_sums && R > LinArgs::pair_rows(same_sums, K)) in_order = true;
     GemmPlan best = {0, 1};
     int ntot = 0;
     for (int s = 0; s < nseg; ++s) {

@@ -151,7 +151,7 @@ def _wide(rows, **kw):
 @pytest.mark.parametrize("cfg", [
     # row counts on both sides of where the projections' sums change their order, at widths where a launch of one matrix
     # and one of several would choose differently if they were free to
-    _wide(9), _wide(60), _wide(111), _wide(130), _wide(33, d=8192, H=64),
+    _wide(9), _wide(60), _wide(111), _wide(130), _wide(33, d=8192, H=64), _wide(128, d=8192, H=64), _wide(130, d=8192),
     # single precision: a grouped launch has enough output tiles for the large kernel, its parts alone have not
     _wide(100, dtype="f32", B=4, d=512, H=8, Hkv=4, dh=64, d_lsa_in=512)], ids=lambda c: f"{c.dtype}-{c.B}x{c.M}x{c.d}")
 def test_schedules_give_the_same_bits(G, cfg):
