@@ -368,9 +368,7 @@ int32_t moa_fold_projection(int32_t dtype, const void *w_outer, const void *w_in
  *  MOA_SCHED_TWO_STREAM (1): the grouped launches, with the first of them (the CA query and first-layer
  *    Q/K/V projections, which depend on nothing else in the step) and the pass that adds up its slices on a
  *    second, library-owned stream that is forked from and joined back into `stream` with one event each,
- *    beside the LSA kernel on `stream`.  With lsa_w_packed the LSA kernel runs in a lean form that shares
- *    its compute units with the projection kernel; without, with its largest token tile, so that compute
- *    units are left over.  Same requirements as MOA_SCHED_GROUPED.  One side stream exists per device:
+ *    beside the LSA kernel on `stream`.  Same requirements as MOA_SCHED_GROUPED.  One side stream exists per device:
  *    steps of several host threads on one device are enqueued one after the other (a mutex), and the
  *    branch is joined back even when a launch fails half way.
  *    With the Self-Attention layer (sa_emb != NULL) and the LSA as one kernel, the branches are cut differently:

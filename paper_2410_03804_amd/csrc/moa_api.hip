@@ -1530,11 +1530,10 @@ static int32_t draft_step_grouped(const moa_step_args_t *a)
 // ---- the same pieces on two streams.
 // Dependencies inside one step: the LSA kernel depends on nothing else in the step, and neither do the projections of
 // the cross-attention queries and the first verification layer.  The LSA kernel is bound by the matrix cores and the
-// L2, those projections by HBM, so the two want different parts of the chip.  From packed weights the LSA kernel has a
-// lean form (a third of a SIMD's registers per wavefront, 67 KB of LDS) beside which a compute unit still holds a
-// workgroup of the weight-streaming kernel, so the two launches run on the same compute units at the same time; from
-// plain weights the LSA kernel fills the LDS and runs with its largest token tile instead, which at decode sizes leaves
-// half of the compute units to the other launch.  The projections run on a library-owned stream that is forked from
+// L2, those projections by HBM, so the two want different parts of the chip; what one launch leaves idle the other can
+// use.  (A form of the LSA kernel held to a third of the registers, so that a compute unit holds a workgroup of each,
+// costs more than the sharing gives: 60 nodes, 8B shape, with the Self-Attention layer 157 us against 143 with the kernel
+// as it is, 4 x 64 nodes 411 against 345; so do projection tiles small enough to fit beside it.)  The projections run on a library-owned stream that is forked from
 // and joined back into the caller's stream with one event each (an edge between two hardware queues costs several
 // microseconds, so there are only these two), and the caller still sees one stream's worth of ordering (a stream
 // capture records both branches).
@@ -1613,7 +1612,6 @@ static int32_t two_stream_main(const moa_step_args_t *a, const StepBufs &bf, cha
         const LsaBufs b = lsa_carve(sh, T, scr, scr_bytes);
         void *abar = a->lsa_wo ? (void *)b.abar0 : a->lsa_out;
         LsaFusedCall fc = lsa_fused_call(sh, a->lsa_hs, 0, T, a->lsa_wq, a->lsa_wk, a->lsa_wv, abar, step_lsa_packed(a));
-        fc.leave_room = 1;                   // the form that shares the chip with the other branch
         fc.rider = small_args(a, bf);        // tree masks, accept walk, old memory lengths
         fc.rider_units = 2 * a->B + 1;
         prof_set_site(S_LSA_FUSED);
@@ -1706,7 +1704,6 @@ static int32_t two_stream_sa_side_lsa(const moa_step_args_t *a, const StepBufs &
     st->b = lsa_carve(sh, T, scr, scr_bytes);
     void *abar = a->lsa_wo ? (void *)st->b.abar0 : a->lsa_out;
     LsaFusedCall fc = lsa_fused_call(sh, a->lsa_hs, 0, T, a->lsa_wq, a->lsa_wk, a->lsa_wv, abar, step_lsa_packed(a));
-    fc.leave_room = 1;
     fc.rider = small_args(a, bf);        // accept walk, old memory lengths
     fc.rider.skip_masks = 1;             // built in front of the fork
     fc.rider_units = 2 * a->B + 1;

@@ -25,9 +25,8 @@
 //              abar = sum_j pbar_j V_j  (mean_i(P V) = (1^T P / L) V, exact in real arithmetic).  The output
 //              projection follows in another launch on one row per token.
 //
-// Three kernels share that second half: k_lsa_fused (plain weights, as above), k_lsa_fused_pk (weights packed once
-// into MFMA-operand order and read straight into registers; the form a step runs when it is given the packed copy)
-// and k_lsa_fused_pk_lean (the same held to a third of a SIMD's registers, for the two-stream schedule).
+// Two kernels share that second half: k_lsa_fused (plain weights, as above) and k_lsa_fused_pk (weights packed once
+// into MFMA-operand order and read straight into registers; the form a step runs when it is given the packed copy).
 //
 // Arithmetic is that of the three-kernel form (same MFMA order along d_in, Q/K/V rounded once to the storage type,
 // the same order of additions in the column sums), so all give the same bits.
@@ -413,11 +412,11 @@ __device__ __forceinline__ void lsa_warm_block(const LsaFusedArgs &a, int h, bf1
 // flight per wavefront in registers, which the 160 KB of LDS could not hold.  The activation tile goes through
 // registers into a two-stage LDS ring (one bare barrier per tile); all loads are ordinary loads, so the waits are the
 // compiler's.  Same MFMA order along d_in as the unpacked form: same bits.
-template <int DH, int NB, int TT, int WS, bool SPREAD>
-__device__ __forceinline__ void lsa_fused_pk_body(const LsaFusedArgs &a)
+template <int DH, int NB, int TT>
+__global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
 {
     using Gm = LsaFusedGeom<DH, NB, TT>;
-    constexpr int FW = Gm::FW, RB = Gm::RB, BK = Gm::BK;
+    constexpr int FW = Gm::FW, RB = Gm::RB, BK = Gm::BK, WS = Gm::WS;
     constexpr int WFB = FW / 32;                 // 32-feature blocks per wavefront
     constexpr int NRB = RB / 32;                 // 32-row blocks
     constexpr int NWP = 4 * WFB;                 // operand pieces per lane and weight tile
@@ -505,8 +504,7 @@ __device__ __forceinline__ void lsa_fused_pk_body(const LsaFusedArgs &a)
     // barriers keep the compiler from regrouping them.  No branch surrounds a load: the compiler's load counter then
     // stays exact (partial waits), where a conditional request makes it wait for everything in flight; requests past
     // the last tile repeat the last tile.  GUARDED steps (the few behind the last whole trip) may lie past the last
-    // tile and then skip their arithmetic; they refill in one go behind it, and so do the forms without SPREAD (128-row
-    // tiles and the lean form: the spread-out order costs registers they do not have).
+    // tile and then skip their arithmetic; they refill in one go behind it.
     auto tile_step = [&](auto stage_c, auto guarded_c, int kt) {
         constexpr int S = decltype(stage_c)::value;
         constexpr bool GUARDED = decltype(guarded_c)::value;
@@ -527,8 +525,8 @@ __device__ __forceinline__ void lsa_fused_pk_body(const LsaFusedArgs &a)
                 fb[j] = *(const bf16x8 *)&xb[row * BK + 8 * ((2 * ks + half) ^ ((row >> 1) & 7))];
             }
         };
-        if constexpr (GUARDED || !SPREAD) {
-            if (!GUARDED || kt < nk) {
+        if constexpr (GUARDED) {
+            if (kt < nk) {
                 bf16x8 bfr[2][NRB];
                 read_frags(0, bfr[0]);
 #pragma unroll
@@ -576,22 +574,6 @@ __device__ __forceinline__ void lsa_fused_pk_body(const LsaFusedArgs &a)
     for (int kt0 = nk_main; kt0 < nk_end; kt0 += WS)
         static_for<WS>([&](auto u) { tile_step(u, std::true_type{}, kt0 + decltype(u)::value); });
     lsa_fused_epilogue<DH, NB, TT>(acc, a, sm, tile, g, part);
-}
-
-template <int DH, int NB, int TT>
-__global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
-{
-    lsa_fused_pk_body<DH, NB, TT, LsaFusedGeom<DH, NB, TT>::WS, true>(a);
-}
-
-// The same with two register stages and the compiler held to a third of a SIMD's registers per wavefront (168): beside
-// a workgroup of this kernel a compute unit still has registers and LDS for a workgroup of the weight-streaming
-// projection kernel, so a step that runs its two independent branches on two streams gets them side by side on the same
-// compute units.  (64-row tiles only: larger tiles need the registers for their accumulators.)
-template <int DH, int NB, int TT>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_lsa_fused_pk_lean(LsaFusedArgs a)
-{
-    lsa_fused_pk_body<DH, NB, TT, 2, false>(a);
 }
 
 // Packs Wq / Wk / Wv for k_lsa_fused_pk: piece (unit, wavefront, k tile, k step, feature block, lane) holds the 8
@@ -651,7 +633,7 @@ static size_t lds_limit()
 }
 
 template <int NB, int TT>
-static hipError_t launch_lsa_fused_as(LsaFusedArgs &fa, hipStream_t stream, bool lean = false)
+static hipError_t launch_lsa_fused_as(LsaFusedArgs &fa, hipStream_t stream)
 {
     using Gm = LsaFusedGeom<128, NB, TT>;
     const int64_t tiles = (fa.T + TT - 1) / TT;
@@ -668,22 +650,11 @@ static hipError_t launch_lsa_fused_as(LsaFusedArgs &fa, hipStream_t stream, bool
         }
         const int64_t own = 8 * (int64_t)fa.units_per_xcd * tiles;
         const size_t w_per_xcd = (size_t)fa.units_per_xcd * (size_t)(fa.d_in / 64) * 65536;
-        if (lean || own + fa.pf_lead > cus || w_per_xcd > ((size_t)3 << 20)) fa.pf_lead = 0;
+        if (own + fa.pf_lead > cus || w_per_xcd > ((size_t)3 << 20)) fa.pf_lead = 0;
         fa.lead_blocks += fa.pf_lead;
     }
     const int64_t grid = fa.lead_blocks + 8 * (int64_t)fa.units_per_xcd * tiles;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    if constexpr (Gm::RB <= 64) {
-        if (fa.wpk && lean) {
-            static bool raised[16] = {};
-            hipError_t e = raise_lds_limit_once(raised, (const void *)k_lsa_fused_pk_lean<128, NB, TT>, Gm::pk_bytes);
-            if (e != hipSuccess) return e;
-            prof_begin(K_LSA_FUSED_PK_LEAN + 64 * (NB * 8 + TT), stream);
-            MOA_KLAUNCH((k_lsa_fused_pk_lean<128, NB, TT>), dim3((unsigned)grid), dim3(512), Gm::pk_bytes, stream, fa);
-            prof_end(stream);
-            return hipGetLastError();
-        }
-    }
     if (fa.wpk) {
         static bool raised[16] = {};
         hipError_t e = raise_lds_limit_once(raised, (const void *)k_lsa_fused_pk<128, NB, TT>, Gm::pk_bytes);
@@ -748,7 +719,7 @@ hipError_t launch_lsa_fused(const LsaFusedCall &c, hipStream_t stream)
         fa.red_blocks = c.carry_sum->blocks;
     }
     fa.lead_blocks = fa.small_lead + ((((fa.red_blocks + 1) / 2) + 7) & ~7);   // a lead workgroup of 512 threads does two blocks of the pass
-    fa.pf_lead = (c.w_packed && !c.leave_room) ? 16 : 0;     // wanted; launch_lsa_fused_as decides when it knows the grid
+    fa.pf_lead = c.w_packed ? 16 : 0;     // wanted; launch_lsa_fused_as decides when it knows the grid
     // Rows per workgroup.  Measured at the Llama-3-8B shape (d_in 2048), a workgroup takes about 31 + 9 (rows / 32)
     // microseconds from plain weights and 10 + 11.7 (rows / 32) from packed ones, whatever else runs (it is bound by
     // its own chain of tile fetches from the L2 and its matrix work), and the chip runs 256 of them at a time: few
@@ -761,23 +732,17 @@ hipError_t launch_lsa_fused(const LsaFusedCall &c, hipStream_t stream)
         const double wgs = (double)fa.units * (double)((c.T + tt - 1) / tt);
         return ceil(wgs / 256.0) * (fixed + per_block * nb * tt);    // one workgroup per compute unit, all equally long: whole rounds
     };
-    // leave_room: another stream's kernels are meant to run beside this launch.  From packed weights that is the
-    // 64-row tile in its lean form, which shares a compute unit with them; from plain weights (LDS full either way) the
-    // largest tile, which leaves whole compute units empty.
-    const bool lean = c.leave_room && fa.wpk;
     if (nb == 1) {
         int best = 2;
-        if (!lean) {
-            if (cost(3) < cost(best)) best = 3;
-            if (big_ok && (cost(4) < cost(best) || c.leave_room)) best = 4;
-        }
+        if (cost(3) < cost(best)) best = 3;
+        if (big_ok && cost(4) < cost(best)) best = 4;
         if (best == 4) return launch_lsa_fused_as<1, 4>(fa, stream);
         if (best == 3) return launch_lsa_fused_as<1, 3>(fa, stream);
-        return launch_lsa_fused_as<1, 2>(fa, stream, lean);
+        return launch_lsa_fused_as<1, 2>(fa, stream);
     }
     if (nb == 2) {
-        if (!lean && big_ok && (cost(2) < cost(1) || c.leave_room)) return launch_lsa_fused_as<2, 2>(fa, stream);
-        return launch_lsa_fused_as<2, 1>(fa, stream, lean);
+        if (big_ok && cost(2) < cost(1)) return launch_lsa_fused_as<2, 2>(fa, stream);
+        return launch_lsa_fused_as<2, 1>(fa, stream);
     }
     return launch_lsa_fused_as<3, 1>(fa, stream);
 }

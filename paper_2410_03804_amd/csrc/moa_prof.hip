@@ -35,7 +35,7 @@ hipEvent_t take_event()
 const char *const kKernelNames[K_COUNT] = {
     "k_tree_build", "k_tree_accept", "k_append_lengths", "k_linear_generic",
     "k_linear_splitk_reduce", "k_scatter_copy", "k_attn_generic", "k_attn_mfma", "k_attn_merge", "k_lsa_attn", "k_lsa_attn_mfma", "k_step_small", "k_attn_fused", "k_probe_read", "k_probe_mfma",
-    "k_rmsnorm", "k_rope", "k_swiglu", "k_add_out", "k_tree_expand", "k_tree_finalize", "k_topk_slices", "k_lm_head_argmax", "k_lm_head_reduce", "k_topk_merge", "k_msg_tree", "k_msg_accept", "k_lsa_fused", "k_lsa_fused_pk", "k_lsa_pack_weights", "k_lsa_fused_pk_lean", "k_linear_f32_latency", "k_linear_f32_tile", "k_attn_f32", "k_linear_bf16", "k_attn_long<128>"};
+    "k_rmsnorm", "k_rope", "k_swiglu", "k_add_out", "k_tree_expand", "k_tree_finalize", "k_topk_slices", "k_lm_head_argmax", "k_lm_head_reduce", "k_topk_merge", "k_msg_tree", "k_msg_accept", "k_lsa_fused", "k_lsa_fused_pk", "k_lsa_pack_weights", "k_linear_f32_latency", "k_linear_f32_tile", "k_attn_f32", "k_linear_bf16", "k_attn_long<128>"};
 const char *const kSiteNames[S_COUNT] = {
     "none", "tree_build", "lsa.qkv_proj", "lsa.layer_attn", "lsa.o_proj", "ca_append.kv_proj", "ca_append.lengths",
     "ca.q_proj", "ca.core", "ca.o_proj", "verify.qkv_proj", "verify.core", "verify.o_proj", "tree_accept",
@@ -192,7 +192,7 @@ const char *moa_profile_kernel_name(int32_t kernel)
     if (var == 0) return kKernelNames[base];
     if (base == K_LIN_BF16) return linear_bf16_name(var);
     if (base == K_ATTN_FUSED) snprintf(buf, sizeof(buf), "%s<%d, %d>", kKernelNames[base], var >> 3, 4 * (var & 7));
-    else if (base == K_LSA_FUSED || base == K_LSA_FUSED_PK || base == K_LSA_FUSED_PK_LEAN) snprintf(buf, sizeof(buf), "%s<128, %d, %d>", kKernelNames[base], var >> 3, var & 7);
+    else if (base == K_LSA_FUSED || base == K_LSA_FUSED_PK) snprintf(buf, sizeof(buf), "%s<128, %d, %d>", kKernelNames[base], var >> 3, var & 7);
     else if (base == K_ATTN_MERGE) snprintf(buf, sizeof(buf), "%s<%d>", kKernelNames[base], var >> 3);
     else snprintf(buf, sizeof(buf), "%s<%d, %d>", kKernelNames[base], var >> 3, var & 7);
     return buf;
