@@ -366,11 +366,11 @@ int32_t moa_fold_projection(int32_t dtype, const void *w_outer, const void *w_in
  *    moa_workspace_bytes asks for; otherwise the step runs as MOA_SCHED_SEQUENTIAL.  tok[], tgt[]
  *    and ca_len[] are read by the first launch of the step, so nothing in the step may produce them.
  *  MOA_SCHED_TWO_STREAM (1): the grouped launches, with the first of them (the CA query and first-layer
- *    Q/K/V projections, which depend on nothing else in the step) and the pass that adds up its slices on a
- *    second, library-owned stream that is forked from and joined back into `stream` with one event each,
- *    beside the LSA kernel on `stream`.  Same requirements as MOA_SCHED_GROUPED.  One side stream exists per device:
- *    steps of several host threads on one device are enqueued one after the other (a mutex), and the
- *    branch is joined back even when a launch fails half way.
+ *    Q/K/V projections, which depend on nothing else in the step) on a second, library-owned stream that
+ *    is forked from and joined back into `stream` with one event each, beside the LSA kernel on `stream`.
+ *    Same requirements as MOA_SCHED_GROUPED.  One side stream exists per device: steps of several host
+ *    threads on one device are enqueued one after the other (a mutex), and the branch is joined back even
+ *    when a launch fails half way.
  *    With the Self-Attention layer (sa_emb != NULL) and the LSA as one kernel, the branches are cut differently:
  *    `stream` carries the step's one long chain (tree masks, the Self-Attention layer, the CA query projection,
  *    the CA core and its output projection), the library's stream the LSA with the memory append and then the

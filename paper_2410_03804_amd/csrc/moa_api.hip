@@ -153,15 +153,11 @@ struct GroupLayout {
 GroupLayout group_layout(const moa_shape_t *s, int B, int M, int P_cap, int ca_P_cap, int64_t T, bool upto = false)
 {
     GroupLayout L;
-    const int e = s->n_q_heads * s->head_dim, ekv = s->n_kv_heads * s->head_dim;
-    const int64_t R = (int64_t)B * M;
     L.len_bytes = align256((size_t)B * sizeof(int32_t));
-    L.qa = align256((size_t)R * e * esize(s->dtype));
+    L.qa = align256((size_t)B * M * s->n_q_heads * s->head_dim * esize(s->dtype));
     const int cap = P_cap > ca_P_cap ? P_cap : ca_P_cap;
     L.attn_each = align256(attn_workspace_bytes(s->dtype, B, M, s->n_q_heads, s->n_kv_heads, s->head_dim, cap, upto));
-    size_t n = 2 * L.attn_each;
-    n = max2(n, linear_workspace_bytes(s->dtype, R, s->d_model, {e, e, ekv, ekv}, upto));
-    n = max2(n, linear_workspace_bytes(s->dtype, R, e, {s->d_model, s->d_model}, upto));
+    size_t n = 2 * L.attn_each;                                       // (the grouped projections cut no K)
     n = max2(n, attn_ws_bytes(s, B, M, P_cap, upto));                       // verification layers after the first
     n = max2(n, attn_ws_bytes(s, B, M, ca_P_cap, upto));
     if (T > 0) {
@@ -1259,11 +1255,8 @@ static int32_t piece_small(const moa_step_args_t *a, const StepBufs &bf, hipStre
 // cross-attention queries + first verification layer's Q/K/V in one launch (which = 3), or the queries (1) or the
 // verification layer's three (2) alone
 // with_small: the integer work rides in spare workgroups of this launch's grid instead of being a launch of its
-// own (nothing before the LSA chain's append and the attention cores needs its results).  sum_out: the pass that
-// adds up this projection's K slices is left to the caller (scr is then a region nobody else writes until that pass
-// has run).
-static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, void *scr, size_t scr_bytes, hipStream_t st,
-                                 bool with_small, SumArgs *sum_out = nullptr, int which = 3)
+// own (nothing before the LSA chain's append and the attention cores needs its results).
+static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, hipStream_t st, bool with_small, int which = 3)
 {
     const moa_shape_t *sh = a->shape;
     const int dh = sh->head_dim, Hkv = sh->n_kv_heads, d = sh->d_model, M = a->M;
@@ -1272,8 +1265,6 @@ static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, v
     la.R = (int64_t)a->B * M;
     la.K = d;
     la.ldx = d;
-    la.ws = scr;
-    la.ws_bytes = scr_bytes;
     la.same_sums = LinArgs::SAME_SUMS_IN;
     if (which & 1) {
         LinSeg &q = la.seg[la.nseg++];
@@ -1302,7 +1293,6 @@ static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, v
         la.rider = small_args(a, bf);
         la.rider_units = 2 * a->B + 1;
     }
-    la.sum_out = sum_out;
     prof_set_site(which == 3 ? S_PAIR_QKV : which == 1 ? S_CA_QPROJ : S_VERIFY_QKV);
     MOA_TRY_HIP(launch_linear(sh->dtype, la, st), "draft_step: projections");
     return MOA_OK;
@@ -1391,34 +1381,27 @@ static int32_t piece_lsa_append(const moa_step_args_t *a, const StepBufs &bf, vo
 // The step's first projections and an LSA chain that is one pass (at most LSA_CHUNK tokens, or an output-projection
 // block of them in the one-kernel form), with the small kernels riding in launches that do not depend on them:
 //   1. CA query + verification Q/K/V projections  + the step's integer work
-//   2. LSA in one kernel (or its Q/K/V projection) + the pass that adds up launch 1's K slices, if it has any (the
-//                                                    one-kernel form carries it; else that pass is a launch of its own)
-//   3. (attention over the layers, when apart)     4. LSA W_o (+ the memory's folded K/V)
-// scr2 is the second scratch region: launch 1's partial sums live there while the LSA chain uses the first.
-static int32_t piece_lsa_interleaved(const moa_step_args_t *a, const StepBufs &bf, char *scr, size_t scr_bytes, char *scr2,
-                                     hipStream_t st)
+//   2. LSA in one kernel (or its Q/K/V projection, then the attention over the layers)
+//   3. LSA W_o (+ the memory's folded K/V)
+static int32_t piece_lsa_interleaved(const moa_step_args_t *a, const StepBufs &bf, char *scr, size_t scr_bytes, hipStream_t st)
 {
     const moa_shape_t *sh = a->shape;
     const int dt = sh->dtype;
     const int64_t T = a->T_lsa;
     int32_t rc = lsa_check(sh, a->lsa_hs, T, a->lsa_wq, a->lsa_wk, a->lsa_wv, a->lsa_out, scr, scr_bytes);
     if (rc) return rc;
-    SumArgs sum_pair = {};
-    rc = piece_projections(a, bf, scr2, scr_bytes, st, true, &sum_pair);
+    rc = piece_projections(a, bf, st, true);
     if (rc) return rc;
     const LsaBufs b = lsa_carve(sh, T, scr, scr_bytes);
     void *abar = a->lsa_wo ? (void *)b.abar0 : a->lsa_out;
     if (lsa_takes_fused(sh, T, a->lsa_hs, a->lsa_wq, a->lsa_wk, a->lsa_wv, abar)) {
         LsaFusedCall fc = lsa_fused_call(sh, a->lsa_hs, 0, T, a->lsa_wq, a->lsa_wk, a->lsa_wv, abar, step_lsa_packed(a));
-        fc.carry_sum = &sum_pair;
         prof_set_site(S_LSA_FUSED);
         MOA_TRY_HIP(launch_lsa_fused(fc, st), "lsa: fused kernel");
     } else {
         LinArgs la;
         LsaAttnArgs aa;
         lsa_chunk_args(sh, a->lsa_hs, 0, T, a->lsa_wq, a->lsa_wk, a->lsa_wv, abar, b, &la, &aa);
-        prof_set_site(S_PAIR_QKV);
-        MOA_TRY_HIP(launch_splitk_sum(sum_pair, st), "draft_step: projections");
         prof_set_site(S_LSA_QKV);
         if (la.nseg) MOA_TRY_HIP(launch_linear(dt, la, st), "lsa: projection");
         prof_set_site(S_LSA_ATTN);
@@ -1504,16 +1487,14 @@ static int32_t draft_step_grouped(const moa_step_args_t *a)
     const GroupLayout L = group_layout(a->shape, a->B, a->M, a->P_cap, a->ca_P_cap, a->T_lsa);
     char *scr = nullptr;
     const StepBufs bf = carve_step_bufs(a, L, &scr);
-    // With room for a second scratch region (the first projections keep their partial sums there while the LSA chain
-    // uses the first) and all LSA tokens in one chunk, the two are interleaved; else one after the other.
     int32_t rc;
     const bool one_pass = a->T_lsa <= LSA_CHUNK ||
                           (a->T_lsa <= LSA_OBLOCK && lsa_takes_fused(a->shape, a->T_lsa, a->lsa_hs, a->lsa_wq, a->lsa_wk, a->lsa_wv, a->ws));
-    if (a->T_lsa > 0 && one_pass && a->ws_bytes >= L.total() + L.scratch) {
-        rc = piece_lsa_interleaved(a, bf, scr, L.scratch, scr + L.scratch, st);
+    if (a->T_lsa > 0 && one_pass) {
+        rc = piece_lsa_interleaved(a, bf, scr, L.scratch, st);
         if (rc) return rc;
     } else {
-        rc = piece_projections(a, bf, scr, L.scratch, st, true);
+        rc = piece_projections(a, bf, st, true);
         if (rc) return rc;
         rc = piece_lsa_append(a, bf, scr, L.scratch, st);
         if (rc) return rc;
@@ -1537,7 +1518,7 @@ static int32_t draft_step_grouped(const moa_step_args_t *a)
 // and joined back into the caller's stream with one event each (an edge between two hardware queues costs several
 // microseconds, so there are only these two), and the caller still sees one stream's worth of ordering (a stream
 // capture records both branches).
-//   side: E_fork -> [CA query + verification Q/K/V projections] -> [sum of its K slices] -> E_join
+//   side: E_fork -> [CA query + verification Q/K/V projections] -> E_join
 //   main: E_fork -> [LSA + the step's integer work] -> LSA W_o + memory append -> wait E_join -> both attention cores
 //         -> both output projections -> further verification layers
 // (When the LSA cannot run as the one kernel, the integer work rides with the projections and the main branch waits
@@ -1572,24 +1553,11 @@ static SideStream *side_stream_for_current_device()
     return s.ok ? &s : nullptr;
 }
 
-// the grouped layout with a second scratch region for the side branch
-static size_t two_stream_bytes(const moa_step_args_t *a)
+// the grouped layout, with a second scratch region where the side branch needs one (the Self-Attention layer's form)
+static size_t two_stream_bytes(const moa_step_args_t *a, bool sa)
 {
     const GroupLayout L = group_layout(a->shape, a->B, a->M, a->P_cap, a->ca_P_cap, a->T_lsa);
-    return L.total() + L.scratch;
-}
-
-// side branch
-static int32_t two_stream_side(const moa_step_args_t *a, const StepBufs &bf, char *scr, size_t scr_bytes, SideStream *ss,
-                               bool with_small)
-{
-    hipStream_t side = ss->stream;
-    SumArgs sum_pair = {};
-    int32_t rc = piece_projections(a, bf, scr, scr_bytes, side, with_small, &sum_pair);
-    if (rc) return rc;
-    prof_set_site(S_PAIR_QKV);
-    MOA_TRY_HIP(launch_splitk_sum(sum_pair, side), "draft_step: projections");
-    return MOA_OK;
+    return L.total() + (sa ? L.scratch : 0);
 }
 
 // whether the main branch of a two-stream step runs the LSA as the one kernel (which then also carries the step's
@@ -1649,7 +1617,6 @@ static int32_t draft_step_concurrent(const moa_step_args_t *a, SideStream *ss)
     const GroupLayout L = group_layout(a->shape, a->B, a->M, a->P_cap, a->ca_P_cap, a->T_lsa);
     char *scr_main = nullptr;
     const StepBufs bf = carve_step_bufs(a, L, &scr_main);
-    char *scr_side = scr_main + L.scratch;
     std::lock_guard<std::mutex> lk(ss->enqueue);
 
     MOA_TRY_HIP(hipEventRecord(ss->fork, main), "draft_step: fork");
@@ -1658,7 +1625,7 @@ static int32_t draft_step_concurrent(const moa_step_args_t *a, SideStream *ss)
     // left with an unjoined branch): the main branch waits for the join event on its way; when either branch fails,
     // the wait is enqueued here (a second wait for the same event is harmless).
     const bool fused = two_stream_lsa_fused(a);
-    int32_t rc = two_stream_side(a, bf, scr_side, L.scratch, ss, !fused);
+    int32_t rc = piece_projections(a, bf, side, !fused);
     const hipError_t ej = hipEventRecord(ss->join, side);
     if (rc == MOA_OK && ej != hipSuccess) rc = hip_fail(ej, "draft_step: join");
     if (rc == MOA_OK) {
@@ -1728,7 +1695,7 @@ static int32_t two_stream_sa_side_memory(const moa_step_args_t *a, const StepBuf
 static int32_t two_stream_sa_side_verify(const moa_step_args_t *a, const StepBufs &bf, char *scr, size_t scr_bytes,
                                          size_t attn_each, hipStream_t side)
 {
-    int32_t rc = piece_projections(a, bf, scr, scr_bytes, side, false, nullptr, 2);
+    int32_t rc = piece_projections(a, bf, side, false, 2);
     if (rc) return rc;
     const AttnArgs ve = piece_verify_core_args(a, bf, scr, attn_each);
     prof_set_site(S_VERIFY_CORE);
@@ -1760,7 +1727,7 @@ static int32_t draft_step_concurrent_sa(const moa_step_args_t *args, const moa_s
     SaSideState st;
     rc = two_stream_sa_side_lsa(a, bf, scr_side, L.scratch, side, &st);
     if (rc == MOA_OK) rc = step_self_attn_layer(args, scr_main, L.scratch, main);
-    if (rc == MOA_OK) rc = piece_projections(a, bf, scr_main, L.scratch, main, false, nullptr, 1);
+    if (rc == MOA_OK) rc = piece_projections(a, bf, main, false, 1);
     if (rc == MOA_OK) rc = two_stream_sa_side_memory(a, bf, scr_side, L.scratch, side, &st);
     if (rc == MOA_OK) {
         hipError_t e = hipEventRecord(ss->mid, side);
@@ -1810,7 +1777,7 @@ int32_t moa_draft_step(const moa_step_args_t *args)
     if (rc) return rc;
     // grouped launches by default; two streams on request when the workspace has room for both branches'
     // scratch; otherwise one stage after another
-    const bool two = a->schedule == MOA_SCHED_TWO_STREAM && pieces_ok(a) && a->ws_bytes >= two_stream_bytes(a);
+    const bool two = a->schedule == MOA_SCHED_TWO_STREAM && pieces_ok(a) && a->ws_bytes >= two_stream_bytes(a, sa);
     SideStream *ss = two ? side_stream_for_current_device() : nullptr;
     // On two streams the layer is one branch's first piece; otherwise it runs in front of whichever schedule follows
     // (whose first launch writes the same masks again).

@@ -182,8 +182,6 @@ struct LsaAttnArgs {
     void *abar;              // [T, Hq*dh]
 };
 
-// The pass that adds up the K slices of a projection, as data: what launch_linear leaves behind when asked not to launch
-// it (LinArgs::sum_out), what the LSA kernel can carry (LsaFusedCall::carry_sum) and what launch_splitk_sum runs.
 // Rotary position embedding of a decoder layer's queries and draft keys (position = clamped prefix length + depth of
 // the node; the pair (c, c + dh/2) of every head is rotated by position * theta^(-2c/dh), the angle in double
 // precision): everything launch_rope needs, so that a projection can apply it on the way out.
@@ -270,10 +268,6 @@ struct LinArgs {
     enum { SAME_SUMS_IN = 1, SAME_SUMS_OUT };
     static int pair_rows(int same_sums, int K) { return same_sums == SAME_SUMS_IN ? 64 : 16384 / K * 64; }
     int same_sums;
-    // Where K is cut into slices: do not launch the pass that adds them up but describe it here (blocks = 0 when nothing
-    // is left to do).  The caller has it carried by a later launch or runs launch_splitk_sum;
-    // the partial sums (ws) must stay untouched until then.
-    SumArgs *sum_out;
 };
 
 // Y_s = X_s W_s^T for up to four weight matrices (one launch on the fast paths; segments usually share X).
@@ -341,8 +335,7 @@ hipError_t launch_swiglu(int dtype, const void *gu, int64_t R, int d_ff, void *a
 hipError_t launch_add_out(int dtype, const float *h, const void *t, int64_t n, void *out, hipStream_t stream);
 
 // ---- LSA in one kernel: projection of a token's layer rows, attention over the layers, mean; writes the mean-folded
-// heads abar [T, Hq*dh] (the output projection is a launch of its own, on one row per token).  rider as in LinArgs;
-// carry_sum: the pass over an earlier projection's K slices; both in spare workgroups at the front of the grid.
+// heads abar [T, Hq*dh] (the output projection is a launch of its own, on one row per token).  rider as in LinArgs.
 struct LsaFusedCall {
     int dtype;
     const void *hs, *wq, *wk, *wv;
@@ -352,7 +345,6 @@ struct LsaFusedCall {
     int L, d_in, Hq, Hkv, dh;
     StepSmallArgs rider;
     int rider_units;
-    const SumArgs *carry_sum;
 };
 // shapes and alignments the kernel takes (bf16, head_dim 128, L <= 96, d_in in 64s, an even number of query heads per KV head)
 bool lsa_fused_ok(int dtype, int L, int d_in, int Hq, int Hkv, int dh, const void *hs, const void *wq, const void *wk,

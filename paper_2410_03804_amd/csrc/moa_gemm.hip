@@ -149,7 +149,7 @@ static LinPath linear_path(int dtype, const LinArgs &a)
 
 static hipError_t launch_linear_impl(int dtype, const LinArgs &a, hipStream_t stream, bool *rode, bool *fused);
 
-// the pass that adds up the K slices launch_linear_bf16 has left in a.ws: launched, or handed to the caller
+// the pass that adds up the K slices launch_linear_bf16 has left in a.ws
 static hipError_t finish_splits(const LinArgs &a, int splits, hipStream_t stream, bool *fused)
 {
     SumArgs sum = {};
@@ -159,9 +159,9 @@ static hipError_t finish_splits(const LinArgs &a, int splits, hipStream_t stream
         sum.ntot += a.seg[s].N;
     }
     sum.tile_begin[a.nseg] = sum.ntot / 64;
-    // the residual + norm pass takes rows of at most 8192 values with 16-byte aligned operands, and is never carried
+    // the residual + norm pass takes rows of at most 8192 values with 16-byte aligned operands
     const bool norm_ok = a.epi != LinArgs::EPI_ADD_NORM ||
-                         (sum.ntot <= 256 * 8 * 4 && !a.sum_out && a.norm.x && a.norm.g && a.norm.h && a.norm.n &&
+                         (sum.ntot <= 256 * 8 * 4 && a.norm.x && a.norm.g && a.norm.h && a.norm.n &&
                           ((((uintptr_t)a.norm.x) | ((uintptr_t)a.norm.g) | ((uintptr_t)a.norm.h) | ((uintptr_t)a.norm.n)) & 15) == 0);
     *fused = a.epi != LinArgs::EPI_NONE && norm_ok;
     const int64_t items = a.R * ((a.epi == LinArgs::EPI_SWIGLU ? sum.ntot / 2 : sum.ntot) / 8);
@@ -178,10 +178,6 @@ static hipError_t finish_splits(const LinArgs &a, int splits, hipStream_t stream
         sum.rope = a.rope;
         sum.rope_log_theta = log(a.rope.theta);
     }
-    if (a.sum_out) {                         // the caller has it carried by a later launch, or launches it
-        *a.sum_out = sum;
-        return hipSuccess;
-    }
     return launch_splitk_sum(sum, stream);
 }
 
@@ -191,7 +187,6 @@ static hipError_t launch_linear_each(int dtype, const LinArgs &a, hipStream_t st
     for (int s = 0; s < a.nseg; ++s) {
         LinArgs one = a;
         one.rider_units = 0;
-        one.sum_out = nullptr;
         one.nseg = 1;
         one.seg[0] = a.seg[s];
         if (a.seg[s].X) { one.X = a.seg[s].X; one.ldx = a.seg[s].ldx; }
@@ -242,7 +237,6 @@ static hipError_t launch_linear_impl(int dtype, const LinArgs &a, hipStream_t st
 
 hipError_t launch_linear(int dtype, const LinArgs &a, hipStream_t stream)
 {
-    if (a.sum_out) *a.sum_out = SumArgs{};
     if (a.epi == LinArgs::EPI_ADD_F32 && a.nseg != 1) return hipErrorInvalidValue;
     if (a.epi == LinArgs::EPI_SWIGLU && (a.nseg != 2 || a.seg[0].N != a.seg[1].N)) return hipErrorInvalidValue;
     if (a.epi == LinArgs::EPI_ADD_NORM && a.nseg != 1) return hipErrorInvalidValue;

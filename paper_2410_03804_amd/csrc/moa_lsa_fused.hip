@@ -31,7 +31,6 @@
 // Arithmetic is that of the three-kernel form (same MFMA order along d_in, Q/K/V rounded once to the storage type,
 // the same order of additions in the column sums), so all give the same bits.
 #include "moa_common.h"
-#include "moa_sum_device.h"
 #include "moa_tree_device.h"
 
 #include <math.h>
@@ -53,11 +52,10 @@ struct LsaFusedArgs {
     int parts;                     // Hq / Hkv / 2: workgroups per KV head
     int units;                     // Hkv * parts
     int units_per_xcd;
-    int lead_blocks, small_lead, red_blocks;   // workgroups in front of the kernel's own: integer work of a step, a carried summing pass
+    int lead_blocks;                           // workgroups in front of the kernel's own: integer work of a step
     int pf_lead;                               // the last of them (a multiple of the XCD count) only read ahead: see lsa_warm_block
     int rider_units;
     StepSmallArgs rider;
-    SumArgs red;
 };
 
 template <int DH, int NB, int TT>
@@ -232,14 +230,9 @@ __global__ __launch_bounds__(512) void k_lsa_fused(LsaFusedArgs a)
     constexpr int XD = XS - 1;                   // activation tiles requested ahead
     extern __shared__ __attribute__((aligned(16))) bf16_t sm[];
 
-    if ((int)blockIdx.x < a.lead_blocks) {       // the first workgroups of the grid carry work of other calls
-        if ((int)blockIdx.x < a.small_lead) {
-            if ((int)blockIdx.x < a.rider_units && threadIdx.x < 64)
-                step_small_unit(a.rider, (int)blockIdx.x, (int32_t *)sm, (int32_t *)sm + MOA_MAX_TREE);
-        } else {
-            const int blk = 2 * ((int)blockIdx.x - a.small_lead) + (int)(threadIdx.x >> 8);
-            if (blk < a.red_blocks) splitk_reduce_block(a.red, blk, (int)(threadIdx.x & 255));
-        }
+    if ((int)blockIdx.x < a.lead_blocks) {       // the first workgroups of the grid carry the step's integer work
+        if ((int)blockIdx.x < a.rider_units && threadIdx.x < 64)
+            step_small_unit(a.rider, (int)blockIdx.x, (int32_t *)sm, (int32_t *)sm + MOA_MAX_TREE);
         return;
     }
     // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2: an XCD keeps the weight slices of its
@@ -423,18 +416,13 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
     constexpr int NXI = (RB / 8 + 7) / 8;        // activation-tile load instructions per wavefront
     extern __shared__ __attribute__((aligned(16))) bf16_t sm[];
 
-    if ((int)blockIdx.x < a.lead_blocks) {       // the first workgroups of the grid carry work of other calls
+    if ((int)blockIdx.x < a.lead_blocks) {       // the first workgroups of the grid carry the step's integer work
         if ((int)blockIdx.x >= a.lead_blocks - a.pf_lead) {
             lsa_warm_block<DH, NB, TT>(a, (int)blockIdx.x - (a.lead_blocks - a.pf_lead), sm);
             return;
         }
-        if ((int)blockIdx.x < a.small_lead) {
-            if ((int)blockIdx.x < a.rider_units && threadIdx.x < 64)
-                step_small_unit(a.rider, (int)blockIdx.x, (int32_t *)sm, (int32_t *)sm + MOA_MAX_TREE);
-        } else {
-            const int blk = 2 * ((int)blockIdx.x - a.small_lead) + (int)(threadIdx.x >> 8);
-            if (blk < a.red_blocks) splitk_reduce_block(a.red, blk, (int)(threadIdx.x & 255));
-        }
+        if ((int)blockIdx.x < a.rider_units && threadIdx.x < 64)
+            step_small_unit(a.rider, (int)blockIdx.x, (int32_t *)sm, (int32_t *)sm + MOA_MAX_TREE);
         return;
     }
     const int bx = (int)blockIdx.x - a.lead_blocks;
@@ -712,13 +700,7 @@ hipError_t launch_lsa_fused(const LsaFusedCall &c, hipStream_t stream)
     fa.units_per_xcd = (fa.units + 7) / 8;
     fa.rider_units = c.rider_units;
     if (c.rider_units > 0) fa.rider = c.rider;
-    fa.small_lead = (c.rider_units + 7) & ~7;    // multiples of the XCD count: the unit mapping keeps its phase
-    fa.red_blocks = 0;
-    if (c.carry_sum && c.carry_sum->blocks > 0) {
-        fa.red = *c.carry_sum;
-        fa.red_blocks = c.carry_sum->blocks;
-    }
-    fa.lead_blocks = fa.small_lead + ((((fa.red_blocks + 1) / 2) + 7) & ~7);   // a lead workgroup of 512 threads does two blocks of the pass
+    fa.lead_blocks = (c.rider_units + 7) & ~7;   // multiples of the XCD count: the unit mapping keeps its phase
     fa.pf_lead = c.w_packed ? 16 : 0;     // wanted; launch_lsa_fused_as decides when it knows the grid
     // Rows per workgroup.  Measured at the Llama-3-8B shape (d_in 2048), a workgroup takes about 31 + 9 (rows / 32)
     // microseconds from plain weights and 10 + 11.7 (rows / 32) from packed ones, whatever else runs (it is bound by

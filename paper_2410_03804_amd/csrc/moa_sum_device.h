@@ -1,5 +1,4 @@
-// Device-side body of the pass that adds up the K slices of a weight-streaming projection (fp32 partial sums, fixed
-// slice order), shared by the kernel of its own and by the kernels that carry the pass in spare workgroups.
+// Device-side body of the pass that adds up the K slices of a projection (fp32 partial sums, fixed slice order).
 #ifndef MOA_SUM_DEVICE_H
 #define MOA_SUM_DEVICE_H
 #include "moa_common.h"

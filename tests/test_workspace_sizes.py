@@ -80,6 +80,18 @@ def test_a_query_covers_smaller_sizes(name):
             assert lsa_need(s, t) <= have, (name, (B, P, M, T), t)
 
 
+@pytest.mark.parametrize("name", ["8b", "70b", "dh64", "mha"])
+def test_a_steps_query_covers_its_self_attention_layer(name):
+    """That layer has key / value heads of its own."""
+    rng = random.Random(11)
+    s = SHAPES[name]
+    for _ in range(1500):
+        B, M, P = rng.randint(1, 16), rng.randint(1, 200), rng.choice([1, 64, 300, 1024, 8192])
+        kv = rng.choice([h for h in range(1, s.n_q_heads + 1) if s.n_q_heads % h == 0])
+        sa = moa.Shape(s.n_layers, s.d_model, s.n_q_heads, kv, s.head_dim, s.d_lsa_in, s.lsa_q_heads, s.lsa_kv_heads, s.dtype)
+        assert sa_need(sa, B, M, 0, M, P) <= moa.workspace_bytes(s, B, P, M, 1), (name, B, M, P, kv)
+
+
 @pytest.mark.parametrize("name", ["8b", "70b", "dh64", "fp32"])
 def test_queries_of_blocks_cover_smaller_sizes(name):
     rng = random.Random(9)
