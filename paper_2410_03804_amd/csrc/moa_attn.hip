@@ -401,12 +401,6 @@ constexpr int LK = 64;            // keys per tile
 constexpr int LRING = 4;
 constexpr float RESCALE_AT = 8.f; // log2
 
-__device__ __forceinline__ void lds_dma16_any(uint32_t lds, uint32_t off, const void *base)
-{
-    // base may have been written by a vector instruction: five wait states before it is read as a scalar address
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base));
-}
-
 template <int DH>
 __global__ __launch_bounds__(256, 1) void k_attn_long(AttnGroup grp, SplitGeom geo)
 {
@@ -464,8 +458,8 @@ __global__ __launch_bounds__(256, 1) void k_attn_long(AttnGroup grp, SplitGeom g
         for (int j = 0; j < 4; ++j) {
             const int row = 16 * wave + 4 * j + (lane >> 4);
             const uint32_t off = (uint32_t)min(row, last) * ROWB + 16 * ((lane & 15) ^ (4 * (lane >> 4) + j));
-            lds_dma16_any(dst + 4 * j * ROWB, off, kp);
-            lds_dma16_any(dst + HALFT + 4 * j * ROWB, off, vp);
+            lds_dma16(dst + 4 * j * ROWB, off, kp);
+            lds_dma16(dst + HALFT + 4 * j * ROWB, off, vp);
         }
     };
 

@@ -9,11 +9,15 @@ namespace moa {
 
 // 64 lanes x 16 bytes from base + off (each lane its own) to 1 KB of LDS at `lds`.  Written out because the compiler, which
 // knows what the builtin writes, waits for every such load in flight in front of any LDS read that might alias it: the
-// loads of later k tiles would be waited for with the current one's.  base must be the product of scalar arithmetic (a
-// scalar written by a vector instruction may be read too early by this one, and nobody inserts the wait states here).
+// loads of later k tiles would be waited for with the current one's.  A vector memory instruction reads a scalar too early
+// when a vector instruction wrote it less than five wait states before (one restored from a lane of a spill register, say),
+// and nobody inserts wait states in here: the base goes through a scalar move, which waits for it in hardware and is at the
+// same time the wait state between the write of m0 and its use.  (m0 is reserved and cannot be named as clobbered; nothing
+// else in the kernels that use this touches it.)
 __device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t off, const void *base)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base));
+    uint64_t at;
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0" : "=&s"(at) : "s"(lds), "v"(off), "s"(base));
 }
 template <int N>
 __device__ __forceinline__ void wait_loads_and_barrier()
