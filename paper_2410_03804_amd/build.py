@@ -10,9 +10,11 @@ from pathlib import Path
 HERE = Path(__file__).resolve().parent
 CSRC = HERE / "csrc"
 LIB = HERE / "libmoa.so"
-SOURCES = ["moa_api.hip", "moa_tree.hip", "moa_gemm.hip", "moa_gemm_f32.hip", "moa_gemm_bf16.hip", "moa_attn.hip", "moa_lsa.hip", "moa_lsa_fused.hip", "moa_block.hip", "moa_draft_tree.hip", "moa_lm_head.hip", "moa_msg.hip", "moa_gzip.hip", "moa_prof.hip"]
+SOURCES = ["moa_api.hip", "moa_tree.hip", "moa_gemm.hip", "moa_gemm_f32.hip", "moa_gemm_bf16.hip", "moa_attn.hip", "moa_attn_long.hip", "moa_lsa.hip", "moa_lsa_fused.hip", "moa_block.hip", "moa_draft_tree.hip", "moa_lm_head.hip", "moa_msg.hip", "moa_gzip.hip", "moa_prof.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# results of matrix instructions in vector registers (said in the source why)
+SOURCE_FLAGS = {"moa_attn_long.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _hipcc() -> str:
@@ -24,7 +26,7 @@ def _hipcc() -> str:
 
 def _compile(src: str, objdir: Path) -> Path:
     obj = objdir / (Path(src).stem + ".o")
-    cmd = [_hipcc(), *FLAGS, "-c", str(CSRC / src), "-o", str(obj)]
+    cmd = [_hipcc(), *FLAGS, *SOURCE_FLAGS.get(src, []), "-c", str(CSRC / src), "-o", str(obj)]
     r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
     err = "\n".join(l for l in r.stderr.splitlines() if noise not in l)

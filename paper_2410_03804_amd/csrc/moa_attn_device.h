@@ -1,0 +1,46 @@
+// What the attention kernels of moa_attn.hip and moa_attn_long.hip share.
+#ifndef MOA_ATTN_DEVICE_H
+#define MOA_ATTN_DEVICE_H
+#include "moa_common.h"
+#include "../../include/moa.h"
+
+namespace moa {
+
+__device__ __forceinline__ int clamp_len(int len, int cap, int32_t *dev_status)
+{
+    if (len < 0 || len > cap) {
+        if (dev_status) atomicOr(dev_status, MOA_DEV_BAD_LENGTH);
+        len = len < 0 ? 0 : cap;
+    }
+    return len;
+}
+
+struct SplitGeom {
+    int nsplit;     // key-range slices
+    int rowtiles;   // workgroups along the G*Mq rows of one (sequence, KV head)
+    int rows_pad;   // rowtiles * rows per workgroup
+    bool wide;      // 256 rows per workgroup (k_attn_long) instead of 128
+};
+
+typedef _Float16 f16_t;
+typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
+
+// up to two independent calls of the same shape in one launch (blockIdx.z / nbg picks the call)
+struct AttnGroup {
+    AttnArgs a[2];
+    int nbg;      // B * Hkv of one call
+    int ncalls;   // 1 or 2
+};
+
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+
+// 2^x by the hardware instruction alone: arguments here are <= 0 and results below the normal range may
+// become 0, which a softmax weight may
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// the kernel in 256-row tiles (moa_attn_long.hip): keys per tile, and the launch of the split pass
+constexpr int LK = 64;
+hipError_t launch_attn_long(const AttnGroup &grp, const SplitGeom &g, hipStream_t stream);
+
+}  // namespace moa
+#endif

@@ -1,0 +1,295 @@
+// The attention core over a split key range (see moa_attn.hip) in tiles of 256 query rows per workgroup.
+// head_dim 128 and more than 128 rows per (sequence, KV head).  Four wavefronts, one per SIMD, 64 query rows each (two blocks
+// of 32), so that an operand read from LDS serves two MFMAs: with 32 rows per wavefront the reads of K and V alone keep LDS
+// busy for three quarters of the matrix time.  Per 32 keys a wavefront has 32 MFMAs (1024 clocks) and about 1000 clocks of
+// softmax arithmetic, and nobody else on its SIMD to overlap them with, so the loop is laid out as phases of 16 MFMAs with
+// one score element's arithmetic behind each:
+//   phase 0 of 32 keys j:  S(j+1) of block 0 and P V(j-1) of block 1, between them the softmax of S(j) of block 0
+//   phase 1:               S(j+1) of block 1 and P V(j)   of block 0, between them the softmax of S(j) of block 1
+// The operands of a phase were read from LDS one phase earlier, each into the place of one just used.
+// K and V come in tiles of 64 keys straight into an LDS ring of four (a piece of row r lies at position c ^ f(r), f a
+// permutation of 0 .. 15 on 16 neighbouring rows: operand reads of K touch 16 rows of one column, the transposing reads of V
+// eight rows of 64 bytes); one barrier per tile, two tiles in flight behind the current one.
+// The reference of the exponent is the running maximum, exactly: the heaviest weights then sit at the top of a binade, where
+// their rounding to bf16 is smallest (a reference that lags behind it by up to 2^8 gives 1.04 to 1.24 times the error against
+// 64 bits, and would save 7 to 14 % of the time).  A rescale is 64 multiplications, so the accumulators are kept in vector
+// registers and the operands that come from LDS in the accumulation registers, the other way round than the compiler's
+// default (-amdgpu-mfma-vgpr-form for this file; in accumulation registers a rescale takes four times as long).
+// What bounds it is the matrix pipe and the softmax arithmetic together.  8 x 32768 keys x 128 tree tokens, both cores:
+// 1366 us (0.81 PFLOP/s), where 128 rows per workgroup take 1440.
+#include "moa_attn_device.h"
+#include "moa_gemm_device.h"
+
+#include <math.h>
+
+#include <type_traits>
+
+namespace moa {
+
+constexpr int LRING = 4;
+
+template <int DH>
+__global__ __launch_bounds__(256, 1) void k_attn_long(AttnGroup grp, SplitGeom geo)
+{
+    static_assert(DH == 128, "a row is 16 pieces of 16 bytes");
+    constexpr int NKS = DH / 16, NDB = DH / 32;
+    constexpr uint32_t ROWB = DH * 2, HALFT = LK * ROWB, TILEB = 2 * HALFT;    // bytes of a row, of a tile's K or V, of a tile
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+
+    // Workgroups are dealt to the 8 XCDs round-robin: the row tiles of one key range are neighbours on one XCD, whose L2
+    // then serves all but the first.
+    const int xcd = (int)blockIdx.x & 7, slot0 = (int)blockIdx.x >> 3;
+    const int unit = 8 * (slot0 / geo.rowtiles) + xcd, rowtile = slot0 % geo.rowtiles;
+    if (unit >= geo.nsplit * grp.nbg * grp.ncalls) return;       // the whole workgroup, before any barrier
+    const int split = unit % geo.nsplit, cbg = unit / geo.nsplit;
+    const int call = cbg / grp.nbg, bg = cbg - call * grp.nbg;
+    const AttnArgs &a = grp.a[call];
+    const int b = bg / a.Hkv, g = bg - b * a.Hkv;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int G = a.H / a.Hkv, RG = G * a.Mq, W = (a.mask_rows + 63) >> 6;
+    const float sc = 1.4426950408889634f / sqrtf((float)DH);   // scores are kept in the log2 domain
+
+    const int len = clamp_len(a.len[b], a.P_cap, tid == 0 ? a.dev_status : nullptr);
+    const int nt = (len + LK - 1) / LK;
+    const int per = (nt + geo.nsplit - 1) / geo.nsplit;
+    const int t0 = min(split * per, nt), nc = min(t0 + per, nt) - t0;          // this slice's tiles of the cache
+    const int Mt = a.mask ? a.Mt : 0;
+    const int ntiles = __builtin_amdgcn_readfirstlane(nc + (split == geo.nsplit - 1 ? (Mt + LK - 1) / LK : 0));
+
+    const char *kc = (const char *)a.kcache + (int64_t)bg * a.P_cap * ROWB, *vc = (const char *)a.vcache + (int64_t)bg * a.P_cap * ROWB;
+    const char *ktp = (const char *)a.ktree + (int64_t)bg * a.tree_cap * ROWB, *vtp = (const char *)a.vtree + (int64_t)bg * a.tree_cap * ROWB;
+
+    const int rowbase = rowtile * 256 + wave * 64;
+    bf16x8 qf[2][NKS];
+    int mrow[2];
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+        const int rho = min(rowbase + 32 * blk + l32, RG - 1);
+        mrow[blk] = rho / G;
+        const bf16_t *qrow = (const bf16_t *)a.q + (((int64_t)b * a.Mq + mrow[blk]) * a.H + g * G + (rho - mrow[blk] * G)) * DH;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) qf[blk][ks] = *(const bf16x8 *)(qrow + 16 * ks + 8 * half);
+    }
+
+    // tile i of this workgroup: cache tile t0 + i, then the tree's; past the last one it is the last one again (nobody reads
+    // that).  Wavefront w moves rows 16 w .. 16 w + 15 of K and of V, four rows an instruction.
+    auto first_row = [&](int i) { return i < nc ? (t0 + i) * LK : (i - nc) * LK; };
+    auto rows_valid = [&](int i) { return (i < nc ? len : Mt) - first_row(i); };             // >= 1
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
+    auto issue = [&](int i_) {
+        const int i = min(i_, ntiles - 1), last = min(rows_valid(i), LK) - 1;
+        const char *kp = (i < nc ? kc : ktp) + (int64_t)first_row(i) * ROWB, *vp = (i < nc ? vc : vtp) + (int64_t)first_row(i) * ROWB;
+        const uint32_t dst = lds0 + (uint32_t)(i_ & (LRING - 1)) * TILEB + (uint32_t)wave * 16 * ROWB;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int row = 16 * wave + 4 * j + (lane >> 4);
+            const uint32_t off = (uint32_t)min(row, last) * ROWB + 16 * ((lane & 15) ^ (4 * (lane >> 4) + j));
+            lds_dma16(dst + 4 * j * ROWB, off, kp);
+            lds_dma16(dst + HALFT + 4 * j * ROWB, off, vp);
+        }
+    };
+
+    f32x16 acc[2][NDB];
+    float mref[2] = {-INFINITY, -INFINITY}, lsum[2] = {0.f, 0.f};     // exponent's reference (log2 domain); this lane's part of the sum
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+        for (int d = 0; d < NDB; ++d)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[blk][d][e] = 0.f;
+
+    if (ntiles > 0) {
+        uint32_t koff[NKS], voff[NDB][2];
+        const int fk = 4 * (l32 & 3) + ((l32 >> 2) & 3);
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) koff[ks] = l32 * ROWB + 16 * ((2 * ks + half) ^ fk);
+        // transpose read: lane j of a 16-lane group addresses key (j >> 2), head_dim 4 (j & 3) of the group's 16
+        const int vkey = (lane & 15) >> 2;
+#pragma unroll
+        for (int d = 0; d < NDB; ++d)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                voff[d][h] = HALFT + (8 * h + 4 * half + vkey) * ROWB + 8 * (lane & 1) +
+                             16 * ((4 * d + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ (4 * vkey + 2 * h + half));
+
+        bf16x8 kf[NKS], vf[2 * NDB], pf[2][2];
+        f32x16 sraw;                              // the scores that the last phase's MFMAs left
+        float sv[2][16], tmax[2];                 // the scores of the next softmax of either block, and their maximum
+        auto read_k = [&](int ks, uint32_t at) { kf[ks] = *(const bf16x8 *)(smem + (koff[ks] + at)); };
+        auto read_v = [&](int x, uint32_t at) {           // x = 4 st2 + d: keys 16 st2 .., head_dim 32 d ..
+            union { i16x4 h[2]; bf16x8 v; } u;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                u.h[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) i16x4 *)(smem + (voff[x % NDB][h] + at + (x / NDB) * 16 * ROWB)));
+            vf[x] = u.v;
+        };
+        // keys that do not count (tree rows outside the ancestor set, rows past the end) get -inf
+        auto mask_scores = [&](int blk, int i, int sub) {
+            if (i >= ntiles) return;
+            const int base = 32 * sub, nvalid = rows_valid(i) - base;
+            if (i < nc && nvalid >= 32) return;                  // the same decision in the whole workgroup
+            uint32_t vis = nvalid >= 32 ? 0xffffffffu : nvalid <= 0 ? 0u : (1u << nvalid) - 1u;
+            if (i >= nc && nvalid > 0)
+                vis &= (uint32_t)(a.mask[((int64_t)b * a.mask_rows + a.mask_row0 + mrow[blk]) * W + (i - nc)] >> base);
+            float tm = -INFINITY;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                if (!((vis >> (8 * (v >> 2) + 4 * half + (v & 3))) & 1u)) sv[blk][v] = -INFINITY;
+                tm = fmaxf(tm, sv[blk][v]);
+            }
+            tmax[blk] = tm;
+        };
+        // BLK: the block whose softmax this phase does.  LDS offsets of the V rows read in phase 0, the K rows read in phase 1.
+        // The empty asm statements keep each step's arithmetic in its place between the MFMAs.
+        auto phase = [&](auto blk_c, uint32_t vat, uint32_t kat) {
+            constexpr int BLK = decltype(blk_c)::value, OB = 1 - BLK;
+            if (__any(tmax[BLK] * sc > mref[BLK])) {
+                const float tm = fmaxf(tmax[BLK], __shfl_xor(tmax[BLK], 32));
+                const float mnew = fmaxf(mref[BLK], tm * sc);    // sc > 0: scaling keeps the order (and -inf)
+                const float corr = fast_exp2(mref[BLK] - (mnew == -INFINITY ? 0.f : mnew));
+                mref[BLK] = mnew;
+                lsum[BLK] *= corr;
+#pragma unroll
+                for (int d = 0; d < NDB; ++d)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[BLK][d][e] *= corr;
+            }
+            const float neg = mref[BLK] == -INFINITY ? 0.f : -mref[BLK];
+            float p[16], sum = lsum[BLK], tm = -INFINITY;
+            f32x16 snew = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int x = e / 2;
+                if (e % 2 == 0) snew = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[x], qf[BLK][x], snew, 0, 0, 0);
+                else acc[OB][x % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[x], pf[OB][x / NDB], acc[OB][x % NDB], 0, 0, 0);
+                if (BLK == 0 && e % 2 == 1) read_v(x, vat);
+                if (BLK == 1 && e % 2 == 0) read_k(x, kat);
+                p[e] = fast_exp2(fmaf(sv[BLK][e], sc, neg));
+                if (e > 0) sum += p[e - 1];
+                asm volatile("" : "+v"(p[e]), "+v"(sum));
+                sv[OB][e] = sraw[e];
+                if (e % 2 == 1) {
+                    tm = fmaxf(fmaxf(tm, sv[OB][e - 1]), sv[OB][e]);
+                    asm volatile("" : "+v"(sv[OB][e - 1]), "+v"(sv[OB][e]), "+v"(tm));
+                }
+                if (e % 2 == 1) {                               // P^T slot t of step st2 is key 16 st2 + 8 (t >> 2) + 4 half + (t & 3)
+                    pf[BLK][e / 8][e % 8 - 1] = (__bf16)p[e - 1];
+                    pf[BLK][e / 8][e % 8] = (__bf16)p[e];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            lsum[BLK] = sum + p[15];
+            tmax[OB] = tm;
+            sraw = snew;
+        };
+        typedef std::integral_constant<int, 0> B0;
+        typedef std::integral_constant<int, 1> B1;
+
+        issue(0);
+        issue(1);
+        wait_loads_and_barrier<8>();
+        issue(2);
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) read_k(ks, 0);
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) sraw[e] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) sraw = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[blk][ks], sraw, 0, 0, 0);
+            if (blk == 1) break;
+            tmax[0] = sraw[0];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                sv[0][e] = sraw[e];
+                tmax[0] = fmaxf(tmax[0], sraw[e]);
+            }
+            mask_scores(0, 0, 0);
+        }
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) read_k(ks, 32 * ROWB);
+#pragma unroll
+        for (int x = 0; x < 2 * NDB; ++x)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) vf[x][t] = (__bf16)0.f;
+#pragma unroll
+        for (int st2 = 0; st2 < 2; ++st2)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) pf[1][st2][t] = (__bf16)0.f;
+
+        for (int t = 0; t < ntiles; ++t) {
+            const uint32_t cur = (uint32_t)(t & (LRING - 1)) * TILEB, nxt = (uint32_t)((t + 1) & (LRING - 1)) * TILEB;
+            wait_loads_and_barrier<8>();           // tile t + 1 is in LDS for everybody, nobody reads tile t - 1 any more
+            issue(t + 3);
+#pragma unroll
+            for (int sub = 0; sub < 2; ++sub) {
+                phase(B0{}, cur + sub * 32 * ROWB, 0u);
+                mask_scores(1, t, sub);
+                phase(B1{}, 0u, nxt + sub * 32 * ROWB);
+                mask_scores(0, t + sub, 1 - sub);
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < 2 * NDB; ++x)
+            acc[1][x % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[x], pf[1][x / NDB], acc[1][x % NDB], 0, 0, 0);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+
+    // One slice: the result.  Several: the slice's own normalised output (a convex combination of V rows, so it fits fp16
+    // with 2^-12 relative rounding, eight times finer than the bf16 result), reference and sum in fp32.
+    f16_t *__restrict__ part_o = (f16_t *)a.ws;
+    float *__restrict__ part_ml = (float *)(part_o + (size_t)grp.nbg * geo.nsplit * geo.rows_pad * DH);
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+        const float l = lsum[blk] + __shfl_xor(lsum[blk], 32);
+        const int rho = rowbase + 32 * blk + l32;
+        if (rho >= RG) continue;
+        const float inv = l > 0.f ? 1.0f / l : 0.f;
+        if (geo.nsplit == 1) {
+            bf16_t *o = (bf16_t *)a.out + (((int64_t)b * a.Mq + mrow[blk]) * a.H + g * G + (rho - mrow[blk] * G)) * DH + 4 * half;
+#pragma unroll
+            for (int d = 0; d < NDB; ++d)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    u32x2 pk;
+                    pk[0] = pack_bf16x2(acc[blk][d][4 * q4] * inv, acc[blk][d][4 * q4 + 1] * inv);
+                    pk[1] = pack_bf16x2(acc[blk][d][4 * q4 + 2] * inv, acc[blk][d][4 * q4 + 3] * inv);
+                    *(u32x2 *)(o + 32 * d + 8 * q4) = pk;
+                }
+            if (l == 0.f && a.empty_is_error && half == 0 && a.dev_status) atomicOr(a.dev_status, MOA_DEV_EMPTY_KEYS);
+            continue;
+        }
+        const int64_t prow = ((int64_t)bg * geo.nsplit + split) * geo.rows_pad + rho;
+        if (half == 0) {
+            part_ml[prow * 2 + 0] = mref[blk];
+            part_ml[prow * 2 + 1] = l;
+        }
+#pragma unroll
+        for (int d = 0; d < NDB; ++d)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                f16x4 v = {(f16_t)(acc[blk][d][4 * q4] * inv), (f16_t)(acc[blk][d][4 * q4 + 1] * inv),
+                           (f16_t)(acc[blk][d][4 * q4 + 2] * inv), (f16_t)(acc[blk][d][4 * q4 + 3] * inv)};
+                *(f16x4 *)(part_o + prow * DH + 32 * d + 8 * q4 + 4 * half) = v;
+            }
+    }
+}
+
+hipError_t launch_attn_long(const AttnGroup &grp, const SplitGeom &g, hipStream_t stream)
+{
+    constexpr size_t lds = (size_t)LRING * LK * 128 * 2 * 2;
+    static bool raised[16] = {};
+    hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_long<128>, lds);
+    if (e != hipSuccess) return e;
+    const int64_t units8 = ((int64_t)g.nsplit * grp.ncalls * grp.nbg + 7) / 8, grid = 8 * units8 * g.rowtiles;
+    if (grid > 0x7fffffff) return hipErrorInvalidValue;
+    prof_begin(K_ATTN_LONG, stream);
+    MOA_KLAUNCH((k_attn_long<128>), dim3((unsigned)grid), dim3(256), lds, stream, grp, g);
+    prof_end(stream);
+    return hipGetLastError();
+}
+
+}  // namespace moa

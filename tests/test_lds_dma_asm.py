@@ -8,13 +8,13 @@ import pytest
 
 from paper_2410_03804_amd import build
 
-SOURCES = ["moa_gemm_bf16.hip", "moa_lm_head.hip", "moa_attn.hip"]
+SOURCES = ["moa_gemm_bf16.hip", "moa_lm_head.hip", "moa_attn_long.hip"]
 
 
 @pytest.fixture(scope="module")
 def asm():
     def compile_one(src):
-        cmd = [build._hipcc(), *build.FLAGS, "--cuda-device-only", "-S", "-o", "-", str(build.CSRC / src)]
+        cmd = [build._hipcc(), *build.FLAGS, *build.SOURCE_FLAGS.get(src, []), "--cuda-device-only", "-S", "-o", "-", str(build.CSRC / src)]
         return subprocess.run(cmd, capture_output=True, text=True, check=True).stdout
     with ThreadPoolExecutor(3) as ex:
         return dict(zip(SOURCES, ex.map(compile_one, SOURCES)))
