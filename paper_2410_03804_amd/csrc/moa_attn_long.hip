@@ -12,7 +12,7 @@
 // eight rows of 64 bytes); one barrier per tile, two tiles in flight behind the current one.
 // The reference of the exponent is the running maximum, exactly: the heaviest weights then sit at the top of a binade, where
 // their rounding to bf16 is smallest (a reference that lags behind it by up to 2^8 gives 1.04 to 1.24 times the error against
-// 64 bits, and would save 7 to 14 % of the time).  A rescale is 64 multiplications, so the accumulators are kept in vector
+// 64 bits, and would save 5 to 13 % of the time).  A rescale is 64 multiplications, so the accumulators are kept in vector
 // registers and the operands that come from LDS in the accumulation registers, the other way round than the compiler's
 // default (-amdgpu-mfma-vgpr-form for this file; in accumulation registers a rescale takes four times as long).
 // What bounds it is the matrix pipe and the softmax arithmetic together.  8 x 32768 keys x 128 tree tokens, both cores:
@@ -146,7 +146,9 @@ __global__ __launch_bounds__(256, 1) void k_attn_long(AttnGroup grp, SplitGeom g
         auto phase = [&](auto blk_c, uint32_t vat, uint32_t kat) {
             constexpr int BLK = decltype(blk_c)::value, OB = 1 - BLK;
             if (__any(tmax[BLK] * sc > mref[BLK])) {
-                const float tm = fmaxf(tmax[BLK], __shfl_xor(tmax[BLK], 32));
+                // the other half's maximum by a lane swap in the vector unit: a shuffle would wait for the operand reads in flight
+                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(tmax[BLK]), __float_as_uint(tmax[BLK]), false, false);
+                const float tm = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
                 const float mnew = fmaxf(mref[BLK], tm * sc);    // sc > 0: scaling keeps the order (and -inf)
                 const float corr = fast_exp2(mref[BLK] - (mnew == -INFINITY ? 0.f : mnew));
                 mref[BLK] = mnew;
