@@ -253,9 +253,9 @@ static thread_local bool t_lsa_extra_taken = false;
 static std::atomic<int> g_lsa_form{0};
 
 // Whether a Layer Self-Attention pass over T tokens runs as the one kernel.  Left to itself the library keeps the
-// separate kernels in two corners where they measured faster: a handful of rows (T L <= 192: the weight-streaming
-// projection spreads the weights over every compute unit, the one-kernel form over T x 8 workgroups only -- 28 against
-// 48 us for 5 tokens at the Llama-3-8B shape), and many tokens whose layer count fills its last 32-row block badly
+// separate kernels in two corners where they measured faster: a handful of rows (T L <= 192: the projection of its own
+// spreads the weights over every compute unit, the one-kernel form over T x 8 workgroups only -- 27 against 42 us for 5
+// tokens at the Llama-3-8B shape), and many tokens whose layer count fills its last 32-row block badly
 // (L = 80 in 96 rows: 535 against 492 us for 256 tokens at the Llama-2-70B shape).
 static bool lsa_takes_fused(const moa_shape_t *shape, int64_t T, const void *hs, const void *wq, const void *wk,
                             const void *wv, const void *abar)

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void k_tree_expand(int level, int Bw, int n_ma
 
 // One thread per candidate (several where there are more than 1024).  Bound by the n^2 comparisons of one compute unit, so
 // the keys are 32-bit values: which of two equal ones is ahead follows from the index alone, and for every candidate
-// outside the wavefront's own 64 that is decided by >= against >.  328 candidates: 5.7 us against 12.2 with 64-bit keys and
+// outside the wavefront's own 64 that is decided by >= against >.  328 candidates: 8.4 us against 12.3 with 64-bit keys and
 // runs of candidates per thread.
 __global__ __launch_bounds__(1024) void k_tree_finalize(int n, int n_max, int keep, int ld_out, const int32_t *__restrict__ root_tok,
                                                         const float *__restrict__ cand_logp, const int32_t *__restrict__ cand_tok,
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(1024) void k_tree_finalize(int n, int n_max, int ke
 // bound that Bw of its own values reach, so nothing below the largest of the four wavefronts' bounds can be among the
 // slice's Bw best, and what reaches it (a few times Bw values, all of them in at most 4 Bw threads) is ranked in LDS.  A
 // second kernel ranks the S*Bw survivors of a row and merges the slices' (max, sum of exponentials).
-// Latency bound: two barriers per slice.  8 rows of 128256 bf16 logits: 5.9 + 4.0 us against 16.9 + 6.4 with every thread's
+// Latency bound: two barriers per slice.  8 rows of 128256 bf16 logits: 6.4 + 6.1 us against 14.1 + 6.3 with every thread's
 // values sorted, Bw rounds of two barriers over the heads of the 256 lists, and 2-byte loads.
 
 // Wavefront-wide maximum of an unsigned value by data-parallel-primitive moves inside the vector ALU (four shifts within

@@ -1,8 +1,6 @@
-"""GPU parity of the bare projection (moa_linear) across the kernels it dispatches to -- weight streaming with the
-activation slice resident in LDS or re-read in chunks (at most 64 rows, K in 1024s or 512s), weight streaming in one
-shot (up to 192 rows), the tiled GEMM, the narrow and
-the generic forms -- against the oracle's projection, with ragged row counts and the smallest and largest row count of each
-form."""
+"""GPU parity of the bare projection (moa_linear) at the row counts and widths of a decoding program against the oracle's
+projection: the bf16 matrix kernel in its tiles with and without slices of K, the single-precision kernels, the generic one.
+The edges of the bf16 kernel's tiles are in test_gpu_gemm_tiles.py."""
 import numpy as np
 import pytest
 import torch
@@ -26,25 +24,25 @@ def moa(G):
     return m
 
 
-# (dtype, rows, K, N): what decides the kernel is in the comment
+# (dtype, rows, K, N)
 CASES = [
-    ("bf16", 1, 4096, 4096),      # chunks of a 1024-wide slice: 64 tiles x 4 slices, one row
-    ("bf16", 33, 4096, 8192),     # the same, ragged rows
-    ("bf16", 64, 1024, 16384),    # a single slice: nothing to add up but the chunks
-    ("bf16", 60, 2048, 4096),     # 512-wide slices in two chunks (64 tiles x 4)
-    ("bf16", 60, 14336, 4096),    # 14 slices (activation slice resident: 18 workgroups per slice, 15 wavefronts each)
-    ("bf16", 60, 4096, 10240),    # activation slice resident, one group of 16 features per wavefront, ten wavefronts
-    ("bf16", 64, 4096, 28672),    # the same with two groups per wavefront
-    ("bf16", 5, 2048, 14336),     # two slices, seven wavefronts
-    ("bf16", 47, 4096, 6208),     # groups do not divide: the last workgroup of a slice has idle wavefronts
-    ("bf16", 65, 4096, 4096),     # one row more: two row tiles, one shot per 512-wide slice
+    ("bf16", 1, 4096, 4096),      # one row
+    ("bf16", 33, 4096, 8192),     # just above the 32-row tiles
+    ("bf16", 64, 1024, 16384),    # short K, many features
+    ("bf16", 60, 2048, 4096),     # the LSA output projection with the folded memory K / V
+    ("bf16", 60, 14336, 4096),    # K in slices
+    ("bf16", 60, 4096, 10240),    # the grouped projections of a step
+    ("bf16", 64, 4096, 28672),    # gate and up projections
+    ("bf16", 5, 2048, 14336),     # a few rows
+    ("bf16", 47, 4096, 6208),     # a ragged last feature tile
+    ("bf16", 65, 4096, 4096),     # a second row tile with one row
     ("bf16", 128, 2048, 2048),
-    ("bf16", 160, 2048, 6144),    # three row tiles, wide slices
-    ("bf16", 193, 2048, 2048),    # tiled GEMM
+    ("bf16", 160, 2048, 6144),    # three row tiles
+    ("bf16", 193, 2048, 2048),    # one row more than K is cut for
     ("bf16", 700, 512, 1024),
-    ("bf16", 60, 4096, 1024),     # too few tiles for chunks: one shot
-    ("bf16", 17, 384, 96),        # K not in 512s, N in 32s: narrow form
-    ("bf16", 9, 200, 50),         # nothing aligned: generic
+    ("bf16", 60, 4096, 1024),     # few features: K in slices
+    ("bf16", 17, 384, 96),        # features in 32s
+    ("bf16", 9, 200, 50),         # K a multiple of 8 only: single-precision kernels
     ("f32", 19, 320, 70),
 ]
 

@@ -1,7 +1,6 @@
 """moa_draft_step on the launch configurations it takes at the batched and long-context workloads: the grouped
-projection through the tiled kernel (four segments with their own activations, the integer work riding in its
-grid), a carried slice-summing pass over several row tiles, both attention cores in one split-KV launch + merge,
-two-word tree masks.  The library runs the whole batch as the benchmark does; the oracle recomputes sampled
+projection over several row tiles (four segments with their own activations, the integer work riding in its
+grid), both attention cores in one split-KV launch + merge, two-word tree masks.  The library runs the whole batch as the benchmark does; the oracle recomputes sampled
 sequences (each sequence of a step is independent of the others, so the sample is exact for the rows it covers)."""
 import numpy as np
 import pytest
@@ -29,10 +28,9 @@ def _cfg(name, index, **kw):
 
 # name -> (config, verify layers, sampled sequences, attention form forced for the run)
 LARGE_CASES = {
-    # 256 rows: the grouped projection takes the tiled kernel (several row tiles, four segments, riding integer work)
+    # 256 rows: the grouped projection in several row tiles, four segments, riding integer work
     "tiled_pair_256_rows": (_cfg("T256", 21), 2, 4, "auto"),
-    # 180 rows: weight-streaming projection over three row tiles whose slice-summing pass (180 rows) is carried by
-    # the LSA projection's tiled launch
+    # 180 rows: three row tiles, the last one ragged
     "carried_sum_180_rows": (_cfg("S180", 22, B=3, M=60, d=1024, H=8, Hkv=2, d_lsa_in=512, L=8), 1, 3, "auto"),
     # both cores of the step in one split-KV launch + one merge, at a size that would otherwise take the other form
     "split_pair_forced": (_cfg("SP", 23, B=3, M=37, P_min=80, P_max=300), 2, 3, "split"),
