@@ -16,7 +16,7 @@
 // registers and the operands that come from LDS in the accumulation registers, the other way round than the compiler's
 // default (-amdgpu-mfma-vgpr-form for this file; in accumulation registers a rescale takes four times as long).
 // What bounds it is the matrix pipe and the softmax arithmetic together.  8 x 32768 keys x 128 tree tokens, both cores:
-// 1366 us (0.81 PFLOP/s), where 128 rows per workgroup take 1440.
+// 1352 us (0.81 PFLOP/s), where 128 rows per workgroup take 1464 on the same card.
 #include "moa_attn_device.h"
 #include "moa_gemm_device.h"
 
