@@ -12,7 +12,7 @@
 // eight rows of 64 bytes); one barrier per tile, two tiles in flight behind the current one.
 // The reference of the exponent is the running maximum, exactly: the heaviest weights then sit at the top of a binade, where
 // their rounding to bf16 is smallest (a reference that lags behind it by up to 2^8 gives 1.04 to 1.24 times the error against
-// 64 bits, and would save 5 to 13 % of the time).  A rescale is 64 multiplications, so the accumulators are kept in vector
+// 64 bits, and would save 5 to 12 % of the time).  A rescale is 64 multiplications, so the accumulators are kept in vector
 // registers and the operands that come from LDS in the accumulation registers, the other way round than the compiler's
 // default (-amdgpu-mfma-vgpr-form for this file; in accumulation registers a rescale takes four times as long).
 // What bounds it is the matrix pipe and the softmax arithmetic together.  8 x 32768 keys x 128 tree tokens, both cores:
