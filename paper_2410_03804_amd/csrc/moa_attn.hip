@@ -862,21 +862,20 @@ static SplitGeom split_geometry(int B, int Mq, int H, int Hkv, int dh, int P_cap
     while (want > 1 && (int64_t)want * w.rows_pad > (int64_t)g.nsplit * g.rows_pad) --want;
     if (want < 1) want = 1;
     w.nsplit = want;
-    // Which one, by an estimate in microseconds.  A round of 128-row workgroups takes 3 per tile of 64 keys with two per
-    // compute unit and 2.4 with one; one of 256-row workgroups 2.4, 0.2 for each time its accumulators follow a new maximum
-    // (nearly always on the first 32 half tiles of a slice, then ever more rarely), and 4 more in front and behind.  It
-    // decides where the rows fill their last tile badly (8 sequences x 32768 keys x 8 KV heads: 260 .. 384 rows 638 .. 660 us in three tiles of 128
-    // against 1052 in two of 256, which leaves half of the chip idle; 416 .. 512 rows 743 .. 767 against 631 .. 638), where
-    // the rows of an XCD's units need one workgroup more than it has compute units, and where a slice is a few tiles (8 x
-    // 1024 keys, 512 rows: 42 us either way).  Two calls in one launch can fill what one leaves idle.  Over 690 measured
-    // calls it is 1.9 % behind the better form, and slower than 128-row tiles by 6 % at most (23 calls by more than 2 %).
+    // Which one, by an estimate in microseconds.  A round of 128-row workgroups takes 1.5 per tile of 32 keys with two per
+    // compute unit and 1.2 with one; one of 256-row workgroups 1.05, 0.15 for each time its accumulators follow a new maximum
+    // (nearly always on the first 32 tiles of a slice, then ever more rarely), and 4 more in front and behind.  It
+    // decides where the rows fill their last tile badly (8 sequences x 32768 keys x 8 KV heads: 260 .. 384 rows in three tiles
+    // of 128 against two of 256, which leave half of the chip idle), where the rows of an XCD's units need one workgroup
+    // more than it has compute units, and where a slice is a few tiles.  Two calls in one launch can fill what one leaves idle.
+    // Over 456 measured calls (512 .. 32768 keys, 1 .. 16 sequences, 132 .. 1024 rows) it is 0.5 % behind the better form.
     const int64_t units = (int64_t)ncalls * B * Hkv;
     const int64_t per128 = (tiles_cap + g.nsplit - 1) / g.nsplit, wgs128 = units * g.nsplit * g.rowtiles;
     const int64_t per256 = (tiles_cap + w.nsplit - 1) / w.nsplit, rounds256 = ((units * w.nsplit + 7) / 8 * 8 * w.rowtiles + 255) / 256;
     const int64_t rest = wgs128 % 512;
-    const float us128 = (float)per128 * (3.f * (float)(wgs128 / 512) + (rest == 0 ? 0.f : rest <= 256 ? 2.4f : 3.f));
-    const float halves = (float)(2 * per256), follows = halves <= 32.f ? halves : 32.f + 32.f * logf(halves / 32.f);
-    const bool wide = form == MOA_ATTN_KERNEL_SPLIT_WIDE || 4.f + (float)rounds256 * (2.4f * (float)per256 + 0.2f * follows) < us128;
+    const float us128 = (float)per128 * (1.5f * (float)(wgs128 / 512) + (rest == 0 ? 0.f : rest <= 256 ? 1.2f : 1.5f));
+    const float tiles = (float)per256, follows = tiles <= 32.f ? tiles : 32.f + 32.f * logf(tiles / 32.f);
+    const bool wide = form == MOA_ATTN_KERNEL_SPLIT_WIDE || 4.f + (float)rounds256 * (1.05f * tiles + 0.15f * follows) < us128;
     return wide ? w : g;
 }
 

@@ -127,3 +127,32 @@ def test_wide_row_tiles_round_the_weights_no_worse(G, factor):
         err[form] = ((got - want).norm() / want.norm()).item()
     print(err)
     assert err["split_wide"] <= 1.02 * err["whole"], err
+
+
+@pytest.mark.parametrize("M,H,factor", [(33, 32, 1.0), (64, 32, 6.0)])
+def test_rounds_of_three_full_tiles_and_what_follows_them(G, moa, M, H, factor):
+    """Slices of 2 .. 13 tiles of 64 keys, ending on, before and behind a tile: rounds of three unmasked tiles, their one to five
+    masked followers and slices that have only those.  Against 64 bits; weights and result are rounded to bf16 (2^-9 each) and a
+    slice's result to fp16, a largest element of 10^6 at six times that."""
+    B, Hkv, P = 16, 8, 1600
+    lens = [255, 256, 257, 383, 384, 447, 448, 511, 513, 640, 769, 896, 1023, 1280, 1537, 1600]
+    g = torch.Generator(device="cuda").manual_seed(5)
+    import paper_2410_03804_amd as m
+    shape = m.Shape(2, H * 128, H, Hkv, 128, 256, 2, 1, m.BF16)
+    q = (torch.randn(B, M, H * 128, generator=g, device="cuda") * factor).bfloat16()
+    k, v = (torch.randn(B, Hkv, P, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
+    for b, n in enumerate(lens):                                # rows past a sequence's length are never used
+        k[b, :, n:], v[b, :, n:] = float("nan"), float("nan")
+    print(f"[case] cross_attn_draft M={M} factor={factor}", flush=True)
+    out = torch.empty_like(q)
+    ws = torch.empty(m.workspace_bytes(shape, B, P, M, 0), dtype=torch.uint8, device="cuda")
+    m.cross_attn_draft(shape, q, None, None, k, v, torch.tensor(lens, dtype=torch.int32, device="cuda"), P, out, ws, G.status_word())
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        qb = q[b].view(M, Hkv, H // Hkv, 128).permute(1, 0, 2, 3).reshape(Hkv, -1, 128).double().cpu()
+        got = out[b].view(M, Hkv, H // Hkv, 128).permute(1, 0, 2, 3).reshape(Hkv, -1, 128).double().cpu()
+        for h in range(Hkv):
+            want = torch.softmax(qb[h] @ k[b, h, :n].double().cpu().T / 128 ** 0.5, -1) @ v[b, h, :n].double().cpu()
+            diff, rms = got[h] - want, want.square().mean().sqrt()
+            assert diff.square().mean().sqrt() <= 2.0 ** -8 * rms, (b, h)
+            assert diff.abs().max() <= 6 * 2.0 ** -8 * max(rms, want.abs().max() / 4), (b, h)
