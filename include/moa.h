@@ -468,7 +468,8 @@ int32_t moa_debug_force_attn_kernel(int32_t form);
  * cores (d_lsa_in a multiple of 128), and agree within rounding otherwise.  MOA_LSA_KERNEL_SEPARATE forces the three-kernel form,
  * MOA_LSA_KERNEL_FUSED the one-kernel form wherever it applies; left to itself (_AUTO) the library takes the
  * one-kernel form except for at most 192 rows (T * n_layers) and for more than 1024 workgroups' worth of tokens whose
- * layer count leaves over a tenth of its last 32-row block empty, where the three kernels measured faster. */
+ * layer count leaves over a tenth of its last 32-row block empty (65 .. 80 layers from packed weights excepted), where
+ * the three kernels measured faster. */
 enum { MOA_LSA_KERNEL_AUTO = 0, MOA_LSA_KERNEL_FUSED = 1, MOA_LSA_KERNEL_SEPARATE = 2 };
 int32_t moa_debug_force_lsa_kernel(int32_t form);
 

@@ -256,9 +256,10 @@ static std::atomic<int> g_lsa_form{0};
 // separate kernels in two corners where they measured faster: a handful of rows (T L <= 192: the projection of its own
 // spreads the weights over every compute unit, the one-kernel form over T x 8 workgroups only -- 27 against 42 us for 5
 // tokens at the Llama-3-8B shape), and many tokens whose layer count fills its last 32-row block badly
-// (L = 80 in 96 rows: 535 against 492 us for 256 tokens at the Llama-2-70B shape).
+// (L = 80 in 96 rows from plain weights: 535 against 492 us for 256 tokens at the Llama-2-70B shape), unless the weights are
+// packed and two tokens go into 160 rows (240 tokens: 286 us against 365).
 static bool lsa_takes_fused(const moa_shape_t *shape, int64_t T, const void *hs, const void *wq, const void *wk,
-                            const void *wv, const void *abar)
+                            const void *wv, const void *abar, bool packed = false)
 {
     const int form = g_lsa_form.load(std::memory_order_relaxed);
     if (form == MOA_LSA_KERNEL_SEPARATE) return false;
@@ -269,7 +270,7 @@ static bool lsa_takes_fused(const moa_shape_t *shape, int64_t T, const void *hs,
     if (form == MOA_LSA_KERNEL_FUSED) return true;
     const int64_t L = shape->n_layers, padded = (L + 31) / 32 * 32;
     if (T * L <= 192) return false;
-    if (10 * padded > 11 * L && T * (shape->lsa_q_heads / 2) > 1024) return false;
+    if (10 * padded > 11 * L && T * (shape->lsa_q_heads / 2) > 1024 && !(packed && L > 64 && L <= 80)) return false;
     return true;
 }
 
@@ -1166,10 +1167,16 @@ int32_t moa_linear(int32_t dtype, const void *x, int64_t R, int32_t K, const voi
 
 // The packed copy of the LSA weights a step may use: only where the one-kernel form runs anyway (the other form
 // reads the plain matrices), and only if it is aligned like every other operand of that kernel.
+static const void *step_lsa_abar(const moa_step_args_t *a) { return a->lsa_wo ? a->ws : a->lsa_out; }   // (or from there on, in 256s)
 static const void *step_lsa_packed(const moa_step_args_t *a)
 {
     if (!a->lsa_w_packed || (((uintptr_t)a->lsa_w_packed) & 15)) return nullptr;
-    return lsa_takes_fused(a->shape, a->T_lsa, a->lsa_hs, a->lsa_wq, a->lsa_wk, a->lsa_wv, a->ws) ? a->lsa_w_packed : nullptr;
+    return lsa_takes_fused(a->shape, a->T_lsa, a->lsa_hs, a->lsa_wq, a->lsa_wk, a->lsa_wv, step_lsa_abar(a), true) ? a->lsa_w_packed : nullptr;
+}
+// whether a step's LSA pass is the one kernel, from packed weights or plain ones
+static bool step_lsa_fused(const moa_step_args_t *a)
+{
+    return step_lsa_packed(a) || lsa_takes_fused(a->shape, a->T_lsa, a->lsa_hs, a->lsa_wq, a->lsa_wk, a->lsa_wv, step_lsa_abar(a));
 }
 
 // moa_lsa for a step: the same checks, and the packed weights where they apply
@@ -1394,7 +1401,7 @@ static int32_t piece_lsa_interleaved(const moa_step_args_t *a, const StepBufs &b
     if (rc) return rc;
     const LsaBufs b = lsa_carve(sh, T, scr, scr_bytes);
     void *abar = a->lsa_wo ? (void *)b.abar0 : a->lsa_out;
-    if (lsa_takes_fused(sh, T, a->lsa_hs, a->lsa_wq, a->lsa_wk, a->lsa_wv, abar)) {
+    if (step_lsa_fused(a)) {
         LsaFusedCall fc = lsa_fused_call(sh, a->lsa_hs, 0, T, a->lsa_wq, a->lsa_wk, a->lsa_wv, abar, step_lsa_packed(a));
         prof_set_site(S_LSA_FUSED);
         MOA_TRY_HIP(launch_lsa_fused(fc, st), "lsa: fused kernel");
@@ -1489,7 +1496,7 @@ static int32_t draft_step_grouped(const moa_step_args_t *a)
     const StepBufs bf = carve_step_bufs(a, L, &scr);
     int32_t rc;
     const bool one_pass = a->T_lsa <= LSA_CHUNK ||
-                          (a->T_lsa <= LSA_OBLOCK && lsa_takes_fused(a->shape, a->T_lsa, a->lsa_hs, a->lsa_wq, a->lsa_wk, a->lsa_wv, a->ws));
+                          (a->T_lsa <= LSA_OBLOCK && step_lsa_fused(a));
     if (a->T_lsa > 0 && one_pass) {
         rc = piece_lsa_interleaved(a, bf, scr, L.scratch, st);
         if (rc) return rc;
@@ -1564,8 +1571,7 @@ static size_t two_stream_bytes(const moa_step_args_t *a, bool sa)
 // integer work, so that nothing in the LSA chain has to wait for the other branch)
 static bool two_stream_lsa_fused(const moa_step_args_t *a)
 {
-    return a->T_lsa > 0 && a->T_lsa <= LSA_OBLOCK &&
-           lsa_takes_fused(a->shape, a->T_lsa, a->lsa_hs, a->lsa_wq, a->lsa_wk, a->lsa_wv, a->ws);
+    return a->T_lsa > 0 && a->T_lsa <= LSA_OBLOCK && step_lsa_fused(a);
 }
 
 static int32_t two_stream_main(const moa_step_args_t *a, const StepBufs &bf, char *scr, size_t scr_bytes, size_t attn_each,

@@ -58,23 +58,28 @@ struct LsaFusedArgs {
     StepSmallArgs rider;
 };
 
-template <int DH, int NB, int TT>
+// DENSE: the rows of a tile's tokens follow one another (TT L <= RB) instead of each token starting a block of 32
+template <int DH, int NB, int TT, bool DENSE = false>
 struct LsaFusedGeom {
     static constexpr int NF = 4 * DH;            // features per workgroup
     static constexpr int FW = NF / 8;            // per wavefront
-    static constexpr int RB = 32 * NB * TT;      // rows per workgroup
+    static constexpr int RB = DENSE ? 160 : 32 * NB * TT;    // rows per workgroup
     static constexpr int BK = 64;
     static constexpr int XS = RB <= 64 ? 3 : 2;  // stages of the activation ring
     static constexpr size_t w_bytes = (size_t)8 * 2 * FW * BK * sizeof(bf16_t);
     static constexpr size_t x_bytes = (size_t)XS * RB * BK * sizeof(bf16_t);
-    static constexpr int TLD = NF + 8;           // row of the parked Q/K/V tile: 16-byte reads of 8 rows hit all banks
+    // row of the parked Q/K/V tile: 16-byte reads of 8 rows hit all banks.  A dense tile fills the LDS to the last byte: its
+    // rows are not padded, piece c of row r lies at c ^ (r & 15), and the column means go where the wavefront's Q was
+    static constexpr int TLD = DENSE ? NF : NF + 8;
     static constexpr size_t tile_bytes = (size_t)RB * TLD * sizeof(bf16_t);
-    static constexpr size_t pbar_bytes = (size_t)8 * 32 * NB * sizeof(float);
+    static constexpr size_t pbar_bytes = DENSE ? 0 : (size_t)8 * 32 * NB * sizeof(float);
     static constexpr size_t loop_bytes = w_bytes + x_bytes;
     static constexpr size_t epi_bytes = tile_bytes + pbar_bytes;
     static constexpr size_t bytes = loop_bytes > epi_bytes ? loop_bytes : epi_bytes;
     // the form that takes packed weights keeps them in registers: only a two-stage activation ring is left in LDS
-    static constexpr int WS = 2;                 // weight tiles held in registers per wavefront: with the requests spread between the MFMAs two do as well as four
+    // weight tiles held in registers per wavefront: with the requests spread between the MFMAs two do as well as four; beside
+    // the accumulators of 160 rows there is room for one, and three quarters of a tile's MFMAs hide a request
+    static constexpr int WS = DENSE ? 1 : 2;
     static constexpr int UN = 8;                 // tile steps per trip of the tile loop (a multiple of WS)
     static constexpr size_t pk_loop_bytes = (size_t)2 * RB * BK * sizeof(bf16_t);
     static constexpr size_t pk_bytes = pk_loop_bytes > epi_bytes ? pk_loop_bytes : epi_bytes;
@@ -84,10 +89,10 @@ struct LsaFusedGeom {
 // feature wave FW + 32 i + 8 (v / 4) + 4 half + v % 4, row 32 j + lane % 32) are rounded to the storage type and
 // parked in LDS, then one wavefront per (token of the tile, query head) runs the attention over the layer axis and the
 // mean.  Called by all 512 threads; `sm` is the workgroup's whole LDS, free to reuse after the barrier in here.
-template <int DH, int NB, int TT, typename Acc>
+template <int DH, int NB, int TT, bool DENSE, typename Acc>
 __device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs &a, bf16_t *sm, int64_t tile, int g, int part)
 {
-    using Gm = LsaFusedGeom<DH, NB, TT>;
+    using Gm = LsaFusedGeom<DH, NB, TT, DENSE>;
     constexpr int FW = Gm::FW, RB = Gm::RB, TLD = Gm::TLD;
     constexpr int WFB = FW / 32, NRB = RB / 32;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
@@ -96,7 +101,9 @@ __device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs 
     // park Q | Q' | K | V of the RB rows in LDS, rounded to the storage type
     __syncthreads();                             // every wavefront is done with the rings
     bf16_t *tile_s = sm;
-    float *pbar_s = (float *)((char *)sm + Gm::tile_bytes) + wave * 32 * NB;
+    auto at = [&](int row, int col) {            // column `col` of a row, and what follows it in its piece of eight
+        return DENSE ? tile_s + row * TLD + 8 * ((col >> 3) ^ (row & 15)) + (col & 7) : tile_s + row * TLD + col;
+    };
     // acc[i][j][v]: feature = f0 + 32 i + 8 (v / 4) + 4 half + v % 4, row = 32 j + l32
     const int f0 = wave * FW;
     {
@@ -109,21 +116,31 @@ __device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs 
                     u32x2 pk;
                     pk[0] = pack_bf16x2(acc[i][j][4 * q + 0], acc[i][j][4 * q + 1]);
                     pk[1] = pack_bf16x2(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-                    *(u32x2 *)&tile_s[(32 * j + l32) * TLD + f0 + 32 * i + 8 * q + 4 * half] = pk;
+                    *(u32x2 *)at(32 * j + l32, f0 + 32 * i + 8 * q + 4 * half) = pk;
                 }
     }
     __syncthreads();
 
     // attention over the layer axis: one wavefront per (token of the tile, query head); spare wavefronts redo a
-    // unit and store nothing, so that the barriers below are reached by all
+    // unit and store nothing, so that the barriers below are reached by all.  In a dense tile four units have two wavefronts
+    // each: the second takes the last block of query rows and hands its weights over (49 rows of 64; a token has more than 64).
     constexpr int NU = 2 * TT;
     constexpr int NKS = DH / 16;
+    static_assert(!DENSE || NU == 4, "two wavefronts per unit");
     const bool live_wave = wave < NU;
+    const int ib0 = DENSE && !live_wave ? NB - 1 : 0, ib1 = DENSE && live_wave ? NB - 1 : NB;
     const int u = wave % NU, tt = u >> 1, hq = u & 1;
     const int64_t tok = tile * TT + tt;
-    const bf16_t *trow = tile_s + (size_t)tt * 32 * NB * TLD;
+    const int row0 = tt * (DENSE ? L : 32 * NB);                  // the token's first row
+    const bf16_t *trow = tile_s + (size_t)row0 * TLD;
+    auto tok_at = [&](int row, int col) {                         // rows past L are masked, or weighted 0
+        return DENSE ? (const bf16_t *)at(row0 + min(row, L - 1), col) : trow + row * TLD + col;
+    };
+    float *pbar_s = (float *)((char *)sm + Gm::tile_bytes) + wave * 32 * NB;
+    auto pbar = [&](int j) -> float & { return DENSE ? ((float *)(tile_s + (row0 + (j >> 6)) * TLD + hq * DH))[j & 63] : pbar_s[j]; };
     const float sc = 1.4426950408889634f / sqrtf((float)DH);      // log2 domain
 
+    float hand_inv = 0.f;
     // column sums of P in the S^T register layout: csum[jb][v] belongs to key 32 jb + 8 (v/4) + 4 half + v%4
     float csum[NB][16];
 #pragma unroll
@@ -132,10 +149,11 @@ __device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs 
         for (int e = 0; e < 16; ++e) csum[jb][e] = 0.f;
 #pragma unroll
     for (int ib = 0; ib < NB; ++ib) {
+        if (DENSE && (ib < ib0 || ib >= ib1)) continue;
         const bool qvalid = 32 * ib + l32 < L;
         bf16x8 qf[NKS];
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const bf16x8 *)&trow[(32 * ib + l32) * TLD + hq * DH + 16 * ks + 8 * half];
+        for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const bf16x8 *)tok_at(32 * ib + l32, hq * DH + 16 * ks + 8 * half);
         f32x16 s[NB];
 #pragma unroll
         for (int jb = 0; jb < NB; ++jb) {
@@ -143,7 +161,7 @@ __device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs 
             for (int e = 0; e < 16; ++e) s[jb][e] = 0.f;
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) {        // key fragments straight from the parked tile: nothing to keep across blocks
-                const bf16x8 kf = *(const bf16x8 *)&trow[(32 * jb + l32) * TLD + 2 * DH + 16 * ks + 8 * half];
+                const bf16x8 kf = *(const bf16x8 *)tok_at(32 * jb + l32, 2 * DH + 16 * ks + 8 * half);
                 s[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s[jb], 0, 0, 0);
             }
         }
@@ -168,7 +186,30 @@ __device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs 
 #pragma unroll
         for (int jb = 0; jb < NB; ++jb)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) csum[jb][e] += s[jb][e] * inv;
+            for (int e = 0; e < 16; ++e) {
+                if (DENSE && !live_wave) csum[jb][e] = s[jb][e];             // scaled where it is added: the same rounding
+                else csum[jb][e] += s[jb][e] * inv;
+            }
+        hand_inv = inv;
+    }
+    if (DENSE) {                                 // through the rows of the unit's Q, which nobody reads any more
+        __syncthreads();
+        auto place = [&](int jb, int e) -> float & { return ((float *)(tile_s + (row0 + 16 * jb + e) * TLD + hq * DH))[lane]; };
+        if (!live_wave) {
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) place(jb, e) = csum[jb][e];
+            place(NB, 0) = hand_inv;
+        }
+        __syncthreads();
+        if (live_wave) {
+            const float inv = place(NB, 0);
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) csum[jb][e] += place(jb, e) * inv;
+        }
     }
 #pragma unroll
     for (int jb = 0; jb < NB; ++jb)
@@ -176,12 +217,12 @@ __device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs 
         for (int e = 0; e < 16; ++e) {
             csum[jb][e] = sum_over_lanes32(csum[jb][e]);
         }
-    if (l32 == 0) {
+    if (l32 == 0 && (!DENSE || live_wave)) {     // (a dense tile has one place per unit, which its own wavefront is done with)
         const float invL = 1.0f / (float)L;
 #pragma unroll
         for (int jb = 0; jb < NB; ++jb)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) pbar_s[32 * jb + 8 * (e >> 2) + 4 * half + (e & 3)] = csum[jb][e] * invL;
+            for (int e = 0; e < 16; ++e) pbar(32 * jb + 8 * (e >> 2) + 4 * half + (e & 3)) = csum[jb][e] * invL;
     }
     __syncthreads();
 
@@ -198,8 +239,8 @@ __device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs 
 #pragma unroll
         for (int i = 0; i < NVI; ++i) {
             const int row = 32 * jb + RPI * i + vrow0;
-            const float pj = row < L ? pbar_s[row] : 0.f;
-            const u32x4 vv = *(const u32x4 *)&trow[row * TLD + 3 * DH + 8 * vpiece];
+            const float pj = row < L ? pbar(row) : 0.f;
+            const u32x4 vv = *(const u32x4 *)tok_at(row, 3 * DH + 8 * vpiece);
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
                 o[2 * w] = fmaf(pj, __uint_as_float(vv[w] << 16), o[2 * w]);
@@ -345,7 +386,7 @@ __global__ __launch_bounds__(512) void k_lsa_fused(LsaFusedArgs a)
         }
     }
 
-    lsa_fused_epilogue<DH, NB, TT>(acc, a, sm, tile, g, part);
+    lsa_fused_epilogue<DH, NB, TT, false>(acc, a, sm, tile, g, part);
 }
 
 // f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N - 1>{}): a loop whose index is a constant
@@ -405,10 +446,10 @@ __device__ __forceinline__ void lsa_warm_block(const LsaFusedArgs &a, int h, bf1
 // flight per wavefront in registers, which the 160 KB of LDS could not hold.  The activation tile goes through
 // registers into a two-stage LDS ring (one bare barrier per tile); all loads are ordinary loads, so the waits are the
 // compiler's.  Same MFMA order along d_in as the unpacked form: same bits.
-template <int DH, int NB, int TT>
-__global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
+template <int DH, int NB, int TT, bool DENSE>
+__device__ __forceinline__ void lsa_pk_block(const LsaFusedArgs &a)
 {
-    using Gm = LsaFusedGeom<DH, NB, TT>;
+    using Gm = LsaFusedGeom<DH, NB, TT, DENSE>;
     constexpr int FW = Gm::FW, RB = Gm::RB, BK = Gm::BK, WS = Gm::WS;
     constexpr int WFB = FW / 32;                 // 32-feature blocks per wavefront
     constexpr int NRB = RB / 32;                 // 32-row blocks
@@ -457,16 +498,17 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
         if (xi > RB / 8 - 1) xi = RB / 8 - 1;
         xrow0[n] = 8 * xi;
         const int s = 8 * xi + lrow;
-        int64_t tok = tile * TT + s / (32 * NB);
-        int lay = s % (32 * NB);
+        const int in = DENSE ? min(s / L, TT - 1) : s / (32 * NB);
+        int64_t tok = tile * TT + in;
+        int lay = DENSE ? s - in * L : s % (32 * NB);
         if (tok > a.T - 1) tok = a.T - 1;
         if (lay > L - 1) lay = L - 1;
         xsrc[n] = a.hs + (tok * L + lay) * (int64_t)K + 8 * (lpos ^ ((s >> 1) & 7));
     }
     bf16_t *xl = sm;                             // [2][RB][BK]
 
-    // both operands are requested WS - 1 tiles ahead into register rings (a weight stage is refilled as soon as its
-    // tile has been multiplied, an activation stage as soon as it has been copied to LDS)
+    // weights are requested WS tiles ahead into a register ring (a k-step's registers are refilled as soon as it has been
+    // multiplied), activations one tile ahead
     bf16x8 wr[WS][NWP];
     bf16x8 xr[WS][NXI];
     auto load_w = [&](int kt, bf16x8 (&dst)[NWP]) {
@@ -479,12 +521,12 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
     };
 #pragma unroll
     for (int s = 0; s < WS; ++s) {               // a tile past the last repeats the last (nk >= 2)
-        if (s < WS - 1) load_x(s < nk ? s : nk - 1, xr[s]);
+        if (s == 0) load_x(s < nk ? s : nk - 1, xr[s]);
         load_w(s < nk ? s : nk - 1, wr[s]);
     }
 
     // One tile step on register stage S.  The activation tile of this step goes to LDS (the place was last read two
-    // tiles ago, before the previous barrier) and the one WS - 1 ahead is requested into the registers it leaves.
+    // tiles ago, before the previous barrier) and the next one is requested into the registers it leaves.
     // Inside the step the weight requests are spread between the MFMAs: as soon as a k-step's MFMAs have been issued
     // its weight registers are refilled with the same k-step of the tile WS ahead.  Issued in one burst at the top of
     // a step, the requests of all eight wavefronts queue up at the compute unit's one address unit while the matrix
@@ -503,7 +545,7 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
             for (int n = 0; n < NXI; ++n) *(bf16x8 *)&xw[xrow0[n] * BK + 8 * lane] = xr[S][n];
         }
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        load_x(kt + WS - 1 < nk ? kt + WS - 1 : nk - 1, xr[(S + WS - 1) % WS]);
+        load_x(kt + 1 < nk ? kt + 1 : nk - 1, xr[(S + 1) % WS]);
         const int kw = kt + WS < nk ? kt + WS : nk - 1;
         const bf16x8 *wnext = wp + (int64_t)kw * NWP * 64;
         auto read_frags = [&](int ks, bf16x8 (&fb)[NRB]) {
@@ -542,6 +584,9 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
 #pragma unroll
                     for (int j = 0; j < NRB; ++j)
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[S][ks * WFB + i], bfr[ks % NBUF][j], acc[i][j], 0, 0, 0);
+                // (64-row tiles: the refill strictly behind them, 35.1 -> 34.3 us at 60 tokens; with single-buffered fragments the
+                // compiler's mixture of MFMAs, fragment reads and requests is as good as any order tried)
+                if (NBUF == 2) __builtin_amdgcn_sched_barrier(0);
                 if (NBUF == 1 && ks + 1 < BK / 16) read_frags(ks + 1, bfr[0]);
 #pragma unroll
                 for (int i = 0; i < WFB; ++i) wr[S][ks * WFB + i] = wnext[(ks * WFB + i) * 64];
@@ -561,8 +606,19 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
 #pragma unroll 1
     for (int kt0 = nk_main; kt0 < nk_end; kt0 += WS)
         static_for<WS>([&](auto u) { tile_step(u, std::true_type{}, kt0 + decltype(u)::value); });
-    lsa_fused_epilogue<DH, NB, TT>(acc, a, sm, tile, g, part);
+    lsa_fused_epilogue<DH, NB, TT, DENSE>(acc, a, sm, tile, g, part);
 }
+
+template <int DH, int NB, int TT>
+__global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a) { lsa_pk_block<DH, NB, TT, false>(a); }
+// The same with the rows of TT tokens one behind another in 160 (five blocks of 32), for layer counts that leave much of
+// their last block empty: 80 layers in 96 rows waste a sixth of the matrix work, two tokens in 160 nothing, and a weight
+// tile serves 160 rows.  The accumulators take 160 registers, so one weight tile is in registers instead of two, and the parked tile
+// fills the LDS to the last byte.  240 tokens x 80 layers (d_in 2048): 286 us, where a token per workgroup takes 412 and
+// projection and attention as kernels of their own 305 + 60.  1.80 us per k tile at 160 rows and the 1.75 GHz the power limit
+// leaves (1.46 of them MFMA) and 17 us in front and behind, 6 of which were saved by giving a unit's query blocks to two wavefronts.
+template <int DH, int NB, int TT>
+__global__ __launch_bounds__(512) void k_lsa_fused_pk_dense(LsaFusedArgs a) { lsa_pk_block<DH, NB, TT, true>(a); }
 
 // Packs Wq / Wk / Wv for k_lsa_fused_pk: piece (unit, wavefront, k tile, k step, feature block, lane) holds the 8
 // elements that lane supplies as the A operand of that MFMA, i.e. row  f(unit, wavefront) + 32 block + lane % 32  of
@@ -620,10 +676,10 @@ static size_t lds_limit()
     return limit[dev];
 }
 
-template <int NB, int TT>
+template <int NB, int TT, bool DENSE = false>
 static hipError_t launch_lsa_fused_as(LsaFusedArgs &fa, hipStream_t stream)
 {
-    using Gm = LsaFusedGeom<128, NB, TT>;
+    using Gm = LsaFusedGeom<128, NB, TT, DENSE>;
     const int64_t tiles = (fa.T + TT - 1) / TT;
     // Two helper workgroups per XCD (lsa_warm_block), where they cost nothing and can do their job: the kernel's own
     // workgroups leave that many compute units idle (decode sizes), and an XCD's share of the weights fits its L2
@@ -643,7 +699,13 @@ static hipError_t launch_lsa_fused_as(LsaFusedArgs &fa, hipStream_t stream)
     }
     const int64_t grid = fa.lead_blocks + 8 * (int64_t)fa.units_per_xcd * tiles;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    if (fa.wpk) {
+    if constexpr (DENSE) {
+        static bool raised[16] = {};
+        hipError_t e = raise_lds_limit_once(raised, (const void *)k_lsa_fused_pk_dense<128, NB, TT>, Gm::pk_bytes);
+        if (e != hipSuccess) return e;
+        prof_begin(K_LSA_FUSED_PK + 64 * (64 + NB * 8 + TT), stream);
+        MOA_KLAUNCH((k_lsa_fused_pk_dense<128, NB, TT>), dim3((unsigned)grid), dim3(512), Gm::pk_bytes, stream, fa);
+    } else if (fa.wpk) {
         static bool raised[16] = {};
         hipError_t e = raise_lds_limit_once(raised, (const void *)k_lsa_fused_pk<128, NB, TT>, Gm::pk_bytes);
         if (e != hipSuccess) return e;
@@ -726,6 +788,9 @@ hipError_t launch_lsa_fused(const LsaFusedCall &c, hipStream_t stream)
         if (big_ok && cost(2) < cost(1)) return launch_lsa_fused_as<2, 2>(fa, stream);
         return launch_lsa_fused_as<2, 1>(fa, stream);
     }
+    // two tokens in 160 rows take 68 us where one in 96 takes 45: as soon as that saves a round
+    const double dense = ceil((double)fa.units * (double)((c.T + 1) / 2) / 256.0) * (fixed + per_block * 5);
+    if (fa.wpk && c.L <= 80 && dense < cost(1)) return launch_lsa_fused_as<3, 2, true>(fa, stream);
     return launch_lsa_fused_as<3, 1>(fa, stream);
 }
 

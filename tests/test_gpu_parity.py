@@ -217,6 +217,32 @@ def test_lsa_one_kernel_form_shapes(G, moa, oracle, L, d_in, Hkv, T):
     assert torch.equal(outs["fused"], out), "packing changes where a weight is read from, not the arithmetic"
 
 
+@pytest.mark.parametrize("L,d_in,Hkv,T", [(80, 512, 2, 301), (65, 320, 1, 602), (77, 768, 1, 515), (80, 512, 2, 130)])
+def test_lsa_rows_of_two_tokens_one_behind_another(G, moa, L, d_in, Hkv, T):
+    """65 .. 80 layers from packed weights: two tokens share 160 rows without padding between them.  Odd token counts (the last
+    tile holds one), rows left over behind the second token, input widths of 5, 8 and 12 tiles of 64; 130 tokens keep the form
+    that has one token per workgroup.  The bits are those of the plain-weight form, which pads every token to 96 rows."""
+    cfg = small_cfg("bf16", L=L, d_lsa_in=d_in, dh=128, Hkv=Hkv)
+    if (cfg.lsa_heads // Hkv) % 2:
+        cfg = small_cfg("bf16", L=L, d_lsa_in=256 * Hkv * (d_in // (256 * Hkv) or 1), dh=128, Hkv=Hkv)
+    print(f"[case] lsa dense L={L} d_in={cfg.d_lsa_in} heads={cfg.lsa_heads}/{Hkv} T={T}", flush=True)
+    shape = G.shape_of(cfg)
+    w = mi.lsa_weights(cfg)
+    hs = G.dev(mi.lsa_inputs(cfg, T), cfg.dtype)
+    ws = G.workspace(shape, cfg.B, cfg.P_cap, cfg.M, T)
+    dw = [G.dev(w[k], cfg.dtype) for k in ("wq", "wk", "wv", "wo")]
+    out, want = (torch.full((T, cfg.d_lsa), float("nan"), dtype=G.TDT[cfg.dtype], device="cuda") for _ in range(2))
+    moa.debug_force_lsa_kernel("fused")
+    try:
+        moa.lsa(shape, hs, *dw, want, ws)
+    finally:
+        moa.debug_force_lsa_kernel("auto")
+    packed = moa.lsa_pack_weights(shape, *dw[:3])
+    moa.lsa_packed(shape, hs, packed, dw[3], out, ws)
+    torch.cuda.synchronize()
+    assert torch.isfinite(want.float()).all() and torch.equal(out, want)
+
+
 def ca_setup(cfg, Mq):
     w = mi.ca_weights(cfg)
     xq = mi.ca_queries(cfg, Mq)
