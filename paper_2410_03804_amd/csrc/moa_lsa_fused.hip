@@ -52,6 +52,7 @@ struct LsaFusedArgs {
     int parts;                     // Hq / Hkv / 2: workgroups per KV head
     int units;                     // Hkv * parts
     int units_per_xcd;
+    int64_t wide_tiles;            // k_lsa_fused_pk_wide: tiles of five tokens in front of the others
     int lead_blocks;                           // workgroups in front of the kernel's own: integer work of a step
     int pf_lead;                               // the last of them (a multiple of the XCD count) only read ahead: see lsa_warm_block
     int rider_units;
@@ -64,22 +65,23 @@ struct LsaFusedGeom {
     static constexpr int NF = 4 * DH;            // features per workgroup
     static constexpr int FW = NF / 8;            // per wavefront
     static constexpr int RB = DENSE ? 160 : 32 * NB * TT;    // rows per workgroup
+    static constexpr bool FULL = RB == 160;      // the parked tile fills the LDS to the last byte
     static constexpr int BK = 64;
     static constexpr int XS = RB <= 64 ? 3 : 2;  // stages of the activation ring
     static constexpr size_t w_bytes = (size_t)8 * 2 * FW * BK * sizeof(bf16_t);
     static constexpr size_t x_bytes = (size_t)XS * RB * BK * sizeof(bf16_t);
-    // row of the parked Q/K/V tile: 16-byte reads of 8 rows hit all banks.  A dense tile fills the LDS to the last byte: its
-    // rows are not padded, piece c of row r lies at c ^ (r & 15), and the column means go where the wavefront's Q was
-    static constexpr int TLD = DENSE ? NF : NF + 8;
+    // row of the parked Q/K/V tile: 16-byte reads of 8 rows hit all banks.  Where it fills the LDS its rows are not padded,
+    // piece c of row r lies at c ^ (r & 15), and the column means go where the wavefront's Q was
+    static constexpr int TLD = FULL ? NF : NF + 8;
     static constexpr size_t tile_bytes = (size_t)RB * TLD * sizeof(bf16_t);
-    static constexpr size_t pbar_bytes = DENSE ? 0 : (size_t)8 * 32 * NB * sizeof(float);
+    static constexpr size_t pbar_bytes = FULL ? 0 : (size_t)8 * 32 * NB * sizeof(float);
     static constexpr size_t loop_bytes = w_bytes + x_bytes;
     static constexpr size_t epi_bytes = tile_bytes + pbar_bytes;
     static constexpr size_t bytes = loop_bytes > epi_bytes ? loop_bytes : epi_bytes;
     // the form that takes packed weights keeps them in registers: only a two-stage activation ring is left in LDS
     // weight tiles held in registers per wavefront: with the requests spread between the MFMAs two do as well as four; beside
     // the accumulators of 160 rows there is room for one, and three quarters of a tile's MFMAs hide a request
-    static constexpr int WS = DENSE ? 1 : 2;
+    static constexpr int WS = FULL ? 1 : 2;
     static constexpr int UN = 8;                 // tile steps per trip of the tile loop (a multiple of WS)
     static constexpr size_t pk_loop_bytes = (size_t)2 * RB * BK * sizeof(bf16_t);
     static constexpr size_t pk_bytes = pk_loop_bytes > epi_bytes ? pk_loop_bytes : epi_bytes;
@@ -90,7 +92,7 @@ struct LsaFusedGeom {
 // parked in LDS, then one wavefront per (token of the tile, query head) runs the attention over the layer axis and the
 // mean.  Called by all 512 threads; `sm` is the workgroup's whole LDS, free to reuse after the barrier in here.
 template <int DH, int NB, int TT, bool DENSE, typename Acc>
-__device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs &a, bf16_t *sm, int64_t tile, int g, int part)
+__device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs &a, bf16_t *sm, int64_t tok0, int g, int part)
 {
     using Gm = LsaFusedGeom<DH, NB, TT, DENSE>;
     constexpr int FW = Gm::FW, RB = Gm::RB, TLD = Gm::TLD;
@@ -102,7 +104,7 @@ __device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs 
     __syncthreads();                             // every wavefront is done with the rings
     bf16_t *tile_s = sm;
     auto at = [&](int row, int col) {            // column `col` of a row, and what follows it in its piece of eight
-        return DENSE ? tile_s + row * TLD + 8 * ((col >> 3) ^ (row & 15)) + (col & 7) : tile_s + row * TLD + col;
+        return Gm::FULL ? tile_s + row * TLD + 8 * ((col >> 3) ^ (row & 15)) + (col & 7) : tile_s + row * TLD + col;
     };
     // acc[i][j][v]: feature = f0 + 32 i + 8 (v / 4) + 4 half + v % 4, row = 32 j + l32
     const int f0 = wave * FW;
@@ -124,139 +126,144 @@ __device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs 
     // attention over the layer axis: one wavefront per (token of the tile, query head); spare wavefronts redo a
     // unit and store nothing, so that the barriers below are reached by all.  In a dense tile four units have two wavefronts
     // each: the second takes the last block of query rows and hands its weights over (49 rows of 64; a token has more than 64).
+    // Of ten units two wavefronts do two, one after another.
     constexpr int NU = 2 * TT;
     constexpr int NKS = DH / 16;
     static_assert(!DENSE || NU == 4, "two wavefronts per unit");
     const bool live_wave = wave < NU;
     const int ib0 = DENSE && !live_wave ? NB - 1 : 0, ib1 = DENSE && live_wave ? NB - 1 : NB;
-    const int u = wave % NU, tt = u >> 1, hq = u & 1;
-    const int64_t tok = tile * TT + tt;
-    const int row0 = tt * (DENSE ? L : 32 * NB);                  // the token's first row
-    const bf16_t *trow = tile_s + (size_t)row0 * TLD;
-    auto tok_at = [&](int row, int col) {                         // rows past L are masked, or weighted 0
-        return DENSE ? (const bf16_t *)at(row0 + min(row, L - 1), col) : trow + row * TLD + col;
-    };
-    float *pbar_s = (float *)((char *)sm + Gm::tile_bytes) + wave * 32 * NB;
-    auto pbar = [&](int j) -> float & { return DENSE ? ((float *)(tile_s + (row0 + (j >> 6)) * TLD + hq * DH))[j & 63] : pbar_s[j]; };
-    const float sc = 1.4426950408889634f / sqrtf((float)DH);      // log2 domain
+    int u = NU > 8 ? __builtin_amdgcn_readfirstlane(wave) : wave % NU;
+    do {
+        const int tt = u >> 1, hq = u & 1;
+        const int64_t tok = tok0 + tt;
+        const int row0 = tt * (DENSE ? L : 32 * NB);                  // the token's first row
+        const bf16_t *trow = tile_s + (size_t)row0 * TLD;
+        auto tok_at = [&](int row, int col) {                         // rows past L are masked, or weighted 0
+            return DENSE ? (const bf16_t *)at(row0 + min(row, L - 1), col) : Gm::FULL ? (const bf16_t *)at(row0 + row, col) : trow + row * TLD + col;
+        };
+        float *pbar_s = (float *)((char *)sm + Gm::tile_bytes) + wave * 32 * NB;
+        auto pbar = [&](int j) -> float & { return Gm::FULL ? ((float *)(tile_s + (row0 + (j >> 6)) * TLD + hq * DH))[j & 63] : pbar_s[j]; };
+        const float sc = 1.4426950408889634f / sqrtf((float)DH);      // log2 domain
 
-    float hand_inv = 0.f;
-    // column sums of P in the S^T register layout: csum[jb][v] belongs to key 32 jb + 8 (v/4) + 4 half + v%4
-    float csum[NB][16];
+        float hand_inv = 0.f;
+        // column sums of P in the S^T register layout: csum[jb][v] belongs to key 32 jb + 8 (v/4) + 4 half + v%4
+        float csum[NB][16];
 #pragma unroll
-    for (int jb = 0; jb < NB; ++jb)
+        for (int jb = 0; jb < NB; ++jb)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) csum[jb][e] = 0.f;
+            for (int e = 0; e < 16; ++e) csum[jb][e] = 0.f;
 #pragma unroll
-    for (int ib = 0; ib < NB; ++ib) {
-        if (DENSE && (ib < ib0 || ib >= ib1)) continue;
-        const bool qvalid = 32 * ib + l32 < L;
-        bf16x8 qf[NKS];
+        for (int ib = 0; ib < NB; ++ib) {
+            if (DENSE && (ib < ib0 || ib >= ib1)) continue;
+            const bool qvalid = 32 * ib + l32 < L;
+            bf16x8 qf[NKS];
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const bf16x8 *)tok_at(32 * ib + l32, hq * DH + 16 * ks + 8 * half);
-        f32x16 s[NB];
+            for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const bf16x8 *)tok_at(32 * ib + l32, hq * DH + 16 * ks + 8 * half);
+            f32x16 s[NB];
 #pragma unroll
-        for (int jb = 0; jb < NB; ++jb) {
+            for (int jb = 0; jb < NB; ++jb) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) s[jb][e] = 0.f;
+                for (int e = 0; e < 16; ++e) s[jb][e] = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) {        // key fragments straight from the parked tile: nothing to keep across blocks
-                const bf16x8 kf = *(const bf16x8 *)tok_at(32 * jb + l32, 2 * DH + 16 * ks + 8 * half);
-                s[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s[jb], 0, 0, 0);
+                for (int ks = 0; ks < NKS; ++ks) {        // key fragments straight from the parked tile: nothing to keep across blocks
+                    const bf16x8 kf = *(const bf16x8 *)tok_at(32 * jb + l32, 2 * DH + 16 * ks + 8 * half);
+                    s[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s[jb], 0, 0, 0);
+                }
+            }
+            float mx = -INFINITY;
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int key = 32 * jb + 8 * (e >> 2) + 4 * half + (e & 3);
+                    const float x = key < L ? s[jb][e] * sc : -INFINITY;
+                    s[jb][e] = x;
+                    mx = fmaxf(mx, x);
+                }
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            float sum = 0.f;
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) { const float p = exp2f(s[jb][e] - mx); s[jb][e] = p; sum += p; }
+            sum += __shfl_xor(sum, 32);
+            const float inv = qvalid ? 1.0f / sum : 0.f;              // padded query columns contribute nothing
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    if (DENSE && !live_wave) csum[jb][e] = s[jb][e];             // scaled where it is added: the same rounding
+                    else csum[jb][e] += s[jb][e] * inv;
+                }
+            hand_inv = inv;
+        }
+        if (DENSE) {                                 // through the rows of the unit's Q, which nobody reads any more
+            __syncthreads();
+            auto place = [&](int jb, int e) -> float & { return ((float *)(tile_s + (row0 + 16 * jb + e) * TLD + hq * DH))[lane]; };
+            if (!live_wave) {
+#pragma unroll
+                for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) place(jb, e) = csum[jb][e];
+                place(NB, 0) = hand_inv;
+            }
+            __syncthreads();
+            if (live_wave) {
+                const float inv = place(NB, 0);
+#pragma unroll
+                for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) csum[jb][e] += place(jb, e) * inv;
             }
         }
-        float mx = -INFINITY;
 #pragma unroll
         for (int jb = 0; jb < NB; ++jb)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const int key = 32 * jb + 8 * (e >> 2) + 4 * half + (e & 3);
-                const float x = key < L ? s[jb][e] * sc : -INFINITY;
-                s[jb][e] = x;
-                mx = fmaxf(mx, x);
+                csum[jb][e] = sum_over_lanes32(csum[jb][e]);
             }
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        float sum = 0.f;
-#pragma unroll
-        for (int jb = 0; jb < NB; ++jb)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) { const float p = exp2f(s[jb][e] - mx); s[jb][e] = p; sum += p; }
-        sum += __shfl_xor(sum, 32);
-        const float inv = qvalid ? 1.0f / sum : 0.f;              // padded query columns contribute nothing
-#pragma unroll
-        for (int jb = 0; jb < NB; ++jb)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                if (DENSE && !live_wave) csum[jb][e] = s[jb][e];             // scaled where it is added: the same rounding
-                else csum[jb][e] += s[jb][e] * inv;
-            }
-        hand_inv = inv;
-    }
-    if (DENSE) {                                 // through the rows of the unit's Q, which nobody reads any more
-        __syncthreads();
-        auto place = [&](int jb, int e) -> float & { return ((float *)(tile_s + (row0 + 16 * jb + e) * TLD + hq * DH))[lane]; };
-        if (!live_wave) {
+        if (l32 == 0 && (!DENSE || live_wave)) {     // (a dense tile has one place per unit, which its own wavefront is done with)
+            const float invL = 1.0f / (float)L;
 #pragma unroll
             for (int jb = 0; jb < NB; ++jb)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) place(jb, e) = csum[jb][e];
-            place(NB, 0) = hand_inv;
+                for (int e = 0; e < 16; ++e) pbar(32 * jb + 8 * (e >> 2) + 4 * half + (e & 3)) = csum[jb][e] * invL;
         }
-        __syncthreads();
-        if (live_wave) {
-            const float inv = place(NB, 0);
-#pragma unroll
-            for (int jb = 0; jb < NB; ++jb)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) csum[jb][e] += place(jb, e) * inv;
-        }
-    }
-#pragma unroll
-    for (int jb = 0; jb < NB; ++jb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            csum[jb][e] = sum_over_lanes32(csum[jb][e]);
-        }
-    if (l32 == 0 && (!DENSE || live_wave)) {     // (a dense tile has one place per unit, which its own wavefront is done with)
-        const float invL = 1.0f / (float)L;
-#pragma unroll
-        for (int jb = 0; jb < NB; ++jb)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) pbar(32 * jb + 8 * (e >> 2) + 4 * half + (e & 3)) = csum[jb][e] * invL;
-    }
-    __syncthreads();
+        if (NU <= 8) __syncthreads();
+        else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the wavefront's own
 
-    // abar[c] = sum_j pbar[j] V[j][c]: a lane weights 8 components of its rows, then the row groups are added up
-    constexpr int CPR = DH / 8;                  // 16-byte pieces per V row
-    constexpr int RPI = 64 / CPR;                // rows per instruction
-    constexpr int NVI = 32 / RPI;
-    const int vrow0 = lane / CPR, vpiece = lane % CPR;
-    float o[8];
+        // abar[c] = sum_j pbar[j] V[j][c]: a lane weights 8 components of its rows, then the row groups are added up
+        constexpr int CPR = DH / 8;                  // 16-byte pieces per V row
+        constexpr int RPI = 64 / CPR;                // rows per instruction
+        constexpr int NVI = 32 / RPI;
+        const int vrow0 = lane / CPR, vpiece = lane % CPR;
+        float o[8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) o[c] = 0.f;
+        for (int c = 0; c < 8; ++c) o[c] = 0.f;
 #pragma unroll
-    for (int jb = 0; jb < NB; ++jb)
+        for (int jb = 0; jb < NB; ++jb)
 #pragma unroll
-        for (int i = 0; i < NVI; ++i) {
-            const int row = 32 * jb + RPI * i + vrow0;
-            const float pj = row < L ? pbar(row) : 0.f;
-            const u32x4 vv = *(const u32x4 *)tok_at(row, 3 * DH + 8 * vpiece);
+            for (int i = 0; i < NVI; ++i) {
+                const int row = 32 * jb + RPI * i + vrow0;
+                const float pj = row < L ? pbar(row) : 0.f;
+                const u32x4 vv = *(const u32x4 *)tok_at(row, 3 * DH + 8 * vpiece);
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                o[2 * w] = fmaf(pj, __uint_as_float(vv[w] << 16), o[2 * w]);
-                o[2 * w + 1] = fmaf(pj, __uint_as_float(vv[w] & 0xffff0000u), o[2 * w + 1]);
+                for (int w = 0; w < 4; ++w) {
+                    o[2 * w] = fmaf(pj, __uint_as_float(vv[w] << 16), o[2 * w]);
+                    o[2 * w + 1] = fmaf(pj, __uint_as_float(vv[w] & 0xffff0000u), o[2 * w + 1]);
+                }
             }
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+#pragma unroll
+            for (int off = CPR; off < 64; off <<= 1) o[c] += __shfl_xor(o[c], off);
+        if ((NU > 8 || live_wave) && tok < a.T && lane < CPR) {
+            u32x4 pk;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) pk[w] = pack_bf16x2(o[2 * w], o[2 * w + 1]);
+            *(u32x4 *)(a.abar + tok * (int64_t)a.Hq * DH + (int64_t)(g * G + 2 * part + hq) * DH + 8 * lane) = pk;
         }
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-#pragma unroll
-        for (int off = CPR; off < 64; off <<= 1) o[c] += __shfl_xor(o[c], off);
-    if (live_wave && tok < a.T && lane < CPR) {
-        u32x4 pk;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) pk[w] = pack_bf16x2(o[2 * w], o[2 * w + 1]);
-        *(u32x4 *)(a.abar + tok * (int64_t)a.Hq * DH + (int64_t)(g * G + 2 * part + hq) * DH + 8 * lane) = pk;
-    }
+    } while (NU > 8 && (u += 8) < NU);
 }
 
 template <int DH, int NB, int TT>
@@ -386,7 +393,7 @@ __global__ __launch_bounds__(512) void k_lsa_fused(LsaFusedArgs a)
         }
     }
 
-    lsa_fused_epilogue<DH, NB, TT, false>(acc, a, sm, tile, g, part);
+    lsa_fused_epilogue<DH, NB, TT, false>(acc, a, sm, tile * TT, g, part);
 }
 
 // f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N - 1>{}): a loop whose index is a constant
@@ -446,8 +453,10 @@ __device__ __forceinline__ void lsa_warm_block(const LsaFusedArgs &a, int h, bf1
 // flight per wavefront in registers, which the 160 KB of LDS could not hold.  The activation tile goes through
 // registers into a two-stage LDS ring (one bare barrier per tile); all loads are ordinary loads, so the waits are the
 // compiler's.  Same MFMA order along d_in as the unpacked form: same bits.
+//
+// The tile of TT tokens from tok0 on, of one unit.
 template <int DH, int NB, int TT, bool DENSE>
-__device__ __forceinline__ void lsa_pk_block(const LsaFusedArgs &a)
+__device__ __forceinline__ void lsa_pk_tile(const LsaFusedArgs &a, int unit, int64_t tok0)
 {
     using Gm = LsaFusedGeom<DH, NB, TT, DENSE>;
     constexpr int FW = Gm::FW, RB = Gm::RB, BK = Gm::BK, WS = Gm::WS;
@@ -457,20 +466,6 @@ __device__ __forceinline__ void lsa_pk_block(const LsaFusedArgs &a)
     constexpr int NXI = (RB / 8 + 7) / 8;        // activation-tile load instructions per wavefront
     extern __shared__ __attribute__((aligned(16))) bf16_t sm[];
 
-    if ((int)blockIdx.x < a.lead_blocks) {       // the first workgroups of the grid carry the step's integer work
-        if ((int)blockIdx.x >= a.lead_blocks - a.pf_lead) {
-            lsa_warm_block<DH, NB, TT>(a, (int)blockIdx.x - (a.lead_blocks - a.pf_lead), sm);
-            return;
-        }
-        if ((int)blockIdx.x < a.rider_units && threadIdx.x < 64)
-            step_small_unit(a.rider, (int)blockIdx.x, (int32_t *)sm, (int32_t *)sm + MOA_MAX_TREE);
-        return;
-    }
-    const int bx = (int)blockIdx.x - a.lead_blocks;
-    const int xcd = bx & 7, slot = bx >> 3;
-    const int unit = xcd * a.units_per_xcd + slot % a.units_per_xcd;
-    const int64_t tile = slot / a.units_per_xcd;
-    if (unit >= a.units) return;                 // the whole workgroup leaves before any barrier
     const int g = unit / a.parts, part = unit - g * a.parts;
     const int L = a.L, K = a.d_in;
 
@@ -499,7 +494,7 @@ __device__ __forceinline__ void lsa_pk_block(const LsaFusedArgs &a)
         xrow0[n] = 8 * xi;
         const int s = 8 * xi + lrow;
         const int in = DENSE ? min(s / L, TT - 1) : s / (32 * NB);
-        int64_t tok = tile * TT + in;
+        int64_t tok = tok0 + in;
         int lay = DENSE ? s - in * L : s % (32 * NB);
         if (tok > a.T - 1) tok = a.T - 1;
         if (lay > L - 1) lay = L - 1;
@@ -606,11 +601,48 @@ __device__ __forceinline__ void lsa_pk_block(const LsaFusedArgs &a)
 #pragma unroll 1
     for (int kt0 = nk_main; kt0 < nk_end; kt0 += WS)
         static_for<WS>([&](auto u) { tile_step(u, std::true_type{}, kt0 + decltype(u)::value); });
-    lsa_fused_epilogue<DH, NB, TT, DENSE>(acc, a, sm, tile, g, part);
+    lsa_fused_epilogue<DH, NB, TT, DENSE>(acc, a, sm, tok0, g, part);
+}
+
+// The workgroups in front of the kernel's own do the step's integer work or read ahead (WNB, WTT: the tile that asks for it);
+// true for the others.
+template <int DH, int WNB, int WTT>
+__device__ __forceinline__ bool lsa_pk_unit(const LsaFusedArgs &a, int *unit, int64_t *tile)
+{
+    extern __shared__ __attribute__((aligned(16))) bf16_t sm[];
+    if ((int)blockIdx.x < a.lead_blocks) {       // the first workgroups of the grid carry the step's integer work
+        if ((int)blockIdx.x >= a.lead_blocks - a.pf_lead)
+            lsa_warm_block<DH, WNB, WTT>(a, (int)blockIdx.x - (a.lead_blocks - a.pf_lead), sm);
+        else if ((int)blockIdx.x < a.rider_units && threadIdx.x < 64)
+            step_small_unit(a.rider, (int)blockIdx.x, (int32_t *)sm, (int32_t *)sm + MOA_MAX_TREE);
+        return false;
+    }
+    const int bx = (int)blockIdx.x - a.lead_blocks;
+    const int xcd = bx & 7, slot = bx >> 3;
+    *unit = xcd * a.units_per_xcd + slot % a.units_per_xcd;
+    *tile = slot / a.units_per_xcd;
+    return *unit < a.units;                      // the whole workgroup leaves before any barrier
 }
 
 template <int DH, int NB, int TT>
-__global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a) { lsa_pk_block<DH, NB, TT, false>(a); }
+__global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
+{
+    int unit;
+    int64_t tile;
+    if (lsa_pk_unit<DH, NB, TT>(a, &unit, &tile)) lsa_pk_tile<DH, NB, TT, false>(a, unit, tile * TT);
+}
+// The first `wide_tiles` tiles take five tokens (160 rows), those behind them TT (where the line lies: launch_lsa_fused).  160
+// rows bring a weight tile to more of them (1.80 us per k tile against 1.61 for 128), and their parked tile fills the LDS
+// like a dense one's; ten (token, head) units on eight wavefronts cost the second pass.
+template <int DH, int TT>
+__global__ __launch_bounds__(512) void k_lsa_fused_pk_wide(LsaFusedArgs a)
+{
+    int unit;
+    int64_t tile;
+    if (!lsa_pk_unit<DH, 1, TT>(a, &unit, &tile)) return;
+    if (tile < a.wide_tiles) lsa_pk_tile<DH, 1, 5, false>(a, unit, tile * 5);
+    else lsa_pk_tile<DH, 1, TT, false>(a, unit, a.wide_tiles * 5 + (tile - a.wide_tiles) * TT);
+}
 // The same with the rows of TT tokens one behind another in 160 (five blocks of 32), for layer counts that leave much of
 // their last block empty: 80 layers in 96 rows waste a sixth of the matrix work, two tokens in 160 nothing, and a weight
 // tile serves 160 rows.  The accumulators take 160 registers, so one weight tile is in registers instead of two, and the parked tile
@@ -618,7 +650,12 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a) { lsa_pk_b
 // projection and attention as kernels of their own 305 + 60.  1.80 us per k tile at 160 rows and the 1.75 GHz the power limit
 // leaves (1.46 of them MFMA) and 17 us in front and behind, 6 of which were saved by giving a unit's query blocks to two wavefronts.
 template <int DH, int NB, int TT>
-__global__ __launch_bounds__(512) void k_lsa_fused_pk_dense(LsaFusedArgs a) { lsa_pk_block<DH, NB, TT, true>(a); }
+__global__ __launch_bounds__(512) void k_lsa_fused_pk_dense(LsaFusedArgs a)
+{
+    int unit;
+    int64_t tile;
+    if (lsa_pk_unit<DH, NB, TT>(a, &unit, &tile)) lsa_pk_tile<DH, NB, TT, true>(a, unit, tile * TT);
+}
 
 // Packs Wq / Wk / Wv for k_lsa_fused_pk: piece (unit, wavefront, k tile, k step, feature block, lane) holds the 8
 // elements that lane supplies as the A operand of that MFMA, i.e. row  f(unit, wavefront) + 32 block + lane % 32  of
@@ -680,7 +717,7 @@ template <int NB, int TT, bool DENSE = false>
 static hipError_t launch_lsa_fused_as(LsaFusedArgs &fa, hipStream_t stream)
 {
     using Gm = LsaFusedGeom<128, NB, TT, DENSE>;
-    const int64_t tiles = (fa.T + TT - 1) / TT;
+    const int64_t rest = fa.T - 5 * fa.wide_tiles, tiles = fa.wide_tiles + (rest > 0 ? (rest + TT - 1) / TT : 0);
     // Two helper workgroups per XCD (lsa_warm_block), where they cost nothing and can do their job: the kernel's own
     // workgroups leave that many compute units idle (decode sizes), and an XCD's share of the weights fits its L2
     // beside the activations streaming through.  Otherwise they take compute units and L2 from the workgroups they
@@ -705,6 +742,16 @@ static hipError_t launch_lsa_fused_as(LsaFusedArgs &fa, hipStream_t stream)
         if (e != hipSuccess) return e;
         prof_begin(K_LSA_FUSED_PK + 64 * (64 + NB * 8 + TT), stream);
         MOA_KLAUNCH((k_lsa_fused_pk_dense<128, NB, TT>), dim3((unsigned)grid), dim3(512), Gm::pk_bytes, stream, fa);
+    } else if (fa.wide_tiles) {
+        if constexpr (NB == 1) {
+            using Wide = LsaFusedGeom<128, 1, 5>;
+            constexpr size_t lds = Wide::pk_bytes > Gm::pk_bytes ? Wide::pk_bytes : Gm::pk_bytes;
+            static bool raised[16] = {};
+            hipError_t e = raise_lds_limit_once(raised, (const void *)k_lsa_fused_pk_wide<128, TT>, lds);
+            if (e != hipSuccess) return e;
+            prof_begin(K_LSA_FUSED_PK + 64 * (32 + TT), stream);
+            MOA_KLAUNCH((k_lsa_fused_pk_wide<128, TT>), dim3((unsigned)grid), dim3(512), lds, stream, fa);
+        }
     } else if (fa.wpk) {
         static bool raised[16] = {};
         hipError_t e = raise_lds_limit_once(raised, (const void *)k_lsa_fused_pk<128, NB, TT>, Gm::pk_bytes);
@@ -771,7 +818,7 @@ hipError_t launch_lsa_fused(const LsaFusedCall &c, hipStream_t stream)
     // the tile that minimises rounds x time per round.
     const int nb = (c.L + 31) / 32;
     const bool big_ok = lds_limit() >= LsaFusedGeom<128, 1, 4>::bytes;      // the 128-row tiles fill the LDS to the last byte
-    const double fixed = fa.wpk ? 10.0 : 31.0, per_block = fa.wpk ? 11.7 : 9.0;
+    const double fixed = fa.wpk ? 10.0 : 31.0, per_block = fa.wpk ? 11.7 * fa.d_in / 2048 : 9.0;
     auto cost = [&](int tt) {
         const double wgs = (double)fa.units * (double)((c.T + tt - 1) / tt);
         return ceil(wgs / 256.0) * (fixed + per_block * nb * tt);    // one workgroup per compute unit, all equally long: whole rounds
@@ -780,6 +827,27 @@ hipError_t launch_lsa_fused(const LsaFusedCall &c, hipStream_t stream)
         int best = 2;
         if (cost(3) < cost(best)) best = 3;
         if (big_ok && cost(4) < cost(best)) best = 4;
+        // Packed: whole rounds of 160-row tiles and what is left in smaller ones.  A row costs as much in 160 as in 128 (69 us a
+        // round against 55: the power limit), so this is about rounds that are nearly empty, and has to promise 4 % since a
+        // round with idle compute units also clocks higher (with the output projection, d_in 2048: 140 tokens 93 -> 78 us, 300
+        // 175 -> 153, 400 229 -> 199, 960 478 -> 448; 1024, where it promises 2 %, 472 -> 478).
+        const int64_t round = 32 / fa.units_per_xcd;       // tiles of one unit in a round of an XCD's 32 compute units
+        if (fa.wpk && big_ok && round > 0) {
+            auto us = [&](int64_t tokens, int tt) {
+                return (double)(((tokens + tt - 1) / tt * fa.units_per_xcd + 31) / 32) * (fixed + per_block * tt);
+            };
+            double least = 0.96 * us(fa.T, best);
+            const int64_t full = fa.T / (5 * round);
+            for (int64_t w = full > 3 ? full - 3 : 0; w <= full; ++w)
+                for (int tt = 2; tt <= 5; ++tt) {
+                    if (w == 0 && tt < 5) continue;
+                    const double t = (double)w * (fixed + per_block * 5) + us(fa.T - 5 * round * w, tt);
+                    if (t >= least) continue;
+                    least = t;
+                    best = tt < 5 ? tt : 4;
+                    fa.wide_tiles = tt < 5 ? round * w : (fa.T + 4) / 5;
+                }
+        }
         if (best == 4) return launch_lsa_fused_as<1, 4>(fa, stream);
         if (best == 3) return launch_lsa_fused_as<1, 3>(fa, stream);
         return launch_lsa_fused_as<1, 2>(fa, stream);

@@ -192,6 +192,7 @@ const char *moa_profile_kernel_name(int32_t kernel)
     if (var == 0) return kKernelNames[base];
     if (base == K_LIN_BF16) return linear_bf16_name(var);
     if (base == K_ATTN_FUSED) snprintf(buf, sizeof(buf), "%s<%d, %d>", kKernelNames[base], var >> 3, 4 * (var & 7));
+    else if (base == K_LSA_FUSED_PK && var >> 3 == 4) snprintf(buf, sizeof(buf), "%s_wide<128, %d>", kKernelNames[base], var & 7);
     else if (base == K_LSA_FUSED || base == K_LSA_FUSED_PK) snprintf(buf, sizeof(buf), "%s%s<128, %d, %d>", kKernelNames[base], var & 64 ? "_dense" : "", (var >> 3) & 7, var & 7);
     else if (base == K_ATTN_MERGE) snprintf(buf, sizeof(buf), "%s<%d>", kKernelNames[base], var >> 3);
     else snprintf(buf, sizeof(buf), "%s<%d, %d>", kKernelNames[base], var >> 3, var & 7);

@@ -243,6 +243,30 @@ def test_lsa_rows_of_two_tokens_one_behind_another(G, moa, L, d_in, Hkv, T):
     assert torch.isfinite(want.float()).all() and torch.equal(out, want)
 
 
+@pytest.mark.parametrize("L,d_in,Hkv,T", [(32, 512, 2, 67), (32, 512, 2, 163), (32, 512, 2, 226), (32, 512, 2, 258), (21, 320, 1, 162),
+                                          (1, 512, 2, 160), (29, 1024, 4, 290), (32, 1024, 4, 701)])
+def test_lsa_five_tokens_per_workgroup(G, moa, L, d_in, Hkv, T):
+    """Up to 32 layers from packed weights: 160-row tiles alone (67, 160, 290 tokens: the last tile ragged, full, full) and in
+    front of tiles of two, three and four tokens (163, 162 | 226 | 258, 701; the last of them ragged too); padded rows; 5, 8 and 16
+    tiles of 64 along the width.  The bits are those of the plain-weight form, whose tiles have at most 128 rows."""
+    cfg = small_cfg("bf16", L=L, d_lsa_in=d_in, dh=128, Hkv=Hkv)
+    print(f"[case] lsa wide L={L} d_in={d_in} heads={cfg.lsa_heads}/{Hkv} T={T}", flush=True)
+    shape = G.shape_of(cfg)
+    w = mi.lsa_weights(cfg)
+    hs = G.dev(mi.lsa_inputs(cfg, T), cfg.dtype)
+    ws = G.workspace(shape, cfg.B, cfg.P_cap, cfg.M, T)
+    dw = [G.dev(w[k], cfg.dtype) for k in ("wq", "wk", "wv", "wo")]
+    out, want = (torch.full((T, cfg.d_lsa), float("nan"), dtype=G.TDT[cfg.dtype], device="cuda") for _ in range(2))
+    moa.debug_force_lsa_kernel("fused")
+    try:
+        moa.lsa(shape, hs, *dw, want, ws)
+        moa.lsa_packed(shape, hs, moa.lsa_pack_weights(shape, *dw[:3]), dw[3], out, ws)
+        torch.cuda.synchronize()
+    finally:
+        moa.debug_force_lsa_kernel("auto")
+    assert torch.isfinite(want.float()).all() and torch.equal(out, want)
+
+
 def ca_setup(cfg, Mq):
     w = mi.ca_weights(cfg)
     xq = mi.ca_queries(cfg, Mq)
