@@ -18,7 +18,7 @@
 //              Three things cost about the same per tile -- the weight tile's way from the L2 into LDS (64 KB per
 //              64 of d_in, all workgroups of an XCD asking for the same lines at once), the operand reads from LDS
 //              and the matrix work -- and they overlap only in part; the lever that is left is rows per workgroup
-//              (2, 3 or 4 tokens at one 32-layer block each), chosen from the token count on the host.
+//              (2, 3 or 4 tokens at one 32-layer block each, from packed weights 5), chosen from the token count on the host.
 //  attention   the accumulators are rounded to the storage type and parked in LDS as a [RB x 4 dh] tile (the ring
 //              memory is reused); one wavefront per (token, query head): S^T = K Q^T by MFMA, fp32 softmax in
 //              registers, column means of P summed over the 32 query lanes (DPP moves, one shuffle), then
