@@ -64,6 +64,22 @@ def test_gemm_tile_edges(G, moa, R, K, N):
     assert (diff.norm() / want.norm()).item() <= 2.0 ** -9
 
 
+@pytest.mark.parametrize("R,K,N", [(1, 4224, 8192), (8, 640, 53024), (32, 256, 131104), (60, 128, 4096), (200, 1152, 30016)])
+def test_xcds_begin_at_different_places_along_k(G, moa, R, K, N):
+    """64 MB of weights or more at any row count, and 33 .. 128 rows: every XCD walks the k tiles from another one on, around
+    the end.  Tile counts that eight does not divide (66, 33, 18), fewer than eight (5, 2) and one per K group (60 rows x 128)."""
+    print(f"[case] linear bf16 R={R} K={K} N={N}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(R + K)
+    x = torch.randn(R, K, generator=g, device="cuda").bfloat16()
+    w = (torch.randn(N, K, generator=g, device="cuda") / K ** 0.5).bfloat16()
+    y = torch.full((R, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    moa.linear(x, w, y, torch.empty(max(moa.linear_workspace_bytes(moa.BF16, R, K, N), 256), dtype=torch.uint8, device="cuda"))
+    want = x.float() @ w.float().t()                          # bounds as in test_gemm_tile_edges
+    diff = (y.float() - want).abs()
+    assert diff.max().item() <= 2.0 ** -8 * want.abs().max().item()
+    assert (diff.norm() / want.norm()).item() <= 2.0 ** -9
+
+
 @pytest.mark.parametrize("R,K,N", [(64, 14336, 4096), (129, 12288, 1024)])
 def test_without_a_workspace_the_plan_is_made_for_whole_k(G, moa, R, K, N):
     """The tile that is best for several K slices leaves most of the chip idle when there is no room for their sums: without
