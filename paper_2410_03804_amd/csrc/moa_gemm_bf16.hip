@@ -30,7 +30,6 @@ struct GemmArgs {
     int splits;          // slices of K; with more than one the sums go to `part` for a second pass
     float *part;         // [64-row tiles][splits][64][ntot]
     int ntot;            // features of all segments
-    int staggered;       // XCDs begin at different places along K
     int gated;           // EPI_SWIGLU inside the kernel: 32-feature blocks alternate between the two matrices
 };
 
@@ -66,15 +65,7 @@ __global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(GemmArgs ga)
         *first = 32 * (ga.gated ? blk >> 1 : blk);
         return (const char *)a.seg[sel].W + (int64_t)n0 * K * 2;
     });
-    // Where along K to begin.  Workgroups that walk the rows of W in step are all at the same columns, and those lie on the same
-    // memory channels (rows are a power of two apart): each XCD begins an eighth of K further on.  60 x 4096 x 28672: 53.0 ->
-    // 43.4 us, 64 x 8192 x 28672 105 -> 83, 8 x 4096 x 32000 51.0 -> 45.2; from 512 rows on nothing; with less than 64 MB of
-    // weights it gains at 33 .. 128 rows (60 x 4096 x 4096 from memory 12.2 -> 11.4) and costs elsewhere (8 x 4096 x 5120 11.9 -> 12.2).  The order of the sums goes with it, so where a step's schedules have to
-    // agree it may depend on the feature alone: blocks of 512, which no tile straddles (60 x 4096 x 10240 25.8 -> 25.2, 60 x
-    // 4096 x 8192 19.9 -> 18.6; blocks of 256 put neighbours of one XCD apart and cost 10 %); none where the sums are one chain in order.
-    const int first = a.same_sums ? (WK == 1 ? 0 : ((n0 >> 9) & 7) * nk / 8) : ga.staggered ? xcd * nk / 8 : 0;
-    static_assert(WK == 1 || 512 % BN == 0, "a tile is in one block of 512 features");
-    if (!g.run(smem, split * nk, nk, first)) return;
+    if (!g.run(smem, split * nk, nk)) return;
     f32x16 (&acc)[NF][MR] = g.acc;
     const int l32 = g.lane & 31, half = g.lane >> 5, wfi = g.wave % WF;
 
@@ -285,7 +276,6 @@ hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused,
     ga.part = (float *)a.ws;
     ga.ntot = ntot;
     ga.gated = a.epi == LinArgs::EPI_SWIGLU && t.gated && p.splits == 1;
-    ga.staggered = !a.in_order && !a.same_sums && ((int64_t)a.K * ntot * 2 >= (int64_t)64 << 20 || (a.R > 32 && a.R <= 128));
     *fused = ga.gated || (a.epi == LinArgs::EPI_ADD_F32 && p.splits == 1);
     int ft = 0;
     for (int s = 0; s < a.nseg; ++s) {

@@ -86,26 +86,22 @@ struct GemmLoop {
     }
 
     // nk k tiles of this K group, from column 64 (kt0 WK + kgrp) on in steps of 64 WK; with WK > 1 only group 0 has the
-    // sums afterwards (the others return false).  They are walked from `first` (below nk) on, around the end.  Ends behind a barrier when WK > 1, and with no load in flight.
-    __device__ __forceinline__ bool run(char *smem, int kt0, int nk, int first = 0)
+    // sums afterwards (the others return false).  Ends behind a barrier when WK > 1, and with no load in flight.
+    __device__ __forceinline__ bool run(char *smem, int kt0, int nk)
     {
         const int64_t kbyte0 = ((int64_t)kt0 * WK + kgrp) * (BK * 2);
         const uint32_t ring = (uint32_t)kgrp * (SX * XST + SW * WST);
         const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem + ring;
         const int l32 = lane & 31, half = lane >> 5;
         uint32_t xfill = 0, wfill = 0;             // stage (byte offset) the next load goes to
-        auto place = [&](int kt) {                 // tiles past the last repeat it (nobody reads them)
-            const int at = (kt < nk ? kt : nk - 1) + first;
-            return (int64_t)(at < nk ? at : at - nk) * (WK * BK * 2);
-        };
-        auto issue_x = [&](int kt) {
-            const int64_t ko = kbyte0 + place(kt);
+        auto issue_x = [&](int kt) {               // tiles past the last repeat it (nobody reads them)
+            const int64_t ko = kbyte0 + (int64_t)(kt < nk ? kt : nk - 1) * (WK * BK * 2);
 #pragma unroll
             for (int i = 0; i < NXI; ++i) lds_dma16(lds0 + xdst[i] + xfill, xoff[i], xbase + ko);
             xfill = xfill + XST == SX * XST ? 0 : xfill + XST;
         };
         auto issue_w = [&](int kt) {
-            const int64_t ko = kbyte0 + place(kt);
+            const int64_t ko = kbyte0 + (int64_t)(kt < nk ? kt : nk - 1) * (WK * BK * 2);
 #pragma unroll
             for (int i = 0; i < NWI; ++i) lds_dma16(lds0 + wdst[i] + wfill, woff[i], wbase[i] + ko);
             wfill = wfill + WST == SW * WST ? 0 : wfill + WST;

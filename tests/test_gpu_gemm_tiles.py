@@ -65,9 +65,9 @@ def test_gemm_tile_edges(G, moa, R, K, N):
 
 
 @pytest.mark.parametrize("R,K,N", [(1, 4224, 8192), (8, 640, 53024), (32, 256, 131104), (60, 128, 4096), (200, 1152, 30016)])
-def test_xcds_begin_at_different_places_along_k(G, moa, R, K, N):
-    """64 MB of weights or more at any row count, and 33 .. 128 rows: every XCD walks the k tiles from another one on, around
-    the end.  Tile counts that eight does not divide (66, 33, 18), fewer than eight (5, 2) and one per K group (60 rows x 128)."""
+def test_wide_matrices_at_odd_k_tile_counts(G, moa, R, K, N):
+    """64 MB of weights at a few row counts, and narrower ones: k tile counts that eight does not divide (66, 33, 18), fewer
+    than eight (5, 2) and one per K group (60 rows x 128)."""
     print(f"[case] linear bf16 R={R} K={K} N={N}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(R + K)
     x = torch.randn(R, K, generator=g, device="cuda").bfloat16()
@@ -78,6 +78,49 @@ def test_xcds_begin_at_different_places_along_k(G, moa, R, K, N):
     diff = (y.float() - want).abs()
     assert diff.max().item() <= 2.0 ** -8 * want.abs().max().item()
     assert (diff.norm() / want.norm()).item() <= 2.0 ** -9
+
+
+@pytest.mark.parametrize("R,K,N,period", [(8, 4096, 128256, 4096), (1, 4096, 32000, 2048), (60, 4096, 28672, 1024), (60, 4096, 4160, 128),
+                                          (96, 2048, 8192, 512), (200, 4096, 8224, 512), (64, 14336, 4096, 256)])
+def test_equal_weight_rows_give_equal_logits(G, moa, R, K, N, period):
+    """The order of a sum along K does not depend on where its feature lies: rows that stand once in every XCD's share of the matrix
+    give the same bits everywhere, so that tied tokens stay tied and the most probable ones are the lowest ids.  (Another
+    order moves about one sum in two thousand to the next bf16 number: there are 2000 .. 200000 pairs here.)"""
+    print(f"[case] linear + topk_logprob R={R} K={K} N={N}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(R + K + N)
+    x = torch.randn(R, K, generator=g, device="cuda").bfloat16()
+    rows = (torch.randn(period, K, generator=g, device="cuda") / K ** 0.5).bfloat16()
+    w = rows.repeat(N // period + 1, 1)[:N].contiguous()
+    y = torch.full((R, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    moa.linear(x, w, y, torch.empty(max(moa.linear_workspace_bytes(moa.BF16, R, K, N), 256), dtype=torch.uint8, device="cuda"))
+    tok, logp = torch.full((R, 8), -1, dtype=torch.int32, device="cuda"), torch.empty(R, 8, device="cuda")
+    moa.topk_logprob(y, 8, tok, logp, torch.empty(max(moa.topk_workspace_bytes(R, N, 8), 256), dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert torch.isfinite(y).all()
+    assert (y != y[:, :period].repeat(1, N // period + 1)[:, :N]).sum().item() == 0
+    for r in range(R):                                       # ids in the order of falling logits, ties by rising id
+        ids = torch.sort(y[r].float(), descending=True, stable=True).indices[:8].int()
+        assert torch.equal(tok[r], ids), (r, tok[r].tolist(), ids.tolist())
+
+
+@pytest.mark.parametrize("M", [32, 60, 128])
+def test_equal_weight_rows_give_equal_outputs_in_the_layers(G, moa, M):
+    """The same for the projections whose sums a step's schedules have to agree on (pairs of K groups and single chains):
+    equal rows of W_o give equal features."""
+    print(f"[case] cross_attn_draft M={M}", flush=True)
+    H, Hkv, d = 32, 8, 4096
+    g = torch.Generator(device="cuda").manual_seed(M)
+    shape = moa.Shape(2, d, H, Hkv, 128, 256, 2, 1, moa.BF16)
+    x = torch.randn(1, M, d, generator=g, device="cuda").bfloat16()
+    wq = (torch.randn(H * 128, d, generator=g, device="cuda") / d ** 0.5).bfloat16()
+    wo = (torch.randn(256, H * 128, generator=g, device="cuda") / d ** 0.5).bfloat16().repeat(d // 256, 1).contiguous()
+    k, v = (torch.randn(1, Hkv, 64, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
+    out = torch.full_like(x, float("nan"))
+    moa.cross_attn_draft(shape, x, wq, wo, k, v, torch.tensor([64], dtype=torch.int32, device="cuda"), 64, out,
+                         G.workspace(shape, 1, 64, M, 0), G.status_word())
+    torch.cuda.synchronize()
+    assert torch.isfinite(out).all()
+    assert (out != out[..., :256].repeat(1, 1, d // 256)).sum().item() == 0
 
 
 @pytest.mark.parametrize("R,K,N", [(64, 14336, 4096), (129, 12288, 1024)])
