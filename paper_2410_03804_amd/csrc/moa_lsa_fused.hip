@@ -604,32 +604,42 @@ __device__ __forceinline__ void lsa_pk_tile(const LsaFusedArgs &a, int unit, int
     lsa_fused_epilogue<DH, NB, TT, DENSE>(acc, a, sm, tok0, g, part);
 }
 
-// The workgroups in front of the kernel's own do the step's integer work or read ahead (WNB, WTT: the tile that asks for it);
-// true for the others.
-template <int DH, int WNB, int WTT>
-__device__ __forceinline__ bool lsa_pk_unit(const LsaFusedArgs &a, int *unit, int64_t *tile)
+// The workgroups in front of the kernel's own do the step's integer work or read ahead (NB, TT: the tile that asks for it).
+// (Not one function that also says whether a workgroup is the kernel's own: with that the 96-row form spilled two registers,
+// 10 tokens x 80 layers 49.5 -> 50.3 us.)
+template <int DH, int NB, int TT>
+__device__ __forceinline__ void lsa_pk_lead(const LsaFusedArgs &a)
 {
     extern __shared__ __attribute__((aligned(16))) bf16_t sm[];
-    if ((int)blockIdx.x < a.lead_blocks) {       // the first workgroups of the grid carry the step's integer work
-        if ((int)blockIdx.x >= a.lead_blocks - a.pf_lead)
-            lsa_warm_block<DH, WNB, WTT>(a, (int)blockIdx.x - (a.lead_blocks - a.pf_lead), sm);
-        else if ((int)blockIdx.x < a.rider_units && threadIdx.x < 64)
-            step_small_unit(a.rider, (int)blockIdx.x, (int32_t *)sm, (int32_t *)sm + MOA_MAX_TREE);
-        return false;
-    }
-    const int bx = (int)blockIdx.x - a.lead_blocks;
-    const int xcd = bx & 7, slot = bx >> 3;
-    *unit = xcd * a.units_per_xcd + slot % a.units_per_xcd;
-    *tile = slot / a.units_per_xcd;
-    return *unit < a.units;                      // the whole workgroup leaves before any barrier
+    if ((int)blockIdx.x >= a.lead_blocks - a.pf_lead)
+        lsa_warm_block<DH, NB, TT>(a, (int)blockIdx.x - (a.lead_blocks - a.pf_lead), sm);
+    else if ((int)blockIdx.x < a.rider_units && threadIdx.x < 64)
+        step_small_unit(a.rider, (int)blockIdx.x, (int32_t *)sm, (int32_t *)sm + MOA_MAX_TREE);
 }
+
+// the unit and the tile of one of the kernel's own workgroups; units past the last have nothing to do
+struct LsaPkPlace {
+    int unit;
+    int64_t tile;
+    __device__ __forceinline__ LsaPkPlace(const LsaFusedArgs &a)
+    {
+        const int bx = (int)blockIdx.x - a.lead_blocks;
+        const int xcd = bx & 7, slot = bx >> 3;
+        unit = xcd * a.units_per_xcd + slot % a.units_per_xcd;
+        tile = slot / a.units_per_xcd;
+    }
+};
 
 template <int DH, int NB, int TT>
 __global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
 {
-    int unit;
-    int64_t tile;
-    if (lsa_pk_unit<DH, NB, TT>(a, &unit, &tile)) lsa_pk_tile<DH, NB, TT, false>(a, unit, tile * TT);
+    if ((int)blockIdx.x < a.lead_blocks) {
+        lsa_pk_lead<DH, NB, TT>(a);
+        return;
+    }
+    const LsaPkPlace at(a);
+    if (at.unit >= a.units) return;              // the whole workgroup leaves before any barrier
+    lsa_pk_tile<DH, NB, TT, false>(a, at.unit, at.tile * TT);
 }
 // The first `wide_tiles` tiles take five tokens (160 rows), those behind them TT (where the line lies: launch_lsa_fused).  160
 // rows bring a weight tile to more of them (1.80 us per k tile against 1.61 for 128), and their parked tile fills the LDS
@@ -637,11 +647,14 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
 template <int DH, int TT>
 __global__ __launch_bounds__(512) void k_lsa_fused_pk_wide(LsaFusedArgs a)
 {
-    int unit;
-    int64_t tile;
-    if (!lsa_pk_unit<DH, 1, TT>(a, &unit, &tile)) return;
-    if (tile < a.wide_tiles) lsa_pk_tile<DH, 1, 5, false>(a, unit, tile * 5);
-    else lsa_pk_tile<DH, 1, TT, false>(a, unit, a.wide_tiles * 5 + (tile - a.wide_tiles) * TT);
+    if ((int)blockIdx.x < a.lead_blocks) {
+        lsa_pk_lead<DH, 1, TT>(a);
+        return;
+    }
+    const LsaPkPlace at(a);
+    if (at.unit >= a.units) return;
+    if (at.tile < a.wide_tiles) lsa_pk_tile<DH, 1, 5, false>(a, at.unit, at.tile * 5);
+    else lsa_pk_tile<DH, 1, TT, false>(a, at.unit, a.wide_tiles * 5 + (at.tile - a.wide_tiles) * TT);
 }
 // The same with the rows of TT tokens one behind another in 160 (five blocks of 32), for layer counts that leave much of
 // their last block empty: 80 layers in 96 rows waste a sixth of the matrix work, two tokens in 160 nothing, and a weight
@@ -652,9 +665,13 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk_wide(LsaFusedArgs a)
 template <int DH, int NB, int TT>
 __global__ __launch_bounds__(512) void k_lsa_fused_pk_dense(LsaFusedArgs a)
 {
-    int unit;
-    int64_t tile;
-    if (lsa_pk_unit<DH, NB, TT>(a, &unit, &tile)) lsa_pk_tile<DH, NB, TT, true>(a, unit, tile * TT);
+    if ((int)blockIdx.x < a.lead_blocks) {
+        lsa_pk_lead<DH, NB, TT>(a);
+        return;
+    }
+    const LsaPkPlace at(a);
+    if (at.unit >= a.units) return;
+    lsa_pk_tile<DH, NB, TT, true>(a, at.unit, at.tile * TT);
 }
 
 // Packs Wq / Wk / Wv for k_lsa_fused_pk: piece (unit, wavefront, k tile, k step, feature block, lane) holds the 8
