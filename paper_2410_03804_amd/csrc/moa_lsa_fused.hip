@@ -579,9 +579,8 @@ __device__ __forceinline__ void lsa_pk_tile(const LsaFusedArgs &a, int unit, int
 #pragma unroll
                     for (int j = 0; j < NRB; ++j)
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[S][ks * WFB + i], bfr[ks % NBUF][j], acc[i][j], 0, 0, 0);
-                // (64-row tiles: the refill strictly behind them, 35.1 -> 34.3 us at 60 tokens; with single-buffered fragments the
-                // compiler's mixture of MFMAs, fragment reads and requests is as good as any order tried)
-                if (NBUF == 2) __builtin_amdgcn_sched_barrier(0);
+                // (the compiler's mixture of MFMAs, fragment reads and requests is as good as any order tried; 64-row tiles with the
+                // refill strictly behind the MFMAs: 60 tokens of 32 layers 42.3 us either way, 40 tokens 35.7 -> 36.2, 20 32.1 -> 32.5)
                 if (NBUF == 1 && ks + 1 < BK / 16) read_frags(ks + 1, bfr[0]);
 #pragma unroll
                 for (int i = 0; i < WFB; ++i) wr[S][ks * WFB + i] = wnext[(ks * WFB + i) * 64];
