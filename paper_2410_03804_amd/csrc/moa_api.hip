@@ -270,7 +270,7 @@ static bool lsa_takes_fused(const moa_shape_t *shape, int64_t T, const void *hs,
     if (form == MOA_LSA_KERNEL_FUSED) return true;
     const int64_t L = shape->n_layers, padded = (L + 31) / 32 * 32;
     if (T * L <= 192) return false;
-    if (10 * padded > 11 * L && T * (shape->lsa_q_heads / 2) > 1024 && !(packed && L > 64 && L <= 80)) return false;
+    if (10 * padded > 11 * L && T * (shape->lsa_q_heads / 2) > 1024 && !(packed && lsa_dense_ok((int)L))) return false;
     return true;
 }
 

@@ -350,6 +350,8 @@ struct LsaFusedCall {
 bool lsa_fused_ok(int dtype, int L, int d_in, int Hq, int Hkv, int dh, const void *hs, const void *wq, const void *wk,
                   const void *wv, const void *abar);
 bool lsa_fused_shape_ok(int dtype, int L, int d_in, int Hq, int Hkv, int dh);
+// whether, from packed weights, two tokens of L layers may share a workgroup's 160 rows on the current device
+bool lsa_dense_ok(int L);
 hipError_t launch_lsa_fused(const LsaFusedCall &c, hipStream_t stream);
 // the weights of those shapes rearranged once into MFMA-operand order, for the form of the kernel that keeps them in registers
 size_t lsa_packed_weight_bytes(int d_in, int Hq, int Hkv, int dh);

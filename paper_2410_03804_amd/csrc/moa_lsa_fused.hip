@@ -31,6 +31,7 @@
 // Arithmetic is that of the three-kernel form (same MFMA order along d_in, Q/K/V rounded once to the storage type,
 // the same order of additions in the column sums), so all give the same bits.
 #include "moa_common.h"
+#include "moa_lsa_plan.h"
 #include "moa_tree_device.h"
 
 #include <math.h>
@@ -729,6 +730,12 @@ static size_t lds_limit()
     return limit[dev];
 }
 
+bool lsa_dense_ok(int L) { return lsa_dense_layers(L) && lds_limit() >= LSA_BIG_LDS; }
+static_assert(LsaFusedGeom<128, 1, 4>::bytes == LSA_BIG_LDS && LsaFusedGeom<128, 2, 2>::bytes == LSA_BIG_LDS &&
+                  LsaFusedGeom<128, 1, 5>::pk_bytes == LSA_BIG_LDS && LsaFusedGeom<128, 3, 2, true>::pk_bytes == LSA_BIG_LDS &&
+                  LsaFusedGeom<128, 1, 3>::bytes < LSA_BIG_LDS && LsaFusedGeom<128, 3, 1>::bytes < LSA_BIG_LDS,
+              "the forms the plan takes for those that fill the LDS");
+
 template <int NB, int TT, bool DENSE = false>
 static hipError_t launch_lsa_fused_as(LsaFusedArgs &fa, hipStream_t stream)
 {
@@ -827,54 +834,15 @@ hipError_t launch_lsa_fused(const LsaFusedCall &c, hipStream_t stream)
     if (c.rider_units > 0) fa.rider = c.rider;
     fa.lead_blocks = (c.rider_units + 7) & ~7;   // multiples of the XCD count: the unit mapping keeps its phase
     fa.pf_lead = c.w_packed ? 16 : 0;     // wanted; launch_lsa_fused_as decides when it knows the grid
-    // Rows per workgroup.  Measured at the Llama-3-8B shape (d_in 2048), a workgroup takes about 31 + 9 (rows / 32)
-    // microseconds from plain weights and 10 + 11.7 (rows / 32) from packed ones, whatever else runs (it is bound by
-    // its own chain of tile fetches from the L2 and its matrix work), and the chip runs 256 of them at a time: few
-    // tokens want small tiles (every compute unit busy), many tokens large ones (fewer passes over the weights).  Pick
-    // the tile that minimises rounds x time per round.
+    const LsaFusedPlan plan = lsa_fused_plan(fa.wpk != nullptr, c.T, c.L, c.d_in, fa.units, lds_limit());
+    fa.wide_tiles = plan.wide_tiles;
     const int nb = (c.L + 31) / 32;
-    const bool big_ok = lds_limit() >= LsaFusedGeom<128, 1, 4>::bytes;      // the 128-row tiles fill the LDS to the last byte
-    const double fixed = fa.wpk ? 10.0 : 31.0, per_block = fa.wpk ? 11.7 * fa.d_in / 2048 : 9.0;
-    auto cost = [&](int tt) {
-        const double wgs = (double)fa.units * (double)((c.T + tt - 1) / tt);
-        return ceil(wgs / 256.0) * (fixed + per_block * nb * tt);    // one workgroup per compute unit, all equally long: whole rounds
-    };
-    if (nb == 1) {
-        int best = 2;
-        if (cost(3) < cost(best)) best = 3;
-        if (big_ok && cost(4) < cost(best)) best = 4;
-        // Packed: whole rounds of 160-row tiles and what is left in smaller ones.  A row costs as much in 160 as in 128 (69 us a
-        // round against 55: the power limit), so this is about rounds that are nearly empty, and has to promise 4 % since a
-        // round with idle compute units also clocks higher (with the output projection, d_in 2048: 140 tokens 93 -> 78 us, 300
-        // 175 -> 153, 400 229 -> 199, 960 478 -> 448; 1024, where it promises 2 %, 472 -> 478).
-        const int64_t round = 32 / fa.units_per_xcd;       // tiles of one unit in a round of an XCD's 32 compute units
-        if (fa.wpk && big_ok && round > 0) {
-            auto us = [&](int64_t tokens, int tt) {
-                return (double)(((tokens + tt - 1) / tt * fa.units_per_xcd + 31) / 32) * (fixed + per_block * tt);
-            };
-            double least = 0.96 * us(fa.T, best);
-            const int64_t full = fa.T / (5 * round);
-            for (int64_t w = full > 3 ? full - 3 : 0; w <= full; ++w)
-                for (int tt = 2; tt <= 5; ++tt) {
-                    if (w == 0 && tt < 5) continue;
-                    const double t = (double)w * (fixed + per_block * 5) + us(fa.T - 5 * round * w, tt);
-                    if (t >= least) continue;
-                    least = t;
-                    best = tt < 5 ? tt : 4;
-                    fa.wide_tiles = tt < 5 ? round * w : (fa.T + 4) / 5;
-                }
-        }
-        if (best == 4) return launch_lsa_fused_as<1, 4>(fa, stream);
-        if (best == 3) return launch_lsa_fused_as<1, 3>(fa, stream);
-        return launch_lsa_fused_as<1, 2>(fa, stream);
-    }
-    if (nb == 2) {
-        if (big_ok && cost(2) < cost(1)) return launch_lsa_fused_as<2, 2>(fa, stream);
-        return launch_lsa_fused_as<2, 1>(fa, stream);
-    }
-    // two tokens in 160 rows take 68 us where one in 96 takes 45: as soon as that saves a round
-    const double dense = ceil((double)fa.units * (double)((c.T + 1) / 2) / 256.0) * (fixed + per_block * 5);
-    if (fa.wpk && c.L <= 80 && dense < cost(1)) return launch_lsa_fused_as<3, 2, true>(fa, stream);
+    if (nb == 1 && plan.tokens == 4) return launch_lsa_fused_as<1, 4>(fa, stream);
+    if (nb == 1 && plan.tokens == 3) return launch_lsa_fused_as<1, 3>(fa, stream);
+    if (nb == 1) return launch_lsa_fused_as<1, 2>(fa, stream);
+    if (nb == 2 && plan.tokens == 2) return launch_lsa_fused_as<2, 2>(fa, stream);
+    if (nb == 2) return launch_lsa_fused_as<2, 1>(fa, stream);
+    if (plan.dense) return launch_lsa_fused_as<3, 2, true>(fa, stream);
     return launch_lsa_fused_as<3, 1>(fa, stream);
 }
 
