@@ -25,11 +25,9 @@ inline LsaFusedPlan lsa_fused_plan(bool packed, int64_t T, int L, int d_in, int 
     const int nb = (L + 31) / 32, units_per_xcd = (units + 7) / 8;
     const bool big_ok = lds >= LSA_BIG_LDS;
     const double fixed = packed ? 10.0 : 31.0, per_block = packed ? 11.7 * d_in / 2048 : 9.0;
-    // one workgroup per compute unit, all equally long: whole rounds
-    auto us = [&](int64_t tokens, int tt, int blocks) {
-        return (double)(((int64_t)units * ((tokens + tt - 1) / tt) + 255) / 256) * (fixed + per_block * blocks);
-    };
-    auto us_xcd = [&](int64_t tokens, int tt, int blocks) {
+    // One workgroup per compute unit, all equally long: whole rounds, of the XCD that has the most units (each has 32
+    // compute units, and four units leave half of the XCDs idle).
+    auto us = [&](int64_t tokens, int tt, double blocks) {
         return (double)(((tokens + tt - 1) / tt * units_per_xcd + 31) / 32) * (fixed + per_block * blocks);
     };
     if (nb == 1) {
@@ -43,12 +41,12 @@ inline LsaFusedPlan lsa_fused_plan(bool packed, int64_t T, int L, int d_in, int 
         // 175 -> 153, 400 229 -> 199, 960 478 -> 448; 1024, where it promises 2 %, 472 -> 478).
         const int64_t round = 32 / units_per_xcd;          // tiles of one unit in a round of an XCD's 32 compute units
         if (!packed || !big_ok || round == 0) return plan;
-        double least = 0.96 * us_xcd(T, best, best);
+        double least = 0.96 * us(T, best, best);
         const int64_t full = T / (5 * round);
         for (int64_t w = full > 3 ? full - 3 : 0; w <= full; ++w)
             for (int tt = 2; tt <= 5; ++tt) {
                 if (w == 0 && tt < 5) continue;
-                const double t = (double)w * (fixed + per_block * 5) + us_xcd(T - 5 * round * w, tt, tt);
+                const double t = (double)w * (fixed + per_block * 5) + us(T - 5 * round * w, tt, tt);
                 if (t >= least) continue;
                 least = t;
                 plan = tt < 5 ? LsaFusedPlan{tt, false, round * w} : LsaFusedPlan{4, false, (T + 4) / 5};
@@ -56,8 +54,9 @@ inline LsaFusedPlan lsa_fused_plan(bool packed, int64_t T, int L, int d_in, int 
         return plan;
     }
     if (nb == 2) return {big_ok && us(T, 2, 4) < us(T, 1, 2) ? 2 : 1, false, 0};
-    // two tokens in 160 rows take 68 us where one in 96 takes 45: as soon as that saves a round
-    const bool dense = packed && big_ok && lsa_dense_layers(L) && us(T, 2, 5) < us(T, 1, 3);
+    // two tokens in 160 rows take 68 us a round where one in 96 takes 50, as much as 3.4 blocks: as soon as that saves a round
+    // (6 or 8 units: 78 tokens in two rounds 136 us with the output projection, in three 151)
+    const bool dense = packed && big_ok && lsa_dense_layers(L) && us(T, 2, 5) < us(T, 1, 3.4);
     return {dense ? 2 : 1, dense, 0};
 }
 

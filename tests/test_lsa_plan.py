@@ -56,3 +56,25 @@ def test_tiles_cover_the_tokens(plan):
         assert not (p.dense or p.wide_tiles) or packed
         assert 5 * (p.wide_tiles - 1) < T, "no tile behind the last token"
         assert not p.dense or 2 * L <= 160
+
+
+def test_rounds_are_those_of_the_xcd_with_the_most_units(plan):
+    """Units are dealt to eight XCDs of 32 compute units: 1 .. 8 units put one on some XCD, 9 .. 16 two, so a launch takes as
+    many rounds as one with the units filled up to eights, and the tile is the same."""
+    for packed, T, L, d_in, units in calls(6000, 3):
+        assert plan(packed, T, L, d_in, units) == plan(packed, T, L, d_in, (units + 7) // 8 * 8), (packed, T, L, d_in, units)
+
+
+@pytest.mark.parametrize("T,L,units,want", [
+    (32, 80, 8, Plan(1, False, 0)),         # one round of one token per workgroup
+    (33, 80, 8, Plan(2, True, 0)),          # two would be needed
+    (78, 80, 6, Plan(2, True, 0)),          # three rounds against two
+    (32, 80, 3, Plan(1, False, 0)),
+    (60, 32, 8, Plan(2, False, 0)),
+    (96, 32, 3, Plan(3, False, 0)),
+    (160, 32, 8, Plan(4, False, 32)),       # a round of five tokens per workgroup
+    (1024, 32, 8, Plan(4, False, 0)),       # eight whole rounds of four
+    (40, 64, 2, Plan(2, False, 0)),         # two rounds of 64 rows against one of 128
+])
+def test_packed_tiles_at_width_2048(plan, T, L, units, want):
+    assert plan(True, T, L, 2048, units) == want
