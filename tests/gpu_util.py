@@ -44,6 +44,17 @@ def status_word():
     return torch.zeros(1, dtype=torch.int32, device="cuda")
 
 
+def kernels_of(call):
+    """The names of the kernels that a call launches, as the library's profiler prints them; the call has finished."""
+    moa.profile_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+        return {kernel for _, kernel, _, _ in moa.profile_collect()}
+    finally:
+        moa.profile_enable(False)
+
+
 def mask_u64(mask_t):
     return mask_t.cpu().numpy().view(np.uint64)
 

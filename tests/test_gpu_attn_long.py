@@ -19,7 +19,7 @@ def G():
     return gpu_util
 
 
-@pytest.fixture(scope="module", params=["split_wide", "split"])
+@pytest.fixture(params=["split_wide", "split"])
 def moa(G, request):
     """256-row tiles, then the tiles that the estimate of the time picks (128 rows for most of these small calls)."""
     import paper_2410_03804_amd as m
@@ -87,13 +87,7 @@ def test_row_tile_height_follows_how_well_rows_fill_it(G, M, kernel):
     kc, x = torch.randn(B, 8, P, 128, device="cuda").bfloat16(), torch.randn(B, M, 4096, device="cuda").bfloat16()
     out, ln = torch.empty_like(x), torch.full((B,), P, dtype=torch.int32, device="cuda")
     ws = torch.empty(m.workspace_bytes(shape, B, P, M, 0), dtype=torch.uint8, device="cuda")
-    m.profile_enable(True)
-    try:
-        m.cross_attn_draft(shape, x, None, None, kc, kc, ln, P, out, ws, G.status_word())
-        torch.cuda.synchronize()
-        names = {k for _, k, _, _ in m.profile_collect()}
-    finally:
-        m.profile_enable(False)
+    names = G.kernels_of(lambda: m.cross_attn_draft(shape, x, None, None, kc, kc, ln, P, out, ws, G.status_word()))
     assert kernel in names, names
 
 
@@ -130,24 +124,24 @@ def test_wide_row_tiles_round_the_weights_no_worse(G, factor):
 
 
 @pytest.mark.parametrize("M,H,factor", [(33, 32, 1.0), (64, 32, 6.0)])
-def test_rounds_of_three_full_tiles_and_what_follows_them(G, moa, M, H, factor):
+def test_rounds_of_three_full_tiles_and_what_follows_them(G, moa, request, M, H, factor):
     """Slices of 2 .. 13 tiles of 64 keys, ending on, before and behind a tile: rounds of three unmasked tiles, their one to five
     masked followers and slices that have only those.  Against 64 bits; weights and result are rounded to bf16 (2^-9 each) and a
     slice's result to fp16, a largest element of 10^6 at six times that."""
     B, Hkv, P = 16, 8, 1600
     lens = [255, 256, 257, 383, 384, 447, 448, 511, 513, 640, 769, 896, 1023, 1280, 1537, 1600]
     g = torch.Generator(device="cuda").manual_seed(5)
-    import paper_2410_03804_amd as m
-    shape = m.Shape(2, H * 128, H, Hkv, 128, 256, 2, 1, m.BF16)
+    shape = moa.Shape(2, H * 128, H, Hkv, 128, 256, 2, 1, moa.BF16)
     q = (torch.randn(B, M, H * 128, generator=g, device="cuda") * factor).bfloat16()
     k, v = (torch.randn(B, Hkv, P, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
     for b, n in enumerate(lens):                                # rows past a sequence's length are never used
         k[b, :, n:], v[b, :, n:] = float("nan"), float("nan")
     print(f"[case] cross_attn_draft M={M} factor={factor}", flush=True)
     out = torch.empty_like(q)
-    ws = torch.empty(m.workspace_bytes(shape, B, P, M, 0), dtype=torch.uint8, device="cuda")
-    m.cross_attn_draft(shape, q, None, None, k, v, torch.tensor(lens, dtype=torch.int32, device="cuda"), P, out, ws, G.status_word())
-    torch.cuda.synchronize()
+    ws = torch.empty(moa.workspace_bytes(shape, B, P, M, 0), dtype=torch.uint8, device="cuda")
+    plen = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    names = G.kernels_of(lambda: moa.cross_attn_draft(shape, q, None, None, k, v, plen, P, out, ws, G.status_word()))
+    assert request.node.callspec.params["moa"] != "split_wide" or "k_attn_long<128>" in names, names
     for b, n in enumerate(lens):
         qb = q[b].view(M, Hkv, H // Hkv, 128).permute(1, 0, 2, 3).reshape(Hkv, -1, 128).double().cpu()
         got = out[b].view(M, Hkv, H // Hkv, 128).permute(1, 0, 2, 3).reshape(Hkv, -1, 128).double().cpu()

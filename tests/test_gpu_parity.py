@@ -217,11 +217,17 @@ def test_lsa_one_kernel_form_shapes(G, moa, oracle, L, d_in, Hkv, T):
     assert torch.equal(outs["fused"], out), "packing changes where a weight is read from, not the arithmetic"
 
 
-@pytest.mark.parametrize("L,d_in,Hkv,T", [(80, 512, 2, 301), (65, 320, 1, 602), (77, 768, 1, 515), (80, 512, 2, 130)])
-def test_lsa_rows_of_two_tokens_one_behind_another(G, moa, L, d_in, Hkv, T):
+DENSE, ONE = "k_lsa_fused_pk_dense<128, 3, 2>", "k_lsa_fused_pk<128, 3, 1>"
+
+
+@pytest.mark.parametrize("L,d_in,Hkv,T,kernel", [(80, 512, 2, 301, DENSE), (65, 320, 1, 602, DENSE), (77, 768, 1, 515, DENSE),
+                                                 (80, 512, 2, 130, DENSE), (80, 512, 2, 33, DENSE), (80, 512, 2, 32, ONE),
+                                                 (65, 320, 1, 31, ONE), (81, 512, 2, 130, ONE), (96, 320, 1, 33, ONE)])
+def test_lsa_rows_of_two_tokens_one_behind_another(G, moa, L, d_in, Hkv, T, kernel):
     """65 .. 80 layers from packed weights: two tokens share 160 rows without padding between them.  Odd token counts (the last
-    tile holds one), rows left over behind the second token, input widths of 5, 8 and 12 tiles of 64; 130 tokens keep the form
-    that has one token per workgroup.  The bits are those of the plain-weight form, which pads every token to 96 rows."""
+    tile holds one), rows left over behind the second token, input widths of 5, 8 and 12 tiles of 64; one round of tokens, and
+    more than 80 layers, keep the form that has one token per workgroup.  The bits are those of the plain-weight form, which pads
+    every token to 96 rows."""
     cfg = small_cfg("bf16", L=L, d_lsa_in=d_in, dh=128, Hkv=Hkv)
     if (cfg.lsa_heads // Hkv) % 2:
         cfg = small_cfg("bf16", L=L, d_lsa_in=256 * Hkv * (d_in // (256 * Hkv) or 1), dh=128, Hkv=Hkv)
@@ -238,17 +244,26 @@ def test_lsa_rows_of_two_tokens_one_behind_another(G, moa, L, d_in, Hkv, T):
     finally:
         moa.debug_force_lsa_kernel("auto")
     packed = moa.lsa_pack_weights(shape, *dw[:3])
-    moa.lsa_packed(shape, hs, packed, dw[3], out, ws)
-    torch.cuda.synchronize()
+    names = G.kernels_of(lambda: moa.lsa_packed(shape, hs, packed, dw[3], out, ws))
+    assert kernel in names, names
     assert torch.isfinite(want.float()).all() and torch.equal(out, want)
 
 
-@pytest.mark.parametrize("L,d_in,Hkv,T", [(32, 512, 2, 67), (32, 512, 2, 163), (32, 512, 2, 226), (32, 512, 2, 258), (21, 320, 1, 162),
-                                          (1, 512, 2, 160), (29, 1024, 4, 290), (32, 1024, 4, 701)])
-def test_lsa_five_tokens_per_workgroup(G, moa, L, d_in, Hkv, T):
-    """Up to 32 layers from packed weights: 160-row tiles alone (67, 160, 290 tokens: the last tile ragged, full, full) and in
-    front of tiles of two, three and four tokens (163, 162 | 226 | 258, 701; the last of them ragged too); padded rows; 5, 8 and 16
-    tiles of 64 along the width.  The bits are those of the plain-weight form, whose tiles have at most 128 rows."""
+def wide(tokens):
+    return f"k_lsa_fused_pk_wide<128, {tokens}>"
+
+
+@pytest.mark.parametrize("L,d_in,Hkv,T,kernel", [
+    (32, 512, 2, 67, "k_lsa_fused_pk<128, 1, 3>"), (32, 512, 2, 163, "k_lsa_fused_pk<128, 1, 3>"), (32, 512, 2, 226, "k_lsa_fused_pk<128, 1, 4>"),
+    (21, 320, 1, 162, "k_lsa_fused_pk<128, 1, 3>"), (32, 512, 2, 64, "k_lsa_fused_pk<128, 1, 2>"),
+    (32, 512, 2, 132, wide(4)), (1, 512, 2, 160, wide(4)), (29, 1024, 4, 290, wide(4)), (21, 320, 1, 131, wide(4)),
+    (32, 512, 2, 193, wide(2)), (30, 1024, 4, 224, wide(2)), (32, 512, 2, 321, wide(3)), (32, 1024, 4, 352, wide(3)),
+    (32, 512, 2, 258, wide(4)), (32, 1024, 4, 701, wide(4))])
+def test_lsa_five_tokens_per_workgroup(G, moa, L, d_in, Hkv, T, kernel):
+    """Up to 32 layers from packed weights: 160-row tiles alone (132, 160, 290, 131 tokens: the last tile ragged or full) and in
+    front of tiles of two, three and four tokens (193, 224 | 321, 352 | 258, 701; the last of them ragged or full); padded rows; 5, 8
+    and 16 tiles of 64 along the width; and the counts beside them that keep smaller tiles.  The bits are those of the plain-weight
+    form, whose tiles have at most 128 rows."""
     cfg = small_cfg("bf16", L=L, d_lsa_in=d_in, dh=128, Hkv=Hkv)
     print(f"[case] lsa wide L={L} d_in={d_in} heads={cfg.lsa_heads}/{Hkv} T={T}", flush=True)
     shape = G.shape_of(cfg)
@@ -260,10 +275,11 @@ def test_lsa_five_tokens_per_workgroup(G, moa, L, d_in, Hkv, T):
     moa.debug_force_lsa_kernel("fused")
     try:
         moa.lsa(shape, hs, *dw, want, ws)
-        moa.lsa_packed(shape, hs, moa.lsa_pack_weights(shape, *dw[:3]), dw[3], out, ws)
-        torch.cuda.synchronize()
+        packed = moa.lsa_pack_weights(shape, *dw[:3])
+        names = G.kernels_of(lambda: moa.lsa_packed(shape, hs, packed, dw[3], out, ws))
     finally:
         moa.debug_force_lsa_kernel("auto")
+    assert kernel in names, names
     assert torch.isfinite(want.float()).all() and torch.equal(out, want)
 
 
