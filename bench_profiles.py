@@ -169,9 +169,13 @@ def cmd_counters(a):
     merged = defaultdict(dict)
     launches = {}
     for db in a.db:
+        dur = kernel_durations(db)
         for k, cs in per_kernel_counters(db).items():
             if not ours(k) or k.startswith(SETUP_KERNELS):
                 continue
+            if "GRBM_GUI_ACTIVE" in cs and dur.get(k):           # (one GRBM instance per XCD)
+                merged[k]["launch, us"] = us = sum(dur[k]) / len(dur[k])
+                merged[k]["clock, GHz"] = cs["GRBM_GUI_ACTIVE"][1] / 8 / us / 1e3
             for c, (n, v) in cs.items():
                 merged[k][c] = v
                 launches[k] = n
@@ -179,7 +183,8 @@ def cmd_counters(a):
     lines = [f"# {a.title}", "", "Commands (one counter set per run, from the repository root on the MI355X box):", "", "```", a.cmd, "```", "",
              f"Library commit: `{head_commit()}`. Every figure is per launch: the counter summed over the chip's shader "
              "engines, then averaged over the launches of the run. SQ_WAVE_CYCLES, SQ_WAIT_* and SQ_ACTIVE_* count in units of "
-             "four clocks; SQ_BUSY_CU_CYCLES and SQ_VALU_MFMA_BUSY_CYCLES in clocks (a 32x32x16 bf16 MFMA holds its pipe for 32).", ""]
+             "four clocks; SQ_BUSY_CU_CYCLES and SQ_VALU_MFMA_BUSY_CYCLES in clocks (a 32x32x16 bf16 MFMA holds its pipe for 32); the "
+             "clock is GRBM_GUI_ACTIVE over the launch's time in the same run.", ""]
     for k in sorted(merged, key=lambda k: -merged[k].get("SQ_BUSY_CU_CYCLES", 0.0)):
         if only and k not in only:
             continue

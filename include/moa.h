@@ -341,7 +341,8 @@ int32_t moa_msg_gunzip(const void *gz_host, size_t n, void *out_host, size_t cap
 
 /* y = x w^T, the projection every layer of the path is made of, for the ones the path leaves to the
  * caller (the drafter's LM head when the logits themselves are wanted, Sec. 2.1 LM_head(o); an MLP).
- *   x [R, K], w [N, K] row-major -> y [R, N], all in `dtype`.  Workspace optional
+ *   x [R, K], w [N, K] row-major -> y [R, N], all in `dtype`.  Every row of w is summed in the same order: equal
+ *   rows give equal results, so that equal logits tie (moa_topk_logprob).  Workspace optional
  *   (moa_linear_workspace_bytes; without it short-and-wide shapes take a slower kernel). */
 int32_t moa_linear_workspace_bytes(int32_t dtype, int64_t R, int32_t K, int32_t N, size_t *bytes_host);
 int32_t moa_linear(int32_t dtype, const void *x, int64_t R, int32_t K, const void *w, int32_t N, void *y,

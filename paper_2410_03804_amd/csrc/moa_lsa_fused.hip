@@ -641,7 +641,7 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
     if (at.unit >= a.units) return;              // the whole workgroup leaves before any barrier
     lsa_pk_tile<DH, NB, TT, false>(a, at.unit, at.tile * TT);
 }
-// The first `wide_tiles` tiles take five tokens (160 rows), those behind them TT (where the line lies: launch_lsa_fused).  160
+// The first `wide_tiles` tiles take five tokens (160 rows), those behind them TT (where the line lies: lsa_fused_plan).  160
 // rows bring a weight tile to more of them (1.80 us per k tile against 1.61 for 128), and their parked tile fills the LDS
 // like a dense one's; ten (token, head) units on eight wavefronts cost the second pass.
 template <int DH, int TT>
