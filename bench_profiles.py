@@ -173,9 +173,12 @@ def cmd_counters(a):
         for k, cs in per_kernel_counters(db).items():
             if not ours(k) or k.startswith(SETUP_KERNELS):
                 continue
-            if "GRBM_GUI_ACTIVE" in cs and dur.get(k):           # (one GRBM instance per XCD)
+            if "GRBM_GUI_ACTIVE" in cs and dur.get(k):
                 merged[k]["launch, us"] = us = sum(dur[k]) / len(dur[k])
-                merged[k]["clock, GHz"] = cs["GRBM_GUI_ACTIVE"][1] / 8 / us / 1e3
+                # one GRBM instance per XCD, active for some 16000 clocks longer than the launch (what launches of 10 .. 25 us
+                # read beyond the nominal 2.4 GHz); too much to say anything of a short one
+                if us >= 50.0:
+                    merged[k]["clock, GHz"] = (cs["GRBM_GUI_ACTIVE"][1] / 8 - 16000.0) / us / 1e3
             for c, (n, v) in cs.items():
                 merged[k][c] = v
                 launches[k] = n
@@ -184,7 +187,7 @@ def cmd_counters(a):
              f"Library commit: `{head_commit()}`. Every figure is per launch: the counter summed over the chip's shader "
              "engines, then averaged over the launches of the run. SQ_WAVE_CYCLES, SQ_WAIT_* and SQ_ACTIVE_* count in units of "
              "four clocks; SQ_BUSY_CU_CYCLES and SQ_VALU_MFMA_BUSY_CYCLES in clocks (a 32x32x16 bf16 MFMA holds its pipe for 32); the "
-             "clock is GRBM_GUI_ACTIVE over the launch's time in the same run.", ""]
+             "clock is GRBM_GUI_ACTIVE per XCD, less the 16000 clocks that counting adds to a launch, over the launch's time in the same run.", ""]
     for k in sorted(merged, key=lambda k: -merged[k].get("SQ_BUSY_CU_CYCLES", 0.0)):
         if only and k not in only:
             continue

@@ -9,8 +9,8 @@
 // The operands of a phase were read from LDS one phase earlier, each into the place of one just used.
 // With one wavefront per SIMD every instruction costs its four clocks, one that needs the result of the instruction before it
 // eight, so what is not arithmetic was taken out of the loop and the rest put in an order (measured, 8 x 32768 keys x 128
-// nodes, both cores, clocks per 32 keys x 64 rows: 2480 before, 1850 now, of which 1230 issue, 215 wait for the matrix pipe, 110 at
-// the barrier):
+// nodes, both cores, clocks per 32 keys x 64 rows, by the wavefronts' counters: 2480 before, 1860 now, of which 1240 issue and
+// 210 wait for the matrix pipe):
 //   - three sets of scores change roles from phase to phase and the loop body is three tiles, so no score is moved;
 //   - the queries are pinned to the accumulation registers, which an MFMA reads directly (left alone the compiler keeps
 //     them there and copies four registers in front of each MFMA);
@@ -27,7 +27,7 @@
 // 64 bits, and would save 7 % of the time).  A rescale is 64 multiplications, so the accumulators are kept in vector
 // registers and the operands that come from LDS in the accumulation registers, the other way round than the compiler's
 // default (-amdgpu-mfma-vgpr-form for this file; in accumulation registers a rescale takes four times as long).
-// What bounds it is instruction issue beside the matrix pipe, and power: the clock falls to 1.8 GHz under it.  8 x 32768 keys
+// What bounds it is instruction issue beside the matrix pipe, at the 1.9 GHz that the clock falls to under it.  8 x 32768 keys
 // x 128 tree tokens, both cores, on one card: 1340 us with copies and everything in dependence order, 1150 now (0.96 PFLOP/s);
 // 128 rows per workgroup take 1464 where the former took 1352.
 #include "moa_attn_device.h"

@@ -660,8 +660,8 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk_wide(LsaFusedArgs a)
 // their last block empty: 80 layers in 96 rows waste a sixth of the matrix work, two tokens in 160 nothing, and a weight
 // tile serves 160 rows.  The accumulators take 160 registers, so one weight tile is in registers instead of two, and the parked tile
 // fills the LDS to the last byte.  240 tokens x 80 layers (d_in 2048): 286 us, where a token per workgroup takes 412 and
-// projection and attention as kernels of their own 305 + 60.  1.80 us per k tile at 160 rows and the 1.75 GHz the power limit
-// leaves (1.46 of them MFMA) and 17 us in front and behind, 6 of which were saved by giving a unit's query blocks to two wavefronts.
+// projection and attention as kernels of their own 305 + 60.  1.80 us per k tile at 160 rows, with the MFMA pipe busy for 63 % of
+// the SIMDs' time, and 17 us in front and behind, 6 of which were saved by giving a unit's query blocks to two wavefronts.
 template <int DH, int NB, int TT>
 __global__ __launch_bounds__(512) void k_lsa_fused_pk_dense(LsaFusedArgs a)
 {

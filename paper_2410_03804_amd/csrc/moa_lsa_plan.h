@@ -36,7 +36,7 @@ inline LsaFusedPlan lsa_fused_plan(bool packed, int64_t T, int L, int d_in, int 
         if (big_ok && us(T, 4, 4) < us(T, best, best)) best = 4;
         LsaFusedPlan plan = {best, false, 0};
         // Packed: whole rounds of 160-row tiles and what is left in smaller ones.  A row costs as much in 160 as in 128 (69 us a
-        // round against 55: the power limit), so this is about rounds that are nearly empty, and has to promise 4 % since a
+        // round against 55), so this is about rounds that are nearly empty, and has to promise 4 % since a
         // round with idle compute units also clocks higher (with the output projection, d_in 2048: 140 tokens 93 -> 78 us, 300
         // 175 -> 153, 400 229 -> 199, 960 478 -> 448; 1024, where it promises 2 %, 472 -> 478).
         const int64_t round = 32 / units_per_xcd;          // tiles of one unit in a round of an XCD's 32 compute units
