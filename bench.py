@@ -153,11 +153,11 @@ def site_costs(cfg, n_layers, schedule="grouped", lsa_tokens="tree", with_sa=Fal
     def add(*parts):
         return dict(bytes=sum(p["bytes"] for p in parts), flops=sum(p["flops"] for p in parts))
 
-    # grouped: the first verification layer is launched together with the cross-attention; two-stream: only its
-    # projections are (cores and output projections run on different streams)
-    paired = {"grouped": set(one), "two-stream": {"verify.qkv_proj"}}.get(schedule, set())
+    # the first verification layers, up to four, are launched together with the cross-attention
+    paired = set(one) if schedule in ("grouped", "two-stream") else set()
+    beside = min(n_layers, 4)
     for k, v in one.items():
-        alone = n_layers - 1 if k in paired else n_layers
+        alone = n_layers - beside if k in paired else n_layers
         c[k] = {kk: vv * alone for kk, vv in v.items()}
     # what one whole step must move once: LSA rows, every weight matrix, the two caches, inputs and outputs -- no
     # intermediate (projected queries, heads, partial sums) counts
@@ -174,9 +174,9 @@ def site_costs(cfg, n_layers, schedule="grouped", lsa_tokens="tree", with_sa=Fal
                          c["ca.o_proj"]["flops"] + n_layers * sum(v["flops"] for v in one.values()))
     if paired:
         c["tree_build+accept+lengths"] = add(c["tree_build"], c["tree_accept"], c["ca_append.lengths"])
-        c["ca.q_proj+verify.qkv_proj"] = add(c["ca.q_proj"], one["verify.qkv_proj"])
-        c["ca.core+verify.core"] = add(c["ca.core"], one["verify.core"])
-        c["ca.o_proj+verify.o_proj"] = add(c["ca.o_proj"], one["verify.o_proj"])
+        c["ca.q_proj+verify.qkv_proj"] = add(c["ca.q_proj"], *[one["verify.qkv_proj"]] * beside)
+        c["ca.core+verify.core"] = add(c["ca.core"], *[one["verify.core"]] * beside)
+        c["ca.o_proj+verify.o_proj"] = add(c["ca.o_proj"], *[one["verify.o_proj"]] * beside)
     return c
 
 

@@ -362,7 +362,10 @@ int32_t moa_fold_projection(int32_t dtype, const void *w_outer, const void *w_in
  *  MOA_SCHED_GROUPED (0, default): calls of the step that do not depend on each other and have the
  *    same shape share a launch: the CA query projection with the first verification layer's Q/K/V
  *    projection (the integer work -- tree masks, accept walk, memory lengths -- rides in the first
- *    workgroups of that grid); the two attention cores; the two output projections.
+ *    workgroups of that grid); the two attention cores; the two output projections.  Further verification
+ *    layers join them, up to four in a launch, where they read nothing that the launches before them
+ *    write and the workspace has room for their queries and heads; a layer whose input is another's
+ *    output, or that writes where others read or write, runs after them as before.
  *    Needs Mq == M, n_verify_layers >= 1, non-NULL CA and first-layer weights and the workspace
  *    moa_workspace_bytes asks for; otherwise the step runs as MOA_SCHED_SEQUENTIAL.  tok[], tgt[]
  *    and ca_len[] are read by the first launch of the step, so nothing in the step may produce them.
@@ -381,8 +384,9 @@ int32_t moa_fold_projection(int32_t dtype, const void *w_outer, const void *w_in
  *    per stage, exactly as the single entry points would.
  * Integer results are identical under all three; floating-point results of 0 and 1 are
  * bit-identical (without the Self-Attention layer), those of 2, and of 1 with that layer, differ from
- * them only where the two attention cores end up with a different number of key slices or row tiles of
- * another height (partials merged in another order). */
+ * them only where the attention cores end up with a different number of key slices or row tiles of
+ * another height (partials merged in another order); so may 0 and 1 themselves in workspaces that hold
+ * different numbers of verification layers side by side. */
 enum { MOA_SCHED_GROUPED = 0, MOA_SCHED_TWO_STREAM = 1, MOA_SCHED_SEQUENTIAL = 2 };
 
 typedef struct {

@@ -2,6 +2,7 @@
 // caller's stream.  No device allocation, no host synchronisation.
 #include "../../include/moa.h"
 #include "moa_common.h"
+#include "moa_step_mem.h"
 
 #include <stdarg.h>
 #include <stdio.h>
@@ -1221,7 +1222,11 @@ static int32_t draft_step_stages(const moa_step_args_t *a)
 // schedule.
 struct StepBufs {
     int32_t *old_len;              // memory lengths before this step's append
-    char *q_ca, *h_ca, *q_v, *h_v; // projected queries / concatenated heads of the CA and of verification layer 0
+    char *q_ca, *h_ca;             // projected queries / concatenated heads of the CA
+    int nv;                        // verification layers there are buffers for in common launches
+    char *q_v[STEP_VERIFY_GROUP], *h_v[STEP_VERIFY_GROUP];    // theirs
+    char *core_v[STEP_VERIFY_GROUP];                          // attention scratch of all but the first of them
+    int first;                     // verification layers that share launches with the CA's
 };
 
 static bool pieces_ok(const moa_step_args_t *a)
@@ -1259,11 +1264,11 @@ static int32_t piece_small(const moa_step_args_t *a, const StepBufs &bf, hipStre
     return MOA_OK;
 }
 
-// cross-attention queries + first verification layer's Q/K/V in one launch (which = 3), or the queries (1) or the
-// verification layer's three (2) alone
+// cross-attention queries + Q/K/V of the verification layers l0 .. l0 + n - 1 in one launch (which = 3), or the queries (1) or
+// the verification layers' (2) alone
 // with_small: the integer work rides in spare workgroups of this launch's grid instead of being a launch of its
 // own (nothing before the LSA chain's append and the attention cores needs its results).
-static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, hipStream_t st, bool with_small, int which = 3)
+static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, hipStream_t st, bool with_small, int which, int l0, int n)
 {
     const moa_shape_t *sh = a->shape;
     const int dh = sh->head_dim, Hkv = sh->n_kv_heads, d = sh->d_model, M = a->M;
@@ -1281,16 +1286,16 @@ static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, h
         q.X = a->ca_xq;
         q.ldx = d;
     }
-    if (which & 2) {
-        const void *w[3] = {a->v_wq_host[0], a->v_wk_host[0], a->v_wv_host[0]};
-        const StoreSpec st3[3] = {row_store(bf.q_v, e), heads_store(a->v_ktree_host[0], Hkv, dh, M, M),
-                                  heads_store(a->v_vtree_host[0], Hkv, dh, M, M)};
+    for (int l = l0; (which & 2) && l < l0 + n; ++l) {
+        const void *w[3] = {a->v_wq_host[l], a->v_wk_host[l], a->v_wv_host[l]};
+        const StoreSpec st3[3] = {row_store(bf.q_v[l - l0], e), heads_store(a->v_ktree_host[l], Hkv, dh, M, M),
+                                  heads_store(a->v_vtree_host[l], Hkv, dh, M, M)};
         for (int i = 0; i < 3; ++i) {
             LinSeg &g = la.seg[la.nseg++];
             g.W = w[i];
             g.N = i == 0 ? e : ekv;
             g.st = st3[i];
-            g.X = a->v_x_host[0];
+            g.X = a->v_x_host[l];
             g.ldx = d;
         }
     }
@@ -1397,7 +1402,7 @@ static int32_t piece_lsa_interleaved(const moa_step_args_t *a, const StepBufs &b
     const int64_t T = a->T_lsa;
     int32_t rc = lsa_check(sh, a->lsa_hs, T, a->lsa_wq, a->lsa_wk, a->lsa_wv, a->lsa_out, scr, scr_bytes);
     if (rc) return rc;
-    rc = piece_projections(a, bf, st, true);
+    rc = piece_projections(a, bf, st, true, 3, 0, bf.first);
     if (rc) return rc;
     const LsaBufs b = lsa_carve(sh, T, scr, scr_bytes);
     void *abar = a->lsa_wo ? (void *)b.abar0 : a->lsa_out;
@@ -1431,15 +1436,26 @@ static AttnArgs piece_ca_core_args(const moa_step_args_t *a, const StepBufs &bf,
                           nullptr, nullptr, a->dev_status, scr, scr_bytes);
 }
 
-static AttnArgs piece_verify_core_args(const moa_step_args_t *a, const StepBufs &bf, void *scr, size_t scr_bytes)
+// attention cores: the CA's (which & 1) and those of the verification layers l0 .. l0 + n - 1 (which & 2) as one group.  `scr`
+// holds two calls' scratch (attn_each each): the CA's and the first layer's.
+static int32_t piece_cores(const moa_step_args_t *a, const StepBufs &bf, int which, int l0, int n, char *scr, size_t attn_each, hipStream_t st)
 {
-    return attn_core_args(a->shape, bf.q_v, a->B, a->M, a->v_kcache_host[0], a->v_vcache_host[0], a->prefix_len,
-                          a->P_cap, a->mask, bf.h_v, a->v_ktree_host[0], a->v_vtree_host[0], a->dev_status, scr,
-                          scr_bytes);
+    AttnArgs calls[ATTN_CALLS];
+    int m = 0;
+    if (which & 1) calls[m++] = piece_ca_core_args(a, bf, scr, attn_each);
+    for (int i = 0; (which & 2) && i < n; ++i) {
+        const int l = l0 + i;
+        char *own = i > 0 ? bf.core_v[i] : scr + (which & 1 ? attn_each : 0);
+        calls[m++] = attn_core_args(a->shape, bf.q_v[i], a->B, a->M, a->v_kcache_host[l], a->v_vcache_host[l], a->prefix_len, a->P_cap, a->mask,
+                                    bf.h_v[i], a->v_ktree_host[l], a->v_vtree_host[l], a->dev_status, own, attn_each);
+    }
+    prof_set_site(which == 3 ? S_PAIR_CORE : which == 1 ? S_CA_CORE : S_VERIFY_CORE);
+    MOA_TRY_HIP(launch_attn_group(calls, m, st), "draft_step: attention cores");
+    return MOA_OK;
 }
 
-// output projections: which = 1 (cross-attention), 2 (verification layer 0) or 3 (both in one launch)
-static int32_t piece_oproj(const moa_step_args_t *a, const StepBufs &bf, int which, void *scr, size_t scr_bytes, hipStream_t st)
+// output projections: which = 1 (cross-attention), 2 (the verification layers l0 .. l0 + n - 1) or 3 (both in one launch)
+static int32_t piece_oproj(const moa_step_args_t *a, const StepBufs &bf, int which, int l0, int n, hipStream_t st)
 {
     const moa_shape_t *sh = a->shape;
     const int e = sh->n_q_heads * sh->head_dim;
@@ -1447,40 +1463,71 @@ static int32_t piece_oproj(const moa_step_args_t *a, const StepBufs &bf, int whi
     lo.R = (int64_t)a->B * a->M;
     lo.K = e;
     lo.ldx = e;
-    lo.ws = scr;
-    lo.ws_bytes = scr_bytes;
     lo.same_sums = LinArgs::SAME_SUMS_OUT;
     if (which & 1) lo.seg[lo.nseg++] = oproj_seg(sh, bf.h_ca, a->ca_wo, a->ca_out);
-    if (which & 2) lo.seg[lo.nseg++] = oproj_seg(sh, bf.h_v, a->v_wo_host[0], a->v_out_host[0]);
+    for (int l = l0; (which & 2) && l < l0 + n; ++l) lo.seg[lo.nseg++] = oproj_seg(sh, bf.h_v[l - l0], a->v_wo_host[l], a->v_out_host[l]);
     lo.X = lo.seg[0].X;
     prof_set_site(which == 3 ? S_PAIR_OPROJ : which == 1 ? S_CA_OPROJ : S_VERIFY_OPROJ);
     MOA_TRY_HIP(launch_linear(sh->dtype, lo, st), "draft_step: output projections");
     return MOA_OK;
 }
 
-static int32_t piece_more_verify_layers(const moa_step_args_t *a, void *scr, size_t scr_bytes, hipStream_t st)
+// the verification layers from l0 on, by runs that can share launches
+static int32_t piece_verify_layers(const moa_step_args_t *a, const StepBufs &bf, int l0, char *scr, size_t scr_bytes, size_t attn_each, hipStream_t st)
 {
-    for (int l = 1; l < a->n_verify_layers; ++l) {
-        int32_t rc = attention_layer("tree_verify_attn", a->shape, a->v_x_host[l], a->B, a->M, a->v_wq_host[l],
-                                     a->v_wk_host[l], a->v_wv_host[l], a->v_wo_host[l], a->v_kcache_host[l],
-                                     a->v_vcache_host[l], a->prefix_len, a->P_cap, a->mask, a->v_out_host[l],
-                                     a->v_ktree_host[l], a->v_vtree_host[l], a->dev_status, scr, scr_bytes, st);
+    for (int l = l0, n; l < a->n_verify_layers; l += n) {
+        n = verify_run(a, l, bf.nv, false);
+        int32_t rc;
+        if (n == 1) {
+            rc = attention_layer("tree_verify_attn", a->shape, a->v_x_host[l], a->B, a->M, a->v_wq_host[l],
+                                 a->v_wk_host[l], a->v_wv_host[l], a->v_wo_host[l], a->v_kcache_host[l],
+                                 a->v_vcache_host[l], a->prefix_len, a->P_cap, a->mask, a->v_out_host[l],
+                                 a->v_ktree_host[l], a->v_vtree_host[l], a->dev_status, scr, scr_bytes, st);
+        } else {
+            rc = piece_projections(a, bf, st, false, 2, l, n);
+            if (rc == MOA_OK) rc = piece_cores(a, bf, 2, l, n, scr, attn_each, st);
+            if (rc == MOA_OK) rc = piece_oproj(a, bf, 2, l, n, st);
+        }
         if (rc) return rc;
     }
     return MOA_OK;
 }
 
-static StepBufs carve_step_bufs(const moa_step_args_t *a, const GroupLayout &L, char **scr)
+// Further verification layers' buffers: queries and heads in `spare`, memory that the layout leaves, and where their cores'
+// partial results need any in `idle`, memory that is not in use while the cores run, and then in `spare` too.
+static StepBufs carve_step_bufs(const moa_step_args_t *a, const GroupLayout &L, char *spare, size_t spare_bytes, char *idle, size_t idle_bytes)
 {
     char *p = (char *)a->ws;
     StepBufs bf;
     bf.old_len = (int32_t *)p;
     bf.q_ca = p + L.len_bytes;
     bf.h_ca = bf.q_ca + L.qa;
-    bf.q_v = bf.h_ca + L.qa;
-    bf.h_v = bf.q_v + L.qa;
-    *scr = bf.h_v + L.qa;
+    bf.q_v[0] = bf.h_ca + L.qa;
+    bf.h_v[0] = bf.q_v[0] + L.qa;
+    bf.core_v[0] = nullptr;
+    const moa_shape_t *s = a->shape;
+    const size_t core = attn_takes_whole_range(s->dtype, a->B, a->M, a->M, s->n_q_heads, s->n_kv_heads, s->head_dim, a->P_cap) ? 0 : L.attn_each;
+    for (bf.nv = 1; bf.nv < STEP_VERIFY_GROUP && bf.nv < a->n_verify_layers; ++bf.nv) {
+        const bool in_idle = core <= idle_bytes;
+        const size_t take = 2 * L.qa + (in_idle ? 0 : core);
+        if (spare_bytes < take) break;
+        bf.q_v[bf.nv] = spare;
+        bf.h_v[bf.nv] = spare + L.qa;
+        bf.core_v[bf.nv] = in_idle ? idle : spare + 2 * L.qa;
+        if (in_idle) idle += core, idle_bytes -= core;
+        spare += take;
+        spare_bytes -= take;
+    }
+    bf.first = verify_run(a, 0, bf.nv, true);
     return bf;
+}
+
+// the layout of the schedules whose cores follow the LSA in the caller's stream: spare is what lies behind it, idle the scratch
+// behind the partial results of the cross-attention's and the first layer's core
+static StepBufs carve_step_bufs(const moa_step_args_t *a, const GroupLayout &L, char **scr)
+{
+    *scr = (char *)a->ws + L.total() - L.scratch;
+    return carve_step_bufs(a, L, (char *)a->ws + L.total(), a->ws_bytes - L.total(), *scr + 2 * L.attn_each, L.scratch - 2 * L.attn_each);
 }
 
 static bool can_group(const moa_step_args_t *a)
@@ -1501,18 +1548,16 @@ static int32_t draft_step_grouped(const moa_step_args_t *a)
         rc = piece_lsa_interleaved(a, bf, scr, L.scratch, st);
         if (rc) return rc;
     } else {
-        rc = piece_projections(a, bf, st, true);
+        rc = piece_projections(a, bf, st, true, 3, 0, bf.first);
         if (rc) return rc;
         rc = piece_lsa_append(a, bf, scr, L.scratch, st);
         if (rc) return rc;
     }
-    const AttnArgs ca = piece_ca_core_args(a, bf, scr, L.attn_each);
-    const AttnArgs ve = piece_verify_core_args(a, bf, scr + L.attn_each, L.attn_each);
-    prof_set_site(S_PAIR_CORE);
-    MOA_TRY_HIP(launch_attn_pair(ca, ve, st), "draft_step: attention cores");
-    rc = piece_oproj(a, bf, 3, scr, L.scratch, st);
+    rc = piece_cores(a, bf, 3, 0, bf.first, scr, L.attn_each, st);
     if (rc) return rc;
-    return piece_more_verify_layers(a, scr, L.scratch, st);
+    rc = piece_oproj(a, bf, 3, 0, bf.first, st);
+    if (rc) return rc;
+    return piece_verify_layers(a, bf, bf.first, scr, L.scratch, L.attn_each, st);
 }
 
 // ---- the same pieces on two streams.
@@ -1608,13 +1653,11 @@ static int32_t two_stream_main(const moa_step_args_t *a, const StepBufs &bf, cha
         rc = piece_lsa_append(a, bf, scr, scr_bytes, main);
         if (rc) return rc;
     }
-    const AttnArgs ca = piece_ca_core_args(a, bf, scr, attn_each);
-    const AttnArgs ve = piece_verify_core_args(a, bf, scr + attn_each, attn_each);
-    prof_set_site(S_PAIR_CORE);
-    MOA_TRY_HIP(launch_attn_pair(ca, ve, main), "draft_step: attention cores");
-    rc = piece_oproj(a, bf, 3, scr, scr_bytes, main);
+    rc = piece_cores(a, bf, 3, 0, bf.first, scr, attn_each, main);
     if (rc) return rc;
-    return piece_more_verify_layers(a, scr, scr_bytes, main);
+    rc = piece_oproj(a, bf, 3, 0, bf.first, main);
+    if (rc) return rc;
+    return piece_verify_layers(a, bf, bf.first, scr, scr_bytes, attn_each, main);
 }
 
 static int32_t draft_step_concurrent(const moa_step_args_t *a, SideStream *ss)
@@ -1631,7 +1674,7 @@ static int32_t draft_step_concurrent(const moa_step_args_t *a, SideStream *ss)
     // left with an unjoined branch): the main branch waits for the join event on its way; when either branch fails,
     // the wait is enqueued here (a second wait for the same event is harmless).
     const bool fused = two_stream_lsa_fused(a);
-    int32_t rc = piece_projections(a, bf, side, !fused);
+    int32_t rc = piece_projections(a, bf, side, !fused, 3, 0, bf.first);
     const hipError_t ej = hipEventRecord(ss->join, side);
     if (rc == MOA_OK && ej != hipSuccess) rc = hip_fail(ej, "draft_step: join");
     if (rc == MOA_OK) {
@@ -1701,14 +1744,13 @@ static int32_t two_stream_sa_side_memory(const moa_step_args_t *a, const StepBuf
 static int32_t two_stream_sa_side_verify(const moa_step_args_t *a, const StepBufs &bf, char *scr, size_t scr_bytes,
                                          size_t attn_each, hipStream_t side)
 {
-    int32_t rc = piece_projections(a, bf, side, false, 2);
+    int32_t rc = piece_projections(a, bf, side, false, 2, 0, bf.first);
     if (rc) return rc;
-    const AttnArgs ve = piece_verify_core_args(a, bf, scr, attn_each);
-    prof_set_site(S_VERIFY_CORE);
-    MOA_TRY_HIP(launch_attn(ve, side), "draft_step: verification core");
-    rc = piece_oproj(a, bf, 2, scr, scr_bytes, side);
+    rc = piece_cores(a, bf, 2, 0, bf.first, scr, attn_each, side);
     if (rc) return rc;
-    return piece_more_verify_layers(a, scr, scr_bytes, side);
+    rc = piece_oproj(a, bf, 2, 0, bf.first, side);
+    if (rc) return rc;
+    return piece_verify_layers(a, bf, bf.first, scr, scr_bytes, attn_each, side);
 }
 
 // Enqueue order matters beyond the order inside each stream: the runtime settles where in the producing stream a
@@ -1720,9 +1762,10 @@ static int32_t draft_step_concurrent_sa(const moa_step_args_t *args, const moa_s
 {
     hipStream_t main = (hipStream_t)a->stream, side = ss->stream;
     const GroupLayout L = group_layout(a->shape, a->B, a->M, a->P_cap, a->ca_P_cap, a->T_lsa);
-    char *scr_main = nullptr;
-    const StepBufs bf = carve_step_bufs(a, L, &scr_main);
-    char *scr_side = scr_main + L.scratch;
+    // spare: the side branch's scratch behind its first core's partial results, where the verification layers come when the LSA
+    // is done with it, and what lies behind that
+    char *scr_main = (char *)a->ws + L.total() - L.scratch, *scr_side = scr_main + L.scratch;
+    const StepBufs bf = carve_step_bufs(a, L, scr_side + L.attn_each, a->ws_bytes - L.total() - L.attn_each, nullptr, 0);
     std::lock_guard<std::mutex> lk(ss->enqueue);
 
     int32_t rc = moa_tree_build(a->parent, a->B, a->M, a->mask, a->depth, a->dev_status, main);
@@ -1733,7 +1776,7 @@ static int32_t draft_step_concurrent_sa(const moa_step_args_t *args, const moa_s
     SaSideState st;
     rc = two_stream_sa_side_lsa(a, bf, scr_side, L.scratch, side, &st);
     if (rc == MOA_OK) rc = step_self_attn_layer(args, scr_main, L.scratch, main);
-    if (rc == MOA_OK) rc = piece_projections(a, bf, main, false, 1);
+    if (rc == MOA_OK) rc = piece_projections(a, bf, main, false, 1, 0, 0);
     if (rc == MOA_OK) rc = two_stream_sa_side_memory(a, bf, scr_side, L.scratch, side, &st);
     if (rc == MOA_OK) {
         hipError_t e = hipEventRecord(ss->mid, side);
@@ -1749,7 +1792,7 @@ static int32_t draft_step_concurrent_sa(const moa_step_args_t *args, const moa_s
     if (rc == MOA_OK) rc = two_stream_sa_side_verify(a, bf, scr_side, L.scratch, L.attn_each, side);
     const hipError_t ej = hipEventRecord(ss->join, side);
     if (rc == MOA_OK && ej != hipSuccess) rc = hip_fail(ej, "draft_step: join");
-    if (rc == MOA_OK) rc = piece_oproj(a, bf, 1, scr_main, L.scratch, main);
+    if (rc == MOA_OK) rc = piece_oproj(a, bf, 1, 0, 0, main);
     if (ej == hipSuccess) {
         const hipError_t e = hipStreamWaitEvent(main, ss->join, 0);
         if (rc == MOA_OK && e != hipSuccess) rc = hip_fail(e, "draft_step: join");

@@ -833,7 +833,7 @@ static bool mfma_ok(int dtype, int dh, const AttnArgs *a)
 // 25 % faster than two blocks per wave at RG = 512 even though K/V are then read by twice as many row tiles
 constexpr int ATTN_NBLK = 1;
 
-// ncalls: 1, or 2 of this shape in one launch (the number of key slices of either form does not depend on it)
+// ncalls: how many of this shape in one launch (the number of key slices of either form does not depend on it)
 static SplitGeom split_geometry(int B, int Mq, int H, int Hkv, int dh, int P_cap, int ncalls)
 {
     const int RG = (H / Hkv) * Mq;
@@ -879,11 +879,18 @@ static SplitGeom split_geometry(int B, int Mq, int H, int Hkv, int dh, int P_cap
     return wide ? w : g;
 }
 
+// scratch of one of `ncalls` calls in a launch
+static size_t split_bytes(const SplitGeom &g, int B, int Hkv, int dh)
+{
+    const size_t rows = g.nsplit > 1 || !g.wide ? (size_t)B * Hkv * g.nsplit * g.rows_pad : 0;
+    return rows * ((size_t)dh * sizeof(f16_t) + 2 * sizeof(float)) + 256;
+}
+
 size_t attn_workspace_bytes(int dtype, int B, int Mq, int H, int Hkv, int dh, int P_cap, bool upto)
 {
     if (!mfma_ok(dtype, dh, nullptr)) return 0;
-    const size_t row_bytes = (size_t)dh * sizeof(f16_t) + 2 * sizeof(float);
     if (upto) {
+        const size_t row_bytes = (size_t)dh * sizeof(f16_t) + 2 * sizeof(float);
         // Neither fewer rows nor fewer sequences always need less (they leave room for more key slices), so this is a bound
         // that grows with every size.  `units` row tiles of 128 take at most max(units, min(512, units * most)) slices, and
         // the 256-row form never takes more rows than those.
@@ -894,12 +901,9 @@ size_t attn_workspace_bytes(int dtype, int B, int Mq, int H, int Hkv, int dh, in
         if (slices < units) slices = units;
         return (size_t)slices * 128 * ATTN_NBLK * row_bytes + 256;
     }
-    size_t rows = 0;
-    for (int ncalls : {1, 2}) {
-        const SplitGeom g = split_geometry(B, Mq, H, Hkv, dh, P_cap, ncalls);
-        if (g.nsplit > 1 || !g.wide) rows = std::max(rows, (size_t)B * Hkv * g.nsplit * g.rows_pad);
-    }
-    return rows * row_bytes + 256;
+    size_t bytes = 0;
+    for (int ncalls : {1, 2}) bytes = std::max(bytes, split_bytes(split_geometry(B, Mq, H, Hkv, dh, P_cap, ncalls), B, Hkv, dh));
+    return bytes;
 }
 
 static hipError_t launch_attn_generic(const AttnArgs &a, hipStream_t stream)
@@ -917,6 +921,15 @@ static bool attn_f32_ok(const AttnArgs &a)
     return a.dtype == DT_F32 && (a.dh == 64 || a.dh == 128) && al(a.q) && al(a.kcache) && al(a.ktree);
 }
 
+static AttnGroup group_of(const AttnArgs *calls, int n)
+{
+    AttnGroup grp;
+    for (int i = 0; i < ATTN_CALLS; ++i) grp.a[i] = calls[i < n ? i : n - 1];
+    grp.nbg = calls[0].B * calls[0].Hkv;
+    grp.ncalls = n;
+    return grp;
+}
+
 template <int DH>
 static hipError_t launch_f32_as(const AttnGroup &grp, int nrb, unsigned grid, hipStream_t stream)
 {
@@ -930,15 +943,11 @@ static hipError_t launch_f32_as(const AttnGroup &grp, int nrb, unsigned grid, hi
     return hipGetLastError();
 }
 
-// n = 1 or 2 calls of identical shape (B, Mq, H, Hkv, dh)
+// calls of identical shape (B, Mq, H, Hkv, dh)
 static hipError_t launch_attn_f32(const AttnArgs *calls, int n, hipStream_t stream)
 {
     const AttnArgs &a = calls[0];
-    AttnGroup grp;
-    grp.a[0] = calls[0];
-    grp.a[1] = calls[n - 1];
-    grp.nbg = a.B * a.Hkv;
-    grp.ncalls = n;
+    const AttnGroup grp = group_of(calls, n);
     const int nrb = ((a.H / a.Hkv) * a.Mq + 15) / 16;
     const int64_t grid = (int64_t)n * grp.nbg * nrb;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
@@ -959,16 +968,22 @@ static bool attn_split_ok(const AttnArgs &a, int P_cap_geo)
 // choice (the parity tests run every case through both forms).
 constexpr int FUSED_MAX_KEYS = 8192;
 constexpr int FUSED_MAX_WORKGROUPS = 256;
-static bool want_fused(const AttnArgs &a)
+static bool want_fused(int B, int Mq, int Mt, int H, int Hkv, int P_cap)
 {
     const int form = g_attn_form.load(std::memory_order_relaxed);
     if (form == MOA_ATTN_KERNEL_SPLIT || form == MOA_ATTN_KERNEL_SPLIT_WIDE) return false;
     if (form == MOA_ATTN_KERNEL_WHOLE) return true;
-    const int64_t wgs = (int64_t)a.B * a.Hkv * (((a.H / a.Hkv) * a.Mq + 31) / 32);
-    return a.P_cap + a.Mt <= FUSED_MAX_KEYS && wgs <= FUSED_MAX_WORKGROUPS;
+    const int64_t wgs = (int64_t)B * Hkv * (((H / Hkv) * Mq + 31) / 32);
+    return P_cap + Mt <= FUSED_MAX_KEYS && wgs <= FUSED_MAX_WORKGROUPS;
+}
+static bool want_fused(const AttnArgs &a) { return want_fused(a.B, a.Mq, a.Mt, a.H, a.Hkv, a.P_cap); }
+
+bool attn_takes_whole_range(int dtype, int B, int Mq, int Mt, int H, int Hkv, int dh, int P_cap)
+{
+    return dtype != DT_BF16 || (mfma_ok(dtype, dh, nullptr) && want_fused(B, Mq, Mt, H, Hkv, P_cap));
 }
 
-// n = 1 or 2 calls of identical shape (B, Mq, H, Hkv, dh)
+// calls of identical shape (B, Mq, H, Hkv, dh)
 template <int DH, int NW>
 static hipError_t launch_fused_as(const AttnGroup &grp, int nrb, unsigned grid, hipStream_t stream)
 {
@@ -985,11 +1000,7 @@ static hipError_t launch_fused_as(const AttnGroup &grp, int nrb, unsigned grid, 
 static hipError_t launch_attn_fused(const AttnArgs *calls, int n, hipStream_t stream)
 {
     const AttnArgs &a = calls[0];
-    AttnGroup grp;
-    grp.a[0] = calls[0];
-    grp.a[1] = calls[n - 1];
-    grp.nbg = a.B * a.Hkv;
-    grp.ncalls = n;
+    const AttnGroup grp = group_of(calls, n);
     const int nrb = ((a.H / a.Hkv) * a.Mq + 31) / 32;
     const int64_t units8 = ((int64_t)n * grp.nbg + 7) / 8;
     const int64_t grid = 8 * units8 * nrb;
@@ -1001,13 +1012,18 @@ static hipError_t launch_attn_fused(const AttnArgs *calls, int n, hipStream_t st
 static hipError_t launch_attn_split(const AttnArgs *calls, int n, hipStream_t stream)
 {
     const AttnArgs &a = calls[0];
-    const int cap = n == 2 && calls[1].P_cap > a.P_cap ? calls[1].P_cap : a.P_cap;
+    int cap = a.P_cap;
+    size_t room = a.ws_bytes;
+    for (int i = 1; i < n; ++i) {
+        cap = std::max(cap, calls[i].P_cap);
+        room = std::min(room, calls[i].ws_bytes);
+    }
     const SplitGeom g = split_geometry(a.B, a.Mq, a.H, a.Hkv, a.dh, cap, n);
-    AttnGroup grp;
-    grp.a[0] = calls[0];
-    grp.a[1] = calls[n - 1];
-    grp.nbg = a.B * a.Hkv;
-    grp.ncalls = n;
+    if (n > 2 && split_bytes(g, a.B, a.Hkv, a.dh) > room) {      // row tiles of another height than one or two calls take
+        hipError_t e = launch_attn_split(calls, 2, stream);
+        return e != hipSuccess ? e : launch_attn_split(calls + 2, n - 2, stream);
+    }
+    const AttnGroup grp = group_of(calls, n);
     const int nblocks = n * a.B * a.Mq * a.H;
     hipError_t e;
     if (g.wide) {
@@ -1049,22 +1065,44 @@ hipError_t launch_attn(const AttnArgs &a_in, hipStream_t stream)
     return launch_attn_generic(a, stream);
 }
 
-hipError_t launch_attn_pair(const AttnArgs &a0_in, const AttnArgs &a1_in, hipStream_t stream)
+hipError_t launch_attn_group(const AttnArgs *calls, int n, hipStream_t stream)
 {
-    AttnArgs a0 = a0_in, a1 = a1_in;
-    if (!tree_window(a0) || !tree_window(a1)) return hipErrorInvalidValue;
-    const int cap = a0.P_cap > a1.P_cap ? a0.P_cap : a1.P_cap;
-    const bool same = a0.dtype == a1.dtype && a0.B == a1.B && a0.Mq == a1.Mq && a0.H == a1.H && a0.Hkv == a1.Hkv && a0.dh == a1.dh;
-    const AttnArgs both[2] = {a0, a1};
-    if (same && mfma_ok(a0.dtype, a0.dh, &a0) && mfma_ok(a1.dtype, a1.dh, &a1)) {
-        if (want_fused(a0) && want_fused(a1)) return launch_attn_fused(both, 2, stream);
-        if (!want_fused(a0) && !want_fused(a1) && attn_split_ok(a0, cap) && attn_split_ok(a1, cap))
-            return launch_attn_split(both, 2, stream);
+    if (n < 1 || n > ATTN_CALLS) return hipErrorInvalidValue;
+    AttnArgs a[ATTN_CALLS];
+    int cap = 0;
+    bool same = true, mfma = true, f32 = true;
+    for (int i = 0; i < n; ++i) {
+        a[i] = calls[i];
+        if (!tree_window(a[i])) return hipErrorInvalidValue;
+        cap = std::max(cap, a[i].P_cap);
+        same = same && a[i].dtype == a[0].dtype && a[i].B == a[0].B && a[i].Mq == a[0].Mq && a[i].H == a[0].H && a[i].Hkv == a[0].Hkv && a[i].dh == a[0].dh;
+        mfma = mfma && mfma_ok(a[i].dtype, a[i].dh, &a[i]);
+        f32 = f32 && attn_f32_ok(a[i]);
     }
-    if (same && attn_f32_ok(a0) && attn_f32_ok(a1)) return launch_attn_f32(both, 2, stream);
-    hipError_t e = launch_attn(a0, stream);
-    if (e != hipSuccess) return e;
-    return launch_attn(a1, stream);
+    if (n > 1 && same && mfma) {
+        // those that run over the whole key range in one launch, those that split it in another
+        AttnArgs part[ATTN_CALLS];
+        int whole = 0, split = 0;
+        for (int i = 0; i < n; ++i)
+            if (want_fused(a[i])) part[whole++] = a[i];
+        bool ok = true;
+        for (int i = 0; i < n; ++i) {
+            if (want_fused(a[i])) continue;
+            ok = ok && attn_split_ok(a[i], cap);
+            part[whole + split++] = a[i];
+        }
+        if (ok) {
+            hipError_t e = whole ? launch_attn_fused(part, whole, stream) : hipSuccess;
+            if (e == hipSuccess && split) e = launch_attn_split(part + whole, split, stream);
+            return e;
+        }
+    }
+    if (n > 1 && same && f32) return launch_attn_f32(a, n, stream);
+    for (int i = 0; i < n; ++i) {
+        const hipError_t e = launch_attn(a[i], stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace moa

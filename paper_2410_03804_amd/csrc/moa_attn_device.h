@@ -25,11 +25,11 @@ struct SplitGeom {
 typedef _Float16 f16_t;
 typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
 
-// up to two independent calls of the same shape in one launch (blockIdx.z / nbg picks the call)
+// independent calls of the same shape in one launch (blockIdx.z / nbg picks the call)
 struct AttnGroup {
-    AttnArgs a[2];
+    AttnArgs a[ATTN_CALLS];
     int nbg;      // B * Hkv of one call
-    int ncalls;   // 1 or 2
+    int ncalls;
 };
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));

@@ -220,6 +220,12 @@ struct SumArgs {
 };
 hipError_t launch_splitk_sum(const SumArgs &s, hipStream_t stream);
 
+// Most verification layers whose projections, cores and output projections a step puts into common launches, and what one
+// launch has to hold for it: the cross-attention's queries and three matrices a layer; the cross-attention's core and one a layer.
+constexpr int STEP_VERIFY_GROUP = 4;
+constexpr int LIN_SEGS = 1 + 3 * STEP_VERIFY_GROUP;
+constexpr int ATTN_CALLS = 1 + STEP_VERIFY_GROUP;
+
 struct LinSeg {
     const void *W;  // [N, K] row-major
     int N;
@@ -234,7 +240,7 @@ struct LinArgs {
     int K;
     int64_t ldx;
     int nseg;
-    LinSeg seg[4];
+    LinSeg seg[LIN_SEGS];
     void *ws;          // optional scratch for the sums of K slices (linear_workspace_bytes); without it K is not cut
     size_t ws_bytes;
     StepSmallArgs rider;   // optional: integer work carried in rider_units spare workgroups of the projection's grid
@@ -270,7 +276,7 @@ struct LinArgs {
     int same_sums;
 };
 
-// Y_s = X_s W_s^T for up to four weight matrices (one launch on the fast paths; segments usually share X).
+// Y_s = X_s W_s^T for up to LIN_SEGS weight matrices (one launch on the fast paths; K is cut for up to four only).
 hipError_t launch_linear(int dtype, const LinArgs &a, hipStream_t stream);
 // the bf16 kernel behind launch_linear (moa_gemm_bf16.hip) and its name by profiling variant
 hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused, int *splits);
@@ -321,9 +327,11 @@ struct AttnArgs {
 // scratch for the partial results of a split key range; upto: at least what any call with sizes up to these asks for
 size_t attn_workspace_bytes(int dtype, int B, int Mq, int H, int Hkv, int dh, int P_cap, bool upto = false);
 hipError_t launch_attn(const AttnArgs &a, hipStream_t stream);
-// Two independent cores of the same shape (cross-attention and one verification layer) in one launch; P_cap may
-// differ, each call's ws must hold attn_workspace_bytes for the larger one.  Falls back to two launches.
-hipError_t launch_attn_pair(const AttnArgs &a0, const AttnArgs &a1, hipStream_t stream);
+// whether such a call (Mt tree rows as keys) runs over its whole key range in one launch and needs no scratch
+bool attn_takes_whole_range(int dtype, int B, int Mq, int Mt, int H, int Hkv, int dh, int P_cap);
+// Up to ATTN_CALLS independent cores of the same shape (cross-attention and verification layers) in as few launches as their
+// kernels allow; P_cap may differ, each call's ws must hold attn_workspace_bytes for the largest one.
+hipError_t launch_attn_group(const AttnArgs *calls, int n, hipStream_t stream);
 
 // ---- row-wise pieces of a reused decoder layer
 hipError_t launch_rmsnorm(int dtype, const void *x, const void *res, int64_t R, int d, const void *g, float eps,

@@ -23,7 +23,7 @@ namespace moa {
 
 struct GemmArgs {
     LinArgs a;
-    int tile_begin[5];   // first feature tile of each segment; [nseg] = all
+    int tile_begin[LIN_SEGS + 1];   // first feature tile of each segment; all of them from [nseg] on
     int tiles_per_xcd;   // feature tiles owned by one XCD
     int lead_blocks;     // workgroups in front of the projection's own (LinArgs::rider, padded to the XCD count)
     int row_tiles;
@@ -50,10 +50,11 @@ __global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(GemmArgs ga)
     // feature tiles for all row tiles, so that its slice of W is fetched into its L2 once.
     const int bx = (int)blockIdx.x - ga.lead_blocks, xcd = bx & 7, j = bx >> 3;
     const int ftile = xcd * ga.tiles_per_xcd + j % ga.tiles_per_xcd;
-    if (ftile >= ga.tile_begin[a.nseg]) return;
+    if (ftile >= ga.tile_begin[LIN_SEGS]) return;
     const int rest = j / ga.tiles_per_xcd, rt = rest % ga.row_tiles, split = rest / ga.row_tiles;
     int s = 0;
-    while (s + 1 < a.nseg && ftile >= ga.tile_begin[s + 1]) ++s;
+#pragma unroll
+    for (int q = 1; q < LIN_SEGS; ++q) s += ftile >= ga.tile_begin[q];
     const int n0 = (ftile - ga.tile_begin[s]) * (ga.gated ? BN / 2 : BN), N = a.seg[s].N, K = a.K;
     const int64_t r0 = (int64_t)rt * BM;
     const int64_t ldx = a.seg[s].X ? a.seg[s].ldx : a.ldx;
@@ -191,6 +192,7 @@ static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi,
         ntot += n_seg[s];
         if (n_seg[s] % 64) most_splits = 1;        // the pass over the sums takes features in 64s
     }
+    if (nseg > 4) most_splits = 1;                 // and four matrices
     if (in_order || same_sums || R > 192) most_splits = 1;
     else if (R > 64 && most_splits > 4) most_splits = 4;       // eight pay off where the sums are few (64 x 4096 x 1024: 9.7 against 10.5 us)
     float best_us = 3.4e38f;
@@ -259,7 +261,7 @@ size_t linear_workspace_bytes(int dtype, int64_t R, int K, std::initializer_list
 // One launch.  *fused: it applied a.epi; *splits > 1: the sums of that many K slices are in a.ws, to be added up.
 hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused, int *splits)
 {
-    int ntot = 0, n_seg[4] = {};
+    int ntot = 0, n_seg[LIN_SEGS] = {};
     for (int s = 0; s < a.nseg; ++s) {
         n_seg[s] = a.seg[s].N;
         ntot += a.seg[s].N;
@@ -283,7 +285,7 @@ hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused,
         if (!ga.gated) ft += (a.seg[s].N + t.bn - 1) / t.bn;
         else if (s == 0) ft = (2 * a.seg[0].N + t.bn - 1) / t.bn;
     }
-    for (int s = a.nseg; s < 5; ++s) ga.tile_begin[s] = ft;
+    for (int s = a.nseg; s <= LIN_SEGS; ++s) ga.tile_begin[s] = ft;
     ga.tiles_per_xcd = (ft + 7) / 8;
     ga.row_tiles = (int)((a.R + t.bm - 1) / t.bm);
     ga.lead_blocks = (a.rider_units + 7) & ~7;      // a multiple of the XCD count: the tile mapping keeps its phase

@@ -1,6 +1,6 @@
 // Projections Y = X W^T whose products are formed in single precision: fp32 tensors, and bf16 ones that the bf16 matrix
 // kernels do not take (a K or a feature count outside their tiles).  Both kernels run on the fp32 matrix instructions
-// (v_mfma_f32_*: fp32 products, fp32 sums), read their operands with vector loads, take up to four weight matrices per
+// (v_mfma_f32_*: fp32 products, fp32 sums), read their operands with vector loads, take several weight matrices per
 // launch, each with its own activations if it has any, and carry the step's integer work in workgroups of their own at
 // the front of the grid.
 //
@@ -19,9 +19,9 @@ namespace moa {
 
 struct F32Args {
     LinArgs a;
-    int tile_begin[5];   // first feature tile of each segment; [nseg] = all
+    int tile_begin[LIN_SEGS + 1];   // first feature tile of each segment; all of them from [nseg] on
     int lead_blocks;     // workgroups in front of the projection's own (LinArgs::rider)
-    int vec[4];          // the segment's outputs can be stored four features at a time
+    uint32_t vec;        // bit s: the segment's outputs can be stored four features at a time
 };
 
 __device__ __forceinline__ f32x4 ld4(const float *p) { return *(const f32x4 *)p; }
@@ -52,7 +52,8 @@ __device__ __forceinline__ bool f32_lead_block(const F32Args &fa, int32_t *lds)
 __device__ __forceinline__ int f32_segment(const F32Args &fa, int tile)
 {
     int s = 0;
-    while (s + 1 < fa.a.nseg && tile >= fa.tile_begin[s + 1]) ++s;
+#pragma unroll
+    for (int q = 1; q < LIN_SEGS; ++q) s += tile >= fa.tile_begin[q];
     return s;
 }
 
@@ -63,7 +64,7 @@ __global__ __launch_bounds__(256) void k_linear_f32_latency(F32Args fa)
     __shared__ float red[4][16][20];              // 20: rows of four-float stores land on different banks
     const LinArgs &a = fa.a;
     if (f32_lead_block(fa, (int32_t *)red)) return;
-    const int ntiles = fa.tile_begin[a.nseg];
+    const int ntiles = fa.tile_begin[LIN_SEGS];
     const int bx = (int)blockIdx.x - fa.lead_blocks, tile = bx % ntiles;
     const int64_t r0 = (int64_t)(bx / ntiles) * 16;
     const int s = f32_segment(fa, tile);
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(256) void k_linear_f32_tile(F32Args fa)
     __shared__ __attribute__((aligned(16))) float Xs[2][64 * LD];
     const LinArgs &a = fa.a;
     if (f32_lead_block(fa, (int32_t *)Ws)) return;
-    const int ntiles = fa.tile_begin[a.nseg];
+    const int ntiles = fa.tile_begin[LIN_SEGS];
     const int bx = (int)blockIdx.x - fa.lead_blocks, tile = bx % ntiles;
     const int64_t r0 = (int64_t)(bx / ntiles) * 64;
     const int s = f32_segment(fa, tile);
@@ -190,7 +191,7 @@ __global__ __launch_bounds__(256) void k_linear_f32_tile(F32Args fa)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int n = n0 + wf0 + 8 * q + 4 * half;
-        if (fa.vec[s] && n + 4 <= N) {
+        if ((fa.vec >> s & 1) && n + 4 <= N) {
             st4(dst + rp + store_feat_part(sp, n), f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]});
         } else {
 #pragma unroll
@@ -226,9 +227,10 @@ hipError_t launch_linear_f32(int dtype, const LinArgs &a, hipStream_t stream)
     fa.a = a;
     const size_t piece = dtype == DT_BF16 ? 8 : 16;
     int64_t t64 = 0, widest = 0;
+    fa.vec = 0;
     for (int s = 0; s < a.nseg; ++s) {
         const StoreSpec &st = a.seg[s].st;
-        fa.vec[s] = aligned_to(st.dst, piece) && (st.mode == StoreSpec::ROW ? st.ld % 4 == 0 : st.dh % 4 == 0);
+        fa.vec |= (uint32_t)(aligned_to(st.dst, piece) && (st.mode == StoreSpec::ROW ? st.ld % 4 == 0 : st.dh % 4 == 0)) << s;
         const int64_t n = (a.seg[s].N + 63) / 64;
         t64 += n;
         if (n > widest) widest = n;
@@ -238,7 +240,7 @@ hipError_t launch_linear_f32(int dtype, const LinArgs &a, hipStream_t stream)
     const int edge = big ? 64 : 16;
     int t = 0;
     for (int s = 0; s < a.nseg; ++s) { fa.tile_begin[s] = t; t += (a.seg[s].N + edge - 1) / edge; }
-    for (int s = a.nseg; s < 5; ++s) fa.tile_begin[s] = t;
+    for (int s = a.nseg; s <= LIN_SEGS; ++s) fa.tile_begin[s] = t;
     fa.lead_blocks = a.rider_units;
     const int64_t blocks = fa.lead_blocks + (int64_t)t * ((a.R + edge - 1) / edge);
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;

@@ -1,0 +1,121 @@
+"""Which verification layers of a step share launches (csrc/moa_step_mem.h: host arithmetic, compiled here with g++)."""
+import ctypes as C
+import random
+import subprocess
+from pathlib import Path
+
+import pytest
+
+CSRC = Path(__file__).resolve().parent.parent / "paper_2410_03804_amd" / "csrc"
+LAYER = ("x", "wq", "wk", "wv", "wo", "kcache", "vcache", "out", "ktree", "vtree")
+REST_READS = ("parent", "tok", "tgt", "tok_off", "prefix_len", "lsa_hs", "lsa_wq", "lsa_wk", "lsa_wv", "lsa_wo", "lsa_w_packed", "ca_wk", "ca_wv",
+              "ca_wk_lsa_wo", "ca_wv_lsa_wo", "ca_xq", "ca_wq", "ca_wo")
+REST_WRITES = ("mask", "depth", "path", "n_path", "bonus", "lsa_out", "ca_len", "ca_k", "ca_v", "ca_out", "dev_status")
+S = dict(L=4, d=256, H=4, Hkv=2, dh=64, din=128, Hl=2, Hkvl=2)          # bf16
+B, M, P, CP, T = 2, 19, 50, 60, 7
+
+
+def sizes():
+    es, e, ekv, eq, el = 2, S["H"] * S["dh"], S["Hkv"] * S["dh"], S["Hl"] * S["dh"], S["Hkvl"] * S["dh"]
+    d, din, R = S["d"], S["din"], B * M
+    n = dict(x=R * d * es, wq=e * d * es, wk=ekv * d * es, wv=ekv * d * es, wo=e * d * es, kcache=B * P * ekv * es, vcache=B * P * ekv * es,
+             out=R * d * es, ktree=R * ekv * es, vtree=R * ekv * es, parent=4 * R, tok=4 * R, tgt=4 * R, tok_off=4 * (B + 1), prefix_len=4 * B,
+             lsa_hs=T * S["L"] * din * es, lsa_wq=eq * din * es, lsa_wk=el * din * es, lsa_wv=el * din * es, lsa_wo=eq * eq * es,
+             lsa_w_packed=2 * eq * din * es, ca_wk=ekv * eq * es, ca_wv=ekv * eq * es, ca_wk_lsa_wo=ekv * eq * es, ca_wv_lsa_wo=ekv * eq * es,
+             ca_xq=R * d * es, ca_wq=e * d * es, ca_wo=e * d * es, mask=8 * R, depth=4 * R, path=4 * R, n_path=4 * B, bonus=4 * B,
+             lsa_out=T * eq * es, ca_len=4 * B, ca_k=B * CP * ekv * es, ca_v=B * CP * ekv * es, ca_out=R * d * es, dev_status=4)
+    return n
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    d = tmp_path_factory.mktemp("step_mem")
+    rest = REST_READS + REST_WRITES
+    arrays = {"x": "v_x_host", "wq": "v_wq_host", "wk": "v_wk_host", "wv": "v_wv_host", "wo": "v_wo_host", "kcache": "v_kcache_host",
+              "vcache": "v_vcache_host", "out": "v_out_host", "ktree": "v_ktree_host", "vtree": "v_vtree_host"}
+    src = '#include "moa_step_mem.h"\n' \
+          'extern "C" int run(char **rest, char ***layers, int n, int l0, int most, int with_rest)\n{\n' \
+          f'    moa_shape_t s = {{{S["L"]}, {S["d"]}, {S["H"]}, {S["Hkv"]}, {S["dh"]}, {S["din"]}, {S["Hl"]}, {S["Hkvl"]}, MOA_BF16}};\n' \
+          f'    moa_step_args_t a = {{}};\n    a.shape = &s; a.B = {B}; a.M = a.Mq = {M}; a.P_cap = {P}; a.ca_P_cap = {CP}; a.T_lsa = {T}; a.n_verify_layers = n;\n'
+    src += "".join(f"    a.{name} = (decltype(a.{name}))rest[{i}];\n" for i, name in enumerate(rest))
+    src += "".join(f"    a.{arrays[name]} = (decltype(a.{arrays[name]}))layers[{i}];\n" for i, name in enumerate(LAYER))
+    src += "    return moa::verify_run(&a, l0, most, with_rest);\n}\n"
+    (d / "run.cpp").write_text(src)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-Wno-unused-function", "-O1", "-shared", "-fPIC", f"-I{CSRC}", f"-I{d}", "-o",
+                    str(d / "run.so"), str(d / "run.cpp")], check=True)
+    f = C.CDLL(str(d / "run.so")).run
+
+    def call(rest_at, layers_at, l0, most, with_rest):
+        n = len(layers_at)
+        r = (C.c_void_p * len(rest))(*[rest_at[k] for k in rest])
+        cols = [(C.c_void_p * n)(*[la[k] for la in layers_at]) for k in LAYER]
+        table = (C.c_void_p * len(LAYER))(*[C.addressof(c) for c in cols])
+        return f(r, table, n, l0, most, int(with_rest))
+    return call
+
+
+def expected(rest_at, layers_at, l0, most, with_rest):
+    """From the definition: byte ranges of what is read and written, pairwise."""
+    n = sizes()
+    span = lambda at, keys: [(at[k], at[k] + n[k]) for k in keys if at[k]]
+    meet = lambda a, b: any(p < y and x < q for p, q in a for x, y in b)
+    reads = [span(la, LAYER[:7]) for la in layers_at]
+    writes = [span(la, LAYER[7:]) for la in layers_at]
+    rr, rw = span(rest_at, REST_READS), span(rest_at, REST_WRITES)
+    usable = lambda l: all(layers_at[l][k] for k in ("wq", "wk", "wv", "wo")) and all(layers_at[l][k] % 16 == 0 for k in LAYER)
+    most = min(most, len(layers_at) - l0)
+    if most <= 1 or not usable(l0) or (with_rest and any(rest_at[k] % 16 for k in ("ca_xq", "ca_wq", "ca_wo", "ca_k", "ca_v", "ca_out"))):
+        return 1
+    k = 1
+    while k < most:
+        l = l0 + k
+        if not usable(l) or (with_rest and (meet(writes[l], rr) or meet(writes[l], rw) or meet(reads[l], rw))):
+            break
+        if any(meet(writes[l], reads[i]) or meet(writes[i], reads[l]) or meet(writes[l], writes[i]) for i in range(l0, l)):
+            break
+        k += 1
+    return k
+
+
+def layout(rng, n_layers):
+    """Buffers one behind another, nothing shared."""
+    n, at = sizes(), 1 << 24
+    def place(k):
+        nonlocal at
+        p, at = at, at + (n[k] + 15) // 16 * 16
+        return p
+    rest = {k: place(k) for k in REST_READS + REST_WRITES}
+    return rest, [{k: place(k) for k in LAYER} for _ in range(n_layers)]
+
+
+def test_separate_buffers_share_up_to_what_there_is_room_for(run):
+    rest, layers = layout(random.Random(0), 6)
+    assert [run(rest, layers, 0, most, True) for most in (1, 2, 3, 4)] == [1, 2, 3, 4]
+    assert run(rest, layers, 4, 4, False) == 2 and run(rest, layers, 5, 4, False) == 1
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_any_overlap_ends_a_run(run, seed):
+    """One to three buffers moved onto (or to the edge of, or off the alignment beside) another: the rule and the definition agree."""
+    rng, n = random.Random(seed), sizes()
+    seen = set()
+    for _ in range(400):
+        layers_n = rng.randint(2, 6)
+        rest, layers = layout(rng, layers_n)
+        for _ in range(rng.randint(0, 3)):
+            dst, key = (rng.choice(layers), rng.choice(LAYER)) if rng.random() < 0.8 else (rest, rng.choice(REST_READS + REST_WRITES))
+            src, other = (rng.choice(layers), rng.choice(LAYER)) if rng.random() < 0.6 else (rest, rng.choice(REST_READS + REST_WRITES))
+            kind = rng.randrange(6)
+            if kind == 0: dst[key] = src[other]                                       # the same buffer
+            elif kind == 1: dst[key] = src[other] + n[other] - 16 if n[other] >= 16 else src[other]      # its last piece
+            elif kind == 2: dst[key] = src[other] - n[key] + 16                       # its first piece
+            elif kind == 3: dst[key] = src[other] - (n[key] + 15) // 16 * 16          # up to its edge
+            elif kind == 4: dst[key] += 8                                             # aligned to 8 only
+            elif key in ("wq", "wk", "wv", "wo") and dst is not rest: dst[key] = 0    # already projected
+        l0, most, with_rest = rng.randint(0, layers_n - 1), rng.randint(1, 4), rng.random() < 0.5
+        if with_rest:
+            l0 = 0
+        got, want = run(rest, layers, l0, most, with_rest), expected(rest, layers, l0, most, with_rest)
+        assert got == want, (rest, layers, l0, most, with_rest)
+        seen.add(want)
+    assert seen == {1, 2, 3, 4}
