@@ -7,7 +7,7 @@
 // features of one KV head's group that one attention needs: two query heads, the key head and the value head, 4 dh
 // features.  (A group of more than two query heads is cut into parts of two; each part recomputes K and V.)
 //
-//  projection  [RB x d_in] x [4 dh x d_in]^T on MFMA 32x32x16, walked along d_in in tiles of 64.  Wavefront w owns
+//  projection  [RB x d_in] x [4 dh x d_in]^T on MFMA 16x16x32, walked along d_in in tiles of 64.  Wavefront w owns
 //              the features w dh/2 .. and ALL rows, so its slice of the weight tile is its own: it fetches it itself
 //              (global memory straight into LDS, 128-byte rows, XOR-swizzled against bank conflicts) into a private
 //              two-stage ring and needs no barrier for it, only its own load counter.  As soon as a wavefront has
@@ -15,6 +15,10 @@
 //              another are in flight per compute unit while a tile is being multiplied.  The activation tile (RB rows,
 //              shared by all wavefronts, an eighth of the weight tile) goes through a small ring of its own with one
 //              barrier per tile.
+//              (16x16x32 instructions: they give the bits of 32x32x16 ones chained along d_in -- one takes the place of two --
+//              from the same operand bytes, and at the clock that the power budget leaves they make 2.03 PFLOP/s from
+//              registers against 1.78.  From packed weights 60 tokens of 32 layers 40.9 -> 38.1 us with the output projection,
+//              480 213 -> 194, 1024 443 -> 411, 240 of 80 layers 288 -> 262; from plain ones 1024 tokens 528 -> 475.)
 //              Three things cost about the same per tile -- the weight tile's way from the L2 into LDS (64 KB per
 //              64 of d_in, all workgroups of an XCD asking for the same lines at once), the operand reads from LDS
 //              and the matrix work -- and they overlap only in part; the lever that is left is rows per workgroup
@@ -81,23 +85,22 @@ struct LsaFusedGeom {
     static constexpr size_t bytes = loop_bytes > epi_bytes ? loop_bytes : epi_bytes;
     // the form that takes packed weights keeps them in registers: only a two-stage activation ring is left in LDS
     // weight tiles held in registers per wavefront: with the requests spread between the MFMAs two do as well as four; beside
-    // the accumulators of 160 rows there is room for one, and three quarters of a tile's MFMAs hide a request
-    static constexpr int WS = FULL ? 1 : 2;
+    // the accumulators of 128 rows and more there is room for one, and half of a tile's MFMAs hide a request (1024 tokens 411 us;
+    // with two, twelve registers spilled, 443)
+    static constexpr int WS = RB >= 128 ? 1 : 2;
     static constexpr int UN = 8;                 // tile steps per trip of the tile loop (a multiple of WS)
     static constexpr size_t pk_loop_bytes = (size_t)2 * RB * BK * sizeof(bf16_t);
     static constexpr size_t pk_bytes = pk_loop_bytes > epi_bytes ? pk_loop_bytes : epi_bytes;
 };
 
-// Second half of both kernels below: the accumulators of a workgroup's [RB x 4 dh] projection tile (acc[i][j][v]:
-// feature wave FW + 32 i + 8 (v / 4) + 4 half + v % 4, row 32 j + lane % 32) are rounded to the storage type and
-// parked in LDS, then one wavefront per (token of the tile, query head) runs the attention over the layer axis and the
+// Second half of both kernels below: the accumulators of a workgroup's [RB x 4 dh] projection tile are rounded to the
+// storage type and parked in LDS (`park` hands them over, four features of a row at a time), then one wavefront per (token of the tile, query head) runs the attention over the layer axis and the
 // mean.  Called by all 512 threads; `sm` is the workgroup's whole LDS, free to reuse after the barrier in here.
-template <int DH, int NB, int TT, bool DENSE, typename Acc>
-__device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs &a, bf16_t *sm, int64_t tok0, int g, int part)
+template <int DH, int NB, int TT, bool DENSE, typename Park>
+__device__ __forceinline__ void lsa_fused_epilogue(Park park, const LsaFusedArgs &a, bf16_t *sm, int64_t tok0, int g, int part)
 {
     using Gm = LsaFusedGeom<DH, NB, TT, DENSE>;
-    constexpr int FW = Gm::FW, RB = Gm::RB, TLD = Gm::TLD;
-    constexpr int WFB = FW / 32, NRB = RB / 32;
+    constexpr int TLD = Gm::TLD;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int G = a.Hq / a.Hkv, L = a.L;
 
@@ -107,21 +110,13 @@ __device__ __forceinline__ void lsa_fused_epilogue(Acc &acc, const LsaFusedArgs 
     auto at = [&](int row, int col) {            // column `col` of a row, and what follows it in its piece of eight
         return Gm::FULL ? tile_s + row * TLD + 8 * ((col >> 3) ^ (row & 15)) + (col & 7) : tile_s + row * TLD + col;
     };
-    // acc[i][j][v]: feature = f0 + 32 i + 8 (v / 4) + 4 half + v % 4, row = 32 j + l32
-    const int f0 = wave * FW;
-    {
-#pragma unroll
-        for (int i = 0; i < WFB; ++i)
-#pragma unroll
-            for (int j = 0; j < NRB; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    u32x2 pk;
-                    pk[0] = pack_bf16x2(acc[i][j][4 * q + 0], acc[i][j][4 * q + 1]);
-                    pk[1] = pack_bf16x2(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-                    *(u32x2 *)at(32 * j + l32, f0 + 32 * i + 8 * q + 4 * half) = pk;
-                }
-    }
+    // four features from `col` on of a row, rounded
+    park([&](int row, int col, float x0, float x1, float x2, float x3) {
+        u32x2 pk;
+        pk[0] = pack_bf16x2(x0, x1);
+        pk[1] = pack_bf16x2(x2, x3);
+        *(u32x2 *)at(row, col) = pk;
+    });
     __syncthreads();
 
     // attention over the layer axis: one wavefront per (token of the tile, query head); spare wavefronts redo a
@@ -272,8 +267,9 @@ __global__ __launch_bounds__(512) void k_lsa_fused(LsaFusedArgs a)
 {
     using Gm = LsaFusedGeom<DH, NB, TT>;
     constexpr int FW = Gm::FW, RB = Gm::RB, BK = Gm::BK, XS = Gm::XS;
-    constexpr int WFB = FW / 32;                 // 32-feature blocks per wavefront
-    constexpr int NRB = RB / 32;                 // 32-row blocks
+    constexpr int WFB = FW / 16;                 // 16-feature blocks per wavefront
+    constexpr int NRB = RB / 16;                 // 16-row blocks
+    constexpr int HRB = NRB / 2;                 // those of which a quarter of a tile takes the fragments
     constexpr int NWI = FW / 8;                  // weight-tile load instructions per wavefront (8 rows of 128 B each)
     constexpr int NXI = (RB / 8 + 7) / 8;        // activation-tile load instructions per wavefront
     constexpr int XD = XS - 1;                   // activation tiles requested ahead
@@ -294,16 +290,14 @@ __global__ __launch_bounds__(512) void k_lsa_fused(LsaFusedArgs a)
     const int g = unit / a.parts, part = unit - g * a.parts;
     const int G = a.Hq / a.Hkv, L = a.L, K = a.d_in;
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, quart = lane >> 4;
     const int lrow = lane >> 3, lpos = lane & 7;
 
-    f32x16 acc[WFB][NRB];
+    f32x4 acc[WFB][NRB];
 #pragma unroll
     for (int i = 0; i < WFB; ++i)
 #pragma unroll
-        for (int j = 0; j < NRB; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        for (int j = 0; j < NRB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int nk = K / BK;                       // >= 2 (checked on the host)
 
     // this wavefront's FW feature rows of the weight tile: inside one of Wq (two heads), Wk, Wv
@@ -361,27 +355,30 @@ __global__ __launch_bounds__(512) void k_lsa_fused(LsaFusedArgs a)
         else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
         const bf16_t *wb = wl + (kt & 1) * FW * BK;
         const bf16_t *xb = xl + (kt % XS) * RB * BK;
-        // The four k-steps of a tile are software-pipelined: the fragments of step ks+1 are requested from LDS before
-        // the MFMAs of step ks are issued, so LDS reads and matrix work of one wavefront overlap.  Once the last
-        // step's fragments have been read, the ring places this tile occupied are free and are refilled.
-        auto read_frags = [&](int ks, bf16x8 (&fa)[WFB], bf16x8 (&fb)[NRB]) {
+        // The quarters of a tile -- 32 columns (step p / 2) of one half of the rows -- are software-pipelined: the fragments of
+        // the next one are requested from LDS before the MFMAs of this one are issued, so LDS reads and matrix work of one
+        // wavefront overlap.  Once the last quarter's fragments have been read, the ring places this tile occupied are free and
+        // are refilled.
+        bf16x8 af[2][WFB], bfr[2][HRB];
+        auto read_frags = [&](int p) {
+            const int piece = 4 * (p >> 1) + quart;
 #pragma unroll
             for (int i = 0; i < WFB; ++i) {
-                const int row = 32 * i + l32;
-                fa[i] = *(const bf16x8 *)&wb[row * BK + 8 * ((2 * ks + half) ^ ((row >> 1) & 7))];
+                if (p & 1) continue;                 // both halves of the rows take the same weights
+                const int row = 16 * i + l16;
+                af[p >> 1][i] = *(const bf16x8 *)&wb[row * BK + 8 * (piece ^ ((row >> 1) & 7))];
             }
 #pragma unroll
-            for (int j = 0; j < NRB; ++j) {
-                const int row = 32 * j + l32;
-                fb[j] = *(const bf16x8 *)&xb[row * BK + 8 * ((2 * ks + half) ^ ((row >> 1) & 7))];
+            for (int j = 0; j < HRB; ++j) {
+                const int row = 16 * ((p & 1) * HRB + j) + l16;
+                bfr[p & 1][j] = *(const bf16x8 *)&xb[row * BK + 8 * (piece ^ ((row >> 1) & 7))];
             }
         };
-        bf16x8 af[2][WFB], bfr[2][NRB];
-        read_frags(0, af[0], bfr[0]);
+        read_frags(0);
 #pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            if (ks + 1 < BK / 16) read_frags(ks + 1, af[(ks + 1) & 1], bfr[(ks + 1) & 1]);
-            if (ks == BK / 16 - 1) {
+        for (int p = 0; p < 4; ++p) {
+            if (p < 3) read_frags(p + 1);
+            if (p == 3) {
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 if (kt + XD < nk) issue_x(kt + XD);
                 if (kt + 2 < nk) issue_w(kt + 2);
@@ -389,12 +386,21 @@ __global__ __launch_bounds__(512) void k_lsa_fused(LsaFusedArgs a)
 #pragma unroll
             for (int i = 0; i < WFB; ++i)
 #pragma unroll
-                for (int j = 0; j < NRB; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks & 1][i], bfr[ks & 1][j], acc[i][j], 0, 0, 0);
+                for (int j = 0; j < HRB; ++j) {
+                    f32x4 &c = acc[i][(p & 1) * HRB + j];
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[p >> 1][i], bfr[p & 1][j], c, 0, 0, 0);
+                }
         }
     }
 
-    lsa_fused_epilogue<DH, NB, TT, false>(acc, a, sm, tile * TT, g, part);
+    // acc[i][j][v]: feature wave FW + 16 i + 4 quart + v, row 16 j + l16
+    lsa_fused_epilogue<DH, NB, TT, false>([&](auto put) {
+#pragma unroll
+        for (int i = 0; i < WFB; ++i)
+#pragma unroll
+            for (int j = 0; j < NRB; ++j)
+                put(16 * j + l16, wave * FW + 16 * i + 4 * quart, acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+    }, a, sm, tile * TT, g, part);
 }
 
 // f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N - 1>{}): a loop whose index is a constant
@@ -461,29 +467,29 @@ __device__ __forceinline__ void lsa_pk_tile(const LsaFusedArgs &a, int unit, int
 {
     using Gm = LsaFusedGeom<DH, NB, TT, DENSE>;
     constexpr int FW = Gm::FW, RB = Gm::RB, BK = Gm::BK, WS = Gm::WS;
-    constexpr int WFB = FW / 32;                 // 32-feature blocks per wavefront
-    constexpr int NRB = RB / 32;                 // 32-row blocks
-    constexpr int NWP = 4 * WFB;                 // operand pieces per lane and weight tile
+    constexpr int WFB = FW / 16;                 // 16-feature blocks per wavefront
+    constexpr int NRB = RB / 16;                 // 16-row blocks
+    constexpr int HRB = NRB / 2;                 // those whose fragments are in registers at a time
+    constexpr int NWP = 2 * WFB;                 // operand pieces per lane and weight tile
     constexpr int NXI = (RB / 8 + 7) / 8;        // activation-tile load instructions per wavefront
     extern __shared__ __attribute__((aligned(16))) bf16_t sm[];
 
     const int g = unit / a.parts, part = unit - g * a.parts;
     const int L = a.L, K = a.d_in;
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, quart = lane >> 4;
     const int lrow = lane >> 3, lpos = lane & 7;
 
-    f32x16 acc[WFB][NRB];
+    f32x4 acc[WFB][NRB];
 #pragma unroll
     for (int i = 0; i < WFB; ++i)
 #pragma unroll
-        for (int j = 0; j < NRB; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        for (int j = 0; j < NRB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int nk = K / BK;
 
-    // packed weights: [unit][wavefront][k tile][k step][feature block][lane] pieces of 8 elements
-    const bf16x8 *wp = (const bf16x8 *)a.wpk + ((int64_t)(unit * 8 + wave) * nk) * (NWP * 64) + lane;
+    // packed weights: [unit][wavefront][k tile][k step of 16][block of 32 features][feature + 32 (k half)] pieces of 8 elements
+    const bf16x8 *wp = (const bf16x8 *)a.wpk + ((int64_t)(unit * 8 + wave) * nk) * (NWP * 64) + (quart >> 1) * 128 + (quart & 1) * 32 + l16;
+    auto wpiece = [](int b) { return b / WFB * 256 + (b % WFB >> 1) * 64 + (b & 1) * 16; };     // piece b: step b / WFB, block b % WFB
     // activation rows as in the unpacked form: instruction n covers tile rows xrow0[n] .. + 7, the piece a lane fetches
     // is the one whose swizzled place in LDS is the lane's own
     const bf16_t *xsrc[NXI];
@@ -509,7 +515,7 @@ __device__ __forceinline__ void lsa_pk_tile(const LsaFusedArgs &a, int unit, int
     bf16x8 xr[WS][NXI];
     auto load_w = [&](int kt, bf16x8 (&dst)[NWP]) {
 #pragma unroll
-        for (int b = 0; b < NWP; ++b) dst[b] = wp[((int64_t)kt * NWP + b) * 64];
+        for (int b = 0; b < NWP; ++b) dst[b] = wp[(int64_t)kt * NWP * 64 + wpiece(b)];
     };
     auto load_x = [&](int kt, bf16x8 (&dst)[NXI]) {
 #pragma unroll
@@ -544,47 +550,50 @@ __device__ __forceinline__ void lsa_pk_tile(const LsaFusedArgs &a, int unit, int
         load_x(kt + 1 < nk ? kt + 1 : nk - 1, xr[(S + 1) % WS]);
         const int kw = kt + WS < nk ? kt + WS : nk - 1;
         const bf16x8 *wnext = wp + (int64_t)kw * NWP * 64;
-        auto read_frags = [&](int ks, bf16x8 (&fb)[NRB]) {
+        // quarter p of a tile: 32 columns (step p / 2) of one half of the rows
+        auto read_frags = [&](int p, bf16x8 (&fb)[HRB]) {
 #pragma unroll
-            for (int j = 0; j < NRB; ++j) {
-                const int row = 32 * j + l32;
-                fb[j] = *(const bf16x8 *)&xb[row * BK + 8 * ((2 * ks + half) ^ ((row >> 1) & 7))];
+            for (int j = 0; j < HRB; ++j) {
+                const int row = 16 * ((p & 1) * HRB + j) + l16;
+                fb[j] = *(const bf16x8 *)&xb[row * BK + 8 * ((4 * (p >> 1) + quart) ^ ((row >> 1) & 7))];
             }
+        };
+        auto multiply = [&](int p, const bf16x8 (&fb)[HRB]) {
+#pragma unroll
+            for (int i = 0; i < WFB; ++i)
+#pragma unroll
+                for (int j = 0; j < HRB; ++j) {
+                    f32x4 &c = acc[i][(p & 1) * HRB + j];
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[S][(p >> 1) * WFB + i], fb[j], c, 0, 0, 0);
+                }
         };
         if constexpr (GUARDED) {
             if (kt < nk) {
-                bf16x8 bfr[2][NRB];
+                bf16x8 bfr[2][HRB];
                 read_frags(0, bfr[0]);
 #pragma unroll
-                for (int ks = 0; ks < BK / 16; ++ks) {
-                    if (ks + 1 < BK / 16) read_frags(ks + 1, bfr[(ks + 1) & 1]);
-#pragma unroll
-                    for (int i = 0; i < WFB; ++i)
-#pragma unroll
-                        for (int j = 0; j < NRB; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[S][ks * WFB + i], bfr[ks & 1][j], acc[i][j], 0, 0, 0);
+                for (int p = 0; p < 4; ++p) {
+                    if (p < 3) read_frags(p + 1, bfr[(p + 1) & 1]);
+                    multiply(p, bfr[p & 1]);
                 }
             }
             load_w(kw, wr[S]);
         } else {
-            // operand fragments of the next k-step are read ahead where the registers allow (64-row tiles)
-            constexpr int NBUF = NRB <= 2 ? 2 : 1;
-            bf16x8 bfr[NBUF][NRB];
+            // operand fragments of the next quarter are read ahead where the registers allow (64-row tiles)
+            constexpr int NBUF = HRB <= 2 ? 2 : 1;
+            bf16x8 bfr[NBUF][HRB];
             read_frags(0, bfr[0]);
 #pragma unroll
-            for (int ks = 0; ks < BK / 16; ++ks) {
-                if (NBUF == 2 && ks + 1 < BK / 16) read_frags(ks + 1, bfr[(ks + 1) & 1]);
+            for (int p = 0; p < 4; ++p) {
+                if (NBUF == 2 && p < 3) read_frags(p + 1, bfr[(p + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int i = 0; i < WFB; ++i)
-#pragma unroll
-                    for (int j = 0; j < NRB; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[S][ks * WFB + i], bfr[ks % NBUF][j], acc[i][j], 0, 0, 0);
+                multiply(p, bfr[p % NBUF]);
                 // (the compiler's mixture of MFMAs, fragment reads and requests is as good as any order tried; 64-row tiles with the
                 // refill strictly behind the MFMAs: 60 tokens of 32 layers 42.3 us either way, 40 tokens 35.7 -> 36.2, 20 32.1 -> 32.5)
-                if (NBUF == 1 && ks + 1 < BK / 16) read_frags(ks + 1, bfr[0]);
+                if (NBUF == 1 && p < 3) read_frags(p + 1, bfr[0]);
+                if (p & 1)
 #pragma unroll
-                for (int i = 0; i < WFB; ++i) wr[S][ks * WFB + i] = wnext[(ks * WFB + i) * 64];
+                    for (int i = 0; i < WFB; ++i) wr[S][(p >> 1) * WFB + i] = wnext[wpiece((p >> 1) * WFB + i)];
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -601,7 +610,14 @@ __device__ __forceinline__ void lsa_pk_tile(const LsaFusedArgs &a, int unit, int
 #pragma unroll 1
     for (int kt0 = nk_main; kt0 < nk_end; kt0 += WS)
         static_for<WS>([&](auto u) { tile_step(u, std::true_type{}, kt0 + decltype(u)::value); });
-    lsa_fused_epilogue<DH, NB, TT, DENSE>(acc, a, sm, tok0, g, part);
+    // acc[i][j][v]: feature wave FW + 16 i + 4 quart + v, row 16 j + l16
+    lsa_fused_epilogue<DH, NB, TT, DENSE>([&](auto put) {
+#pragma unroll
+        for (int i = 0; i < WFB; ++i)
+#pragma unroll
+            for (int j = 0; j < NRB; ++j)
+                put(16 * j + l16, wave * FW + 16 * i + 4 * quart, acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+    }, a, sm, tok0, g, part);
 }
 
 // The workgroups in front of the kernel's own do the step's integer work or read ahead (NB, TT: the tile that asks for it).
@@ -642,7 +658,7 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
     lsa_pk_tile<DH, NB, TT, false>(a, at.unit, at.tile * TT);
 }
 // The first `wide_tiles` tiles take five tokens (160 rows), those behind them TT (where the line lies: lsa_fused_plan).  160
-// rows bring a weight tile to more of them (1.80 us per k tile against 1.61 for 128), and their parked tile fills the LDS
+// rows bring a weight tile to more of them (62 us a round against 50 for 128), and their parked tile fills the LDS
 // like a dense one's; ten (token, head) units on eight wavefronts cost the second pass.
 template <int DH, int TT>
 __global__ __launch_bounds__(512) void k_lsa_fused_pk_wide(LsaFusedArgs a)
@@ -659,8 +675,8 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk_wide(LsaFusedArgs a)
 // The same with the rows of TT tokens one behind another in 160 (five blocks of 32), for layer counts that leave much of
 // their last block empty: 80 layers in 96 rows waste a sixth of the matrix work, two tokens in 160 nothing, and a weight
 // tile serves 160 rows.  The accumulators take 160 registers, so one weight tile is in registers instead of two, and the parked tile
-// fills the LDS to the last byte.  240 tokens x 80 layers (d_in 2048): 286 us, where a token per workgroup takes 412 and
-// projection and attention as kernels of their own 305 + 60.  1.80 us per k tile at 160 rows, with the MFMA pipe busy for 63 % of
+// fills the LDS to the last byte.  240 tokens x 80 layers (d_in 2048): 255 us; a token per workgroup takes 1.44 times as long,
+// projection and attention as kernels of their own 1.28 times.  1.6 us per k tile at 160 rows, with the MFMA pipe busy for 63 % of
 // the SIMDs' time, and 17 us in front and behind, 6 of which were saved by giving a unit's query blocks to two wavefronts.
 template <int DH, int NB, int TT>
 __global__ __launch_bounds__(512) void k_lsa_fused_pk_dense(LsaFusedArgs a)

@@ -16,7 +16,8 @@ constexpr size_t LSA_BIG_LDS = (size_t)160 * 512 * 2;
 inline bool lsa_dense_layers(int L) { return L > 64 && L <= 80; }
 
 // Rows per workgroup.  Measured at the Llama-3-8B shape (d_in 2048), a workgroup takes about 31 + 9 (rows / 32)
-// microseconds from plain weights and 10 + 11.7 (rows / 32) from packed ones, whatever else runs (it is bound by
+// microseconds from plain weights and 10 + 11.7 (rows / 32) from packed ones (or, in proportion, a twelfth less: the clock of
+// a full chip follows its power), whatever else runs (it is bound by
 // its own chain of tile fetches from the L2 and its matrix work), and the chip runs 256 of them at a time: few
 // tokens want small tiles (every compute unit busy), many tokens large ones (fewer passes over the weights).  Pick
 // the tile that minimises rounds x time per round.  units: workgroups per tile of tokens; lds: what a workgroup may ask for.
