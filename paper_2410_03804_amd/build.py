@@ -14,7 +14,8 @@ SOURCES = ["moa_api.hip", "moa_tree.hip", "moa_gemm.hip", "moa_gemm_f32.hip", "m
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 # results of matrix instructions in vector registers (said in the source why)
-SOURCE_FLAGS = {"moa_attn_long.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+SOURCE_FLAGS = {"moa_attn_long.hip": VGPR_FORM, "moa_gemm_bf16.hip": VGPR_FORM, "moa_lm_head.hip": VGPR_FORM}
 
 
 def _hipcc() -> str:

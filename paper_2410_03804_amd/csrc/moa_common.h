@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <initializer_list>
@@ -275,6 +276,68 @@ struct LinArgs {
     static int pair_rows(int same_sums, int K) { return same_sums == SAME_SUMS_IN ? 64 : 16384 / K * 64; }
     int same_sums;
 };
+
+// What a projection kernel is given of a launch.  A kernel begins with a chain of reads from here, and every 64 bytes that
+// none of its neighbours has read yet are a trip to memory: what decides where a workgroup belongs comes first and
+// together, then a line for each segment, and what is only needed at the end last.
+struct alignas(64) DevSeg {
+    const void *W, *X;
+    void *dst;
+    int64_t ldx, ld;
+    int N, mode, heads, cap, rows_per_seq;
+};
+struct LinDev {
+    int lead_blocks;                 // workgroups in front of the projection's own (LinArgs::rider)
+    int rider_units;
+    int tiles_per_xcd;               // feature tiles owned by one XCD
+    int row_tiles;
+    int splits;                      // slices of K; with more than one the sums go to `part` for a second pass
+    int gated;                       // EPI_SWIGLU inside the kernel: 32-feature blocks alternate between the two matrices
+    int K, nseg;
+    int64_t R;
+    int tile_begin[LIN_SEGS + 1];    // first feature tile of each segment; all of them from [nseg] on
+    uint32_t vec;                    // bit s: segment s's outputs can be stored four features at a time (single precision)
+    int epi;
+    int ntot;                        // features of all segments
+    int dh;                          // of the segments that go to heads
+    int append_B;                    // and of those that are appended to a memory (all to the same one)
+    DevSeg seg[LIN_SEGS];
+    const int32_t *append_base, *append_off;
+    int32_t *append_status;
+    float *part;                     // [64-row tiles][splits][64][ntot]
+    const float *epi_res;
+    void *epi_out;
+    StepSmallArgs rider;
+    explicit LinDev(const LinArgs &a)
+        : rider_units(a.rider_units), splits(1), gated(0), K(a.K), nseg(a.nseg), R(a.R), vec(0), epi(a.epi), ntot(0), dh(1), append_B(0),
+          append_base(nullptr), append_off(nullptr), append_status(nullptr), part(nullptr), epi_res(a.epi_res), epi_out(a.epi_out), rider(a.rider)
+    {
+        for (int s = 0; s < a.nseg; ++s) {
+            const LinSeg &g = a.seg[s];
+            seg[s] = {g.W, g.X ? g.X : a.X, g.st.dst, g.X ? g.ldx : a.ldx, g.st.ld, g.N, g.st.mode, g.st.heads, g.st.cap, g.st.rows_per_seq};
+            ntot += g.N;
+            if (g.st.mode != StoreSpec::ROW) dh = g.st.dh;
+            if (g.st.mode == StoreSpec::APPEND) {
+                append_B = g.st.B;
+                append_base = g.st.row_base;
+                append_off = g.st.tok_off;
+                append_status = g.st.dev_status;
+            }
+        }
+    }
+    __device__ __forceinline__ int segment(int tile) const
+    {
+        int s = 0;
+#pragma unroll
+        for (int q = 1; q < LIN_SEGS; ++q) s += tile >= tile_begin[q];
+        return s;
+    }
+    __device__ __forceinline__ StoreSpec store(int s) const
+    {
+        return {seg[s].mode, seg[s].dst, seg[s].ld, seg[s].heads, dh, seg[s].cap, seg[s].rows_per_seq, append_B, append_base, append_off, append_status};
+    }
+};
+static_assert(sizeof(DevSeg) == 64 && offsetof(LinDev, seg) == 128, "a line for a segment");
 
 // Y_s = X_s W_s^T for up to LIN_SEGS weight matrices (one launch on the fast paths; K is cut for up to four only).
 hipError_t launch_linear(int dtype, const LinArgs &a, hipStream_t stream);

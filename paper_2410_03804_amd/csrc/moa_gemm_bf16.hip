@@ -1,4 +1,4 @@
-// Projections Y = X W^T of bf16 tensors on the matrix cores (MFMA 32x32x16), for any number of rows: one kernel,
+// Projections Y = X W^T of bf16 tensors on the matrix cores (MFMA 16x16x32), for any number of rows: one kernel,
 // instantiated for the tiles that the path's row counts and widths ask for, and the rule that picks one.
 //
 // A workgroup owns a tile of rows x features and, as a rule, all of K: no partial sums, no second launch.  It walks K in
@@ -8,6 +8,11 @@
 // of the tile have been read, so that the first operands of the next one arrive behind the last quarter.  With WK > 1 the
 // wavefronts form groups that take every WK-th k tile each, with rings of their own, and add up through LDS at the end:
 // for few rows, where one group's chain of barrier, operand read and MFMA is longer than the memory needs.
+//
+// The matrix instruction is 16x16x32: the bits of two 32x32x16 ones chained along K from the same operand bytes, at 2.03 PFLOP/s
+// from registers where the power budget leaves the larger one 1.78 (2048 x 4096 x 28672: 434 -> 421 us, 1024 x 14336 x 4096 140 ->
+// 132), and a tile may have 16 rows: up to 16 rows a workgroup then brings half as many of the activations past its weights
+// (8 x 4096 x 4096: 10.6 -> 8.7 us, 8 x 8192 x 8192 29.2 -> 26.4).
 //
 // What bounds it: for few rows the weights (60 x 4096 x 8192: 17.9 us = 3.7 TB/s and no summing pass, where K slices with
 // fp32 partial sums took 21.0 + 4.0; 8 x 4096 x 128256: 162 us = 6.5 TB/s against 196 + 5), for many the way from L2 to
@@ -21,144 +26,128 @@
 
 namespace moa {
 
-struct GemmArgs {
-    LinArgs a;
-    int tile_begin[LIN_SEGS + 1];   // first feature tile of each segment; all of them from [nseg] on
-    int tiles_per_xcd;   // feature tiles owned by one XCD
-    int lead_blocks;     // workgroups in front of the projection's own (LinArgs::rider, padded to the XCD count)
-    int row_tiles;
-    int splits;          // slices of K; with more than one the sums go to `part` for a second pass
-    float *part;         // [64-row tiles][splits][64][ntot]
-    int ntot;            // features of all segments
-    int gated;           // EPI_SWIGLU inside the kernel: 32-feature blocks alternate between the two matrices
-};
-
 template <int WR, int WF, int MR, int NF, int SX, int SW, int WK>
-__global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(GemmArgs ga)
+__global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(LinDev a)
 {
     using Loop = GemmLoop<WR, WF, MR, NF, SX, SW, WK>;
     constexpr int BM = Loop::BM, BN = Loop::BN;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const LinArgs &a = ga.a;
     const int tid = threadIdx.x;
-    if ((int)blockIdx.x < ga.lead_blocks) {
+    if ((int)blockIdx.x < a.lead_blocks) {
         if ((int)blockIdx.x < a.rider_units && tid < 64)
             step_small_unit(a.rider, (int)blockIdx.x, (int32_t *)smem, (int32_t *)smem + MOA_MAX_TREE);
         return;
     }
     // Workgroups are dealt to the 8 XCDs round-robin, and each XCD has its own L2: an XCD gets a contiguous group of
     // feature tiles for all row tiles, so that its slice of W is fetched into its L2 once.
-    const int bx = (int)blockIdx.x - ga.lead_blocks, xcd = bx & 7, j = bx >> 3;
-    const int ftile = xcd * ga.tiles_per_xcd + j % ga.tiles_per_xcd;
-    if (ftile >= ga.tile_begin[LIN_SEGS]) return;
-    const int rest = j / ga.tiles_per_xcd, rt = rest % ga.row_tiles, split = rest / ga.row_tiles;
-    int s = 0;
-#pragma unroll
-    for (int q = 1; q < LIN_SEGS; ++q) s += ftile >= ga.tile_begin[q];
-    const int n0 = (ftile - ga.tile_begin[s]) * (ga.gated ? BN / 2 : BN), N = a.seg[s].N, K = a.K;
+    const int bx = (int)blockIdx.x - a.lead_blocks, xcd = bx & 7, j = bx >> 3;
+    const int ftile = xcd * a.tiles_per_xcd + j % a.tiles_per_xcd;
+    if (ftile >= a.tile_begin[LIN_SEGS]) return;
+    const int rest = j / a.tiles_per_xcd, rt = rest % a.row_tiles, split = rest / a.row_tiles;
+    const int s = a.segment(ftile);
+    const int n0 = (ftile - a.tile_begin[s]) * (a.gated ? BN / 2 : BN), N = a.seg[s].N, K = a.K;
     const int64_t r0 = (int64_t)rt * BM;
-    const int64_t ldx = a.seg[s].X ? a.seg[s].ldx : a.ldx;
-    const int nk = K / (Loop::BK * WK * ga.splits);
+    const int64_t ldx = a.seg[s].ldx;
+    const int nk = K / (Loop::BK * WK * a.splits);
     Loop g;
-    g.set_x((const char *)(a.seg[s].X ? a.seg[s].X : a.X) + r0 * ldx * 2, ldx, a.R - r0);
+    g.set_x((const char *)a.seg[s].X + r0 * ldx * 2, ldx, a.R - r0);
+    const char *const w0 = (const char *)a.seg[s].W + (int64_t)n0 * K * 2, *const w1 = a.gated ? (const char *)a.seg[1].W + (int64_t)n0 * K * 2 : w0;
     g.set_w(K, N - n0, [&](int blk, int *first) {
-        const int sel = ga.gated ? blk & 1 : s;
-        *first = 32 * (ga.gated ? blk >> 1 : blk);
-        return (const char *)a.seg[sel].W + (int64_t)n0 * K * 2;
+        *first = 32 * (a.gated ? blk >> 1 : blk);
+        return blk & 1 ? w1 : w0;
     });
     if (!g.run(smem, split * nk, nk)) return;
-    f32x16 (&acc)[NF][MR] = g.acc;
-    const int l32 = g.lane & 31, half = g.lane >> 5, wfi = g.wave % WF;
-
-    // acc[i][jj][v]: feature 32 i + 16 half + v of the wavefront's, row 32 jj + l32
+    const StoreSpec st = a.store(s);
+    const int l16 = g.lane & 15, quart = g.lane >> 4, wfi = g.wave % WF;
+    auto store8 = [](bf16_t *d, const float (&v)[8]) {
+        u32x4 pk;
 #pragma unroll
-    for (int jj = 0; jj < MR; ++jj) {
-        const int64_t r = r0 + g.wave_row() + 32 * jj + l32;
+        for (int e = 0; e < 4; ++e) pk[e] = pack_bf16x2(v[2 * e], v[2 * e + 1]);
+        *(u32x4 *)d = pk;
+    };
+
+    // values(i, v): features 32 i + 8 quart .. of the wavefront's, row 16 j + l16
+#pragma unroll
+    for (int j = 0; j < MR; ++j) {
+        const int64_t r = r0 + g.wave_row() + 16 * j + l16;
         if (r >= a.R) continue;
-        if (ga.splits > 1) {
-            float *p = ga.part + (((r >> 6) * ga.splits + split) * 64 + (r & 63)) * ga.ntot;
+        auto values = [&](int i, float (&v)[8]) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = g.acc[i][j][e >> 2][e & 3];
+        };
+        if (a.splits > 1) {
+            float *p = a.part + (((r >> 6) * a.splits + split) * 64 + (r & 63)) * a.ntot;
             int col = 0;
             for (int q = 0; q < s; ++q) col += a.seg[q].N;
 #pragma unroll
             for (int i = 0; i < NF; ++i) {
-                const int n = n0 + wfi * (32 * NF) + 32 * i + 16 * half;
+                const int n = n0 + wfi * (32 * NF) + 32 * i + 8 * quart;
                 if (n >= N) continue;
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *(f32x4 *)(p + col + n + 4 * q) = f32x4{acc[i][jj][4 * q], acc[i][jj][4 * q + 1], acc[i][jj][4 * q + 2], acc[i][jj][4 * q + 3]};
+                for (int q = 0; q < 2; ++q) *(f32x4 *)(p + col + n + 4 * q) = g.acc[i][j][q];
             }
             continue;
         }
-        auto store16 = [&](bf16_t *d, const float (&v)[16]) {
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                u32x4 pk;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) pk[e] = pack_bf16x2(v[8 * q + 2 * e], v[8 * q + 2 * e + 1]);
-                *(u32x4 *)(d + 8 * q) = pk;
-            }
-        };
-        if (NF % 2 == 0 && ga.gated) {             // silu(gate) * up, both through the storage type first
+        if (NF % 2 == 0 && a.gated) {             // silu(gate) * up, both through the storage type first
 #pragma unroll
             for (int i = 0; i + 1 < NF; i += 2) {
-                const int n = n0 + wfi * (16 * NF) + 16 * i + 16 * half;
+                const int n = n0 + wfi * (16 * NF) + 16 * i + 8 * quart;
                 if (n >= N) continue;
-                float v[16];
+                float v[8], u[8];
+                values(i, v);
+                values(i + (NF > 1), u);
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const float t = bf2f(f2bf(acc[i][jj][e]));
-                    v[e] = t / (1.0f + __expf(-t)) * bf2f(f2bf(acc[i + (NF > 1)][jj][e]));
+                for (int e = 0; e < 8; ++e) {
+                    const float t = bf2f(f2bf(v[e]));
+                    v[e] = t / (1.0f + __expf(-t)) * bf2f(f2bf(u[e]));
                 }
-                store16((bf16_t *)a.epi_out + r * N + n, v);
+                store8((bf16_t *)a.epi_out + r * N + n, v);
             }
             continue;
         }
-        const int64_t rp = store_row_part(a.seg[s].st, r);
+        const int64_t rp = store_row_part(st, r);
         if (rp < 0) continue;
 #pragma unroll
         for (int i = 0; i < NF; ++i) {
-            const int n = n0 + wfi * (32 * NF) + 32 * i + 16 * half;
+            const int n = n0 + wfi * (32 * NF) + 32 * i + 8 * quart;
             if (n >= N) continue;
-            float v[16];
-#pragma unroll
-            for (int e = 0; e < 16; ++e) v[e] = acc[i][jj][e];
+            float v[8];
+            values(i, v);
             if (a.epi == LinArgs::EPI_ADD_F32) {
                 const float *h = a.epi_res + r * N + n;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) v[e] = h[e] + bf2f(f2bf(v[e]));
-                store16((bf16_t *)a.epi_out + r * N + n, v);
-            } else {
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {       // eight features never straddle a head
-                    u32x4 pk;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) pk[e] = pack_bf16x2(v[8 * q + 2 * e], v[8 * q + 2 * e + 1]);
-                    *(u32x4 *)((bf16_t *)a.seg[s].st.dst + rp + store_feat_part(a.seg[s].st, n + 8 * q)) = pk;
-                }
+                for (int e = 0; e < 8; ++e) v[e] = h[e] + bf2f(f2bf(v[e]));
+                store8((bf16_t *)a.epi_out + r * N + n, v);
+            } else {                               // eight features never straddle a head
+                store8((bf16_t *)st.dst + rp + store_feat_part(st, n), v);
             }
         }
     }
 }
 
-// The instantiated tiles: wavefronts along rows and features, 32-wide blocks per wavefront along rows and features, stages
+// The instantiated tiles: wavefronts along rows and features, blocks of 16 rows and of 32 features per wavefront, stages
 // of the activation and the weight ring, K groups; then microseconds per k tile of the workgroup's (64 WK columns) with
 // one workgroup on a compute unit, with a second one on up to half of them, and with two on all (0: its LDS holds one),
 // measured over 1 .. 4096 rows, K 2048 .. 14336 and 4096 .. 128256 features.
-#define MOA_GEMM_TILES(T)                                     \
-    T(0, 1, 1, 1, 1, 5, 5, 2, 0.25f, 0.34f, 0.34f)            \
-    T(1, 1, 1, 1, 1, 2, 3, 4, 0.55f, 0.66f, 0.66f)            \
-    T(2, 1, 1, 1, 2, 3, 3, 2, 0.45f, 0.74f, 0.74f)            \
-    T(3, 2, 1, 1, 1, 3, 4, 2, 0.44f, 0.75f, 0.75f)            \
-    T(4, 2, 2, 1, 1, 4, 6, 1, 0.27f, 0.33f, 0.46f)            \
-    T(5, 2, 2, 1, 2, 3, 3, 2, 0.88f, 0.f, 0.f)                \
-    T(6, 4, 2, 1, 2, 4, 4, 1, 0.57f, 0.f, 0.f)                \
-    T(7, 4, 1, 1, 5, 4, 4, 1, 0.72f, 0.f, 0.f)                \
-    T(8, 4, 2, 2, 2, 3, 4, 1, 0.90f, 0.f, 0.f)                \
-    T(9, 8, 1, 1, 5, 3, 3, 1, 1.12f, 0.f, 0.f)                \
-    T(10, 4, 2, 2, 4, 2, 2, 1, 1.55f, 0.f, 0.f)               \
-    T(11, 4, 2, 1, 1, 3, 4, 2, 0.82f, 0.f, 0.f)               \
-    T(12, 4, 2, 2, 3, 2, 3, 1, 1.25f, 0.f, 0.f)               \
-    T(13, 2, 2, 1, 1, 4, 5, 2, 0.66f, 0.f, 0.f)
+#define MOA_GEMM_TILES(T)                           \
+    T(0, 2, 1, 1, 1, 5, 5, 2, 0.24f, 0.34f, 0.34f)  \
+    T(1, 1, 1, 2, 1, 2, 3, 4, 0.55f, 0.66f, 0.66f)  \
+    T(2, 2, 1, 1, 2, 3, 3, 2, 0.42f, 0.70f, 0.70f)  \
+    T(3, 2, 1, 2, 1, 3, 4, 2, 0.44f, 0.75f, 0.75f)  \
+    T(4, 2, 2, 2, 1, 4, 6, 1, 0.27f, 0.33f, 0.46f)  \
+    T(5, 2, 2, 2, 2, 3, 3, 2, 0.88f, 0.f, 0.f)      \
+    T(6, 4, 2, 2, 2, 4, 4, 1, 0.57f, 0.f, 0.f)      \
+    T(7, 4, 1, 2, 5, 4, 4, 1, 0.72f, 0.f, 0.f)      \
+    T(8, 4, 2, 4, 2, 3, 4, 1, 0.90f, 0.f, 0.f)      \
+    T(9, 8, 1, 2, 5, 3, 3, 1, 1.12f, 0.f, 0.f)      \
+    T(10, 4, 2, 4, 4, 2, 2, 1, 1.55f, 0.f, 0.f)     \
+    T(11, 4, 2, 2, 1, 3, 4, 2, 0.82f, 0.f, 0.f)     \
+    T(12, 4, 2, 4, 3, 2, 3, 1, 1.25f, 0.f, 0.f)     \
+    T(13, 2, 2, 2, 1, 4, 5, 2, 0.66f, 0.f, 0.f)     \
+    T(14, 1, 1, 1, 1, 5, 5, 2, 0.24f, 0.34f, 0.34f) \
+    T(15, 1, 1, 1, 1, 2, 3, 4, 0.60f, 0.60f, 0.60f) \
+    T(16, 1, 1, 1, 2, 3, 3, 2, 0.43f, 0.74f, 0.74f) \
+    T(17, 1, 1, 1, 1, 4, 4, 4, 0.46f, 0.f, 0.f)
 
 struct GemmTile {
     int bm, bn, threads, wk;
@@ -167,7 +156,7 @@ struct GemmTile {
     float us1, us_mid, us2;
 };
 #define MOA_GEMM_INFO(id, WR, WF, MR, NF, SX, SW, WK, US1, USM, US2)                                                            \
-    {32 * MR * WR, 32 * NF * WF, 64 * WR * WF * WK, WK, (size_t)(SX * 32 * MR * WR + SW * 32 * NF * WF) * 128 * WK, NF % 2 == 0, US1, USM, US2},
+    {16 * MR * WR, 32 * NF * WF, 64 * WR * WF * WK, WK, (size_t)(SX * 16 * MR * WR + SW * 32 * NF * WF) * 128 * WK, NF % 2 == 0, US1, USM, US2},
 static const GemmTile kTiles[] = {MOA_GEMM_TILES(MOA_GEMM_INFO)};
 
 struct GemmPlan { int tile, splits; };
@@ -176,8 +165,8 @@ struct GemmPlan { int tile, splits; };
 // the measured time per k tile, or the weights at 5.8 TB/s, whichever is longer; slices cost a pass over their sums.  An XCD
 // gets whole feature tiles, so a round is full when its share of them fills its 32 compute units (1600 x 8192 x 9216 in
 // 256 x 256: 252 workgroups, 35 of them on seven XCDs each, 355 us against 232 in 256 x 128).  Against the best tile of each
-// of 693 measured calls (33 shapes, weights from memory) the choice is 1.3 % slower on average.  What it comes to: up to 32
-// rows the 32-row tiles; up to some hundred the 64-row ones; with more, the largest tile that still gives every compute
+// of 693 measured calls (33 shapes, weights from memory) the choice is 1.3 % slower on average.  What it comes to: up to 16
+// rows the 16-row tiles, up to 32 the 32-row ones; up to some hundred the 64-row ones; with more, the largest tile that still gives every compute
 // unit one (1024 x 4096: 256 x 160 for 10240 features, 77.6 us against 98 - 108 with the tiles next to it, 256 x 128 for
 // 8192); slices only for a long K with few features (60 x 14336 x 4096: four, 30 us against 52).  A pass of its own behind
 // an unsplit projection counts against not splitting, since the sum over slices does that work on the way.
@@ -199,7 +188,7 @@ static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi,
     const float stream_us = 6.f + 2.f * (float)K * (float)ntot / 5.8e6f;
     for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
         const GemmTile &t = kTiles[i];
-        if (in_order ? t.wk > 1 : ((t.bm == 32) != (R <= 32) || K % (64 * t.wk) != 0 || (same_sums && t.wk != 2))) continue;
+        if (in_order ? t.wk > 1 : ((R <= 16 ? t.bm != 16 : R <= 32 ? t.bm != 32 : t.bm < 64) || K % (64 * t.wk) != 0 || (same_sums && t.wk != 2))) continue;
         const int64_t row_tiles = (R + t.bm - 1) / t.bm;
         int64_t tiles = 0;
         for (int s = 0; s < nseg; ++s) tiles += (n_seg[s] + t.bn - 1) / t.bn;
@@ -254,7 +243,7 @@ size_t linear_workspace_bytes(int dtype, int64_t R, int K, std::initializer_list
     // slice, so the fewest rows are cut into the most slices, and all have as many 64-row tiles of sums (those of 129 rows
     // or more: three).
     if (upto)
-        for (int64_t r : {1, 33, 65, 129}) ask(r);
+        for (int64_t r : {1, 17, 33, 65, 129}) ask(r);
     return most;
 }
 
@@ -272,11 +261,9 @@ hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused,
     if (p.splits > 1 && !(a.ws && a.ws_bytes >= partial_bytes(a.R, ntot, p.splits) && (((uintptr_t)a.ws) & 15) == 0))
         p = plan_gemm(a.R, a.K, n_seg, a.nseg, a.epi, a.in_order, a.same_sums, 1);
     const GemmTile &t = kTiles[p.tile];
-    GemmArgs ga;
-    ga.a = a;
+    LinDev ga(a);
     ga.splits = *splits = p.splits;
     ga.part = (float *)a.ws;
-    ga.ntot = ntot;
     ga.gated = a.epi == LinArgs::EPI_SWIGLU && t.gated && p.splits == 1;
     *fused = ga.gated || (a.epi == LinArgs::EPI_ADD_F32 && p.splits == 1);
     int ft = 0;

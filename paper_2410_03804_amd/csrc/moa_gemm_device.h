@@ -1,4 +1,4 @@
-// The product of a tile of activation rows and a tile of weight rows (bf16, MFMA 32x32x16), both staged through LDS by
+// The product of a tile of activation rows and a tile of weight rows (bf16, MFMA 16x16x32), both staged through LDS by
 // direct global -> LDS loads: the loop shared by the projections and the LM head.  What bounds it and why it looks like
 // this is said in moa_gemm_bf16.hip.
 #ifndef MOA_GEMM_DEVICE_H
@@ -25,11 +25,11 @@ __device__ __forceinline__ void wait_loads_and_barrier()
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// WR x WF wavefronts along rows x features, MR x NF blocks of 32 per wavefront, SX / SW stages of the activation / weight
+// WR x WF wavefronts along rows x features, MR blocks of 16 rows x NF blocks of 32 features per wavefront, SX / SW stages of the activation / weight
 // ring, WK groups of wavefronts that take every WK-th k tile each.
 template <int WR, int WF, int MR, int NF, int SX, int SW, int WK>
 struct GemmLoop {
-    static constexpr int BM = 32 * MR * WR, BN = 32 * NF * WF, BK = 64, NWV = WR * WF;   // NWV: wavefronts of one K group
+    static constexpr int BM = 16 * MR * WR, BN = 32 * NF * WF, BK = 64, NWV = WR * WF;   // NWV: wavefronts of one K group
     static constexpr int NXI = BM / 8 / NWV, NWI = (BN / 8 + NWV - 1) / NWV;             // load instructions per wavefront and k tile
     static constexpr uint32_t XST = BM * BK * 2, WST = BN * BK * 2;                      // bytes per stage
     static constexpr size_t LDS_BYTES = (size_t)(SX * BM + SW * BN) * 2 * BK * WK;
@@ -39,7 +39,8 @@ struct GemmLoop {
     int lane, wave, kgrp;
     uint32_t xoff[NXI], woff[NWI], xdst[NXI], wdst[NWI];
     const char *xbase, *wbase[NWI];
-    f32x16 acc[NF][MR];       // acc[i][jj][v]: feature 32 i + 16 (lane / 32) + v of the wavefront's, row 32 jj + lane % 32
+    // acc[i][j][b][v]: feature 32 i + 8 (lane / 16) + 4 b + v of the wavefront's, row 16 j + lane % 16
+    f32x4 acc[NF][MR][2];
 
     __device__ __forceinline__ GemmLoop()
     {
@@ -47,13 +48,13 @@ struct GemmLoop {
         wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) % NWV);
         kgrp = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) / NWV);
     }
-    __device__ __forceinline__ int wave_row() const { return (wave / WF) * (32 * MR); }
+    __device__ __forceinline__ int wave_row() const { return (wave / WF) * (16 * MR); }
     __device__ __forceinline__ int wave_feature() const { return (wave % WF) * (32 * NF); }
 
     // This lane's 16-byte pieces as offsets from the bases, for the first k tile.  An instruction moves eight tile rows of
     // 128 bytes into 1 KB of LDS; piece c of row r lives at position c ^ (r / 2 & 7) of its row, which spreads the operand
-    // reads of 16 rows over all banks.  W rows are permuted inside blocks of 32 so that the 16 results a lane gets from
-    // a block are 16 consecutive features.
+    // reads of 16 rows over all banks.  W rows are permuted inside blocks of 32 so that the 8 results a lane gets for a
+    // row from a block are 8 consecutive features.
     // x: first row of the tile, rows_left of them valid (the last one is repeated behind them)
     __device__ __forceinline__ void set_x(const void *x, int64_t ldx, int64_t rows_left)
     {
@@ -78,7 +79,7 @@ struct GemmLoop {
             const int row = 8 * g + (lane >> 3), p = row & 31;
             int first = 0;
             wbase[i] = (const char *)base_of(g >> 2, &first);
-            int f = first + 16 * ((p >> 2) & 1) + 4 * (p >> 3) + (p & 3);
+            int f = first + 8 * ((p >> 2) & 3) + 4 * (p >> 4) + (p & 3);
             if (f > rows_left - 1) f = rows_left - 1;
             woff[i] = (uint32_t)f * (uint32_t)K * 2u + (uint32_t)(16 * ((lane & 7) ^ ((row >> 1) & 7)));
             wdst[i] = SX * XST + (uint32_t)(g * 1024);
@@ -92,7 +93,7 @@ struct GemmLoop {
         const int64_t kbyte0 = ((int64_t)kt0 * WK + kgrp) * (BK * 2);
         const uint32_t ring = (uint32_t)kgrp * (SX * XST + SW * WST);
         const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem + ring;
-        const int l32 = lane & 31, half = lane >> 5;
+        const int l16 = lane & 15, quart = lane >> 4;
         uint32_t xfill = 0, wfill = 0;             // stage (byte offset) the next load goes to
         auto issue_x = [&](int kt) {               // tiles past the last repeat it (nobody reads them)
             const int64_t ko = kbyte0 + (int64_t)(kt < nk ? kt : nk - 1) * (WK * BK * 2);
@@ -114,83 +115,86 @@ struct GemmLoop {
 #pragma unroll
         for (int i = 0; i < NF; ++i)
 #pragma unroll
-            for (int jj = 0; jj < MR; ++jj)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][jj][e] = 0.f;
+            for (int j = 0; j < MR; ++j) acc[i][j][0] = acc[i][j][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-        uint32_t koff[4];
+        uint32_t koff[2];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) koff[ks] = (uint32_t)(l32 * 128 + 16 * ((2 * ks + half) ^ ((l32 >> 1) & 7)));
+        for (int s = 0; s < 2; ++s) koff[s] = (uint32_t)(l16 * 128 + 16 * ((4 * s + quart) ^ ((l16 >> 1) & 7)));
         const uint32_t xrd = ring + (uint32_t)(wave_row() * 128), wrd = ring + (uint32_t)(SX * XST + wave_feature() * 128);
         uint32_t xcur = 0, wcur = 0;                   // stages being read
+        // A tile is multiplied in quarters: columns 32 (p / 2) .. of one half of the wavefront's features.  Both quarters of
+        // 32 columns take the same activation operands.
         bf16x8 af[2][NF], bf[2][MR];
-        auto read = [&](int set, int ks) {
-            const char *wp = smem + (wrd + wcur + koff[ks]), *xp = smem + (xrd + xcur + koff[ks]);
+        auto read = [&](int p) {
+            const char *wp = smem + (wrd + wcur + koff[p >> 1]), *xp = smem + (xrd + xcur + koff[p >> 1]);
 #pragma unroll
-            for (int i = 0; i < NF; ++i) af[set][i] = *(const bf16x8 *)(wp + 4096 * i);
+            for (int i = 0; i < NF; ++i) af[p & 1][i] = *(const bf16x8 *)(wp + 2048 * (i + NF * (p & 1)));
+            if (!(p & 1))
 #pragma unroll
-            for (int i = 0; i < MR; ++i) bf[set][i] = *(const bf16x8 *)(xp + 4096 * i);
+                for (int j = 0; j < MR; ++j) bf[p >> 1][j] = *(const bf16x8 *)(xp + 2048 * j);
         };
-        auto multiply = [&](int set) {
+        auto multiply = [&](int p) {
 #pragma unroll
-            for (int i = 0; i < NF; ++i)
+            for (int i = NF * (p & 1); i < NF * (p & 1) + NF; ++i)
 #pragma unroll
-                for (int jj = 0; jj < MR; ++jj)
-                    acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[set][i], bf[set][jj], acc[i][jj], 0, 0, 0);
+                for (int j = 0; j < MR; ++j) {
+                    f32x4 &c = acc[i >> 1][j][i & 1];
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[p & 1][i - NF * (p & 1)], bf[p >> 1][j], c, 0, 0, 0);
+                }
         };
         auto advance = [&] {
             xcur = xcur + XST == SX * XST ? 0 : xcur + XST;
             wcur = wcur + WST == SW * WST ? 0 : wcur + WST;
         };
         wait_loads_and_barrier<ALLOW>();
-        read(0, 0);
+        read(0);
         int kt = 0;
         for (; kt < nk - SX; ++kt) {
-            read(1, 1);
+            read(1);
             __builtin_amdgcn_sched_barrier(0);
             multiply(0);
-            read(0, 2);
+            read(2);
             __builtin_amdgcn_sched_barrier(0);
             multiply(1);
-            read(1, 3);
+            read(3);
             __builtin_amdgcn_sched_barrier(0);
-            multiply(0);
-            if (NF * MR >= 8) __builtin_amdgcn_sched_barrier(0);
+            multiply(2);
+            if (NF * MR >= 16) __builtin_amdgcn_sched_barrier(0);
             wait_loads_and_barrier<ALLOW>();           // tile kt + 1 is in LDS for everybody, nobody reads tile kt any more
             advance();
-            read(0, 0);
+            read(0);
             __builtin_amdgcn_sched_barrier(0);
-            multiply(1);
+            multiply(3);
             issue_x(kt + SX);
             issue_w(kt + SW);
         }
         for (; kt < nk; ++kt) {
-            read(1, 1);
+            read(1);
             multiply(0);
-            read(0, 2);
+            read(2);
             multiply(1);
-            read(1, 3);
-            multiply(0);
+            read(3);
+            multiply(2);
             if (kt + 1 < nk) {
                 wait_loads_and_barrier<0>();
                 advance();
-                read(0, 0);
+                read(0);
             }
-            multiply(1);
+            multiply(3);
         }
 
         if (WK > 1) {                                  // the K groups' sums, added up in group order
-            constexpr int PER = NF * MR * 16 * 64;
+            constexpr int PER = NF * MR * 8 * 64;
             float *red = (float *)smem;
             wait_loads_and_barrier<0>();
             if (kgrp > 0) {
 #pragma unroll
                 for (int i = 0; i < NF; ++i)
 #pragma unroll
-                    for (int jj = 0; jj < MR; ++jj)
+                    for (int j = 0; j < MR; ++j)
 #pragma unroll
-                        for (int e = 0; e < 16; ++e)
-                            red[((kgrp - 1) * NWV + wave) * PER + ((i * MR + jj) * 16 + e) * 64 + lane] = acc[i][jj][e];
+                        for (int e = 0; e < 8; ++e)
+                            red[((kgrp - 1) * NWV + wave) * PER + ((i * MR + j) * 8 + e) * 64 + lane] = acc[i][j][e >> 2][e & 3];
             }
             __syncthreads();
             if (kgrp > 0) return false;
@@ -199,10 +203,10 @@ struct GemmLoop {
 #pragma unroll
                 for (int i = 0; i < NF; ++i)
 #pragma unroll
-                    for (int jj = 0; jj < MR; ++jj)
+                    for (int j = 0; j < MR; ++j)
 #pragma unroll
-                        for (int e = 0; e < 16; ++e)
-                            acc[i][jj][e] += red[(g * NWV + wave) * PER + ((i * MR + jj) * 16 + e) * 64 + lane];
+                        for (int e = 0; e < 8; ++e)
+                            acc[i][j][e >> 2][e & 3] += red[(g * NWV + wave) * PER + ((i * MR + j) * 8 + e) * 64 + lane];
         }
         return true;
     }

@@ -17,13 +17,6 @@
 
 namespace moa {
 
-struct F32Args {
-    LinArgs a;
-    int tile_begin[LIN_SEGS + 1];   // first feature tile of each segment; all of them from [nseg] on
-    int lead_blocks;     // workgroups in front of the projection's own (LinArgs::rider)
-    uint32_t vec;        // bit s: the segment's outputs can be stored four features at a time
-};
-
 __device__ __forceinline__ f32x4 ld4(const float *p) { return *(const f32x4 *)p; }
 __device__ __forceinline__ f32x4 ld4(const bf16_t *p)
 {
@@ -41,36 +34,27 @@ __device__ __forceinline__ void st4(bf16_t *p, const f32x4 &v)
 }
 
 // the integer work in the first workgroups of the grid; true when this workgroup was one of them
-__device__ __forceinline__ bool f32_lead_block(const F32Args &fa, int32_t *lds)
+__device__ __forceinline__ bool f32_lead_block(const LinDev &a, int32_t *lds)
 {
-    if ((int)blockIdx.x >= fa.lead_blocks) return false;
-    if ((int)blockIdx.x < fa.a.rider_units && threadIdx.x < 64)
-        step_small_unit(fa.a.rider, (int)blockIdx.x, lds, lds + MOA_MAX_TREE);
+    if ((int)blockIdx.x >= a.lead_blocks) return false;
+    if ((int)blockIdx.x < a.rider_units && threadIdx.x < 64)
+        step_small_unit(a.rider, (int)blockIdx.x, lds, lds + MOA_MAX_TREE);
     return true;
 }
 
-__device__ __forceinline__ int f32_segment(const F32Args &fa, int tile)
-{
-    int s = 0;
-#pragma unroll
-    for (int q = 1; q < LIN_SEGS; ++q) s += tile >= fa.tile_begin[q];
-    return s;
-}
-
 template <typename T>
-__global__ __launch_bounds__(256) void k_linear_f32_latency(F32Args fa)
+__global__ __launch_bounds__(256) void k_linear_f32_latency(LinDev a)
 {
     constexpr int UN = 4;                         // 16-column steps of K a wavefront has in flight
     __shared__ float red[4][16][20];              // 20: rows of four-float stores land on different banks
-    const LinArgs &a = fa.a;
-    if (f32_lead_block(fa, (int32_t *)red)) return;
-    const int ntiles = fa.tile_begin[LIN_SEGS];
-    const int bx = (int)blockIdx.x - fa.lead_blocks, tile = bx % ntiles;
+    if (f32_lead_block(a, (int32_t *)red)) return;
+    const int ntiles = a.tile_begin[LIN_SEGS];
+    const int bx = (int)blockIdx.x - a.lead_blocks, tile = bx % ntiles;
     const int64_t r0 = (int64_t)(bx / ntiles) * 16;
-    const int s = f32_segment(fa, tile);
-    const int N = a.seg[s].N, K = a.K, n0 = (tile - fa.tile_begin[s]) * 16;
-    const T *X = (const T *)(a.seg[s].X ? a.seg[s].X : a.X);
-    const int64_t ldx = a.seg[s].X ? a.seg[s].ldx : a.ldx;
+    const int s = a.segment(tile);
+    const int N = a.seg[s].N, K = a.K, n0 = (tile - a.tile_begin[s]) * 16;
+    const T *X = (const T *)a.seg[s].X;
+    const int64_t ldx = a.seg[s].ldx;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, kg = lane >> 4;
 
     // operands of v_mfma_f32_16x16x4: lane (li, kg) loads k = 16 step + 4 kg .. + 3 of its row in one piece, and MFMA j
@@ -111,25 +95,25 @@ __global__ __launch_bounds__(256) void k_linear_f32_latency(F32Args fa)
     const int row = threadIdx.x >> 4, f = threadIdx.x & 15;
     if (r0 + row >= a.R || n0 + f >= N) return;
     const float v = (red[0][row][f] + red[1][row][f]) + (red[2][row][f] + red[3][row][f]);
-    const int64_t off = store_offset(a.seg[s].st, r0 + row, n0 + f);
-    if (off >= 0) st<T>((T *)a.seg[s].st.dst + off, v);
+    const StoreSpec sp = a.store(s);
+    const int64_t off = store_offset(sp, r0 + row, n0 + f);
+    if (off >= 0) st<T>((T *)sp.dst + off, v);
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_linear_f32_tile(F32Args fa)
+__global__ __launch_bounds__(256) void k_linear_f32_tile(LinDev a)
 {
     constexpr int BK = 32, LD = BK + 4;           // 36-float rows: the 32 rows of an operand read hit 64 different banks
     __shared__ __attribute__((aligned(16))) float Ws[2][64 * LD];
     __shared__ __attribute__((aligned(16))) float Xs[2][64 * LD];
-    const LinArgs &a = fa.a;
-    if (f32_lead_block(fa, (int32_t *)Ws)) return;
-    const int ntiles = fa.tile_begin[LIN_SEGS];
-    const int bx = (int)blockIdx.x - fa.lead_blocks, tile = bx % ntiles;
+    if (f32_lead_block(a, (int32_t *)Ws)) return;
+    const int ntiles = a.tile_begin[LIN_SEGS];
+    const int bx = (int)blockIdx.x - a.lead_blocks, tile = bx % ntiles;
     const int64_t r0 = (int64_t)(bx / ntiles) * 64;
-    const int s = f32_segment(fa, tile);
-    const int N = a.seg[s].N, K = a.K, n0 = (tile - fa.tile_begin[s]) * 64;
-    const T *X = (const T *)(a.seg[s].X ? a.seg[s].X : a.X);
-    const int64_t ldx = a.seg[s].X ? a.seg[s].ldx : a.ldx;
+    const int s = a.segment(tile);
+    const int N = a.seg[s].N, K = a.K, n0 = (tile - a.tile_begin[s]) * 64;
+    const T *X = (const T *)a.seg[s].X;
+    const int64_t ldx = a.seg[s].ldx;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wf0 = (wave & 1) * 32, wr0 = (wave >> 1) * 32;
 
@@ -184,14 +168,14 @@ __global__ __launch_bounds__(256) void k_linear_f32_tile(F32Args fa)
     // acc[v]: feature wf0 + 8 (v / 4) + 4 half + v % 4 of row wr0 + l32
     const int64_t r = r0 + wr0 + l32;
     if (r >= a.R) return;
-    const StoreSpec &sp = a.seg[s].st;
+    const StoreSpec sp = a.store(s);
     const int64_t rp = store_row_part(sp, r);
     if (rp < 0) return;
     T *dst = (T *)sp.dst;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int n = n0 + wf0 + 8 * q + 4 * half;
-        if ((fa.vec >> s & 1) && n + 4 <= N) {
+        if ((a.vec >> s & 1) && n + 4 <= N) {
             st4(dst + rp + store_feat_part(sp, n), f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]});
         } else {
 #pragma unroll
@@ -223,11 +207,9 @@ constexpr int64_t F32_TILE_MIN_WORKGROUPS = 128;
 
 hipError_t launch_linear_f32(int dtype, const LinArgs &a, hipStream_t stream)
 {
-    F32Args fa;
-    fa.a = a;
+    LinDev fa(a);
     const size_t piece = dtype == DT_BF16 ? 8 : 16;
     int64_t t64 = 0, widest = 0;
-    fa.vec = 0;
     for (int s = 0; s < a.nseg; ++s) {
         const StoreSpec &st = a.seg[s].st;
         fa.vec |= (uint32_t)(aligned_to(st.dst, piece) && (st.mode == StoreSpec::ROW ? st.ld % 4 == 0 : st.dh % 4 == 0)) << s;

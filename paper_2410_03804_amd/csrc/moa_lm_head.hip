@@ -43,25 +43,28 @@ __global__ __launch_bounds__(64 * WR * WF * WK) void k_lm_head_argmax(LmHeadArgs
     wait_loads_and_barrier<0>();                               // the rings are dead; their memory is reused
     float *wv = (float *)smem;                                 // [WF][BM]
     int32_t *wi = (int32_t *)(wv + WF * BM);
-    const int l32 = g.lane & 31, half = g.lane >> 5;
+    const int l16 = g.lane & 15, quart = g.lane >> 4;
     if (mine) {
 #pragma unroll
-        for (int jj = 0; jj < MR; ++jj) {
+        for (int j = 0; j < MR; ++j) {
             float bv = -INFINITY;
             int bi = 0x7fffffff;
 #pragma unroll
             for (int i = 0; i < NF; ++i)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int id = n0 + g.wave_feature() + 32 * i + 16 * half + e;
-                    const float v = g.acc[i][jj][e];
+                for (int e = 0; e < 8; ++e) {
+                    const int id = n0 + g.wave_feature() + 32 * i + 8 * quart + e;
+                    const float v = g.acc[i][j][e >> 2][e & 3];
                     if (id < a.V && better(v, id, bv, bi)) { bv = v; bi = id; }
                 }
-            const float ov = __shfl_xor(bv, 32);
-            const int oi = __shfl_xor(bi, 32);
-            if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-            if (half == 0) {
-                const int at = (g.wave % WF) * BM + g.wave_row() + 32 * jj + l32;
+#pragma unroll
+            for (int o = 16; o <= 32; o <<= 1) {
+                const float ov = __shfl_xor(bv, o);
+                const int oi = __shfl_xor(bi, o);
+                if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+            }
+            if (quart == 0) {
+                const int at = (g.wave % WF) * BM + g.wave_row() + 16 * j + l16;
                 wv[at] = bv;
                 wi[at] = bi;
             }
@@ -169,10 +172,11 @@ int32_t moa_lm_head_argmax(int32_t dtype, const void *x, int32_t R, int32_t d, c
         // per compute unit the narrow ones fill the chip better (40 x 4096 x 32000: 50 against 58 us).
         const bool wide = V >= 2 * 256 * 128;
         hipError_t e;
-        if (a.R <= 32) e = launch_head<1, 1, 1, 2, 3, 3, 2>(&a, pairs, st);
-        else if (a.R <= 64) e = wide ? launch_head<2, 2, 1, 2, 3, 3, 1>(&a, pairs, st) : launch_head<2, 2, 1, 1, 4, 6, 1>(&a, pairs, st);
-        else if (a.R <= 128) e = wide ? launch_head<2, 2, 2, 2, 2, 3, 1>(&a, pairs, st) : launch_head<4, 2, 1, 2, 4, 4, 1>(&a, pairs, st);
-        else e = launch_head<4, 2, 2, 4, 2, 2, 1>(&a, pairs, st);
+        if (a.R <= 16) e = launch_head<1, 1, 1, 2, 3, 3, 2>(&a, pairs, st);
+        else if (a.R <= 32) e = launch_head<2, 1, 1, 2, 2, 3, 2>(&a, pairs, st);
+        else if (a.R <= 64) e = wide ? launch_head<2, 2, 2, 2, 3, 3, 1>(&a, pairs, st) : launch_head<2, 2, 2, 1, 4, 6, 1>(&a, pairs, st);
+        else if (a.R <= 128) e = wide ? launch_head<2, 2, 4, 2, 2, 3, 1>(&a, pairs, st) : launch_head<4, 2, 2, 2, 4, 4, 1>(&a, pairs, st);
+        else e = launch_head<4, 2, 4, 4, 2, 2, 1>(&a, pairs, st);
         if (e != hipSuccess) return api_fail(MOA_ERR_HIP, "lm_head_argmax: launch failed");
         prof_begin(K_LM_HEAD_REDUCE, st);
         MOA_KLAUNCH(k_lm_head_reduce, dim3(a.R), dim3(256), 0, st, a.pval, a.pid, a.tiles, tgt + r0, best ? best + r0 : nullptr);

@@ -1,0 +1,49 @@
+"""bf16 projections and the LM head around 16 rows, where the tiles change height."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def moa():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_03804_amd as m
+    return m
+
+
+def operands(R, K, N):
+    g = torch.Generator(device="cuda").manual_seed(R + K + N)
+    return (torch.randn(R, K, generator=g, device="cuda").bfloat16(), (torch.randn(N, K, generator=g, device="cuda") / K ** 0.5).bfloat16())
+
+
+@pytest.mark.parametrize("R", [1, 15, 16, 17, 31])
+@pytest.mark.parametrize("K,N", [(128, 32), (1024, 4096), (4096, 4128), (384, 16416), (512, 20000), (640, 31904), (256, 131104), (12288, 1024)])
+def test_projection_rows(moa, R, K, N):
+    print(f"[case] linear bf16 R={R} K={K} N={N}", flush=True)
+    x, w = operands(R, K, N)
+    y = torch.full((R + 1, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(max(moa.linear_workspace_bytes(moa.BF16, R, K, N), 256), dtype=torch.uint8, device="cuda")
+    moa.linear(x, w, y[:R], ws)
+    want = x.float() @ w.float().t()
+    torch.cuda.synchronize()
+    assert torch.isnan(y[R]).all(), "rows past the end are not written"
+    # one bf16 rounding of exact products summed in fp32: 2^-9 of the value at most, its rms 2^-9 / sqrt(3)
+    diff = (y[:R].float() - want).abs()
+    assert diff.max().item() <= 2.0 ** -8 * want.abs().max().item()
+    assert (diff.norm() / want.norm()).item() <= 2.0 ** -9
+
+
+@pytest.mark.parametrize("R", [1, 16, 17, 32])
+def test_head_rows(moa, R, K=256, V=3001):
+    print(f"[case] lm_head R={R} K={K} V={V}", flush=True)
+    x, w = operands(R, K, V)
+    tgt, best = torch.zeros(R, dtype=torch.int32, device="cuda"), torch.zeros(R, device="cuda")
+    moa.lm_head_argmax(x, w, tgt, torch.empty(moa.lm_head_workspace_bytes(V), dtype=torch.uint8, device="cuda"), best=best)
+    want = x.double() @ w.double().t()
+    torch.cuda.synchronize()
+    top = want.max(1).values
+    # fp32 sums of 256 exact products of order-1 results: 256 eps
+    assert (want.gather(1, tgt.long()[:, None])[:, 0] >= top - 256 * 2.0 ** -24 * 4).all()
+    assert ((best.double() - top).abs() <= 256 * 2.0 ** -24 * 4).all()
