@@ -17,6 +17,7 @@ if not _LIB_PATH.exists():
     raise ImportError(f"{_LIB_PATH} is missing: build it with `python -m paper_2410_03804_amd.build` "
                       "(there is no fallback path)")
 _lib = C.CDLL(str(_LIB_PATH))
+from ._argcheck import dev as _dev  # noqa: E402  (built with the library: csrc/argcheck.c)
 
 F32, BF16 = 0, 1
 MAX_TREE = 256
@@ -165,21 +166,6 @@ def last_error() -> str:
 def _check(rc: int):
     if rc != 0:
         raise MoaError(rc, last_error())
-
-
-def _dev(t, dtype, numel, name):
-    """Device pointer (a number: the argument types make the pointer) of tensor t after checking it can hold what the call touches."""
-    if t is None:
-        return None
-    if not isinstance(t, torch.Tensor):
-        raise TypeError(f"{name}: expected a torch tensor")
-    if not t.is_cuda or not t.is_contiguous():
-        raise ValueError(f"{name}: must be a contiguous CUDA tensor")
-    if t.dtype != dtype:
-        raise ValueError(f"{name}: dtype {t.dtype}, expected {dtype}")
-    if t.numel() < numel:
-        raise ValueError(f"{name}: {t.numel()} elements, the call touches {numel}")
-    return t.data_ptr()
 
 
 def _stream(stream):

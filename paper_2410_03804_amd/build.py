@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 from pathlib import Path
 
@@ -38,6 +39,14 @@ def _compile(src: str, objdir: Path) -> Path:
     return obj
 
 
+def build_argcheck() -> None:
+    """The binding's argument check, a CPython extension beside the library (plain C)."""
+    out = HERE / ("_argcheck" + sysconfig.get_config_var("EXT_SUFFIX"))
+    tmp = out.with_suffix(f".tmp{os.getpid()}")
+    subprocess.check_call(["gcc", "-O2", "-Wall", "-shared", "-fPIC", f"-I{sysconfig.get_paths()['include']}", "-o", str(tmp), str(CSRC / "argcheck.c")])
+    os.replace(tmp, out)
+
+
 def build(verbose: bool = False) -> Path:
     """Compile every source (always: a stale library must never be picked up) and link."""
     objdir = HERE / "_build"
@@ -47,6 +56,7 @@ def build(verbose: bool = False) -> Path:
     tmp = LIB.with_suffix(f".tmp{os.getpid()}.so")
     subprocess.check_call([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", str(tmp), *map(str, objs), "-lz"])
     os.replace(tmp, LIB)
+    build_argcheck()
     if verbose:
         print(f"built {LIB}")
     return LIB
