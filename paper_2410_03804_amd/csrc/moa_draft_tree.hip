@@ -176,7 +176,7 @@ __global__ __launch_bounds__(1024) void k_tree_finalize(int n, int n_max, int ke
 // bound that Bw of its own values reach, so nothing below the largest of the four wavefronts' bounds can be among the
 // slice's Bw best, and what reaches it (a few times Bw values, all of them in at most 4 Bw threads) is ranked in LDS.  A
 // second kernel ranks the S*Bw survivors of a row and merges the slices' (max, sum of exponentials).
-// Latency bound: two barriers per slice.  8 rows of 128256 bf16 logits: 6.4 + 6.1 us against 14.1 + 6.3 with every thread's
+// Latency bound: two barriers per slice.  8 rows of 128256 bf16 logits: 6.4 + 3.9 us against 14.1 + 6.3 with every thread's
 // values sorted, Bw rounds of two barriers over the heads of the 256 lists, and 2-byte loads.
 
 // Wavefront-wide maximum of an unsigned value by data-parallel-primitive moves inside the vector ALU (four shifts within
@@ -298,18 +298,20 @@ __global__ __launch_bounds__(256) void k_topk_slices(int is_bf16, const void *__
     if (t >= n && t < Bw) skey[slot * Bw + t] = rank_key(-INFINITY, 0x7fffffff);
 }
 
-// one workgroup per row: rank the S*Bw survivors, merge the log-sum-exp (every wavefront for itself: no barriers)
-__global__ __launch_bounds__(256) void k_topk_merge(int Bw, int S, const uint64_t *__restrict__ skey, const float *__restrict__ smax,
-                                                    const float *__restrict__ ssum, int32_t *__restrict__ tok, float *__restrict__ logp)
+// One workgroup per row: rank the S*Bw survivors, merge the log-sum-exp (every wavefront for itself: no barriers).  Four lanes
+// share a candidate and count a quarter of the keys each: the chain of LDS reads behind one another is what the ranking costs
+// (256 survivors, a thread per candidate: 6.1 us, of which that chain was a third; 3.9 now).
+__global__ __launch_bounds__(1024) void k_topk_merge(int Bw, int S, const uint64_t *__restrict__ skey, const float *__restrict__ smax,
+                                                     const float *__restrict__ ssum, int32_t *__restrict__ tok, float *__restrict__ logp)
 {
-    extern __shared__ __attribute__((aligned(16))) uint64_t ck[];   // [n] order keys
-    const int t = threadIdx.x, lane = t & 63;
+    extern __shared__ __attribute__((aligned(16))) uint64_t ck[];   // order keys, 0 (behind every one) up to a multiple of eight
+    const int t = threadIdx.x, lane = t & 63, nt = blockDim.x;
     const int64_t r = blockIdx.x;
-    const int n = S * Bw;
+    const int n = S * Bw, n8 = (n + 7) & ~7;
     // everything the row needs is requested at once: one trip to memory instead of three
     float m = -INFINITY, mk = -INFINITY, sk = 0.f;
     if (lane < S) { mk = smax[r * S + lane]; sk = ssum[r * S + lane]; }
-    for (int c = t; c < n; c += 256) ck[c] = skey[r * n + c];
+    for (int c = t; c < n8; c += nt) ck[c] = c < n ? skey[r * n + c] : 0;
     m = mk;
     for (int k = lane + 64; k < S; k += 64) m = fmaxf(m, smax[r * S + k]);
 #pragma unroll
@@ -323,12 +325,22 @@ __global__ __launch_bounds__(256) void k_topk_merge(int Bw, int S, const uint64_
     for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
     const float lse = m + __logf(sum);
     __syncthreads();
-    for (int c = t; c < n; c += 256) {
+    const int part = t & 3;
+    for (int c = t >> 2; c < n; c += nt >> 2) {            // the four lanes of a candidate stay together
         const uint64_t mine = ck[c];
+        int rank = 0;
+#pragma unroll 8
+        for (int u = 2 * part; u < n8; u += 8) {
+            const u64x2 a = *(const u64x2 *)&ck[u];
+            rank += (a[0] > mine ? 1 : 0) + (a[1] > mine ? 1 : 0);
+        }
+        rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xf, 0xf, false);     // quad_perm [1, 0, 3, 2]
+        rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xf, 0xf, false);     // quad_perm [2, 3, 0, 1]
         const int id = key_index(mine);
-        if (id == 0x7fffffff) continue;                    // an exhausted slice's filler
-        const int rank = rank_among(ck, n, mine);
-        if (rank < Bw) { tok[r * Bw + rank] = id; logp[r * Bw + rank] = key_value(mine) - lse; }
+        if (part == 0 && id != 0x7fffffff && rank < Bw) {  // (an exhausted slice's filler)
+            tok[r * Bw + rank] = id;
+            logp[r * Bw + rank] = key_value(mine) - lse;
+        }
     }
 }
 
@@ -405,10 +417,10 @@ int32_t moa_topk_logprob(int32_t dtype, const void *logits, int32_t F, int32_t V
     MOA_KLAUNCH(kernel, dim3((unsigned)n), dim3(256), 0, st, dtype == MOA_BF16 ? 1 : 0, logits, V, Vs, Bw, S, skey, smax, ssum);
     prof_end(st);
     if (hipGetLastError() != hipSuccess) return tree_fail(MOA_ERR_HIP, "topk_logprob: launch failed");
-    const size_t lds = (size_t)S * Bw * 8;
+    const size_t lds = ((size_t)S * Bw + 7) / 8 * 8 * 8;
     if (lds + (size_t)S * 8 > 60 * 1024) return tree_fail(MOA_ERR_SHAPE, "topk_logprob: vocabulary too large for the merge");
     prof_begin(K_TOPK_MERGE, st);
-    MOA_KLAUNCH(k_topk_merge, dim3(F), dim3(256), lds, st, Bw, S, skey, smax, ssum, tok, logp);
+    MOA_KLAUNCH(k_topk_merge, dim3(F), dim3(S * Bw <= 64 ? 256 : S * Bw <= 128 ? 512 : 1024), lds, st, Bw, S, skey, smax, ssum, tok, logp);
     prof_end(st);
     return hipGetLastError() == hipSuccess ? MOA_OK : tree_fail(MOA_ERR_HIP, "topk_logprob: launch failed");
 }
