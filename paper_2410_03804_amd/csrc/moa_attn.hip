@@ -613,6 +613,238 @@ __global__ __launch_bounds__(64 * NW) void k_attn_fused(AttnGroup grp, int nrb)
         atomicOr(a.dev_status, MOA_DEV_EMPTY_KEYS);
 }
 
+// The same in blocks of 16 query rows, for calls that would leave much of the chip idle in blocks of 32: twice the workgroups, each
+// with half the arithmetic per key (it reads as many keys).  One MFMA 16x16x32 takes the place of two 32x32x16 along the same
+// products, a lane has the same keys' scores in the same slots, and sums are made in the same order, so the two forms give the
+// same bits and a call may take either.  (Score slots of lane quarter q: keys 16 (q / 2) + 8 b + 4 (q % 2) + v of a tile, b = 0, 1.  The K
+// rows are put into LDS so that the 16 that an operand read touches follow one another, and V rows are 16 longer than head_dim: the
+// four quarters' transpose reads hit different banks.)  One sequence of 60 nodes x 1024 keys, 8 KV heads:
+// 11.9 -> 11.0 us; 8 nodes 11.4 -> 10.4; 8 x 16 x 3000 35.6 -> 32.5.
+template <int DH, int NW>
+struct Fused16Lds {
+    static constexpr int KLD = DH + 8, VSLD = DH + 16, NV = DH / 4;
+    static constexpr size_t q_bytes = (size_t)16 * KLD * sizeof(bf16_t);
+    static constexpr size_t stage_bytes = (size_t)32 * VSLD * sizeof(bf16_t);
+    static constexpr size_t loop_bytes = q_bytes + NW * stage_bytes;
+    static constexpr size_t merge_bytes = ((size_t)NW * NV * 64 + 2 * NW * 16) * sizeof(float);
+    static constexpr size_t bytes = loop_bytes > merge_bytes ? loop_bytes : merge_bytes;
+};
+
+template <int DH, int NW>
+__global__ __launch_bounds__(64 * NW) void k_attn_fused16(AttnGroup grp, int nrb)
+{
+    using L = Fused16Lds<DH, NW>;
+    constexpr int KLD = L::KLD, VSLD = L::VSLD;
+    constexpr int NKS = DH / 32;          // MFMA steps along head_dim
+    constexpr int NDB = DH / 16;          // 16-wide blocks of head_dim in the output
+    constexpr int CPK = DH / 8;           // 16-byte pieces per row
+    constexpr int RPI = 64 / CPK;         // rows covered by one load instruction of the wave
+    constexpr int NLD = KT / RPI;         // load instructions per tile
+    constexpr int NV = L::NV;             // accumulator values per lane
+    static_assert(RPI == 4 && NV == 4 * NW, "K rows are placed by fours; each wave finalises one block of head_dim");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, quart = lane >> 4;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int u = xcd + 8 * (slot / nrb), rb = slot - (slot / nrb) * nrb;
+    if (u >= grp.ncalls * grp.nbg) return;          // the whole workgroup leaves before any barrier
+    const int call = u / grp.nbg, bg = u - call * grp.nbg;
+    const AttnArgs &a = grp.a[call];
+    const int b = bg / a.Hkv, g = bg - b * a.Hkv;
+    const int G = a.H / a.Hkv, RG = G * a.Mq, W = (a.mask_rows + 63) >> 6;
+    const float sc = 1.4426950408889634f / sqrtf((float)DH);   // scores are kept in the log2 domain
+
+    u32x4 qreg;
+    {
+        const int c = min(tid, 16 * CPK - 1);
+        const int rq = min(rb * 16 + c / CPK, RG - 1), m = rq / G, hq = rq - m * G;
+        qreg = *(const u32x4 *)((const bf16_t *)a.q + (((int64_t)b * a.Mq + m) * a.H + g * G + hq) * DH + 8 * (c % CPK));
+    }
+
+    const int len = clamp_len(a.len[b], a.P_cap, tid == 0 ? a.dev_status : nullptr);
+    const int Mt = a.mask ? a.Mt : 0;
+    const int ntc = (len + KT - 1) / KT, nt = ntc + (Mt + KT - 1) / KT;
+
+    const bf16_t *kc = (const bf16_t *)a.kcache + (int64_t)bg * a.P_cap * DH;
+    const bf16_t *vc = (const bf16_t *)a.vcache + (int64_t)bg * a.P_cap * DH;
+    const bf16_t *ktp = (const bf16_t *)a.ktree + (int64_t)bg * a.tree_cap * DH;
+    const bf16_t *vtp = (const bf16_t *)a.vtree + (int64_t)bg * a.tree_cap * DH;
+
+    const int ld_row = lane / CPK, ld_piece = lane % CPK;
+    const int ld_off = ld_row * DH + 8 * ld_piece;
+    u32x4 kreg[NLD], vreg[NLD];
+    auto fetch = [&](int i) {
+        if (i < ntc && (i + 1) * KT <= len) {
+            const bf16_t *kp = kc + (int64_t)i * KT * DH + ld_off, *vp = vc + (int64_t)i * KT * DH + ld_off;
+#pragma unroll
+            for (int j = 0; j < NLD; ++j) {
+                kreg[j] = *(const u32x4 *)(kp + j * RPI * DH);
+                vreg[j] = *(const u32x4 *)(vp + j * RPI * DH);
+            }
+            return;
+        }
+        const bool tree = i >= ntc;
+        const int base = tree ? (i - ntc) * KT : i * KT;
+        const int limit = tree ? Mt : len;
+        const bf16_t *ksrc = tree ? ktp : kc;
+        const bf16_t *vsrc = tree ? vtp : vc;
+#pragma unroll
+        for (int j = 0; j < NLD; ++j) {
+            int row = base + RPI * j + ld_row;
+            if (row > limit - 1) row = limit - 1;              // rows past the end repeat the last valid row
+            const int64_t off = (int64_t)row * DH + 8 * ld_piece;
+            kreg[j] = *(const u32x4 *)(ksrc + off);
+            vreg[j] = *(const u32x4 *)(vsrc + off);
+        }
+    };
+    if (wave < nt) fetch(wave);
+
+    bf16_t *Qs = (bf16_t *)smem;
+    if (tid < 16 * CPK) *(u32x4 *)&Qs[(tid / CPK) * KLD + 8 * (tid % CPK)] = qreg;
+    __syncthreads();
+    bf16x8 qf[NKS];
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const bf16x8 *)&Qs[l16 * KLD + 32 * ks + 8 * quart];
+
+    int rho = rb * 16 + l16;                        // this lane's query column
+    const bool row_ok = rho < RG;
+    if (!row_ok) rho = RG - 1;
+    const int mrow = rho / G, hh = rho - mrow * G;
+
+    f32x4 acc[NDB];
+#pragma unroll
+    for (int d = 0; d < NDB; ++d) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float mrun = -INFINITY, lrun = 0.f;              // running max (scaled, log2 domain) and sum
+
+    bf16_t *stg = (bf16_t *)(smem + L::q_bytes + wave * L::stage_bytes);   // this wave's tile buffer
+    // transpose read: lane j of a 16-lane group addresses key (j >> 2) of the quarter's four, head_dim 4 (j & 3) of the block's 16
+    const int key0 = 16 * (quart >> 1) + 4 * (quart & 1);              // the quarter's keys: key0 .. + 3 and eight further on
+    const int tr_off = (key0 + (l16 >> 2)) * VSLD + 4 * (l16 & 3);
+
+    if (wave < nt) {
+        const int last = wave + ((nt - 1 - wave) / NW) * NW;
+        for (int i = wave; i <= last; i += NW) {
+            // K tile -> LDS (row bits 3 and 4 change places) -> S^T = K Q^T (keys x queries)
+#pragma unroll
+            for (int j = 0; j < NLD; ++j) *(u32x4 *)&stg[(RPI * ((j & 1) | (j & 2) << 1 | (j & 4) >> 1) + ld_row) * KLD + 8 * ld_piece] = kreg[j];
+            wave_lds_sync();
+            f32x4 s[2];
+#pragma unroll
+            for (int blk = 0; blk < 2; ++blk) {
+                s[blk] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) {
+                    const bf16x8 kf = *(const bf16x8 *)&stg[(16 * blk + l16) * KLD + 32 * ks + 8 * quart];
+                    s[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[ks], s[blk], 0, 0, 0);
+                }
+            }
+            wave_lds_sync();
+            // V tile into the same buffer, then the next tile's loads (clamped to the wave's last tile: a
+            // repeated load of valid memory whose result is not used) fly during the softmax and the second MFMA
+#pragma unroll
+            for (int j = 0; j < NLD; ++j) *(u32x4 *)&stg[(RPI * j + ld_row) * VSLD + 8 * ld_piece] = vreg[j];
+            wave_lds_sync();
+            fetch(min(i + NW, last));
+
+            float p[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) p[e] = s[e >> 2][e & 3];
+            // keys that do not count (tree rows outside the ancestor set, rows past the end) get -inf; a cache
+            // tile wholly below the length has none (the decision is the same for the whole wavefront)
+            if (!(i < ntc && (i + 1) * KT <= len)) {
+                const bool tree = i >= ntc;
+                const int base = tree ? (i - ntc) * KT : i * KT;
+                const int nvalid = (tree ? Mt : len) - base;   // >= 1
+                uint32_t vis = 0xffffffffu;
+                if (tree) vis = (uint32_t)(a.mask[((int64_t)b * a.mask_rows + a.mask_row0 + mrow) * W + (base >> 6)] >> (base & 63));
+                if (nvalid < 32) vis &= (1u << nvalid) - 1u;
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (!((vis >> (key0 + 8 * (e >> 2) + (e & 3))) & 1u)) p[e] = -INFINITY;
+            }
+            float tmax = p[0];
+#pragma unroll
+            for (int e = 1; e < 8; ++e) tmax = fmaxf(tmax, p[e]);
+            tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
+            tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+            const float mnew = fmaxf(mrun, tmax * sc);         // sc > 0: scaling keeps the order (and -inf)
+            const float msafe = (mnew == -INFINITY) ? 0.f : mnew;
+            const float corr = fast_exp2(mrun - msafe);
+            float lower = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { p[e] = fast_exp2(fmaf(p[e], sc, -msafe)); lower += p[e]; }
+            // one chain over keys 0 .. 3, 8 .. 11, 16 .. 19, 24 .. 27 (and one over the others): the upper quarters go on where the lower ones ended
+            float psum = __shfl_xor(lower, 32);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) psum += p[e];
+            const float upper = __shfl_xor(psum, 32);
+            if (quart < 2) psum = upper;
+            psum += __shfl_xor(psum, 16);
+            lrun = lrun * corr + psum;
+            mrun = mnew;
+            if (__any(corr != 1.0f)) {                          // the running max moved in some column
+                asm volatile("" ::: "memory");                  // keep this a real branch: the multiplies are skipped
+#pragma unroll
+                for (int d = 0; d < NDB; ++d) acc[d] *= corr;
+            }
+            // O^T += V^T P^T; P^T slot t of the quarter is key key0 + 8 (t >> 2) + (t & 3)
+            bf16x8 pf;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) pf[t] = (__bf16)p[t];
+#pragma unroll
+            for (int d = 0; d < NDB; ++d) {
+                const bf16_t *vp = stg + tr_off + 16 * d;
+                union { i16x4 h[2]; bf16x8 v; } vf;
+                vf.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)vp);
+                vf.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(vp + 8 * VSLD));
+                acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf.v, pf, acc[d], 0, 0, 0);
+            }
+            wave_lds_sync();
+        }
+    }
+
+    // combine the waves' triples: out = sum_w 2^(m_w - m*) acc_w / sum_w 2^(m_w - m*) l_w, waves in order
+    __syncthreads();                                            // the tile buffers are dead; their memory is reused
+    float *red = (float *)smem;                                 // [NW][NV][64]
+    float *msh = red + NW * NV * 64;                            // [NW][16]
+    float *lsh = msh + NW * 16;
+    if (quart == 0) {
+        msh[wave * 16 + l16] = mrun;
+        lsh[wave * 16 + l16] = lrun;
+    }
+#pragma unroll
+    for (int d = 0; d < NDB; ++d)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[(wave * NV + 4 * d + v) * 64 + lane] = acc[d][v];
+    __syncthreads();
+
+    float wgt[NW], mstar = -INFINITY, lsum = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { wgt[w] = msh[w * 16 + l16]; mstar = fmaxf(mstar, wgt[w]); }
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        wgt[w] = (wgt[w] == -INFINITY) ? 0.f : exp2f(wgt[w] - mstar);
+        lsum += wgt[w] * lsh[w * 16 + l16];
+    }
+    const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
+    float o[4];                                                 // head_dim 16 wave + 4 quart ..
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) sum += wgt[w] * red[(w * NV + 4 * wave + t) * 64 + lane];
+        o[t] = sum * inv;
+    }
+    if (row_ok) {
+        u32x2 pk;
+        pk[0] = pack_bf16x2(o[0], o[1]);
+        pk[1] = pack_bf16x2(o[2], o[3]);
+        *(u32x2 *)((bf16_t *)a.out + (((int64_t)b * a.Mq + mrow) * a.H + g * G + hh) * DH + 16 * wave + 4 * quart) = pk;
+    }
+    if (wave == 0 && quart == 0 && row_ok && lsum == 0.f && a.empty_is_error && a.dev_status)
+        atomicOr(a.dev_status, MOA_DEV_EMPTY_KEYS);
+}
+
 // ------------------------------------------------------------------ fp32, whole key range in one workgroup
 // One workgroup owns 16 query rows of one (sequence, KV head) -- heads of the group times tree tokens, as above -- and
 // all of its keys; wavefront w takes the 16-key tiles w, w + 8, ... and the eight (max, sum, accumulator) triples are
@@ -1001,8 +1233,21 @@ static hipError_t launch_attn_fused(const AttnArgs *calls, int n, hipStream_t st
 {
     const AttnArgs &a = calls[0];
     const AttnGroup grp = group_of(calls, n);
-    const int nrb = ((a.H / a.Hkv) * a.Mq + 31) / 32;
+    const int RG = (a.H / a.Hkv) * a.Mq;
     const int64_t units8 = ((int64_t)n * grp.nbg + 7) / 8;
+    // blocks of 16 rows while all of their workgroups run at once
+    if (a.dh == 128 && 8 * units8 * ((RG + 15) / 16) <= 256) {
+        constexpr size_t lds = Fused16Lds<128, 8>::bytes;
+        static bool raised[16] = {};
+        hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_fused16<128, 8>, lds);
+        if (e != hipSuccess) return e;
+        const int nrb16 = (RG + 15) / 16;
+        prof_begin(K_ATTN_FUSED16, stream);
+        MOA_KLAUNCH((k_attn_fused16<128, 8>), dim3((unsigned)(8 * units8 * nrb16)), dim3(512), lds, stream, grp, nrb16);
+        prof_end(stream);
+        return hipGetLastError();
+    }
+    const int nrb = (RG + 31) / 32;
     const int64_t grid = 8 * units8 * nrb;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
     if (a.dh == 128) return launch_fused_as<128, 8>(grp, nrb, (unsigned)grid, stream);
