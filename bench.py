@@ -154,7 +154,7 @@ def site_costs(cfg, n_layers, schedule="grouped", lsa_tokens="tree", with_sa=Fal
         return dict(bytes=sum(p["bytes"] for p in parts), flops=sum(p["flops"] for p in parts))
 
     # the first verification layers, up to four, are launched together with the cross-attention
-    paired = set(one) if schedule in ("grouped", "two-stream") else set()
+    paired = set(one) if schedule == "grouped" or (schedule == "two-stream" and not with_sa) else set()
     beside = min(n_layers, 4)
     for k, v in one.items():
         alone = n_layers - beside if k in paired else n_layers
@@ -175,6 +175,8 @@ def site_costs(cfg, n_layers, schedule="grouped", lsa_tokens="tree", with_sa=Fal
     if paired:
         c["tree_build+accept+lengths"] = add(c["tree_build"], c["tree_accept"], c["ca_append.lengths"])
         c["ca.q_proj+verify.qkv_proj"] = add(c["ca.q_proj"], *[one["verify.qkv_proj"]] * beside)
+        if with_sa:                       # the Self-Attention layer's projections stand in for the cross-attention's
+            c["verify.qkv_proj"] = add(c["sa.qkv_proj"], *[one["verify.qkv_proj"]] * beside)
         c["ca.core+verify.core"] = add(c["ca.core"], *[one["verify.core"]] * beside)
         c["ca.o_proj+verify.o_proj"] = add(c["ca.o_proj"], *[one["verify.o_proj"]] * beside)
     return c

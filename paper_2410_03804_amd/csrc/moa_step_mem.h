@@ -57,6 +57,42 @@ struct LayerMem {
     bool apart(const LayerMem &o) const { return !any_meet(writes, o.reads) && !any_meet(o.writes, reads) && !any_meet(writes, o.writes); }
 };
 
+// the Self-Attention layer in front of the cross-attention
+struct SaMem {
+    MemRange reads[7], writes[3];
+    bool aligned;
+    explicit SaMem(const moa_step_args_t *a)
+    {
+        const moa_shape_t *s = a->sa_shape;
+        const size_t es = elem_bytes(s), d = s->d_model, e = (size_t)s->n_q_heads * s->head_dim, ekv = (size_t)s->n_kv_heads * s->head_dim;
+        const size_t rows = (size_t)a->B * a->M, cache = (size_t)a->B * a->sa_P_cap;
+        reads[0] = {a->sa_emb, rows * d * es};
+        reads[1] = {a->sa_wq, e * d * es};
+        reads[2] = {a->sa_wk, ekv * d * es};
+        reads[3] = {a->sa_wv, ekv * d * es};
+        reads[4] = {a->sa_wo, d * e * es};
+        reads[5] = {a->sa_kcache, cache * ekv * es};
+        reads[6] = {a->sa_vcache, cache * ekv * es};
+        writes[0] = {a->sa_out, rows * d * es};
+        writes[1] = {a->sa_k_draft, rows * ekv * es};
+        writes[2] = {a->sa_v_draft, rows * ekv * es};
+        uintptr_t all = 0;
+        for (const MemRange &r : reads) all |= (uintptr_t)r.lo;
+        for (const MemRange &r : writes) all |= (uintptr_t)r.lo;
+        aligned = (all & 15) == 0;
+    }
+};
+
+// what the step's integer work reads and writes (the masks, which the layer is meant to read, aside)
+inline bool apart_from_integers(const moa_step_args_t *a, const SaMem &m)
+{
+    const size_t ints = (size_t)a->B * a->M * sizeof(int32_t), seqs = a->B * sizeof(int32_t);
+    const MemRange reads[] = {{a->parent, ints}, {a->tok, ints}, {a->tgt, ints}, {a->tok_off, seqs + sizeof(int32_t)}};
+    const MemRange writes[] = {{a->depth, ints}, {a->path, ints}, {a->n_path, seqs}, {a->bonus, seqs}, {a->ca_len, seqs}, {a->dev_status, sizeof(int32_t)}};
+    const MemRange mask[] = {{a->mask, (size_t)a->B * a->M * ((a->M + 63) / 64) * sizeof(uint64_t)}};
+    return !any_meet(m.writes, reads) && !any_meet(m.writes, writes) && !any_meet(m.reads, writes) && !any_meet(m.writes, mask) && !any_meet(m.reads, mask);
+}
+
 // what the rest of a step -- the LSA, the memory, the cross-attention, the integer work -- reads and writes
 inline bool apart_from_rest(const moa_step_args_t *a, const LayerMem &m)
 {

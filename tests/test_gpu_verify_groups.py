@@ -43,6 +43,11 @@ def reads_drafted(step):           # the third layer reads the cross-attention's
     step.v_x[2] = step.ca_out
 
 
+def reads_self_attention(step):    # the first layer reads the Self-Attention layer's output
+    if step.sa:
+        step.v_x[0] = step.sa["out"]
+
+
 def unaligned_weight(step):        # the second layer's projection can only be read eight bytes at a time
     w = step.v_w[1]["wk"]
     odd = torch.empty(w.numel() + 4, dtype=w.dtype, device="cuda")[4 if w.element_size() == 2 else 2:][:w.numel()].view(w.shape)
@@ -51,7 +56,7 @@ def unaligned_weight(step):        # the second layer's projection can only be r
 
 
 @pytest.mark.parametrize("with_sa", [False, True], ids=["", "sa"])
-@pytest.mark.parametrize("change", [apart, chained, one_slab, reads_drafted, unaligned_weight], ids=lambda f: f.__name__)
+@pytest.mark.parametrize("change", [apart, chained, one_slab, reads_drafted, reads_self_attention, unaligned_weight], ids=lambda f: f.__name__)
 @pytest.mark.parametrize("cfg", list(CFGS))
 def test_grouped_layers_give_what_one_after_another_gives(G, cfg, change, with_sa):
     """Six layers (a group of four beside the cross-attention at most, then one of two) against the sequential schedule: the same
@@ -62,8 +67,8 @@ def test_grouped_layers_give_what_one_after_another_gives(G, cfg, change, with_s
     need = None
     outs = {}
     for name in ("sequential", "grouped", "two_stream", "grouped, no room to spare", "two_stream, no room to spare"):
-        if change is reads_drafted and with_sa and name.startswith("two_stream"):
-            continue                       # there the cross-attention is another branch than the verification layers
+        if change in (reads_drafted, reads_self_attention) and with_sa and name.startswith("two_stream"):
+            continue                       # there the drafter's layers are another branch than the verification layers
         print(f"[case] verify groups {cfg} {change.__name__} sa={with_sa} {name}", flush=True)
         step = DeviceStep(work, fold=False)
         change(step)
