@@ -382,8 +382,9 @@ struct FusedLds {
 };
 
 template <int DH, int NW>
-__global__ __launch_bounds__(64 * NW) void k_attn_fused(AttnGroup grp, int nrb)
+__global__ __launch_bounds__(64 * NW) void k_attn_fused(AttnGroup grp)
 {
+    const int nrb = grp.nrb;
     using L = FusedLds<DH, NW>;
     constexpr int KLD = L::KLD, VSLD = L::VSLD;
     constexpr int NKS = DH / 16;          // MFMA steps along head_dim
@@ -631,8 +632,9 @@ struct Fused16Lds {
 };
 
 template <int DH, int NW>
-__global__ __launch_bounds__(64 * NW) void k_attn_fused16(AttnGroup grp, int nrb)
+__global__ __launch_bounds__(64 * NW) void k_attn_fused16(AttnGroup grp)
 {
+    const int nrb = grp.nrb;
     using L = Fused16Lds<DH, NW>;
     constexpr int KLD = L::KLD, VSLD = L::VSLD;
     constexpr int NKS = DH / 32;          // MFMA steps along head_dim
@@ -860,8 +862,9 @@ template <int DH>
 constexpr size_t attn_f32_lds() { return ((size_t)F32_NW * (DH / 4) * 64 + 2 * F32_NW * 16) * sizeof(float); }
 
 template <int DH>
-__global__ __launch_bounds__(64 * F32_NW) void k_attn_f32(AttnGroup grp, int nrb)
+__global__ __launch_bounds__(64 * F32_NW) void k_attn_f32(AttnGroup grp)
 {
+    const int nrb = grp.nrb;
     constexpr int NW = F32_NW, NKS = DH / 16, NDB = DH / 16, NV = 4 * NDB, VPW = NV / NW;
     extern __shared__ __attribute__((aligned(16))) float fsm[];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, kg = lane >> 4;
@@ -1156,6 +1159,7 @@ static bool attn_f32_ok(const AttnArgs &a)
 static AttnGroup group_of(const AttnArgs *calls, int n)
 {
     AttnGroup grp;
+    grp.nrb = 0;
     for (int i = 0; i < ATTN_CALLS; ++i) grp.a[i] = calls[i < n ? i : n - 1];
     grp.nbg = calls[0].B * calls[0].Hkv;
     grp.ncalls = n;
@@ -1163,14 +1167,14 @@ static AttnGroup group_of(const AttnArgs *calls, int n)
 }
 
 template <int DH>
-static hipError_t launch_f32_as(const AttnGroup &grp, int nrb, unsigned grid, hipStream_t stream)
+static hipError_t launch_f32_as(const AttnGroup &grp, unsigned grid, hipStream_t stream)
 {
     constexpr size_t lds = attn_f32_lds<DH>();
     static bool raised[16] = {};
     hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_f32<DH>, lds);
     if (e != hipSuccess) return e;
     prof_begin(K_ATTN_F32, stream);
-    MOA_KLAUNCH((k_attn_f32<DH>), dim3(grid), dim3(64 * F32_NW), lds, stream, grp, nrb);
+    MOA_KLAUNCH((k_attn_f32<DH>), dim3(grid), dim3(64 * F32_NW), lds, stream, grp);
     prof_end(stream);
     return hipGetLastError();
 }
@@ -1179,11 +1183,11 @@ static hipError_t launch_f32_as(const AttnGroup &grp, int nrb, unsigned grid, hi
 static hipError_t launch_attn_f32(const AttnArgs *calls, int n, hipStream_t stream)
 {
     const AttnArgs &a = calls[0];
-    const AttnGroup grp = group_of(calls, n);
-    const int nrb = ((a.H / a.Hkv) * a.Mq + 15) / 16;
+    AttnGroup grp = group_of(calls, n);
+    const int nrb = grp.nrb = ((a.H / a.Hkv) * a.Mq + 15) / 16;
     const int64_t grid = (int64_t)n * grp.nbg * nrb;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    return a.dh == 128 ? launch_f32_as<128>(grp, nrb, (unsigned)grid, stream) : launch_f32_as<64>(grp, nrb, (unsigned)grid, stream);
+    return a.dh == 128 ? launch_f32_as<128>(grp, (unsigned)grid, stream) : launch_f32_as<64>(grp, (unsigned)grid, stream);
 }
 
 static bool attn_split_ok(const AttnArgs &a, int P_cap_geo)
@@ -1217,14 +1221,14 @@ bool attn_takes_whole_range(int dtype, int B, int Mq, int Mt, int H, int Hkv, in
 
 // calls of identical shape (B, Mq, H, Hkv, dh)
 template <int DH, int NW>
-static hipError_t launch_fused_as(const AttnGroup &grp, int nrb, unsigned grid, hipStream_t stream)
+static hipError_t launch_fused_as(const AttnGroup &grp, unsigned grid, hipStream_t stream)
 {
     constexpr size_t lds = FusedLds<DH, NW>::bytes;
     static bool raised[16] = {};
     hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_fused<DH, NW>, lds);
     if (e != hipSuccess) return e;
     prof_begin(K_ATTN_FUSED + 64 * (DH * 8 + NW / 4), stream);
-    MOA_KLAUNCH((k_attn_fused<DH, NW>), dim3(grid), dim3(64 * NW), lds, stream, grp, nrb);
+    MOA_KLAUNCH((k_attn_fused<DH, NW>), dim3(grid), dim3(64 * NW), lds, stream, grp);
     prof_end(stream);
     return hipGetLastError();
 }
@@ -1232,7 +1236,7 @@ static hipError_t launch_fused_as(const AttnGroup &grp, int nrb, unsigned grid, 
 static hipError_t launch_attn_fused(const AttnArgs *calls, int n, hipStream_t stream)
 {
     const AttnArgs &a = calls[0];
-    const AttnGroup grp = group_of(calls, n);
+    AttnGroup grp = group_of(calls, n);
     const int RG = (a.H / a.Hkv) * a.Mq;
     const int64_t units8 = ((int64_t)n * grp.nbg + 7) / 8;
     // blocks of 16 rows while all of their workgroups run at once
@@ -1241,17 +1245,17 @@ static hipError_t launch_attn_fused(const AttnArgs *calls, int n, hipStream_t st
         static bool raised[16] = {};
         hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_fused16<128, 8>, lds);
         if (e != hipSuccess) return e;
-        const int nrb16 = (RG + 15) / 16;
+        grp.nrb = (RG + 15) / 16;
         prof_begin(K_ATTN_FUSED16, stream);
-        MOA_KLAUNCH((k_attn_fused16<128, 8>), dim3((unsigned)(8 * units8 * nrb16)), dim3(512), lds, stream, grp, nrb16);
+        MOA_KLAUNCH((k_attn_fused16<128, 8>), dim3((unsigned)(8 * units8 * grp.nrb)), dim3(512), lds, stream, grp);
         prof_end(stream);
         return hipGetLastError();
     }
-    const int nrb = (RG + 31) / 32;
+    const int nrb = grp.nrb = (RG + 31) / 32;
     const int64_t grid = 8 * units8 * nrb;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    if (a.dh == 128) return launch_fused_as<128, 8>(grp, nrb, (unsigned)grid, stream);
-    return launch_fused_as<64, 8>(grp, nrb, (unsigned)grid, stream);
+    if (a.dh == 128) return launch_fused_as<128, 8>(grp, (unsigned)grid, stream);
+    return launch_fused_as<64, 8>(grp, (unsigned)grid, stream);
 }
 
 static hipError_t launch_attn_split(const AttnArgs *calls, int n, hipStream_t stream)
@@ -1268,7 +1272,7 @@ static hipError_t launch_attn_split(const AttnArgs *calls, int n, hipStream_t st
         hipError_t e = launch_attn_split(calls, 2, stream);
         return e != hipSuccess ? e : launch_attn_split(calls + 2, n - 2, stream);
     }
-    const AttnGroup grp = group_of(calls, n);
+    AttnGroup grp = group_of(calls, n);
     const int nblocks = n * a.B * a.Mq * a.H;
     hipError_t e;
     if (g.wide) {

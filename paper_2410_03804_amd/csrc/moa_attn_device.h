@@ -25,11 +25,13 @@ struct SplitGeom {
 typedef _Float16 f16_t;
 typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
 
-// independent calls of the same shape in one launch (blockIdx.z / nbg picks the call)
+// independent calls of the same shape in one launch (blockIdx.z / nbg picks the call).  What picks it comes first and a call begins a
+// line of its own: every 64 bytes of arguments that a kernel has to wait for are a trip to memory.
 struct AttnGroup {
-    AttnArgs a[ATTN_CALLS];
     int nbg;      // B * Hkv of one call
     int ncalls;
+    int nrb;      // whole key range: row blocks of a (sequence, KV head)
+    alignas(64) AttnArgs a[ATTN_CALLS];
 };
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
