@@ -28,10 +28,12 @@ ROOT = Path(__file__).resolve().parent
 
 
 def short_name(n: str) -> str:
-    """`void moa::k_x<2, 2>(moa::Args)` -> `k_x<2, 2>`; mangled leftovers are demangled by hand."""
+    """`void moa::k_x<2, 2>(moa::Args)` -> `k_x<2, 2>`; mangled leftovers are demangled by hand.  The last template argument of
+    the kernels that take several segments or calls is the room in their arguments: the library's names leave it out, and so
+    does this."""
     m = re.match(r"_ZN3moa\d+(k_[a-z0-9_]+?)I((?:Li\d+E)+)E", n)
     if m:
-        return m.group(1) + "<" + ", ".join(re.findall(r"Li(\d+)E", m.group(2))) + ">"
+        return without_room(m.group(1) + "<" + ", ".join(re.findall(r"Li(\d+)E", m.group(2))) + ">")
     n = re.sub(r"^void\s+", "", n)
     depth, cut = 0, len(n)
     for i, ch in enumerate(n):                  # drop the argument list: the first '(' outside template brackets
@@ -42,7 +44,11 @@ def short_name(n: str) -> str:
         elif ch == "(" and depth == 0:
             cut = i
             break
-    return n[:cut].replace("moa::", "").strip()
+    return without_room(n[:cut].replace("moa::", "").strip())
+
+
+def without_room(n: str) -> str:
+    return re.sub(r", \d+>$", ">", n) if re.match(r"k_(linear_(bf16|f32_tile|f32_latency)|attn_(mfma|long|fused|fused16|f32|merge))<", n) else n
 
 
 COMMIT_OVERRIDE = ""

@@ -119,8 +119,8 @@ __global__ __launch_bounds__(64) void k_attn_generic(AttnArgs a)
 // ------------------------------------------------------------------ MFMA split-KV
 constexpr int KT = 32;        // keys per tile
 
-template <int DH, int NBLK>
-__global__ __launch_bounds__(256, NBLK == 1 ? 2 : 1) void k_attn_mfma(AttnGroup grp, SplitGeom geo)
+template <int DH, int NBLK, int CALLS>
+__global__ __launch_bounds__(256, NBLK == 1 ? 2 : 1) void k_attn_mfma(AttnGroup<CALLS> grp, SplitGeom geo)
 {
     const int call = blockIdx.z / grp.nbg;
     const AttnArgs &a = grp.a[call];
@@ -381,8 +381,8 @@ struct FusedLds {
     static constexpr size_t bytes = loop_bytes > merge_bytes ? loop_bytes : merge_bytes;
 };
 
-template <int DH, int NW>
-__global__ __launch_bounds__(64 * NW) void k_attn_fused(AttnGroup grp)
+template <int DH, int NW, int CALLS>
+__global__ __launch_bounds__(64 * NW) void k_attn_fused(AttnGroup<CALLS> grp)
 {
     const int nrb = grp.nrb;
     using L = FusedLds<DH, NW>;
@@ -631,8 +631,8 @@ struct Fused16Lds {
     static constexpr size_t bytes = loop_bytes > merge_bytes ? loop_bytes : merge_bytes;
 };
 
-template <int DH, int NW>
-__global__ __launch_bounds__(64 * NW) void k_attn_fused16(AttnGroup grp)
+template <int DH, int NW, int CALLS>
+__global__ __launch_bounds__(64 * NW) void k_attn_fused16(AttnGroup<CALLS> grp)
 {
     const int nrb = grp.nrb;
     using L = Fused16Lds<DH, NW>;
@@ -861,8 +861,8 @@ constexpr int F32_NW = 8;
 template <int DH>
 constexpr size_t attn_f32_lds() { return ((size_t)F32_NW * (DH / 4) * 64 + 2 * F32_NW * 16) * sizeof(float); }
 
-template <int DH>
-__global__ __launch_bounds__(64 * F32_NW) void k_attn_f32(AttnGroup grp)
+template <int DH, int CALLS>
+__global__ __launch_bounds__(64 * F32_NW) void k_attn_f32(AttnGroup<CALLS> grp)
 {
     const int nrb = grp.nrb;
     constexpr int NW = F32_NW, NKS = DH / 16, NDB = DH / 16, NV = 4 * NDB, VPW = NV / NW;
@@ -993,8 +993,8 @@ __global__ __launch_bounds__(64 * F32_NW) void k_attn_f32(AttnGroup grp)
 // workgroup of 256 threads folds 2048/DH rows
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 
-template <int DH>
-__global__ __launch_bounds__(256) void k_attn_merge(AttnGroup grp, SplitGeom geo)
+template <int DH, int CALLS>
+__global__ __launch_bounds__(256) void k_attn_merge(AttnGroup<CALLS> grp, SplitGeom geo)
 {
     constexpr int LPR = DH / 8;            // lanes per row
     constexpr int RPB = 256 / LPR;         // rows per workgroup
@@ -1156,38 +1156,40 @@ static bool attn_f32_ok(const AttnArgs &a)
     return a.dtype == DT_F32 && (a.dh == 64 || a.dh == 128) && al(a.q) && al(a.kcache) && al(a.ktree);
 }
 
-static AttnGroup group_of(const AttnArgs *calls, int n)
+template <int CALLS>
+static AttnGroup<CALLS> group_of(const AttnArgs *calls, int n)
 {
-    AttnGroup grp;
+    AttnGroup<CALLS> grp;
     grp.nrb = 0;
-    for (int i = 0; i < ATTN_CALLS; ++i) grp.a[i] = calls[i < n ? i : n - 1];
+    for (int i = 0; i < CALLS; ++i) grp.a[i] = calls[i < n ? i : n - 1];
     grp.nbg = calls[0].B * calls[0].Hkv;
     grp.ncalls = n;
     return grp;
 }
 
-template <int DH>
-static hipError_t launch_f32_as(const AttnGroup &grp, unsigned grid, hipStream_t stream)
+template <int DH, int CALLS>
+static hipError_t launch_f32_as(const AttnGroup<CALLS> &grp, unsigned grid, hipStream_t stream)
 {
     constexpr size_t lds = attn_f32_lds<DH>();
     static bool raised[16] = {};
-    hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_f32<DH>, lds);
+    hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_f32<DH, CALLS>, lds);
     if (e != hipSuccess) return e;
     prof_begin(K_ATTN_F32, stream);
-    MOA_KLAUNCH((k_attn_f32<DH>), dim3(grid), dim3(64 * F32_NW), lds, stream, grp);
+    MOA_KLAUNCH((k_attn_f32<DH, CALLS>), dim3(grid), dim3(64 * F32_NW), lds, stream, grp);
     prof_end(stream);
     return hipGetLastError();
 }
 
 // calls of identical shape (B, Mq, H, Hkv, dh)
-static hipError_t launch_attn_f32(const AttnArgs *calls, int n, hipStream_t stream)
+template <int CALLS>
+static hipError_t launch_attn_f32_as(const AttnArgs *calls, int n, hipStream_t stream)
 {
     const AttnArgs &a = calls[0];
-    AttnGroup grp = group_of(calls, n);
+    AttnGroup<CALLS> grp = group_of<CALLS>(calls, n);
     const int nrb = grp.nrb = ((a.H / a.Hkv) * a.Mq + 15) / 16;
     const int64_t grid = (int64_t)n * grp.nbg * nrb;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    return a.dh == 128 ? launch_f32_as<128>(grp, (unsigned)grid, stream) : launch_f32_as<64>(grp, (unsigned)grid, stream);
+    return a.dh == 128 ? launch_f32_as<128, CALLS>(grp, (unsigned)grid, stream) : launch_f32_as<64, CALLS>(grp, (unsigned)grid, stream);
 }
 
 static bool attn_split_ok(const AttnArgs &a, int P_cap_geo)
@@ -1220,45 +1222,47 @@ bool attn_takes_whole_range(int dtype, int B, int Mq, int Mt, int H, int Hkv, in
 }
 
 // calls of identical shape (B, Mq, H, Hkv, dh)
-template <int DH, int NW>
-static hipError_t launch_fused_as(const AttnGroup &grp, unsigned grid, hipStream_t stream)
+template <int DH, int NW, int CALLS>
+static hipError_t launch_fused_as(const AttnGroup<CALLS> &grp, unsigned grid, hipStream_t stream)
 {
     constexpr size_t lds = FusedLds<DH, NW>::bytes;
     static bool raised[16] = {};
-    hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_fused<DH, NW>, lds);
+    hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_fused<DH, NW, CALLS>, lds);
     if (e != hipSuccess) return e;
     prof_begin(K_ATTN_FUSED + 64 * (DH * 8 + NW / 4), stream);
-    MOA_KLAUNCH((k_attn_fused<DH, NW>), dim3(grid), dim3(64 * NW), lds, stream, grp);
+    MOA_KLAUNCH((k_attn_fused<DH, NW, CALLS>), dim3(grid), dim3(64 * NW), lds, stream, grp);
     prof_end(stream);
     return hipGetLastError();
 }
 
-static hipError_t launch_attn_fused(const AttnArgs *calls, int n, hipStream_t stream)
+template <int CALLS>
+static hipError_t launch_attn_fused_as(const AttnArgs *calls, int n, hipStream_t stream)
 {
     const AttnArgs &a = calls[0];
-    AttnGroup grp = group_of(calls, n);
+    AttnGroup<CALLS> grp = group_of<CALLS>(calls, n);
     const int RG = (a.H / a.Hkv) * a.Mq;
     const int64_t units8 = ((int64_t)n * grp.nbg + 7) / 8;
     // blocks of 16 rows while all of their workgroups run at once
     if (a.dh == 128 && 8 * units8 * ((RG + 15) / 16) <= 256) {
         constexpr size_t lds = Fused16Lds<128, 8>::bytes;
         static bool raised[16] = {};
-        hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_fused16<128, 8>, lds);
+        hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_fused16<128, 8, CALLS>, lds);
         if (e != hipSuccess) return e;
         grp.nrb = (RG + 15) / 16;
         prof_begin(K_ATTN_FUSED16, stream);
-        MOA_KLAUNCH((k_attn_fused16<128, 8>), dim3((unsigned)(8 * units8 * grp.nrb)), dim3(512), lds, stream, grp);
+        MOA_KLAUNCH((k_attn_fused16<128, 8, CALLS>), dim3((unsigned)(8 * units8 * grp.nrb)), dim3(512), lds, stream, grp);
         prof_end(stream);
         return hipGetLastError();
     }
     const int nrb = grp.nrb = (RG + 31) / 32;
     const int64_t grid = 8 * units8 * nrb;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    if (a.dh == 128) return launch_fused_as<128, 8>(grp, (unsigned)grid, stream);
-    return launch_fused_as<64, 8>(grp, (unsigned)grid, stream);
+    if (a.dh == 128) return launch_fused_as<128, 8, CALLS>(grp, (unsigned)grid, stream);
+    return launch_fused_as<64, 8, CALLS>(grp, (unsigned)grid, stream);
 }
 
-static hipError_t launch_attn_split(const AttnArgs *calls, int n, hipStream_t stream)
+template <int CALLS>
+static hipError_t launch_attn_split_as(const AttnArgs *calls, int n, hipStream_t stream)
 {
     const AttnArgs &a = calls[0];
     int cap = a.P_cap;
@@ -1269,10 +1273,10 @@ static hipError_t launch_attn_split(const AttnArgs *calls, int n, hipStream_t st
     }
     const SplitGeom g = split_geometry(a.B, a.Mq, a.H, a.Hkv, a.dh, cap, n);
     if (n > 2 && split_bytes(g, a.B, a.Hkv, a.dh) > room) {      // row tiles of another height than one or two calls take
-        hipError_t e = launch_attn_split(calls, 2, stream);
-        return e != hipSuccess ? e : launch_attn_split(calls + 2, n - 2, stream);
+        hipError_t e = launch_attn_split_as<CALLS>(calls, 2, stream);
+        return e != hipSuccess ? e : launch_attn_split_as<CALLS>(calls + 2, n - 2, stream);
     }
-    AttnGroup grp = group_of(calls, n);
+    AttnGroup<CALLS> grp = group_of<CALLS>(calls, n);
     const int nblocks = n * a.B * a.Mq * a.H;
     hipError_t e;
     if (g.wide) {
@@ -1281,8 +1285,8 @@ static hipError_t launch_attn_split(const AttnArgs *calls, int n, hipStream_t st
     } else {
         const dim3 grid(g.nsplit, g.rowtiles, n * grp.nbg);
         prof_begin(K_ATTN_MFMA + 64 * (a.dh * 8 + ATTN_NBLK), stream);
-        if (a.dh == 128) MOA_KLAUNCH((k_attn_mfma<128, ATTN_NBLK>), grid, dim3(256), 0, stream, grp, g);
-        else MOA_KLAUNCH((k_attn_mfma<64, ATTN_NBLK>), grid, dim3(256), 0, stream, grp, g);
+        if (a.dh == 128) MOA_KLAUNCH((k_attn_mfma<128, ATTN_NBLK, CALLS>), grid, dim3(256), 0, stream, grp, g);
+        else MOA_KLAUNCH((k_attn_mfma<64, ATTN_NBLK, CALLS>), grid, dim3(256), 0, stream, grp, g);
         prof_end(stream);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1290,10 +1294,23 @@ static hipError_t launch_attn_split(const AttnArgs *calls, int n, hipStream_t st
     prof_begin(K_ATTN_MERGE + 64 * (a.dh * 8), stream);
     const int rpb = 2048 / a.dh;                      // rows per merge workgroup
     const unsigned mblocks = (unsigned)(((int64_t)nblocks + rpb - 1) / rpb);
-    if (a.dh == 128) MOA_KLAUNCH(k_attn_merge<128>, dim3(mblocks), dim3(256), 0, stream, grp, g);
-    else MOA_KLAUNCH(k_attn_merge<64>, dim3(mblocks), dim3(256), 0, stream, grp, g);
+    if (a.dh == 128) MOA_KLAUNCH((k_attn_merge<128, CALLS>), dim3(mblocks), dim3(256), 0, stream, grp, g);
+    else MOA_KLAUNCH((k_attn_merge<64, CALLS>), dim3(mblocks), dim3(256), 0, stream, grp, g);
     prof_end(stream);
     return hipGetLastError();
+}
+
+static hipError_t launch_attn_f32(const AttnArgs *calls, int n, hipStream_t stream)
+{
+    return n <= ATTN_FEW ? launch_attn_f32_as<ATTN_FEW>(calls, n, stream) : launch_attn_f32_as<ATTN_CALLS>(calls, n, stream);
+}
+static hipError_t launch_attn_fused(const AttnArgs *calls, int n, hipStream_t stream)
+{
+    return n <= ATTN_FEW ? launch_attn_fused_as<ATTN_FEW>(calls, n, stream) : launch_attn_fused_as<ATTN_CALLS>(calls, n, stream);
+}
+static hipError_t launch_attn_split(const AttnArgs *calls, int n, hipStream_t stream)
+{
+    return n <= ATTN_FEW ? launch_attn_split_as<ATTN_FEW>(calls, n, stream) : launch_attn_split_as<ATTN_CALLS>(calls, n, stream);
 }
 
 // whole-tree defaults of the tree window; false when the window does not fit its tree

@@ -27,11 +27,13 @@ typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
 
 // independent calls of the same shape in one launch (blockIdx.z / nbg picks the call).  What picks it comes first and a call begins a
 // line of its own: every 64 bytes of arguments that a kernel has to wait for are a trip to memory.
+// (CALLS: ATTN_FEW or ATTN_CALLS, see LinDev.)
+template <int CALLS>
 struct AttnGroup {
     int nbg;      // B * Hkv of one call
     int ncalls;
     int nrb;      // whole key range: row blocks of a (sequence, KV head)
-    alignas(64) AttnArgs a[ATTN_CALLS];
+    alignas(64) AttnArgs a[CALLS];
 };
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
@@ -42,7 +44,8 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 // the kernel in 256-row tiles (moa_attn_long.hip): keys per tile, and the launch of the split pass
 constexpr int LK = 64;
-hipError_t launch_attn_long(const AttnGroup &grp, const SplitGeom &g, hipStream_t stream);
+template <int CALLS>
+hipError_t launch_attn_long(const AttnGroup<CALLS> &grp, const SplitGeom &g, hipStream_t stream);
 
 }  // namespace moa
 #endif

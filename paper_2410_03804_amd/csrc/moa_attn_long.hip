@@ -41,8 +41,8 @@ namespace moa {
 
 constexpr int LRING = 4;
 
-template <int DH>
-__global__ __launch_bounds__(256, 1) void k_attn_long(AttnGroup grp, SplitGeom geo)
+template <int DH, int CALLS>
+__global__ __launch_bounds__(256, 1) void k_attn_long(AttnGroup<CALLS> grp, SplitGeom geo)
 {
     static_assert(DH == 128, "a row is 16 pieces of 16 bytes");
     constexpr int NKS = DH / 16, NDB = DH / 32;
@@ -357,18 +357,22 @@ __global__ __launch_bounds__(256, 1) void k_attn_long(AttnGroup grp, SplitGeom g
     }
 }
 
-hipError_t launch_attn_long(const AttnGroup &grp, const SplitGeom &g, hipStream_t stream)
+template <int CALLS>
+hipError_t launch_attn_long(const AttnGroup<CALLS> &grp, const SplitGeom &g, hipStream_t stream)
 {
     constexpr size_t lds = (size_t)LRING * LK * 128 * 2 * 2;
     static bool raised[16] = {};
-    hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_long<128>, lds);
+    hipError_t e = raise_lds_limit_once(raised, (const void *)k_attn_long<128, CALLS>, lds);
     if (e != hipSuccess) return e;
     const int64_t units8 = ((int64_t)g.nsplit * grp.ncalls * grp.nbg + 7) / 8, grid = 8 * units8 * g.rowtiles;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
     prof_begin(K_ATTN_LONG, stream);
-    MOA_KLAUNCH((k_attn_long<128>), dim3((unsigned)grid), dim3(256), lds, stream, grp, g);
+    MOA_KLAUNCH((k_attn_long<128, CALLS>), dim3((unsigned)grid), dim3(256), lds, stream, grp, g);
     prof_end(stream);
     return hipGetLastError();
 }
+
+template hipError_t launch_attn_long(const AttnGroup<ATTN_FEW> &, const SplitGeom &, hipStream_t);
+template hipError_t launch_attn_long(const AttnGroup<ATTN_CALLS> &, const SplitGeom &, hipStream_t);
 
 }  // namespace moa

@@ -226,6 +226,7 @@ hipError_t launch_splitk_sum(const SumArgs &s, hipStream_t stream);
 constexpr int STEP_VERIFY_GROUP = 4;
 constexpr int LIN_SEGS = 1 + 3 * STEP_VERIFY_GROUP;
 constexpr int ATTN_CALLS = 1 + STEP_VERIFY_GROUP;
+constexpr int LIN_FEW = 4, ATTN_FEW = 2;         // and what most launches hold: kernels exist for either
 
 struct LinSeg {
     const void *W;  // [N, K] row-major
@@ -280,12 +281,16 @@ struct LinArgs {
 // What a projection kernel is given of a launch.  A kernel begins with a chain of reads from here, and every 64 bytes that
 // none of its neighbours has read yet are a trip to memory: what decides where a workgroup belongs comes first and
 // together, then a line for each segment, and what is only needed at the end last.
+// SEGS is LIN_FEW or LIN_SEGS: the host writes all of it for every launch, and the device reads it past cold caches (with
+// room for thirteen everywhere and five attention calls: a tiny single-precision step 29.6 us against 28.5, 41 - 47 us
+// to enqueue its first pass on new buffers against 37 - 39; an 8B step 108 against 105.7).
 struct alignas(64) DevSeg {
     const void *W, *X;
     void *dst;
     int64_t ldx, ld;
     int N, mode, heads, cap, rows_per_seq;
 };
+template <int SEGS>
 struct LinDev {
     int lead_blocks;                 // workgroups in front of the projection's own (LinArgs::rider)
     int rider_units;
@@ -295,13 +300,13 @@ struct LinDev {
     int gated;                       // EPI_SWIGLU inside the kernel: 32-feature blocks alternate between the two matrices
     int K, nseg;
     int64_t R;
-    int tile_begin[LIN_SEGS + 1];    // first feature tile of each segment; all of them from [nseg] on
+    int tile_begin[SEGS + 1];        // first feature tile of each segment; all of them from [nseg] on
     uint32_t vec;                    // bit s: segment s's outputs can be stored four features at a time (single precision)
     int epi;
     int ntot;                        // features of all segments
     int dh;                          // of the segments that go to heads
     int append_B;                    // and of those that are appended to a memory (all to the same one)
-    DevSeg seg[LIN_SEGS];
+    DevSeg seg[SEGS];
     const int32_t *append_base, *append_off;
     int32_t *append_status;
     float *part;                     // [64-row tiles][splits][64][ntot]
@@ -329,7 +334,7 @@ struct LinDev {
     {
         int s = 0;
 #pragma unroll
-        for (int q = 1; q < LIN_SEGS; ++q) s += tile >= tile_begin[q];
+        for (int q = 1; q < SEGS; ++q) s += tile >= tile_begin[q];
         return s;
     }
     __device__ __forceinline__ StoreSpec store(int s) const
@@ -337,7 +342,7 @@ struct LinDev {
         return {seg[s].mode, seg[s].dst, seg[s].ld, seg[s].heads, dh, seg[s].cap, seg[s].rows_per_seq, append_B, append_base, append_off, append_status};
     }
 };
-static_assert(sizeof(DevSeg) == 64 && offsetof(LinDev, seg) == 128, "a line for a segment");
+static_assert(sizeof(DevSeg) == 64 && offsetof(LinDev<LIN_SEGS>, seg) == 128 && offsetof(LinDev<LIN_FEW>, seg) == 128, "a line for a segment");
 
 // Y_s = X_s W_s^T for up to LIN_SEGS weight matrices (one launch on the fast paths; K is cut for up to four only).
 hipError_t launch_linear(int dtype, const LinArgs &a, hipStream_t stream);

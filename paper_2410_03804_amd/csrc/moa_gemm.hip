@@ -209,12 +209,16 @@ static hipError_t launch_linear_impl(int dtype, const LinArgs &a, hipStream_t st
     if (path == P_BF16) {
         *rode = a.rider_units > 0;
         int splits = 1;
-        LinArgs b = a;
         // these epilogues store 16 bytes at a time; elsewhere the projection is stored and finished element by element
-        if (!aligned16(a.epi_out)) b.epi = LinArgs::EPI_NONE;
-        hipError_t e = launch_linear_bf16(b, stream, fused, &splits);
+        if (!aligned16(a.epi_out)) {
+            LinArgs b = a;
+            b.epi = LinArgs::EPI_NONE;
+            hipError_t e = launch_linear_bf16(b, stream, fused, &splits);
+            return e != hipSuccess || splits == 1 ? e : finish_splits(b, splits, stream, fused);
+        }
+        hipError_t e = launch_linear_bf16(a, stream, fused, &splits);
         if (e != hipSuccess || splits == 1) return e;
-        return finish_splits(b, splits, stream, fused);
+        return finish_splits(a, splits, stream, fused);
     }
     if (path == P_F32) {
         *rode = a.rider_units > 0;

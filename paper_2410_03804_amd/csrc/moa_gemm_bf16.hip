@@ -26,8 +26,8 @@
 
 namespace moa {
 
-template <int WR, int WF, int MR, int NF, int SX, int SW, int WK>
-__global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(LinDev a)
+template <int WR, int WF, int MR, int NF, int SX, int SW, int WK, int SEGS>
+__global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(LinDev<SEGS> a)
 {
     using Loop = GemmLoop<WR, WF, MR, NF, SX, SW, WK>;
     constexpr int BM = Loop::BM, BN = Loop::BN;
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(LinDev a)
     // feature tiles for all row tiles, so that its slice of W is fetched into its L2 once.
     const int bx = (int)blockIdx.x - a.lead_blocks, xcd = bx & 7, j = bx >> 3;
     const int ftile = xcd * a.tiles_per_xcd + j % a.tiles_per_xcd;
-    if (ftile >= a.tile_begin[LIN_SEGS]) return;
+    if (ftile >= a.tile_begin[SEGS]) return;
     const int rest = j / a.tiles_per_xcd, rt = rest % a.row_tiles, split = rest / a.row_tiles;
     const int s = a.segment(ftile);
     const int n0 = (ftile - a.tile_begin[s]) * (a.gated ? BN / 2 : BN), N = a.seg[s].N, K = a.K;
@@ -247,6 +247,43 @@ size_t linear_workspace_bytes(int dtype, int64_t R, int K, std::initializer_list
     return most;
 }
 
+template <int SEGS>
+static hipError_t launch_tile(const LinArgs &a, const GemmPlan &p, hipStream_t stream, bool *fused, int *splits)
+{
+    const GemmTile &t = kTiles[p.tile];
+    LinDev<SEGS> ga(a);
+    ga.splits = *splits = p.splits;
+    ga.part = (float *)a.ws;
+    ga.gated = a.epi == LinArgs::EPI_SWIGLU && t.gated && p.splits == 1;
+    *fused = ga.gated || (a.epi == LinArgs::EPI_ADD_F32 && p.splits == 1);
+    int ft = 0;
+    for (int s = 0; s < a.nseg; ++s) {
+        ga.tile_begin[s] = ft;
+        if (!ga.gated) ft += (a.seg[s].N + t.bn - 1) / t.bn;
+        else if (s == 0) ft = (2 * a.seg[0].N + t.bn - 1) / t.bn;
+    }
+    for (int s = a.nseg; s <= SEGS; ++s) ga.tile_begin[s] = ft;
+    ga.tiles_per_xcd = (ft + 7) / 8;
+    ga.row_tiles = (int)((a.R + t.bm - 1) / t.bm);
+    ga.lead_blocks = (a.rider_units + 7) & ~7;      // a multiple of the XCD count: the tile mapping keeps its phase
+    const int64_t blocks = ga.lead_blocks + (int64_t)8 * ga.tiles_per_xcd * ga.row_tiles * ga.splits;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    hipError_t e = hipSuccess;
+    static bool raised[sizeof(kTiles) / sizeof(kTiles[0])][16] = {};
+    switch (p.tile) {
+#define MOA_GEMM_LAUNCH(id, WR, WF, MR, NF, SX, SW, WK, US1, USM, US2)                                                               \
+    case id:                                                                                                                         \
+        e = raise_lds_limit_once(raised[id], (const void *)k_linear_bf16<WR, WF, MR, NF, SX, SW, WK, SEGS>, t.lds);                  \
+        if (e != hipSuccess) return e;                                                                                               \
+        prof_begin(K_LIN_BF16 + 64 * (id + 1), stream);                                                                              \
+        MOA_KLAUNCH((k_linear_bf16<WR, WF, MR, NF, SX, SW, WK, SEGS>), dim3((unsigned)blocks), dim3(t.threads), t.lds, stream, ga);  \
+        break;
+        MOA_GEMM_TILES(MOA_GEMM_LAUNCH)
+    }
+    prof_end(stream);
+    return hipGetLastError();
+}
+
 // One launch.  *fused: it applied a.epi; *splits > 1: the sums of that many K slices are in a.ws, to be added up.
 hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused, int *splits)
 {
@@ -260,41 +297,10 @@ hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused,
     // 71 in the 64 x 64 of four slices)
     if (p.splits > 1 && !(a.ws && a.ws_bytes >= partial_bytes(a.R, ntot, p.splits) && (((uintptr_t)a.ws) & 15) == 0))
         p = plan_gemm(a.R, a.K, n_seg, a.nseg, a.epi, a.in_order, a.same_sums, 1);
-    const GemmTile &t = kTiles[p.tile];
-    LinDev ga(a);
-    ga.splits = *splits = p.splits;
-    ga.part = (float *)a.ws;
-    ga.gated = a.epi == LinArgs::EPI_SWIGLU && t.gated && p.splits == 1;
-    *fused = ga.gated || (a.epi == LinArgs::EPI_ADD_F32 && p.splits == 1);
-    int ft = 0;
-    for (int s = 0; s < a.nseg; ++s) {
-        ga.tile_begin[s] = ft;
-        if (!ga.gated) ft += (a.seg[s].N + t.bn - 1) / t.bn;
-        else if (s == 0) ft = (2 * a.seg[0].N + t.bn - 1) / t.bn;
-    }
-    for (int s = a.nseg; s <= LIN_SEGS; ++s) ga.tile_begin[s] = ft;
-    ga.tiles_per_xcd = (ft + 7) / 8;
-    ga.row_tiles = (int)((a.R + t.bm - 1) / t.bm);
-    ga.lead_blocks = (a.rider_units + 7) & ~7;      // a multiple of the XCD count: the tile mapping keeps its phase
-    const int64_t blocks = ga.lead_blocks + (int64_t)8 * ga.tiles_per_xcd * ga.row_tiles * ga.splits;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    hipError_t e = hipSuccess;
-    static bool raised[sizeof(kTiles) / sizeof(kTiles[0])][16] = {};
-    switch (p.tile) {
-#define MOA_GEMM_LAUNCH(id, WR, WF, MR, NF, SX, SW, WK, US1, USM, US2)                                                              \
-    case id:                                                                                                                   \
-        e = raise_lds_limit_once(raised[id], (const void *)k_linear_bf16<WR, WF, MR, NF, SX, SW, WK>, t.lds);                  \
-        if (e != hipSuccess) return e;                                                                                         \
-        prof_begin(K_LIN_BF16 + 64 * (id + 1), stream);                                                                        \
-        MOA_KLAUNCH((k_linear_bf16<WR, WF, MR, NF, SX, SW, WK>), dim3((unsigned)blocks), dim3(t.threads), t.lds, stream, ga);  \
-        break;
-        MOA_GEMM_TILES(MOA_GEMM_LAUNCH)
-    }
-    prof_end(stream);
-    return hipGetLastError();
+    return a.nseg <= LIN_FEW ? launch_tile<LIN_FEW>(a, p, stream, fused, splits) : launch_tile<LIN_SEGS>(a, p, stream, fused, splits);
 }
 
-// the kernel's name as a profiler prints it
+// the kernel's name as a profiler prints it, without SEGS
 const char *linear_bf16_name(int variant)
 {
     static const char *const names[] = {

@@ -34,7 +34,8 @@ __device__ __forceinline__ void st4(bf16_t *p, const f32x4 &v)
 }
 
 // the integer work in the first workgroups of the grid; true when this workgroup was one of them
-__device__ __forceinline__ bool f32_lead_block(const LinDev &a, int32_t *lds)
+template <int SEGS>
+__device__ __forceinline__ bool f32_lead_block(const LinDev<SEGS> &a, int32_t *lds)
 {
     if ((int)blockIdx.x >= a.lead_blocks) return false;
     if ((int)blockIdx.x < a.rider_units && threadIdx.x < 64)
@@ -42,13 +43,13 @@ __device__ __forceinline__ bool f32_lead_block(const LinDev &a, int32_t *lds)
     return true;
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_linear_f32_latency(LinDev a)
+template <typename T, int SEGS>
+__global__ __launch_bounds__(256) void k_linear_f32_latency(LinDev<SEGS> a)
 {
     constexpr int UN = 4;                         // 16-column steps of K a wavefront has in flight
     __shared__ float red[4][16][20];              // 20: rows of four-float stores land on different banks
     if (f32_lead_block(a, (int32_t *)red)) return;
-    const int ntiles = a.tile_begin[LIN_SEGS];
+    const int ntiles = a.tile_begin[SEGS];
     const int bx = (int)blockIdx.x - a.lead_blocks, tile = bx % ntiles;
     const int64_t r0 = (int64_t)(bx / ntiles) * 16;
     const int s = a.segment(tile);
@@ -100,14 +101,14 @@ __global__ __launch_bounds__(256) void k_linear_f32_latency(LinDev a)
     if (off >= 0) st<T>((T *)sp.dst + off, v);
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_linear_f32_tile(LinDev a)
+template <typename T, int SEGS>
+__global__ __launch_bounds__(256) void k_linear_f32_tile(LinDev<SEGS> a)
 {
     constexpr int BK = 32, LD = BK + 4;           // 36-float rows: the 32 rows of an operand read hit 64 different banks
     __shared__ __attribute__((aligned(16))) float Ws[2][64 * LD];
     __shared__ __attribute__((aligned(16))) float Xs[2][64 * LD];
     if (f32_lead_block(a, (int32_t *)Ws)) return;
-    const int ntiles = a.tile_begin[LIN_SEGS];
+    const int ntiles = a.tile_begin[SEGS];
     const int bx = (int)blockIdx.x - a.lead_blocks, tile = bx % ntiles;
     const int64_t r0 = (int64_t)(bx / ntiles) * 64;
     const int s = a.segment(tile);
@@ -205,9 +206,10 @@ bool linear_f32_ok(int dtype, const LinArgs &a)
 // step groups in one way or another (LinArgs::same_sums) count twice their widest segment: a layer's Q/K/V.
 constexpr int64_t F32_TILE_MIN_WORKGROUPS = 128;
 
-hipError_t launch_linear_f32(int dtype, const LinArgs &a, hipStream_t stream)
+template <int SEGS>
+static hipError_t launch_f32_as(int dtype, const LinArgs &a, hipStream_t stream)
 {
-    LinDev fa(a);
+    LinDev<SEGS> fa(a);
     const size_t piece = dtype == DT_BF16 ? 8 : 16;
     int64_t t64 = 0, widest = 0;
     for (int s = 0; s < a.nseg; ++s) {
@@ -222,21 +224,26 @@ hipError_t launch_linear_f32(int dtype, const LinArgs &a, hipStream_t stream)
     const int edge = big ? 64 : 16;
     int t = 0;
     for (int s = 0; s < a.nseg; ++s) { fa.tile_begin[s] = t; t += (a.seg[s].N + edge - 1) / edge; }
-    for (int s = a.nseg; s <= LIN_SEGS; ++s) fa.tile_begin[s] = t;
+    for (int s = a.nseg; s <= SEGS; ++s) fa.tile_begin[s] = t;
     fa.lead_blocks = a.rider_units;
     const int64_t blocks = fa.lead_blocks + (int64_t)t * ((a.R + edge - 1) / edge);
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
     prof_begin(big ? K_LIN_F32_TILE : K_LIN_F32_LATENCY, stream);
     if (dtype == DT_BF16) {
-        if (big) MOA_KLAUNCH(k_linear_f32_tile<bf16_t>, grid, dim3(256), 0, stream, fa);
-        else MOA_KLAUNCH(k_linear_f32_latency<bf16_t>, grid, dim3(256), 0, stream, fa);
+        if (big) MOA_KLAUNCH((k_linear_f32_tile<bf16_t, SEGS>), grid, dim3(256), 0, stream, fa);
+        else MOA_KLAUNCH((k_linear_f32_latency<bf16_t, SEGS>), grid, dim3(256), 0, stream, fa);
     } else {
-        if (big) MOA_KLAUNCH(k_linear_f32_tile<float>, grid, dim3(256), 0, stream, fa);
-        else MOA_KLAUNCH(k_linear_f32_latency<float>, grid, dim3(256), 0, stream, fa);
+        if (big) MOA_KLAUNCH((k_linear_f32_tile<float, SEGS>), grid, dim3(256), 0, stream, fa);
+        else MOA_KLAUNCH((k_linear_f32_latency<float, SEGS>), grid, dim3(256), 0, stream, fa);
     }
     prof_end(stream);
     return hipGetLastError();
+}
+
+hipError_t launch_linear_f32(int dtype, const LinArgs &a, hipStream_t stream)
+{
+    return a.nseg <= LIN_FEW ? launch_f32_as<LIN_FEW>(dtype, a, stream) : launch_f32_as<LIN_SEGS>(dtype, a, stream);
 }
 
 }  // namespace moa

@@ -183,7 +183,8 @@ int32_t moa_probe_mfma(int32_t iters, void *scratch4, int64_t *flops_host, void 
     return hipGetLastError() == hipSuccess ? MOA_OK : MOA_ERR_HIP;
 }
 
-// ids are base + 64 * variant; the variant spells the template arguments the way a profiler prints them
+// ids are base + 64 * variant; the variant spells the template arguments the way a profiler prints them (but not the room for segments or
+// calls, LinDev and AttnGroup)
 const char *moa_profile_kernel_name(int32_t kernel)
 {
     static thread_local char buf[96];
