@@ -572,6 +572,12 @@ struct AttnBufs {
 static thread_local const int *t_sites = nullptr;
 // a Self-Attention layer that is part of a step: its projections too may share a launch with others
 static thread_local bool t_step_sa = false;
+// a step's pieces on two streams at once (AttnArgs::beside)
+static thread_local int t_beside = 0;
+struct BesideScope {
+    BesideScope() { t_beside = 1; }
+    ~BesideScope() { t_beside = 0; }
+};
 static const int kSaSites[3] = {S_SA_QKV, S_SA_CORE, S_SA_OPROJ};
 
 static int32_t attn_check(const char *who, const moa_shape_t *shape, const void *wq, const void *wk, const void *wv,
@@ -648,6 +654,7 @@ static AttnArgs attn_core_args(const moa_shape_t *shape, const void *q, int32_t 
 {
     AttnArgs aa = {};
     aa.dtype = shape->dtype;
+    aa.beside = t_beside;
     aa.q = q;
     aa.kcache = kcache;
     aa.vcache = vcache;
@@ -1824,6 +1831,7 @@ static int32_t draft_step_concurrent_sa(const moa_step_args_t *args, const moa_s
     char *scr_main = (char *)a->ws + L.total() - L.scratch, *scr_side = scr_main + L.scratch;
     const StepBufs bf = carve_step_bufs(a, L, scr_side + L.attn_each, a->ws_bytes - L.total() - L.attn_each, nullptr, 0);
     std::lock_guard<std::mutex> lk(ss->enqueue);
+    BesideScope beside;
 
     int32_t rc = moa_tree_build(a->parent, a->B, a->M, a->mask, a->depth, a->dev_status, main);
     if (rc) return rc;

@@ -388,6 +388,7 @@ struct AttnArgs {
     // first Mt are keys.  Zero = the whole tree: mask_rows = Mq, tree_cap = Mt (filled in by launch_attn).
     int tree_cap, mask_rows, mask_row0;
     int empty_is_error;   // cross-attention: len == 0 -> flag + zeros
+    int beside;           // host: launches of another stream run at the same time
     int32_t *dev_status;
     void *ws;
     size_t ws_bytes;
