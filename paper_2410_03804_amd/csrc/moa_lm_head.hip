@@ -170,10 +170,11 @@ int32_t moa_lm_head_argmax(int32_t dtype, const void *x, int32_t R, int32_t d, c
         prof_set_site(S_LM_HEAD);
         // Wide tiles keep the activations' share of what goes through a compute unit small; with fewer of them than two
         // per compute unit the narrow ones fill the chip better (40 x 4096 x 32000: 50 against 58 us).
+        // 17 to 32 rows: three stages of activations, 18 x 4096 x 128256 174 us, 30 rows 178; two of them up to 4 us more on some cards.
         const bool wide = V >= 2 * 256 * 128;
         hipError_t e;
         if (a.R <= 16) e = launch_head<1, 1, 1, 2, 3, 3, 2>(&a, pairs, st);
-        else if (a.R <= 32) e = launch_head<2, 1, 1, 2, 2, 3, 2>(&a, pairs, st);
+        else if (a.R <= 32) e = launch_head<2, 1, 1, 2, 3, 3, 2>(&a, pairs, st);
         else if (a.R <= 64) e = wide ? launch_head<2, 2, 2, 2, 3, 3, 1>(&a, pairs, st) : launch_head<2, 2, 2, 1, 4, 6, 1>(&a, pairs, st);
         else if (a.R <= 128) e = wide ? launch_head<2, 2, 4, 2, 2, 3, 1>(&a, pairs, st) : launch_head<4, 2, 2, 2, 4, 4, 1>(&a, pairs, st);
         else e = launch_head<4, 2, 4, 4, 2, 2, 1>(&a, pairs, st);
