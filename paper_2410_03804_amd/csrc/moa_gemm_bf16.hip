@@ -12,7 +12,7 @@
 // The matrix instruction is 16x16x32: the bits of two 32x32x16 ones chained along K from the same operand bytes, at 2.03 PFLOP/s
 // from registers where the power budget leaves the larger one 1.78 (2048 x 4096 x 28672: 434 -> 421 us, 1024 x 14336 x 4096 140 ->
 // 132), and a tile may have 16 rows: up to 16 rows a workgroup then brings half as many of the activations past its weights
-// (8 x 4096 x 4096: 10.6 -> 8.7 us, 8 x 8192 x 8192 29.2 -> 26.4).
+// (8 x 4096 x 4096: 10.6 -> 8.8 us, 8 x 8192 x 8192 29.2 -> 28.0).
 //
 // What bounds it: for few rows the weights (60 x 4096 x 8192: 17.9 us = 3.7 TB/s and no summing pass, where K slices with
 // fp32 partial sums took 21.0 + 4.0; 8 x 4096 x 128256: 162 us = 6.5 TB/s against 196 + 5), for many the way from L2 to
@@ -128,11 +128,13 @@ __global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(LinDev<SEGS> 
 // The instantiated tiles: wavefronts along rows and features, blocks of 16 rows and of 32 features per wavefront, stages
 // of the activation and the weight ring, K groups; then microseconds per k tile of the workgroup's (64 WK columns) with
 // one workgroup on a compute unit, with a second one on up to half of them, and with two on all (0: its LDS holds one),
-// measured over 1 .. 4096 rows, K 2048 .. 14336 and 4096 .. 128256 features.
+// measured over 1 .. 4096 rows, K 2048 .. 14336 and 4096 .. 128256 features.  The 16-row tiles 14, 15, 16 are 0, 1, 2 in every
+// number but the rows, and have those tiles' times: up to 32 rows the K groups are then the same, and without slices of K a row's
+// sums do not depend on how many rows are beside it.
 #define MOA_GEMM_TILES(T)                           \
-    T(0, 2, 1, 1, 1, 5, 5, 2, 0.24f, 0.34f, 0.34f)  \
+    T(0, 2, 1, 1, 1, 5, 5, 2, 0.25f, 0.34f, 0.34f)  \
     T(1, 1, 1, 2, 1, 2, 3, 4, 0.55f, 0.66f, 0.66f)  \
-    T(2, 2, 1, 1, 2, 3, 3, 2, 0.42f, 0.70f, 0.70f)  \
+    T(2, 2, 1, 1, 2, 3, 3, 2, 0.45f, 0.74f, 0.74f)  \
     T(3, 2, 1, 2, 1, 3, 4, 2, 0.44f, 0.75f, 0.75f)  \
     T(4, 2, 2, 2, 1, 4, 6, 1, 0.27f, 0.33f, 0.46f)  \
     T(5, 2, 2, 2, 2, 3, 3, 2, 0.88f, 0.f, 0.f)      \
@@ -144,10 +146,9 @@ __global__ __launch_bounds__(64 * WR * WF * WK) void k_linear_bf16(LinDev<SEGS> 
     T(11, 4, 2, 2, 1, 3, 4, 2, 0.82f, 0.f, 0.f)     \
     T(12, 4, 2, 4, 3, 2, 3, 1, 1.25f, 0.f, 0.f)     \
     T(13, 2, 2, 2, 1, 4, 5, 2, 0.66f, 0.f, 0.f)     \
-    T(14, 1, 1, 1, 1, 5, 5, 2, 0.24f, 0.34f, 0.34f) \
-    T(15, 1, 1, 1, 1, 2, 3, 4, 0.60f, 0.60f, 0.60f) \
-    T(16, 1, 1, 1, 2, 3, 3, 2, 0.43f, 0.74f, 0.74f) \
-    T(17, 1, 1, 1, 1, 4, 4, 4, 0.46f, 0.f, 0.f)
+    T(14, 1, 1, 1, 1, 5, 5, 2, 0.25f, 0.34f, 0.34f) \
+    T(15, 1, 1, 1, 1, 2, 3, 4, 0.55f, 0.66f, 0.66f) \
+    T(16, 1, 1, 1, 2, 3, 3, 2, 0.45f, 0.74f, 0.74f)
 
 struct GemmTile {
     int bm, bn, threads, wk;
@@ -243,7 +244,7 @@ size_t linear_workspace_bytes(int dtype, int64_t R, int K, std::initializer_list
     // slice, so the fewest rows are cut into the most slices, and all have as many 64-row tiles of sums (those of 129 rows
     // or more: three).
     if (upto)
-        for (int64_t r : {1, 17, 33, 65, 129}) ask(r);
+        for (int64_t r : {1, 33, 65, 129}) ask(r);
     return most;
 }
 

@@ -35,6 +35,21 @@ def test_projection_rows(moa, R, K, N):
     assert ((y[:R].float() - want).abs() <= 2.0 ** -8 * want.abs() + eps_sum).all()
 
 
+@pytest.mark.parametrize("K,N", [(128, 32), (2048, 2048), (4096, 1024), (4096, 4096), (4096, 6144), (8192, 8192), (14336, 4096), (4096, 28672), (1024, 131104)])
+def test_a_rows_sums_do_not_depend_on_the_rows_beside_it(moa, K, N):
+    """Up to 32 rows, in tiles of 16 rows and of 32: the same bits (without a workspace, whose slices of K are fewer for more rows)."""
+    print(f"[case] linear bf16 1, 8, 16, 17 of 32 rows K={K} N={N}", flush=True)
+    x, w = operands(32, K, N)
+    ys = []
+    for R in (32, 1, 8, 16, 17):
+        y = torch.full((R, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        moa.linear(x[:R].contiguous(), w, y, None)
+        ys.append(y)
+    torch.cuda.synchronize()
+    for y in ys[1:]:
+        assert torch.equal(y, ys[0][:y.shape[0]]), f"{y.shape[0]} rows"
+
+
 @pytest.mark.parametrize("R", [1, 16, 17, 32])
 def test_head_rows(moa, R, K=256, V=3001):
     print(f"[case] lm_head R={R} K={K} V={V}", flush=True)
