@@ -117,8 +117,6 @@ __global__ __launch_bounds__(64) void k_attn_generic(AttnArgs a)
 }
 
 // ------------------------------------------------------------------ MFMA split-KV
-constexpr int KT = 32;        // keys per tile
-
 template <int DH, int NBLK, int CALLS>
 __global__ __launch_bounds__(256, NBLK == 1 ? 2 : 1) void k_attn_mfma(AttnGroup<CALLS> grp, SplitGeom geo)
 {
@@ -1055,70 +1053,15 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnGroup<CALLS> grp, SplitG
     if (lsum == 0.f && a.empty_is_error && piece == 0 && a.dev_status) atomicOr(a.dev_status, MOA_DEV_EMPTY_KEYS);
 }
 
-// ------------------------------------------------------------------ host side
+// ------------------------------------------------------------------ host side (which kernel: moa_attn_plan.h)
+static int attn_form() { return g_attn_form.load(std::memory_order_relaxed); }
+
 static bool mfma_ok(int dtype, int dh, const AttnArgs *a)
 {
     if (dtype != DT_BF16 || (dh != 64 && dh != 128)) return false;
     if (!a) return true;
     auto al = [](const void *p) { return (((uintptr_t)p) & 15) == 0; };
     return al(a->q) && al(a->kcache) && al(a->vcache) && al(a->ktree) && al(a->vtree) && al(a->out);
-}
-
-// 32-row blocks per wave of the split-KV kernel: one block per wave keeps two workgroups per CU, which measured
-// 25 % faster than two blocks per wave at RG = 512 even though K/V are then read by twice as many row tiles
-constexpr int ATTN_NBLK = 1;
-
-// ncalls: how many of this shape in one launch (the number of key slices of either form does not depend on it)
-static SplitGeom split_geometry(int B, int Mq, int H, int Hkv, int dh, int P_cap, int ncalls)
-{
-    const int RG = (H / Hkv) * Mq;
-    const int rows = 128 * ATTN_NBLK, tiles_cap = (P_cap + KT - 1) / KT;
-    SplitGeom g;
-    g.rowtiles = (RG + rows - 1) / rows;
-    g.rows_pad = g.rowtiles * rows;
-    int want = 512 / (B * Hkv * g.rowtiles);        // about two workgroups per compute unit
-    int most = tiles_cap / 2;                        // at least two tiles per slice
-    if (want > most) want = most;
-    if (want > 64) want = 64;
-    if (want < 1) want = 1;
-    g.nsplit = want;
-    g.wide = false;
-    const int form = g_attn_form.load(std::memory_order_relaxed);
-    if (dh != 128 || RG <= 128) return g;
-    // 256-row tiles, one workgroup per compute unit; never more scratch than the 128-row tiles' slices would take
-    SplitGeom w;
-    w.wide = true;
-    w.rowtiles = (RG + 255) / 256;
-    w.rows_pad = w.rowtiles * 256;
-    want = 256 / (B * Hkv * w.rowtiles);
-    most = ((P_cap + LK - 1) / LK) / 2;
-    if (want > most) want = most;
-    if (want > 64) want = 64;
-    while (want > 1 && (int64_t)want * w.rows_pad > (int64_t)g.nsplit * g.rows_pad) --want;
-    if (want < 1) want = 1;
-    w.nsplit = want;
-    // Which one, by an estimate in microseconds.  A round of 128-row workgroups takes 1.5 per tile of 32 keys with two per
-    // compute unit and 1.2 with one; one of 256-row workgroups 1.05, 0.15 for each time its accumulators follow a new maximum
-    // (nearly always on the first 32 tiles of a slice, then ever more rarely), and 4 more in front and behind.  It
-    // decides where the rows fill their last tile badly (8 sequences x 32768 keys x 8 KV heads: 260 .. 384 rows in three tiles
-    // of 128 against two of 256, which leave half of the chip idle), where the rows of an XCD's units need one workgroup
-    // more than it has compute units, and where a slice is a few tiles.  Two calls in one launch can fill what one leaves idle.
-    // Over 456 measured calls (512 .. 32768 keys, 1 .. 16 sequences, 132 .. 1024 rows) it is 0.5 % behind the better form.
-    const int64_t units = (int64_t)ncalls * B * Hkv;
-    const int64_t per128 = (tiles_cap + g.nsplit - 1) / g.nsplit, wgs128 = units * g.nsplit * g.rowtiles;
-    const int64_t per256 = (tiles_cap + w.nsplit - 1) / w.nsplit, rounds256 = ((units * w.nsplit + 7) / 8 * 8 * w.rowtiles + 255) / 256;
-    const int64_t rest = wgs128 % 512;
-    const float us128 = (float)per128 * (1.5f * (float)(wgs128 / 512) + (rest == 0 ? 0.f : rest <= 256 ? 1.2f : 1.5f));
-    const float tiles = (float)per256, follows = tiles <= 32.f ? tiles : 32.f + 32.f * logf(tiles / 32.f);
-    const bool wide = form == MOA_ATTN_KERNEL_SPLIT_WIDE || 4.f + (float)rounds256 * (1.05f * tiles + 0.15f * follows) < us128;
-    return wide ? w : g;
-}
-
-// scratch of one of `ncalls` calls in a launch
-static size_t split_bytes(const SplitGeom &g, int B, int Hkv, int dh)
-{
-    const size_t rows = g.nsplit > 1 || !g.wide ? (size_t)B * Hkv * g.nsplit * g.rows_pad : 0;
-    return rows * ((size_t)dh * sizeof(f16_t) + 2 * sizeof(float)) + 256;
 }
 
 size_t attn_workspace_bytes(int dtype, int B, int Mq, int H, int Hkv, int dh, int P_cap, bool upto)
@@ -1136,9 +1079,12 @@ size_t attn_workspace_bytes(int dtype, int B, int Mq, int H, int Hkv, int dh, in
         if (slices < units) slices = units;
         return (size_t)slices * 128 * ATTN_NBLK * row_bytes + 256;
     }
-    size_t bytes = 0;
-    for (int ncalls : {1, 2}) bytes = std::max(bytes, split_bytes(split_geometry(B, Mq, H, Hkv, dh, P_cap, ncalls), B, Hkv, dh));
-    return bytes;
+    return split_room(attn_form(), B, Mq, H, Hkv, dh, P_cap);
+}
+
+bool attn_takes_whole_range(int dtype, int B, int Mq, int Mt, int H, int Hkv, int dh, int P_cap)
+{
+    return dtype != DT_BF16 || (mfma_ok(dtype, dh, nullptr) && want_whole(attn_form(), B, Mq, Mt, H, Hkv, P_cap));
 }
 
 static hipError_t launch_attn_generic(const AttnArgs &a, hipStream_t stream)
@@ -1192,35 +1138,6 @@ static hipError_t launch_attn_f32_as(const AttnArgs *calls, int n, hipStream_t s
     return a.dh == 128 ? launch_f32_as<128, CALLS>(grp, (unsigned)grid, stream) : launch_f32_as<64, CALLS>(grp, (unsigned)grid, stream);
 }
 
-static bool attn_split_ok(const AttnArgs &a, int P_cap_geo)
-{
-    return mfma_ok(a.dtype, a.dh, &a) && a.ws && (((uintptr_t)a.ws) & 15) == 0 &&
-           a.ws_bytes >= attn_workspace_bytes(a.dtype, a.B, a.Mq, a.H, a.Hkv, a.dh, P_cap_geo);
-}
-
-// Which MFMA kernel.  The whole-key-range form needs one launch, writes no partial results and has the shorter
-// fixed part, but re-reads K/V once per 32 query rows and runs one workgroup per CU: it wins while the call is
-// latency-bound, i.e. while its workgroups fit the chip in one round and the key range is short (C1: 14.5 us
-// against 17.8 + 6.8 us).  With more work the split form (128 rows per workgroup and two workgroups per CU, or 256
-// rows and one, see split_geometry; then the merge) is ahead (B = 16, prefixes up to 2048: 122 against 166 us).  moa_debug_force_attn_kernel overrides the
-// choice (the parity tests run every case through both forms).
-constexpr int FUSED_MAX_KEYS = 8192;
-constexpr int FUSED_MAX_WORKGROUPS = 256;
-static bool want_fused(int B, int Mq, int Mt, int H, int Hkv, int P_cap)
-{
-    const int form = g_attn_form.load(std::memory_order_relaxed);
-    if (form == MOA_ATTN_KERNEL_SPLIT || form == MOA_ATTN_KERNEL_SPLIT_WIDE) return false;
-    if (form == MOA_ATTN_KERNEL_WHOLE) return true;
-    const int64_t wgs = (int64_t)B * Hkv * (((H / Hkv) * Mq + 31) / 32);
-    return P_cap + Mt <= FUSED_MAX_KEYS && wgs <= FUSED_MAX_WORKGROUPS;
-}
-static bool want_fused(const AttnArgs &a) { return want_fused(a.B, a.Mq, a.Mt, a.H, a.Hkv, a.P_cap); }
-
-bool attn_takes_whole_range(int dtype, int B, int Mq, int Mt, int H, int Hkv, int dh, int P_cap)
-{
-    return dtype != DT_BF16 || (mfma_ok(dtype, dh, nullptr) && want_fused(B, Mq, Mt, H, Hkv, P_cap));
-}
-
 // calls of identical shape (B, Mq, H, Hkv, dh)
 template <int DH, int NW, int CALLS>
 static hipError_t launch_fused_as(const AttnGroup<CALLS> &grp, unsigned grid, hipStream_t stream)
@@ -1263,20 +1180,9 @@ static hipError_t launch_attn_fused_as(const AttnArgs *calls, int n, hipStream_t
 }
 
 template <int CALLS>
-static hipError_t launch_attn_split_as(const AttnArgs *calls, int n, hipStream_t stream)
+static hipError_t launch_attn_split_as(const AttnArgs *calls, int n, const SplitGeom &g, hipStream_t stream)
 {
     const AttnArgs &a = calls[0];
-    int cap = a.P_cap;
-    size_t room = a.ws_bytes;
-    for (int i = 1; i < n; ++i) {
-        cap = std::max(cap, calls[i].P_cap);
-        room = std::min(room, calls[i].ws_bytes);
-    }
-    const SplitGeom g = split_geometry(a.B, a.Mq, a.H, a.Hkv, a.dh, cap, n);
-    if (n > 2 && split_bytes(g, a.B, a.Hkv, a.dh) > room) {      // row tiles of another height than one or two calls take
-        hipError_t e = launch_attn_split_as<CALLS>(calls, 2, stream);
-        return e != hipSuccess ? e : launch_attn_split_as<CALLS>(calls + 2, n - 2, stream);
-    }
     AttnGroup<CALLS> grp = group_of<CALLS>(calls, n);
     const int nblocks = n * a.B * a.Mq * a.H;
     hipError_t e;
@@ -1309,9 +1215,9 @@ static hipError_t launch_attn_fused(const AttnArgs *calls, int n, hipStream_t st
 {
     return n <= ATTN_FEW ? launch_attn_fused_as<ATTN_FEW>(calls, n, stream) : launch_attn_fused_as<ATTN_CALLS>(calls, n, stream);
 }
-static hipError_t launch_attn_split(const AttnArgs *calls, int n, hipStream_t stream)
+static hipError_t launch_attn_split(const AttnArgs *calls, int n, const SplitGeom &g, hipStream_t stream)
 {
-    return n <= ATTN_FEW ? launch_attn_split_as<ATTN_FEW>(calls, n, stream) : launch_attn_split_as<ATTN_CALLS>(calls, n, stream);
+    return n <= ATTN_FEW ? launch_attn_split_as<ATTN_FEW>(calls, n, g, stream) : launch_attn_split_as<ATTN_CALLS>(calls, n, g, stream);
 }
 
 // whole-tree defaults of the tree window; false when the window does not fit its tree
@@ -1322,54 +1228,43 @@ static bool tree_window(AttnArgs &a)
     return a.mask_row0 >= 0 && a.mask_row0 + a.Mq <= a.mask_rows && a.Mt <= a.tree_cap;
 }
 
-hipError_t launch_attn(const AttnArgs &a_in, hipStream_t stream)
-{
-    AttnArgs a = a_in;
-    if (!tree_window(a)) return hipErrorInvalidValue;
-    if (mfma_ok(a.dtype, a.dh, &a) && want_fused(a)) return launch_attn_fused(&a, 1, stream);
-    if (attn_split_ok(a, a.P_cap)) return launch_attn_split(&a, 1, stream);
-    if (attn_f32_ok(a)) return launch_attn_f32(&a, 1, stream);
-    return launch_attn_generic(a, stream);
-}
+hipError_t launch_attn(const AttnArgs &a, hipStream_t stream) { return launch_attn_group(&a, 1, stream); }
 
 hipError_t launch_attn_group(const AttnArgs *calls, int n, hipStream_t stream)
 {
     if (n < 1 || n > ATTN_CALLS) return hipErrorInvalidValue;
-    AttnArgs a[ATTN_CALLS];
-    int cap = 0;
-    bool same = true, mfma = true, f32 = true;
+    AttnArgs a[ATTN_CALLS], part[ATTN_CALLS];
+    AttnCore core[ATTN_CALLS];
+    bool same = true, f32 = true;
     for (int i = 0; i < n; ++i) {
         a[i] = calls[i];
         if (!tree_window(a[i])) return hipErrorInvalidValue;
-        cap = std::max(cap, a[i].P_cap);
         same = same && a[i].dtype == a[0].dtype && a[i].B == a[0].B && a[i].Mq == a[0].Mq && a[i].H == a[0].H && a[i].Hkv == a[0].Hkv && a[i].dh == a[0].dh;
-        mfma = mfma && mfma_ok(a[i].dtype, a[i].dh, &a[i]);
         f32 = f32 && attn_f32_ok(a[i]);
+        core[i] = {a[i].P_cap, a[i].Mt, mfma_ok(a[i].dtype, a[i].dh, &a[i]), a[i].ws && ((uintptr_t)a[i].ws & 15) == 0 ? a[i].ws_bytes : 0};
     }
-    if (n > 1 && same && mfma) {
-        // those that run over the whole key range in one launch, those that split it in another
-        AttnArgs part[ATTN_CALLS];
-        int whole = 0, split = 0;
-        for (int i = 0; i < n; ++i)
-            if (want_fused(a[i])) part[whole++] = a[i];
-        bool ok = true;
-        for (int i = 0; i < n; ++i) {
-            if (want_fused(a[i])) continue;
-            ok = ok && attn_split_ok(a[i], cap);
-            part[whole + split++] = a[i];
+    hipError_t e = hipSuccess;
+    if (!same) {
+        for (int i = 0; i < n && e == hipSuccess; ++i) e = launch_attn_group(calls + i, 1, stream);
+        return e;
+    }
+    if (f32) return launch_attn_f32(a, n, stream);
+    AttnChoice choice[ATTN_CALLS];
+    choose_attn(attn_form(), a[0].B, a[0].Mq, a[0].H, a[0].Hkv, a[0].dh, core, n, choice);
+    bool done[ATTN_CALLS] = {};
+    for (int i = 0; i < n && e == hipSuccess; ++i) {
+        if (done[i]) continue;
+        int m = 0;
+        for (int k = i; k < n; ++k) {
+            if (done[k] || !choice[i].shares_with(choice[k])) continue;
+            part[m++] = a[k];
+            done[k] = true;
         }
-        if (ok) {
-            hipError_t e = whole ? launch_attn_fused(part, whole, stream) : hipSuccess;
-            if (e == hipSuccess && split) e = launch_attn_split(part + whole, split, stream);
-            return e;
-        }
+        if (choice[i].kind == AttnChoice::WHOLE) e = launch_attn_fused(part, m, stream);
+        else if (choice[i].kind == AttnChoice::SPLIT) e = launch_attn_split(part, m, choice[i].geo, stream);
+        else for (int k = 0; k < m && e == hipSuccess; ++k) e = attn_f32_ok(part[k]) ? launch_attn_f32(part + k, 1, stream) : launch_attn_generic(part[k], stream);
     }
-    if (n > 1 && same && f32) return launch_attn_f32(a, n, stream);
-    for (int i = 0; i < n; ++i) {
-        const hipError_t e = launch_attn(a[i], stream);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    return e;
 }
 
 }  // namespace moa

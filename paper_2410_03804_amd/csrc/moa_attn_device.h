@@ -1,6 +1,7 @@
 // What the attention kernels of moa_attn.hip and moa_attn_long.hip share.
 #ifndef MOA_ATTN_DEVICE_H
 #define MOA_ATTN_DEVICE_H
+#include "moa_attn_plan.h"
 #include "moa_common.h"
 #include "../../include/moa.h"
 
@@ -14,13 +15,6 @@ __device__ __forceinline__ int clamp_len(int len, int cap, int32_t *dev_status)
     }
     return len;
 }
-
-struct SplitGeom {
-    int nsplit;     // key-range slices
-    int rowtiles;   // workgroups along the G*Mq rows of one (sequence, KV head)
-    int rows_pad;   // rowtiles * rows per workgroup
-    bool wide;      // 256 rows per workgroup (k_attn_long) instead of 128
-};
 
 typedef _Float16 f16_t;
 typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
@@ -42,8 +36,7 @@ typedef short i16x4 __attribute__((ext_vector_type(4)));
 // become 0, which a softmax weight may
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// the kernel in 256-row tiles (moa_attn_long.hip): keys per tile, and the launch of the split pass
-constexpr int LK = 64;
+// the launch of the split pass in 256-row tiles (moa_attn_long.hip)
 template <int CALLS>
 hipError_t launch_attn_long(const AttnGroup<CALLS> &grp, const SplitGeom &g, hipStream_t stream);
 
