@@ -1236,8 +1236,7 @@ struct StepBufs {
     int32_t *old_len;              // memory lengths before this step's append
     char *q_ca, *h_ca;             // projected queries / concatenated heads of the CA
     int nv;                        // verification layers there are buffers for in common launches
-    char *q_v[STEP_VERIFY_GROUP], *h_v[STEP_VERIFY_GROUP];    // theirs
-    char *core_v[STEP_VERIFY_GROUP];                          // attention scratch of all but the first of them
+    VerifyMem v[STEP_VERIFY_GROUP];   // theirs (the first one's core has its scratch where the launch says)
     int first;                     // verification layers that share launches with the CA's
 };
 
@@ -1314,7 +1313,7 @@ static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, h
     }
     for (int l = l0; (which & 2) && l < l0 + n; ++l) {
         const void *w[3] = {a->v_wq_host[l], a->v_wk_host[l], a->v_wv_host[l]};
-        const StoreSpec st3[3] = {row_store(bf.q_v[l - l0], e), heads_store(a->v_ktree_host[l], Hkv, dh, M, M),
+        const StoreSpec st3[3] = {row_store(bf.v[l - l0].q, e), heads_store(a->v_ktree_host[l], Hkv, dh, M, M),
                                   heads_store(a->v_vtree_host[l], Hkv, dh, M, M)};
         for (int i = 0; i < 3; ++i) {
             LinSeg &g = la.seg[la.nseg++];
@@ -1471,9 +1470,10 @@ static int32_t piece_cores(const moa_step_args_t *a, const StepBufs &bf, int whi
     if (which & 1) calls[m++] = piece_ca_core_args(a, bf, scr, attn_each);
     for (int i = 0; (which & 2) && i < n; ++i) {
         const int l = l0 + i;
-        char *own = i > 0 ? bf.core_v[i] : scr + (which & 1 ? attn_each : 0);
-        calls[m++] = attn_core_args(a->shape, bf.q_v[i], a->B, a->M, a->v_kcache_host[l], a->v_vcache_host[l], a->prefix_len, a->P_cap, a->mask,
-                                    bf.h_v[i], a->v_ktree_host[l], a->v_vtree_host[l], a->dev_status, own, attn_each);
+        const VerifyMem &v = bf.v[i];
+        char *own = i > 0 ? v.core : scr + (which & 1 ? attn_each : 0);
+        calls[m++] = attn_core_args(a->shape, v.q, a->B, a->M, a->v_kcache_host[l], a->v_vcache_host[l], a->prefix_len, a->P_cap, a->mask,
+                                    v.h, a->v_ktree_host[l], a->v_vtree_host[l], a->dev_status, own, i > 0 ? v.core_bytes : attn_each);
     }
     prof_set_site(which == 3 ? S_PAIR_CORE : which == 1 ? S_CA_CORE : S_VERIFY_CORE);
     MOA_TRY_HIP(launch_attn_group(calls, m, st), "draft_step: attention cores");
@@ -1491,7 +1491,7 @@ static int32_t piece_oproj(const moa_step_args_t *a, const StepBufs &bf, int whi
     lo.ldx = e;
     lo.same_sums = LinArgs::SAME_SUMS_OUT;
     if (which & 1) lo.seg[lo.nseg++] = oproj_seg(sh, bf.h_ca, a->ca_wo, a->ca_out);
-    for (int l = l0; (which & 2) && l < l0 + n; ++l) lo.seg[lo.nseg++] = oproj_seg(sh, bf.h_v[l - l0], a->v_wo_host[l], a->v_out_host[l]);
+    for (int l = l0; (which & 2) && l < l0 + n; ++l) lo.seg[lo.nseg++] = oproj_seg(sh, bf.v[l - l0].h, a->v_wo_host[l], a->v_out_host[l]);
     lo.X = lo.seg[0].X;
     prof_set_site(which == 3 ? S_PAIR_OPROJ : which == 1 ? S_CA_OPROJ : S_VERIFY_OPROJ);
     MOA_TRY_HIP(launch_linear(sh->dtype, lo, st), "draft_step: output projections");
@@ -1519,8 +1519,7 @@ static int32_t piece_verify_layers(const moa_step_args_t *a, const StepBufs &bf,
     return MOA_OK;
 }
 
-// Further verification layers' buffers: queries and heads in `spare`, memory that the layout leaves, and where their cores'
-// partial results need any in `idle`, memory that is not in use while the cores run, and then in `spare` too.
+// spare, idle: see carve_verify
 static StepBufs carve_step_bufs(const moa_step_args_t *a, const GroupLayout &L, char *spare, size_t spare_bytes, char *idle, size_t idle_bytes)
 {
     char *p = (char *)a->ws;
@@ -1528,22 +1527,11 @@ static StepBufs carve_step_bufs(const moa_step_args_t *a, const GroupLayout &L, 
     bf.old_len = (int32_t *)p;
     bf.q_ca = p + L.len_bytes;
     bf.h_ca = bf.q_ca + L.qa;
-    bf.q_v[0] = bf.h_ca + L.qa;
-    bf.h_v[0] = bf.q_v[0] + L.qa;
-    bf.core_v[0] = nullptr;
+    bf.v[0] = {bf.h_ca + L.qa, bf.h_ca + 2 * L.qa, nullptr, 0};
     const moa_shape_t *s = a->shape;
     const size_t core = attn_takes_whole_range(s->dtype, a->B, a->M, a->M, s->n_q_heads, s->n_kv_heads, s->head_dim, a->P_cap) ? 0 : L.attn_each;
-    for (bf.nv = 1; bf.nv < STEP_VERIFY_GROUP && bf.nv < a->n_verify_layers; ++bf.nv) {
-        const bool in_idle = core <= idle_bytes;
-        const size_t take = 2 * L.qa + (in_idle ? 0 : core);
-        if (spare_bytes < take) break;
-        bf.q_v[bf.nv] = spare;
-        bf.h_v[bf.nv] = spare + L.qa;
-        bf.core_v[bf.nv] = in_idle ? idle : spare + 2 * L.qa;
-        if (in_idle) idle += core, idle_bytes -= core;
-        spare += take;
-        spare_bytes -= take;
-    }
+    const int most = a->n_verify_layers < STEP_VERIFY_GROUP ? a->n_verify_layers : STEP_VERIFY_GROUP;
+    bf.nv = carve_verify(bf.v, most, L.qa, core, spare, spare_bytes, idle, idle_bytes);
     bf.first = verify_run(a, 0, bf.nv, true);
     return bf;
 }

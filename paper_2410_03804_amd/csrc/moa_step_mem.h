@@ -1,4 +1,5 @@
-// Which verification layers of a step may share launches: a question of what memory they read and write.  Host arithmetic only.
+// Which verification layers of a step may share launches: a question of what memory they read and write, and of where their
+// intermediate results go.  Host arithmetic only.
 #pragma once
 #include <stddef.h>
 #include <stdint.h>
@@ -127,6 +128,31 @@ inline int verify_run(const moa_step_args_t *a, int l0, int most, bool with_rest
         bool joins = whole(l0 + n) && m.aligned && (!with_rest || apart_from_rest(a, m));
         for (int i = 0; joins && i < n; ++i) joins = m.apart(LayerMem(a, l0 + i));
         if (!joins) break;
+    }
+    return n;
+}
+
+// A verification layer's buffers in common launches: queries and heads, and scratch of its core -- none where cores of this
+// shape run over the whole key range (whatever they are made to do after all, nothing says that there is any).
+struct VerifyMem {
+    char *q, *h, *core;
+    size_t core_bytes;
+};
+
+// Those of the layers after the first (mem[0] is there), up to `most` in all: queries and heads of qa bytes each in `spare`, memory that
+// the step's layout leaves, and scratch of `core` bytes in `idle`, memory that is not in use while the cores run, and then in `spare` too.
+// How many layers there are buffers for.
+inline int carve_verify(VerifyMem *mem, int most, size_t qa, size_t core, char *spare, size_t spare_bytes, char *idle, size_t idle_bytes)
+{
+    int n = 1;
+    for (; n < most; ++n) {
+        const bool in_idle = core <= idle_bytes;
+        const size_t take = 2 * qa + (in_idle ? 0 : core);
+        if (spare_bytes < take) break;
+        mem[n] = {spare, spare + qa, core == 0 ? nullptr : in_idle ? idle : spare + 2 * qa, core};
+        if (core && in_idle) idle += core, idle_bytes -= core;
+        spare += take;
+        spare_bytes -= take;
     }
     return n;
 }

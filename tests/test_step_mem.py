@@ -39,11 +39,16 @@ def run(tmp_path_factory):
           f'    moa_step_args_t a = {{}};\n    a.shape = &s; a.B = {B}; a.M = a.Mq = {M}; a.P_cap = {P}; a.ca_P_cap = {CP}; a.T_lsa = {T}; a.n_verify_layers = n;\n'
     src += "".join(f"    a.{name} = (decltype(a.{name}))rest[{i}];\n" for i, name in enumerate(rest))
     src += "".join(f"    a.{arrays[name]} = (decltype(a.{arrays[name]}))layers[{i}];\n" for i, name in enumerate(LAYER))
-    src += "    return moa::verify_run(&a, l0, most, with_rest);\n}\n"
+    src += "    return moa::verify_run(&a, l0, most, with_rest);\n}\n" \
+           'extern "C" int carve(int most, size_t qa, size_t core, char *spare, size_t ns, char *idle, size_t ni, size_t *out)\n{\n' \
+           "    moa::VerifyMem m[4] = {};\n    const int n = moa::carve_verify(m, most, qa, core, spare, ns, idle, ni);\n" \
+           "    for (int i = 1; i < n; ++i, out += 4) out[0] = (size_t)m[i].q, out[1] = (size_t)m[i].h, out[2] = (size_t)m[i].core, out[3] = m[i].core_bytes;\n" \
+           "    return n;\n}\n"
     (d / "run.cpp").write_text(src)
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-Wno-unused-function", "-O1", "-shared", "-fPIC", f"-I{CSRC}", f"-I{d}", "-o",
                     str(d / "run.so"), str(d / "run.cpp")], check=True)
-    f = C.CDLL(str(d / "run.so")).run
+    so = C.CDLL(str(d / "run.so"))
+    f = so.run
 
     def call(rest_at, layers_at, l0, most, with_rest):
         n = len(layers_at)
@@ -51,6 +56,14 @@ def run(tmp_path_factory):
         cols = [(C.c_void_p * n)(*[la[k] for la in layers_at]) for k in LAYER]
         table = (C.c_void_p * len(LAYER))(*[C.addressof(c) for c in cols])
         return f(r, table, n, l0, most, int(with_rest))
+
+    def carve(most, qa, core, spare, spare_bytes, idle, idle_bytes):
+        """(queries, heads, core scratch, its bytes) of every layer after the first"""
+        out = (C.c_size_t * 12)()
+        z = C.c_size_t
+        n = so.carve(most, z(qa), z(core), C.c_void_p(spare), z(spare_bytes), C.c_void_p(idle), z(idle_bytes), out)
+        return [tuple(out[4 * i:4 * i + 4]) for i in range(n - 1)]
+    call.carve = carve
     return call
 
 
@@ -119,3 +132,30 @@ def test_any_overlap_ends_a_run(run, seed):
         assert got == want, (rest, layers, l0, most, with_rest)
         seen.add(want)
     assert seen == {1, 2, 3, 4}
+
+
+@pytest.mark.parametrize("core", [0, 512, 4096])
+def test_buffers_lie_apart_in_what_they_are_carved_from(run, core):
+    """Queries, heads and as much core scratch as is said to be there: each in the spare or the idle memory, none over another.
+    As many layers as there is room for: a core's scratch goes to the idle memory while that lasts, then to the spare one."""
+    rng, seen = random.Random(core), set()
+    for _ in range(300):
+        most, qa = rng.randint(1, 4), 256 * rng.randint(1, 6)
+        spare, idle = (1 << 20, 256 * rng.randint(0, 120)), (1 << 24, 256 * rng.randint(0, 50))
+        got = run.carve(most, qa, core, *spare, *idle)
+        spans = []
+        for q, h, at, there in got:
+            assert there == core and (at != 0) == (core > 0)
+            spans += [(q, q + qa), (h, h + qa)] + [(at, at + there)] * (there > 0)
+        for lo, hi in spans:
+            assert any(base <= lo and hi <= base + n for base, n in (spare, idle))
+        spans.sort()
+        assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:]))
+        in_idle = min(most - 1, idle[1] // core if core else most - 1)
+        fit = min(in_idle, spare[1] // (2 * qa))
+        fit += min(most - 1 - fit, max(0, spare[1] - 2 * qa * fit) // (2 * qa + core)) if fit == in_idle else 0
+        assert len(got) == fit
+        seen.add((len(got), any(at >= idle[0] for _, _, at, _ in got), any(0 < at < idle[0] for _, _, at, _ in got)))
+    assert {n for n, _, _ in seen} == {0, 1, 2, 3}
+    if core:
+        assert {(3, True, False), (3, True, True), (3, False, True)} <= seen
