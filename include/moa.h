@@ -384,9 +384,9 @@ int32_t moa_fold_projection(int32_t dtype, const void *w_outer, const void *w_in
  *    per stage, exactly as the single entry points would.
  * Integer results are identical under all three; floating-point results of 0 and 1 are
  * bit-identical (without the Self-Attention layer), those of 2, and of 1 with that layer, differ from
- * them only where the attention cores end up with a different number of key slices or row tiles of
- * another height (partials merged in another order); so may 0 and 1 themselves in workspaces that hold
- * different numbers of verification layers side by side. */
+ * them only where the cross-attention's core and the first verification layer's end up with a different
+ * number of key slices or row tiles of another height (partials merged in another order).  How much room
+ * the workspace has beyond what moa_workspace_bytes asks for changes no result. */
 enum { MOA_SCHED_GROUPED = 0, MOA_SCHED_TWO_STREAM = 1, MOA_SCHED_SEQUENTIAL = 2 };
 
 typedef struct {

@@ -1476,7 +1476,7 @@ static int32_t piece_cores(const moa_step_args_t *a, const StepBufs &bf, int whi
                                     v.h, a->v_ktree_host[l], a->v_vtree_host[l], a->dev_status, own, i > 0 ? v.core_bytes : attn_each);
     }
     prof_set_site(which == 3 ? S_PAIR_CORE : which == 1 ? S_CA_CORE : S_VERIFY_CORE);
-    MOA_TRY_HIP(launch_attn_group(calls, m, st), "draft_step: attention cores");
+    MOA_TRY_HIP(launch_attn_group(calls, m, which == 3, st), "draft_step: attention cores");
     return MOA_OK;
 }
 

@@ -1228,9 +1228,9 @@ static bool tree_window(AttnArgs &a)
     return a.mask_row0 >= 0 && a.mask_row0 + a.Mq <= a.mask_rows && a.Mt <= a.tree_cap;
 }
 
-hipError_t launch_attn(const AttnArgs &a, hipStream_t stream) { return launch_attn_group(&a, 1, stream); }
+hipError_t launch_attn(const AttnArgs &a, hipStream_t stream) { return launch_attn_group(&a, 1, false, stream); }
 
-hipError_t launch_attn_group(const AttnArgs *calls, int n, hipStream_t stream)
+hipError_t launch_attn_group(const AttnArgs *calls, int n, bool pair, hipStream_t stream)
 {
     if (n < 1 || n > ATTN_CALLS) return hipErrorInvalidValue;
     AttnArgs a[ATTN_CALLS], part[ATTN_CALLS];
@@ -1245,12 +1245,12 @@ hipError_t launch_attn_group(const AttnArgs *calls, int n, hipStream_t stream)
     }
     hipError_t e = hipSuccess;
     if (!same) {
-        for (int i = 0; i < n && e == hipSuccess; ++i) e = launch_attn_group(calls + i, 1, stream);
+        for (int i = 0; i < n && e == hipSuccess; ++i) e = launch_attn_group(calls + i, 1, false, stream);
         return e;
     }
     if (f32) return launch_attn_f32(a, n, stream);
     AttnChoice choice[ATTN_CALLS];
-    choose_attn(attn_form(), a[0].B, a[0].Mq, a[0].H, a[0].Hkv, a[0].dh, core, n, choice);
+    choose_attn(attn_form(), a[0].B, a[0].Mq, a[0].H, a[0].Hkv, a[0].dh, core, n, pair, choice);
     bool done[ATTN_CALLS] = {};
     for (int i = 0; i < n && e == hipSuccess; ++i) {
         if (done[i]) continue;

@@ -25,7 +25,7 @@ struct SplitGeom {
     bool wide;      // 256 rows per workgroup (k_attn_long) instead of 128
 };
 
-// ncalls: how many of this shape in one launch (the number of key slices of either form does not depend on it)
+// ncalls: 1, or 2 of this shape in one launch (the number of key slices of either form does not depend on it)
 inline SplitGeom split_geometry(int form, int B, int Mq, int H, int Hkv, int dh, int P_cap, int ncalls)
 {
     const int RG = (H / Hkv) * Mq;
@@ -114,29 +114,29 @@ struct AttnChoice {
     }
 };
 
-// What each of n cores that may share launches takes; those with the same choice can share one.  Whatever geometry a core is
-// given is one that its own scratch holds: geometries at a smaller P_cap can need more than at a larger one (4 sequences x 1408 rows:
-// 135 KB more at 8065 keys than at 8192), so scratch is compared at the P_cap that the geometry is for.
-inline void choose_attn(int form, int B, int Mq, int H, int Hkv, int dh, const AttnCore *core, int n, AttnChoice *out)
+// What each of n cores that may share launches takes; those with the same choice can share one.  A core takes what it would
+// take alone, so that its result does not depend on who else there is room for in a launch -- but `pair`: the first two, a step's
+// cross-attention and first verification layer, have row tiles as two calls take them, at the larger P_cap.  (Tiles by the number
+// of calls that are in the launch gain nothing that shows: a step of 32768 keys x 100 nodes x 4 layers 585 - 589 us so, 588 - 592 this
+// way, 8 x 2048 x 60 x 4 443 - 444 and 445 - 448.)
+// A geometry is one that the core's own scratch holds: geometries at a smaller P_cap can need more than at a larger one (4
+// sequences x 1408 rows: 135 KB more at 8065 keys than at 8192), so scratch is compared at the P_cap that the geometry is for.
+inline void choose_attn(int form, int B, int Mq, int H, int Hkv, int dh, const AttnCore *core, int n, bool pair, AttnChoice *out)
 {
-    int cap = 0, split = 0;
-    size_t room = SIZE_MAX;
-    for (int i = 0; i < n; ++i) {
+    auto split = [&](int i, int cap, int ncalls) {
+        if (core[i].room < split_room(form, B, Mq, H, Hkv, dh, cap)) return false;
+        out[i].geo = split_geometry(form, B, Mq, H, Hkv, dh, cap, ncalls);
+        return true;
+    };
+    for (int i = 0; i < n; ++i)
         out[i].kind = !core[i].mfma ? AttnChoice::OTHER : want_whole(form, B, Mq, core[i].Mt, H, Hkv, core[i].P_cap) ? AttnChoice::WHOLE : AttnChoice::SPLIT;
-        if (out[i].kind != AttnChoice::SPLIT) continue;
-        ++split;
-        cap = std::max(cap, core[i].P_cap);
-        room = std::min(room, core[i].room);
+    int i = 0;
+    if (pair && n > 1 && out[0].kind == AttnChoice::SPLIT && out[1].kind == AttnChoice::SPLIT) {
+        const int cap = std::max(core[0].P_cap, core[1].P_cap);
+        if (split(0, cap, 2) && split(1, cap, 2)) i = 2;
     }
-    if (split == 0) return;
-    const SplitGeom all = split_geometry(form, B, Mq, H, Hkv, dh, cap, split);
-    const bool fits = room >= split_room(form, B, Mq, H, Hkv, dh, cap) && room >= split_bytes(all, B, Hkv, dh);
-    for (int i = 0; i < n; ++i) {
-        if (out[i].kind != AttnChoice::SPLIT) continue;
-        if (fits) out[i].geo = all;
-        else if (core[i].room >= split_room(form, B, Mq, H, Hkv, dh, core[i].P_cap)) out[i].geo = split_geometry(form, B, Mq, H, Hkv, dh, core[i].P_cap, 1);
-        else out[i].kind = AttnChoice::OTHER;
-    }
+    for (; i < n; ++i)
+        if (out[i].kind == AttnChoice::SPLIT && !split(i, core[i].P_cap, 1)) out[i].kind = AttnChoice::OTHER;
 }
 
 }  // namespace moa

@@ -399,8 +399,8 @@ hipError_t launch_attn(const AttnArgs &a, hipStream_t stream);
 // whether such a call (Mt tree rows as keys) runs over its whole key range in one launch and needs no scratch
 bool attn_takes_whole_range(int dtype, int B, int Mq, int Mt, int H, int Hkv, int dh, int P_cap);
 // Up to ATTN_CALLS independent cores of the same shape (cross-attention and verification layers) in as few launches as their
-// kernels allow; P_cap may differ.  A core whose ws is smaller than attn_workspace_bytes runs without one.
-hipError_t launch_attn_group(const AttnArgs *calls, int n, hipStream_t stream);
+// kernels allow; P_cap may differ.  A core whose ws is smaller than attn_workspace_bytes runs without one.  pair: see choose_attn.
+hipError_t launch_attn_group(const AttnArgs *calls, int n, bool pair, hipStream_t stream);
 
 // ---- row-wise pieces of a reused decoder layer
 hipError_t launch_rmsnorm(int dtype, const void *x, const void *res, int64_t R, int d, const void *g, float eps,

@@ -44,15 +44,19 @@ def status_word():
     return torch.zeros(1, dtype=torch.int32, device="cuda")
 
 
-def kernels_of(call):
-    """The names of the kernels that a call launches, as the library's profiler prints them; the call has finished."""
+def launches_of(call):
+    """The names of the kernels that a call launches, one for each launch, as the library's profiler prints them; the call has finished."""
     moa.profile_enable(True)
     try:
         call()
         torch.cuda.synchronize()
-        return {kernel for _, kernel, _, _ in moa.profile_collect()}
+        return [kernel for _, kernel, n, _ in moa.profile_collect() for _ in range(n)]
     finally:
         moa.profile_enable(False)
+
+
+def kernels_of(call):
+    return set(launches_of(call))
 
 
 def mask_u64(mask_t):

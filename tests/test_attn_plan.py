@@ -19,9 +19,9 @@ def lib(tmp_path_factory):
     d = tmp_path_factory.mktemp("attn_plan")
     (d / "plan.cpp").write_text(
         '#include "moa_attn_plan.h"\nextern "C" size_t room(int form, const int *s, int cap) { return moa::split_room(form, s[0], s[1], s[2], s[3], s[4], cap); }\n'
-        'extern "C" void choose(int form, const int *s, int n, const int *cap, const int *mt, const int *mfma, const size_t *room, int64_t *out)\n{\n'
+        'extern "C" void choose(int form, const int *s, int n, const int *cap, const int *mt, const int *mfma, const size_t *room, int pair, int64_t *out)\n{\n'
         "    moa::AttnCore c[8] = {};\n    moa::AttnChoice r[8] = {};\n    for (int i = 0; i < n; ++i) c[i] = {cap[i], mt[i], mfma[i] != 0, room[i]};\n"
-        "    moa::choose_attn(form, s[0], s[1], s[2], s[3], s[4], c, n, r);\n"
+        "    moa::choose_attn(form, s[0], s[1], s[2], s[3], s[4], c, n, pair != 0, r);\n"
         "    for (int i = 0; i < n; ++i) {\n        const bool split = r[i].kind == moa::AttnChoice::SPLIT;\n        int64_t *o = out + 5 * i;\n"
         "        o[0] = r[i].kind, o[1] = split ? r[i].geo.nsplit : 0, o[2] = split ? r[i].geo.rows_pad : 0, o[3] = split && r[i].geo.wide;\n"
         "        o[4] = split ? (int64_t)moa::split_bytes(r[i].geo, s[0], s[3], s[4]) : 0;\n    }\n}\n")
@@ -36,11 +36,11 @@ def room(lib, shape, cap, form=AUTO):
     return lib.room(form, (C.c_int * 5)(*shape), cap)
 
 
-def choose(lib, shape, cores, form=AUTO):
+def choose(lib, shape, cores, form=AUTO, pair=True):
     """cores: (P_cap, tree keys, operands fit, scratch) each"""
     n, out = len(cores), (C.c_int64 * (5 * len(cores)))()
     cap, mt, mfma = ((C.c_int * n)(*[int(c[i]) for c in cores]) for i in range(3))
-    lib.choose(form, (C.c_int * 5)(*shape), n, cap, mt, mfma, (C.c_size_t * n)(*[c[3] for c in cores]), out)
+    lib.choose(form, (C.c_int * 5)(*shape), n, cap, mt, mfma, (C.c_size_t * n)(*[c[3] for c in cores]), int(pair), out)
     return [Choice(out[5 * i], out[5 * i + 1], out[5 * i + 2], bool(out[5 * i + 3]), out[5 * i + 4]) for i in range(n)]
 
 
@@ -69,7 +69,7 @@ def test_a_core_is_given_slices_that_its_own_scratch_holds(lib, form):
     split = 0
     for rng, shape in shapes(4000, form):
         cores = step_cores(rng, lib, shape, form, rng.randint(1, 5))
-        for core, c in zip(cores, choose(lib, shape, cores, form)):
+        for core, c in zip(cores, choose(lib, shape, cores, form, rng.random() < 0.7)):
             assert c.kind != 1 or (core[2] and c.bytes <= core[3]), (shape, cores, c)
             split += c.kind == 1
     assert split > 2000
@@ -85,3 +85,18 @@ def test_a_smaller_capacity_that_needs_more_scratch(lib):
     assert got[0].kind == 0 and got[1].kind == 2
     got = choose(lib, shape, [(8192, 0, True, each), (8065, 128, True, room(lib, shape, 8065))])
     assert got[0].kind == 0 and got[1].kind == 1
+
+
+@pytest.mark.parametrize("form", [AUTO, SPLIT, SPLIT_WIDE])
+def test_a_core_takes_the_same_whoever_is_beside_it(lib, form):
+    """Alone, or as one of the first two of a step: the layers behind them change nothing, nor does their number."""
+    wide = 0
+    for rng, shape in shapes(2000, 10 + form):
+        cores = step_cores(rng, lib, shape, form, 5)
+        alone = [choose(lib, shape, [c], form)[0] for c in cores]
+        pair = choose(lib, shape, cores[:2], form)
+        for n in (3, 4, 5):
+            assert choose(lib, shape, cores[:n], form) == pair + alone[2:n], (shape, cores)
+            assert choose(lib, shape, cores[:n], form, pair=False) == alone[:n], (shape, cores)
+        wide += alone[4].wide
+    assert wide > 200

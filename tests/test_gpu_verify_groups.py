@@ -11,10 +11,14 @@ SMALL = dict(B=3, P_min=80, P_max=300, M=37, D=5, max_branch=4, L=6, rms_norm=Tr
 CFGS = {
     "bf16": mi.Config(name="VG", index=31, dtype="bf16", d=512, H=8, Hkv=2, dh=128, d_lsa_in=512, **SMALL),
     "f32": mi.Config(name="VGf", index=32, dtype="f32", d=256, H=4, Hkv=2, dh=64, d_lsa_in=256, **SMALL),
-    # a key range that is split (16 sequences, too many workgroups for the whole-range form)
-    "bf16_split": mi.Config(name="VGs", index=33, dtype="bf16", B=16, P_min=300, P_max=700, M=60, D=6, max_branch=4, L=4, d=512, H=8, Hkv=4, dh=128,
+    # a key range that is split: 15 x 4 x ceil(4 x 37 / 32) = 300 workgroups, more than the whole-range form takes.  148 rows per KV head: one or two
+    # calls in a launch take 128-row tiles, five would take 256-row ones.
+    "bf16_split": mi.Config(name="VGs", index=33, dtype="bf16", B=15, P_min=120, P_max=220, M=37, D=5, max_branch=4, L=4, d=512, H=16, Hkv=4, dh=128,
                             d_lsa_in=512, rms_norm=True),
 }
+CFGS["bf16_wide"] = CFGS["bf16_split"]                # the same in 256-row tiles, by the switch for tests
+CORES = {"bf16": {"k_attn_fused16<128, 8>", "k_attn_fused<128, 8>"}, "f32": {"k_attn_f32"}, "bf16_split": {"k_attn_mfma<128, 1>", "k_attn_merge<128>"},
+         "bf16_wide": {"k_attn_long<128>", "k_attn_merge<128>"}}
 SCHEDULES = {"grouped": 0, "two_stream": 1, "sequential": 2}
 
 
@@ -55,34 +59,76 @@ def unaligned_weight(step):        # the second layer's projection can only be r
     step.v_w[1]["wk"] = odd
 
 
+def least_workspace(G, step, schedule):
+    """The smallest workspace (to 4 KB) in which the step still groups: one verification layer beside the cross-attention."""
+    def grouped(n):
+        step.ws, step._plans = whole[:n], {}
+        G.moa.profile_enable(True)
+        try:
+            step.run(schedule=schedule)
+            torch.cuda.synchronize()
+            return any(site == "ca.core+verify.core" for site, *_ in G.moa.profile_collect())
+        except G.moa.MoaError:
+            return False
+        finally:
+            G.moa.profile_enable(False)
+    whole = step.ws
+    lo, hi = 0, whole.numel() // 4096
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if grouped(4096 * mid) else (mid, hi)
+    return 4096 * hi
+
+
 @pytest.mark.parametrize("with_sa", [False, True], ids=["", "sa"])
 @pytest.mark.parametrize("change", [apart, chained, one_slab, reads_drafted, reads_self_attention, unaligned_weight], ids=lambda f: f.__name__)
 @pytest.mark.parametrize("cfg", list(CFGS))
 def test_grouped_layers_give_what_one_after_another_gives(G, cfg, change, with_sa):
     """Six layers (a group of four beside the cross-attention at most, then one of two) against the sequential schedule: the same
-    bits where the attention runs over the whole key range in one form, to rounding where the key range is split."""
+    bits -- but for the cross-attention and the first layer where the key range is split, whose tiles may be others than those of
+    a call alone: to rounding, and the same bits however much room the workspace has."""
     from paper_2410_03804_amd.workload import DeviceStep
     c = CFGS[cfg]
     work = mi.step_workload(c, n_verify_layers=6, with_sa=with_sa)
-    need = None
-    outs = {}
-    for name in ("sequential", "grouped", "two_stream", "grouped, no room to spare", "two_stream, no room to spare"):
-        if change in (reads_drafted, reads_self_attention) and with_sa and name.startswith("two_stream"):
-            continue                       # there the drafter's layers are another branch than the verification layers
-        print(f"[case] verify groups {cfg} {change.__name__} sa={with_sa} {name}", flush=True)
-        step = DeviceStep(work, fold=False)
-        change(step)
-        need = need or step.ws.numel()
-        spare = 0 if "no room" in name else 5 * 3 * (2 * c.B * c.M * c.H * c.dh * 4 + (1 << 20))
-        step.ws = torch.empty(need + spare, dtype=torch.uint8, device="cuda")
-        step.run(schedule=SCHEDULES[name.split(",")[0]])
-        torch.cuda.synchronize()
-        assert step.dev_status.item() == 0
-        outs[name] = [t.clone() for t in (*step.v_out, *step.v_ktree, *step.v_vtree, step.ca_out, step.mask, step.path, step.bonus)]
+    outs, cores = {}, {}
+    G.moa.debug_force_attn_kernel("split_wide" if cfg == "bf16_wide" else "auto")
+    try:
+        probe = DeviceStep(work, fold=False)
+        need = probe.ws.numel()
+        least = least_workspace(G, probe, SCHEDULES["grouped"])
+        for name in ("sequential", "grouped", "two_stream", "grouped, as asked for", "two_stream, as asked for", "grouped, least", "two_stream, least"):
+            if with_sa and name == "two_stream, least":
+                continue                       # (needs more room than grouping does)
+            if change in (reads_drafted, reads_self_attention) and with_sa and name.startswith("two_stream"):
+                continue                       # there the drafter's layers are another branch than the verification layers
+            print(f"[case] verify groups {cfg} {change.__name__} sa={with_sa} {name}", flush=True)
+            step = DeviceStep(work, fold=False)
+            change(step)
+            spare = 5 * 3 * (2 * c.B * c.M * c.H * c.dh * 4 + (1 << 20))
+            step.ws = torch.empty(least if "least" in name else need if "asked" in name else need + spare, dtype=torch.uint8, device="cuda")
+            launched = G.launches_of(lambda: step.run(schedule=SCHEDULES[name.split(",")[0]]))
+            cores[name] = [kernel for kernel in launched if kernel in CORES[cfg]]
+            assert step.dev_status.item() == 0
+            outs[name] = [t.clone() for t in (step.v_out[0], step.ca_out, *step.v_out[1:], *step.v_ktree, *step.v_vtree, step.mask, step.path, step.bonus)]
+    finally:
+        G.moa.debug_force_attn_kernel("auto")
     for name, out in outs.items():
         for i, (a, b) in enumerate(zip(outs["sequential"], out)):
-            if cfg == "bf16_split":
+            if CORES[cfg] & {"k_attn_merge<128>"} and (i < 2 or change in (chained, reads_drafted)):
                 assert torch.allclose(a.float(), b.float(), atol=G.ABS_TOL[c.dtype], rtol=G.REL_TOL[c.dtype]), (name, i)
             else:
                 assert torch.equal(a, b), (name, i)
+        like = name.split(",")[0] if with_sa else "sequential" if name == "sequential" else "grouped"
+        assert all(torch.equal(a, b) for a, b in zip(outs[like], out)), (name, like)
     assert np.isfinite(outs["grouped"][0].float().cpu().numpy()).all()
+    # cores launched: one a layer and the drafter's; with room two groups (where the key range is split the first two may have tiles of
+    # their own); one by one behind the first two where layers meet, or where there is room for one
+    each = 2 if "k_attn_merge<128>" in CORES[cfg] else 1
+    n = {name: len(got) for name, got in cores.items()}
+    assert all(set(got) <= CORES[cfg] for got in cores.values()), cores
+    assert n["sequential"] == (7 + with_sa) * each, cores
+    assert n["grouped, least"] == (6 + with_sa) * each, cores
+    if change is apart:
+        assert (2 + with_sa) * each <= n["grouped"] <= (2 + with_sa + each - 1) * each, cores
+    if change in (chained, one_slab):
+        assert n["grouped"] == (6 + with_sa) * each, cores
