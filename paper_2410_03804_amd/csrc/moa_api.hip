@@ -570,8 +570,6 @@ struct AttnBufs {
 
 // launch sites of the layer being run, {projections, core, output projection}; nullptr = by kind of layer
 static thread_local const int *t_sites = nullptr;
-// a Self-Attention layer that is part of a step: its projections too may share a launch with others
-static thread_local bool t_step_sa = false;
 // a step's pieces on two streams at once (AttnArgs::beside)
 static thread_local int t_beside = 0;
 struct BesideScope {
@@ -608,7 +606,7 @@ static int32_t attn_stage_project(const char *who, const moa_shape_t *shape, con
     la.ldx = d;
     la.ws = bf.scratch_p;
     la.ws_bytes = bf.scratch_p_bytes;
-    la.same_sums = t_sites && !t_step_sa ? 0 : LinArgs::SAME_SUMS_IN;      // cross-attention, verification: a step may group them
+    la.same_sums = t_sites ? 0 : LinArgs::SAME_SUMS_IN;      // cross-attention, verification: a step may group them
     *q_out = x;
     if (wq) {
         la.seg[la.nseg].W = wq;
@@ -875,12 +873,9 @@ static int32_t step_self_attn_check(const moa_step_args_t *a)
 
 static int32_t step_self_attn_layer(const moa_step_args_t *a, void *ws, size_t ws_bytes, void *stream)
 {
-    t_step_sa = true;
-    const int32_t rc = moa_self_attn_draft(a->sa_shape, a->sa_emb, a->B, a->M, 0, a->M, a->sa_wq, a->sa_wk, a->sa_wv, a->sa_wo,
-                                           a->sa_kcache, a->sa_vcache, a->prefix_len, a->sa_P_cap, a->mask, a->sa_out,
-                                           a->sa_k_draft, a->sa_v_draft, a->dev_status, ws, ws_bytes, stream);
-    t_step_sa = false;
-    return rc;
+    return moa_self_attn_draft(a->sa_shape, a->sa_emb, a->B, a->M, 0, a->M, a->sa_wq, a->sa_wk, a->sa_wv, a->sa_wo,
+                               a->sa_kcache, a->sa_vcache, a->prefix_len, a->sa_P_cap, a->mask, a->sa_out,
+                               a->sa_k_draft, a->sa_v_draft, a->dev_status, ws, ws_bytes, stream);
 }
 
 static int32_t step_self_attn(const moa_step_args_t *a)
@@ -1275,12 +1270,26 @@ static int32_t piece_small(const moa_step_args_t *a, const StepBufs &bf, hipStre
     return MOA_OK;
 }
 
+// a step's Self-Attention layer: query, key and value projections, the queries to `q`
+static void self_attn_segments(const moa_step_args_t *a, char *q, LinSeg *seg)
+{
+    const moa_shape_t *sh = a->sa_shape;
+    const int dh = sh->head_dim, e = sh->n_q_heads * dh, h = sh->n_kv_heads, M = a->M;
+    const void *w[3] = {a->sa_wq, a->sa_wk, a->sa_wv};
+    const StoreSpec st[3] = {row_store(q, e), heads_store(a->sa_k_draft, h, dh, M, M), heads_store(a->sa_v_draft, h, dh, M, M)};
+    for (int i = 0; i < 3; ++i) {
+        seg[i].W = w[i];
+        seg[i].N = i == 0 ? e : h * dh;
+        seg[i].st = st[i];
+        seg[i].X = a->sa_emb;
+        seg[i].ldx = sh->d_model;
+    }
+}
+
 // cross-attention queries + Q/K/V of the verification layers l0 .. l0 + n - 1 in one launch (which = 3), or the queries (1) or
 // the verification layers' (2) alone
-// with_small: the integer work rides in spare workgroups of this launch's grid instead of being a launch of its
-// own (nothing before the LSA chain's append and the attention cores needs its results).
 // sa_q: not NULL (which = 2) -- the Self-Attention layer's Q/K/V in front of them, the queries to sa_q
-static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, hipStream_t st, bool with_small, int which, int l0, int n, char *sa_q = nullptr)
+static LinArgs projection_args(const moa_step_args_t *a, const StepBufs &bf, int which, int l0, int n, char *sa_q)
 {
     const moa_shape_t *sh = a->shape;
     const int dh = sh->head_dim, Hkv = sh->n_kv_heads, d = sh->d_model, M = a->M;
@@ -1299,17 +1308,8 @@ static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, h
         q.ldx = d;
     }
     if (sa_q) {
-        const int e_sa = a->sa_shape->n_q_heads * dh, h_sa = a->sa_shape->n_kv_heads;
-        const void *w[3] = {a->sa_wq, a->sa_wk, a->sa_wv};
-        const StoreSpec st3[3] = {row_store(sa_q, e_sa), heads_store(a->sa_k_draft, h_sa, dh, M, M), heads_store(a->sa_v_draft, h_sa, dh, M, M)};
-        for (int i = 0; i < 3; ++i) {
-            LinSeg &g = la.seg[la.nseg++];
-            g.W = w[i];
-            g.N = i == 0 ? e_sa : h_sa * dh;
-            g.st = st3[i];
-            g.X = a->sa_emb;
-            g.ldx = d;
-        }
+        self_attn_segments(a, sa_q, la.seg);
+        la.nseg = 3;
     }
     for (int l = l0; (which & 2) && l < l0 + n; ++l) {
         const void *w[3] = {a->v_wq_host[l], a->v_wk_host[l], a->v_wv_host[l]};
@@ -1326,12 +1326,20 @@ static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, h
     }
     la.X = la.seg[0].X;
     la.seg[0].X = nullptr;               // the first segment reads the launch's own rows
+    return la;
+}
+
+// with_small: the integer work rides in spare workgroups of this launch's grid instead of being a launch of its
+// own (nothing before the LSA chain's append and the attention cores needs its results).
+static int32_t piece_projections(const moa_step_args_t *a, const StepBufs &bf, hipStream_t st, bool with_small, int which, int l0, int n, char *sa_q = nullptr)
+{
+    LinArgs la = projection_args(a, bf, which, l0, n, sa_q);
     if (with_small) {
         la.rider = small_args(a, bf);
         la.rider_units = 2 * a->B + 1;
     }
     prof_set_site(which == 3 ? S_PAIR_QKV : which == 1 ? S_CA_QPROJ : S_VERIFY_QKV);
-    MOA_TRY_HIP(launch_linear(sh->dtype, la, st), "draft_step: projections");
+    MOA_TRY_HIP(launch_linear(a->shape->dtype, la, st), "draft_step: projections");
     return MOA_OK;
 }
 
@@ -1582,8 +1590,10 @@ static int32_t draft_step_grouped(const moa_step_args_t *a)
 // With the Self-Attention layer the CA's queries come after it, and what shares the first launch are that layer's projections,
 // the verification layers' and the step's integer work (the tree masks among it, which otherwise are a launch in front of the
 // layer): [SA + verification Q/K/V, integer work] -> SA core -> SA output projection -> CA queries -> LSA -> as without.  60
-// nodes, five accepted tokens, 8B shape: 139.6 -> 137.1 us.  Only where neither reads or writes what the other writes.
-static bool grouped_takes_sa(const moa_step_args_t *args, const moa_step_args_t *a, const GroupLayout &L, StepBufs *bf)
+// nodes, five accepted tokens, 8B shape: 139.6 -> 137.1 us.  Only where neither reads or writes what the other writes, and where
+// every projection sums along K as it does without the other: the layer as moa_self_attn_draft plans it (other head counts or
+// few rows of a wide model may want another kernel), the verification layers as beside the CA's queries.
+static bool grouped_takes_sa(const moa_step_args_t *args, const moa_step_args_t *a, const GroupLayout &L, char *scr, StepBufs *bf)
 {
     const moa_shape_t *sa = args->sa_shape;
     if (!args->sa_wq || !args->sa_wk || !args->sa_wv || !args->sa_wo || sa->head_dim != a->shape->head_dim) return false;
@@ -1595,7 +1605,19 @@ static bool grouped_takes_sa(const moa_step_args_t *args, const moa_step_args_t 
         const LayerMem v(a, l);
         if (!v.aligned || any_meet(v.writes, m.reads) || any_meet(v.writes, m.writes) || any_meet(v.reads, m.writes)) return false;
     }
-    return true;
+    const AttnBufs sb = attn_carve(sa, a->B, a->M, scr, L.scratch);
+    LinArgs alone = {};
+    alone.X = a->sa_emb;
+    alone.R = (int64_t)a->B * a->M;
+    alone.K = sa->d_model;
+    alone.ldx = sa->d_model;
+    alone.nseg = 3;
+    self_attn_segments(a, sb.qbuf, alone.seg);
+    alone.ws = sb.scratch_p;
+    alone.ws_bytes = sb.scratch_p_bytes;
+    const int order = linear_order(sa->dtype, alone);
+    return order != 0 && linear_order(sa->dtype, projection_args(a, *bf, 2, 0, bf->first, sb.qbuf)) == order &&
+           linear_order(sa->dtype, projection_args(a, *bf, 3, 0, bf->first, nullptr)) == order;
 }
 
 static int32_t draft_step_grouped_sa(const moa_step_args_t *args, const moa_step_args_t *a, const GroupLayout &L, const StepBufs &bf, char *scr)
@@ -1888,7 +1910,7 @@ int32_t moa_draft_step(const moa_step_args_t *args)
         const GroupLayout L = group_layout(a->shape, a->B, a->M, a->P_cap, a->ca_P_cap, a->T_lsa);
         char *scr = nullptr;
         StepBufs bf = carve_step_bufs(a, L, &scr);
-        if (grouped_takes_sa(args, a, L, &bf)) return draft_step_grouped_sa(args, a, L, bf, scr);
+        if (grouped_takes_sa(args, a, L, scr, &bf)) return draft_step_grouped_sa(args, a, L, bf, scr);
     }
     if (sa) {
         rc = step_self_attn(args);

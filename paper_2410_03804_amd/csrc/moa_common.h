@@ -346,11 +346,16 @@ static_assert(sizeof(DevSeg) == 64 && offsetof(LinDev<LIN_SEGS>, seg) == 128 && 
 
 // Y_s = X_s W_s^T for up to LIN_SEGS weight matrices (one launch on the fast paths; K is cut for up to four only).
 hipError_t launch_linear(int dtype, const LinArgs &a, hipStream_t stream);
+// In which order launch_linear sums along K: calls with the same number give a projection the same bits.  0: one kernel a segment,
+// or one that reads element by element.
+int linear_order(int dtype, const LinArgs &a);
 // the bf16 kernel behind launch_linear (moa_gemm_bf16.hip) and its name by profiling variant
 hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused, int *splits);
+int linear_bf16_order(const LinArgs &a);       // K groups and slices
 const char *linear_bf16_name(int variant);
 // the single-precision kernels behind launch_linear (moa_gemm_f32.hip): operands they can read, and the launch
 bool linear_f32_ok(int dtype, const LinArgs &a);
+bool linear_f32_big(const LinArgs &a);         // in 64 x 64 tiles
 hipError_t launch_linear_f32(int dtype, const LinArgs &a, hipStream_t stream);
 // scratch for the sums of K slices of a launch of R rows on matrices of n output features each (0 = K is not cut);
 // upto: the most that any row count from 1 to R asks for

@@ -147,6 +147,15 @@ static LinPath linear_path(int dtype, const LinArgs &a)
     return linear_f32_ok(dtype, a) ? P_F32 : own_x ? P_EACH : P_GENERIC;
 }
 
+int linear_order(int dtype, const LinArgs &a)
+{
+    switch (linear_path(dtype, a)) {
+    case P_BF16: return 2 + linear_bf16_order(a);
+    case P_F32: return linear_f32_big(a) ? 2 : 1;
+    default: return 0;
+    }
+}
+
 static hipError_t launch_linear_impl(int dtype, const LinArgs &a, hipStream_t stream, bool *rode, bool *fused);
 
 // the pass that adds up the K slices launch_linear_bf16 has left in a.ws

@@ -285,8 +285,7 @@ static hipError_t launch_tile(const LinArgs &a, const GemmPlan &p, hipStream_t s
     return hipGetLastError();
 }
 
-// One launch.  *fused: it applied a.epi; *splits > 1: the sums of that many K slices are in a.ws, to be added up.
-hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused, int *splits)
+static GemmPlan plan_of(const LinArgs &a)
 {
     int ntot = 0, n_seg[LIN_SEGS] = {};
     for (int s = 0; s < a.nseg; ++s) {
@@ -298,6 +297,19 @@ hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused,
     // 71 in the 64 x 64 of four slices)
     if (p.splits > 1 && !(a.ws && a.ws_bytes >= partial_bytes(a.R, ntot, p.splits) && (((uintptr_t)a.ws) & 15) == 0))
         p = plan_gemm(a.R, a.K, n_seg, a.nseg, a.epi, a.in_order, a.same_sums, 1);
+    return p;
+}
+
+int linear_bf16_order(const LinArgs &a)
+{
+    const GemmPlan p = plan_of(a);
+    return kTiles[p.tile].wk * 16 + p.splits;
+}
+
+// One launch.  *fused: it applied a.epi; *splits > 1: the sums of that many K slices are in a.ws, to be added up.
+hipError_t launch_linear_bf16(const LinArgs &a, hipStream_t stream, bool *fused, int *splits)
+{
+    const GemmPlan p = plan_of(a);
     return a.nseg <= LIN_FEW ? launch_tile<LIN_FEW>(a, p, stream, fused, splits) : launch_tile<LIN_SEGS>(a, p, stream, fused, splits);
 }
 

@@ -206,21 +206,28 @@ bool linear_f32_ok(int dtype, const LinArgs &a)
 // step groups in one way or another (LinArgs::same_sums) count twice their widest segment: a layer's Q/K/V.
 constexpr int64_t F32_TILE_MIN_WORKGROUPS = 128;
 
-template <int SEGS>
-static hipError_t launch_f32_as(int dtype, const LinArgs &a, hipStream_t stream)
+bool linear_f32_big(const LinArgs &a)
 {
-    LinDev<SEGS> fa(a);
-    const size_t piece = dtype == DT_BF16 ? 8 : 16;
     int64_t t64 = 0, widest = 0;
     for (int s = 0; s < a.nseg; ++s) {
-        const StoreSpec &st = a.seg[s].st;
-        fa.vec |= (uint32_t)(aligned_to(st.dst, piece) && (st.mode == StoreSpec::ROW ? st.ld % 4 == 0 : st.dh % 4 == 0)) << s;
         const int64_t n = (a.seg[s].N + 63) / 64;
         t64 += n;
         if (n > widest) widest = n;
     }
     if (a.same_sums) t64 = 2 * widest;
-    const bool big = t64 * ((a.R + 63) / 64) >= F32_TILE_MIN_WORKGROUPS;
+    return t64 * ((a.R + 63) / 64) >= F32_TILE_MIN_WORKGROUPS;
+}
+
+template <int SEGS>
+static hipError_t launch_f32_as(int dtype, const LinArgs &a, hipStream_t stream)
+{
+    LinDev<SEGS> fa(a);
+    const size_t piece = dtype == DT_BF16 ? 8 : 16;
+    for (int s = 0; s < a.nseg; ++s) {
+        const StoreSpec &st = a.seg[s].st;
+        fa.vec |= (uint32_t)(aligned_to(st.dst, piece) && (st.mode == StoreSpec::ROW ? st.ld % 4 == 0 : st.dh % 4 == 0)) << s;
+    }
+    const bool big = linear_f32_big(a);
     const int edge = big ? 64 : 16;
     int t = 0;
     for (int s = 0; s < a.nseg; ++s) { fa.tile_begin[s] = t; t += (a.seg[s].N + edge - 1) / edge; }

@@ -132,3 +132,59 @@ def test_grouped_layers_give_what_one_after_another_gives(G, cfg, change, with_s
         assert (2 + with_sa) * each <= n["grouped"] <= (2 + with_sa + each - 1) * each, cores
     if change in (chained, one_slab):
         assert n["grouped"] == (6 + with_sa) * each, cores
+
+
+# Shapes where the Self-Attention layer's projections in a launch with the verification layers' would take another kernel than alone,
+# or take the verification layers' to one: (step, query heads and KV heads of the layer)
+SELF = {
+    # fp32, 64 + 4 + 4 tiles of 64 features alone, twice the 64 in a launch of the step: on either side of 128
+    "f32_wide": (mi.Config(name="VSw", index=34, dtype="f32", B=1, P_min=30, P_max=60, M=20, D=4, max_branch=4, L=4, d=256, H=64, Hkv=4, dh=64,
+                           d_lsa_in=256, rms_norm=True), 64, 4),
+    # fp32, a layer four times as wide as the others
+    "f32_wider": (mi.Config(name="VSv", index=35, dtype="f32", B=1, P_min=30, P_max=60, M=20, D=4, max_branch=4, L=4, d=256, H=16, Hkv=4, dh=64,
+                            d_lsa_in=256, rms_norm=True), 64, 8),
+    # bf16, 16 key features, which the bf16 matrix kernels do not take
+    "bf16_narrow": (mi.Config(name="VSn", index=36, dtype="bf16", B=2, P_min=30, P_max=60, M=20, D=4, max_branch=4, L=4, d=256, H=8, Hkv=2, dh=16,
+                              d_lsa_in=256, rms_norm=True), 8, 1),
+    # bf16, long K and few features: slices of K alone
+    "bf16_sliced": (mi.Config(name="VSs", index=37, dtype="bf16", B=1, P_min=30, P_max=60, M=8, D=4, max_branch=4, L=4, d=8192, H=2, Hkv=1, dh=128,
+                              d_lsa_in=256, rms_norm=True), 2, 1),
+    # no such edge: shares the launch
+    "bf16": (mi.Config(name="VSb", index=38, dtype="bf16", B=1, P_min=30, P_max=60, M=12, D=4, max_branch=4, L=4, d=4096, H=32, Hkv=8, dh=128,
+                       d_lsa_in=1024, rms_norm=True), 32, 8),
+}
+
+
+@pytest.mark.parametrize("case", list(SELF))
+def test_self_attention_in_a_step_gives_what_the_call_alone_gives(G, case):
+    """Under every schedule, and the verification layers what they give without it."""
+    from paper_2410_03804_amd.workload import DeviceStep
+    moa = G.moa
+    c, H, hkv = SELF[case]
+    work = mi.step_workload(c, n_verify_layers=2, with_sa=True)
+    dt, rng = c.dtype, np.random.default_rng(c.index)
+    zeros = lambda *shape: torch.zeros(shape, dtype=G.TDT[dt], device="cuda")
+    w = {k: rng.standard_normal(s) * s[1] ** -0.5 for k, s in (("wq", (H * c.dh, c.d)), ("wk", (hkv * c.dh, c.d)), ("wv", (hkv * c.dh, c.d)), ("wo", (c.d, H * c.dh)))}
+    sa = dict(shape=moa.Shape(c.L, c.d, H, hkv, c.dh, c.d_lsa_in, c.lsa_heads, c.Hkv, G.MDT[dt]), emb=G.dev(work["sa"]["emb"], dt), w={k: G.dev(v, dt) for k, v in w.items()},
+              kcache=zeros(c.B, hkv, c.P_cap, c.dh).normal_(), vcache=zeros(c.B, hkv, c.P_cap, c.dh).normal_(), P_cap=c.P_cap)
+    outs, sites = {}, {}
+    for name, schedule in SCHEDULES.items():
+        print(f"[case] self-attention in a step {case} {name}", flush=True)
+        step = DeviceStep(work, fold=False)
+        step.sa = dict(sa, k_draft=zeros(c.B, hkv, c.M, c.dh), v_draft=zeros(c.B, hkv, c.M, c.dh), out=zeros(c.B, c.M, c.d))
+        step.ws = torch.empty(2 * max(step.ws.numel(), moa.workspace_bytes(sa["shape"], c.B, c.P_cap, c.M, 0)), dtype=torch.uint8, device="cuda")
+        moa.profile_enable(True)
+        step.run(schedule=schedule)
+        torch.cuda.synchronize()
+        sites[name] = {site for site, *_ in moa.profile_collect()}
+        moa.profile_enable(False)
+        assert step.dev_status.item() == 0
+        outs[name] = [t.clone() for t in (step.sa["out"], step.sa["k_draft"], step.sa["v_draft"], *step.v_out, *step.v_ktree, *step.v_vtree)]
+    alone = [torch.zeros_like(t) for t in outs["grouped"][:3]]
+    moa.self_attn_draft(sa["shape"], sa["emb"], 0, *(sa["w"][k] for k in ("wq", "wk", "wv", "wo")), sa["kcache"], sa["vcache"], step.prefix_len, c.P_cap, step.mask,
+                        *alone, G.workspace(sa["shape"], c.B, c.P_cap, c.M, 0), G.status_word())
+    torch.cuda.synchronize()
+    for name, out in outs.items():
+        for i, (a, b) in enumerate(zip(alone + outs["sequential"][3:], out)):
+            assert torch.equal(a, b), (name, i)
+    assert ("sa.qkv_proj" in sites["grouped"]) == (case != "bf16"), sites
