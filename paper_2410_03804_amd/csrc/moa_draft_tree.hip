@@ -418,7 +418,7 @@ int32_t moa_topk_logprob(int32_t dtype, const void *logits, int32_t F, int32_t V
     prof_end(st);
     if (hipGetLastError() != hipSuccess) return tree_fail(MOA_ERR_HIP, "topk_logprob: launch failed");
     const size_t lds = ((size_t)S * Bw + 7) / 8 * 8 * 8;
-    if (lds + (size_t)S * 8 > 60 * 1024) return tree_fail(MOA_ERR_SHAPE, "topk_logprob: vocabulary too large for the merge");
+    if ((size_t)S * Bw * 8 + (size_t)S * 8 > 60 * 1024) return tree_fail(MOA_ERR_SHAPE, "topk_logprob: vocabulary too large for the merge");
     prof_begin(K_TOPK_MERGE, st);
     MOA_KLAUNCH(k_topk_merge, dim3(F), dim3(S * Bw <= 64 ? 256 : S * Bw <= 128 ? 512 : 1024), lds, st, Bw, S, skey, smax, ssum, tok, logp);
     prof_end(st);

@@ -216,3 +216,28 @@ def test_lm_head_argmax_parity(G, moa, oracle, R, d, V):
     if V > 100:
         assert got[0] == 11
     assert np.max(np.abs(best.cpu().numpy()[rows] - chosen)) <= 2e-4 * np.sqrt(d)
+
+
+@pytest.mark.parametrize("Bw,S", [(6, 1097), (10, 698)])
+def test_topk_logprob_largest_vocabulary(moa, Bw, S):
+    """The most slices that the merge takes at a breadth, where eight of their survivors do not divide the number of all; one
+    slice more is refused."""
+    V = S * 8192
+    assert (S * Bw) % 8 and S * (Bw + 1) * 8 <= 60 * 1024 < (S + 1) * (Bw + 1) * 8
+    print(f"[case] topk_logprob V={V} breadth={Bw}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(S)
+    x = torch.randn(1, V + 8192, generator=g, device="cuda").bfloat16()
+    at = torch.randperm(V, generator=g, device="cuda")[:Bw]
+    at[0] = V - 1
+    x[0, at] = 6.0 + torch.arange(Bw, device="cuda", dtype=torch.bfloat16)      # whole numbers: distinct in bf16
+    tok = torch.empty((1, Bw), dtype=torch.int32, device="cuda")
+    logp = torch.empty((1, Bw), device="cuda")
+    ws = torch.empty(moa.topk_workspace_bytes(1, V + 8192, Bw), dtype=torch.uint8, device="cuda")
+    row = x[:, :V].contiguous()
+    moa.topk_logprob(row, Bw, tok, logp, ws)
+    assert torch.equal(tok[0].long(), at.flip(0))
+    want = row[0, at.flip(0)].double() - row[0].double().logsumexp(0)
+    # a sum of 9e6 exponentials in fp32 partial sums (at most 256 chained), its logarithm and one subtraction of order-16 values
+    assert ((logp[0].double() - want).abs() <= 256 * 2.0 ** -24 + 4 * 16 * 2.0 ** -23).all()
+    with pytest.raises(moa.MoaError, match="vocabulary too large"):
+        moa.topk_logprob(x, Bw, tok, logp, ws)
