@@ -14,10 +14,13 @@ import torch
 
 _LIB_PATH = Path(__file__).resolve().parent / "libmoa.so"
 if not _LIB_PATH.exists():
-    raise ImportError(f"{_LIB_PATH} is missing: build it with `python -m paper_2410_03804_amd.build` "
-                      "(there is no fallback path)")
+    raise ImportError(f"{_LIB_PATH} is missing: build it with `python {_LIB_PATH.with_name('build.py')}` (there is no fallback path)")
 _lib = C.CDLL(str(_LIB_PATH))
-from ._argcheck import dev as _dev  # noqa: E402  (built with the library: csrc/argcheck.c)
+try:
+    from ._argcheck import dev as _dev  # built with the library: csrc/argcheck.c
+except ImportError as e:
+    raise ImportError(f"{_LIB_PATH.with_name('_argcheck.abi3.so')}, the argument check built with the library, does not load ({e}): "
+                      f"build both with `python {_LIB_PATH.with_name('build.py')}` (there is no fallback path)") from e
 
 F32, BF16 = 0, 1
 MAX_TREE = 256

@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -40,10 +41,16 @@ def _compile(src: str, objdir: Path) -> Path:
 
 
 def build_argcheck() -> None:
-    """The binding's argument check, a CPython extension beside the library (plain C)."""
-    out = HERE / ("_argcheck" + sysconfig.get_config_var("EXT_SUFFIX"))
-    tmp = out.with_suffix(f".tmp{os.getpid()}")
-    subprocess.check_call(["gcc", "-O2", "-Wall", "-shared", "-fPIC", f"-I{sysconfig.get_paths()['include']}", "-o", str(tmp), str(CSRC / "argcheck.c")])
+    """The binding's argument check, an extension beside the library (plain C, compiled by hipcc's own clang; for CPython 3.10 and later,
+    whichever of them builds it)."""
+    out = HERE / "_argcheck.abi3.so"
+    tmp = HERE / f"_argcheck.tmp{os.getpid()}"
+    hipcc = shutil.which(_hipcc())
+    clang = Path(hipcc).resolve().parent.parent / "llvm" / "bin" / "clang" if hipcc else Path("clang")
+    subprocess.check_call([str(clang) if clang.exists() else "cc", "-O2", "-Wall", "-shared", "-fPIC", f"-I{sysconfig.get_paths()['include']}", "-o", str(tmp),
+                           str(CSRC / "argcheck.c")])
+    for stale in HERE.glob("_argcheck.*.so"):         # one for this version alone would be found first
+        stale.unlink()
     os.replace(tmp, out)
 
 

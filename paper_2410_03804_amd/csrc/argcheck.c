@@ -1,7 +1,8 @@
 /* The check of one tensor argument, for binding.py: what a call costs on the host is mostly this, six times or so (0.6 us each
- * in Python, 0.25 here; a client-server cycle's 19 calls: 141 -> 100 us enqueued).  Plain CPython API; whatever the tensor's
+ * in Python, 0.25 here; a client-server cycle's 19 calls: 141 -> 100 us enqueued).  The stable CPython API; whatever the tensor's
  * attributes say, they say here as they would there. */
 #define PY_SSIZE_T_CLEAN
+#define Py_LIMITED_API 0x030a0000      /* CPython 3.10 and later load the same file */
 #include <Python.h>
 
 static PyObject *tensor_type, *s_is_cuda, *s_is_contiguous, *s_dtype, *s_numel, *s_data_ptr;
@@ -28,7 +29,7 @@ static PyObject *dev(PyObject *self, PyObject *const *args, Py_ssize_t n)
         if (!is) return PyErr_Format(PyExc_TypeError, "%S: expected a torch tensor", name);
     }
     int ok = truth(PyObject_GetAttr(t, s_is_cuda));
-    if (ok > 0) ok = truth(PyObject_CallMethodNoArgs(t, s_is_contiguous));
+    if (ok > 0) ok = truth(PyObject_CallMethodObjArgs(t, s_is_contiguous, NULL));
     if (ok < 0) return NULL;
     if (!ok) return PyErr_Format(PyExc_ValueError, "%S: must be a contiguous CUDA tensor", name);
     PyObject *dtype = PyObject_GetAttr(t, s_dtype);
@@ -42,13 +43,13 @@ static PyObject *dev(PyObject *self, PyObject *const *args, Py_ssize_t n)
         }
     }
     Py_DECREF(dtype);
-    PyObject *have = PyObject_CallMethodNoArgs(t, s_numel);
+    PyObject *have = PyObject_CallMethodObjArgs(t, s_numel, NULL);
     if (!have) return NULL;
     const int less = PyObject_RichCompareBool(have, args[2], Py_LT);
     if (less > 0) PyErr_Format(PyExc_ValueError, "%S: %S elements, the call touches %S", name, have, args[2]);
     Py_DECREF(have);
     if (less) return NULL;
-    return PyObject_CallMethodNoArgs(t, s_data_ptr);
+    return PyObject_CallMethodObjArgs(t, s_data_ptr, NULL);
 }
 
 static PyMethodDef methods[] = {

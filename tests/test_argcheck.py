@@ -1,7 +1,13 @@
 """The binding's check of one tensor argument (csrc/argcheck.c).  A tensor that says it is on the GPU stands in for one."""
+import shutil
+import subprocess
+import sys
+from pathlib import Path
+
 import pytest
 import torch
 
+import paper_2410_03804_amd as moa
 from paper_2410_03804_amd.binding import _dev
 
 
@@ -37,3 +43,18 @@ def test_errors_of_its_arguments_pass_through():
         _dev(gpu(4), torch.int32, "four", "x")
     with pytest.raises(TypeError):
         _dev(gpu(4), torch.int32, 4)
+
+
+@pytest.mark.parametrize("missing", ["libmoa.so", "_argcheck.abi3.so"])
+def test_what_is_not_built_says_how_to_build_it(tmp_path, missing):
+    """In a copy of the package that lacks one of the two built files, or has one that is no extension."""
+    here, pkg = Path(moa.library_path()).parent, tmp_path / "paper_2410_03804_amd"
+    pkg.mkdir()
+    for f in (*here.glob("*.py"), *here.glob("*.so")):
+        if f.name != missing:
+            shutil.copy(f, pkg)
+    for broken in (False, True):
+        if broken:
+            (pkg / "_argcheck.abi3.so").write_bytes(b"not an extension")
+        r = subprocess.run([sys.executable, "-c", "import paper_2410_03804_amd"], cwd=tmp_path, capture_output=True, text=True)
+        assert r.returncode != 0 and "build.py` (there is no fallback path)" in r.stderr and f"ImportError: {pkg}" in r.stderr, r.stderr
