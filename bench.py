@@ -103,9 +103,9 @@ def lsa_token_count(cfg, lsa_tokens):
     return cfg.B * int(lsa_tokens)
 
 
-def site_costs(cfg, n_layers, schedule="grouped", lsa_tokens="tree", with_sa=False, fold=True):
+def site_costs(cfg, n_layers, schedule="grouped", lsa_tokens="tree", with_sa=False, fold=True, ran=()):
     """Algorithmic bytes and flops per launch site for one step: what the call must read and write once
-    (inputs, weights, caches, outputs) and 2*MACs of the contractions as defined."""
+    (inputs, weights, caches, outputs) and 2*MACs of the contractions as defined.  ran: the sites that were launched."""
     es = 2 if cfg.dtype == "bf16" else 4
     B, M, L, d, H, Hkv, dh = cfg.B, cfg.M, cfg.L, cfg.d, cfg.H, cfg.Hkv, cfg.dh
     T = B * M
@@ -153,11 +153,14 @@ def site_costs(cfg, n_layers, schedule="grouped", lsa_tokens="tree", with_sa=Fal
     def add(*parts):
         return dict(bytes=sum(p["bytes"] for p in parts), flops=sum(p["flops"] for p in parts))
 
-    # the first verification layers, up to four, are launched together with the cross-attention
+    # The first verification layers, up to four, are launched together with the cross-attention.  Where the Self-Attention layer's
+    # projections lead those launches -- it then has no launch of its own for them -- there are three, and the projections of all
+    # layers are launched at one site.  (A workspace that holds fewer layers side by side than the one asked for does is not modelled.)
     paired = set(one) if schedule == "grouped" or (schedule == "two-stream" and not with_sa) else set()
-    beside = min(n_layers, 4)
+    sa_leads = bool(with_sa and paired and "sa.qkv_proj" not in ran)
+    beside = min(n_layers, 3 if sa_leads else 4)
     for k, v in one.items():
-        alone = n_layers - beside if k in paired else n_layers
+        alone = n_layers - beside if k in paired and not (sa_leads and k == "verify.qkv_proj") else n_layers
         c[k] = {kk: vv * alone for kk, vv in v.items()}
     # what one whole step must move once: LSA rows, every weight matrix, the two caches, inputs and outputs -- no
     # intermediate (projected queries, heads, partial sums) counts
@@ -174,9 +177,10 @@ def site_costs(cfg, n_layers, schedule="grouped", lsa_tokens="tree", with_sa=Fal
                          c["ca.o_proj"]["flops"] + n_layers * sum(v["flops"] for v in one.values()))
     if paired:
         c["tree_build+accept+lengths"] = add(c["tree_build"], c["tree_accept"], c["ca_append.lengths"])
-        c["ca.q_proj+verify.qkv_proj"] = add(c["ca.q_proj"], *[one["verify.qkv_proj"]] * beside)
-        if with_sa:                       # the Self-Attention layer's projections stand in for the cross-attention's
-            c["verify.qkv_proj"] = add(c["sa.qkv_proj"], *[one["verify.qkv_proj"]] * beside)
+        if sa_leads:
+            c["verify.qkv_proj"] = add(c["sa.qkv_proj"], c["verify.qkv_proj"])
+        else:
+            c["ca.q_proj+verify.qkv_proj"] = add(c["ca.q_proj"], *[one["verify.qkv_proj"]] * beside)
         c["ca.core+verify.core"] = add(c["ca.core"], *[one["verify.core"]] * beside)
         c["ca.o_proj+verify.o_proj"] = add(c["ca.o_proj"], *[one["verify.o_proj"]] * beside)
     return c
@@ -426,7 +430,8 @@ def main():
     tokens = cfg.B * cfg.M
     value = tokens / (ms_per_step * 1e-3)
 
-    costs = site_costs(cfg, NL, schedule=args.schedule, lsa_tokens=lsa_tokens, with_sa=args.with_sa, fold=not args.no_fold)
+    costs = site_costs(cfg, NL, schedule=args.schedule, lsa_tokens=lsa_tokens, with_sa=args.with_sa, fold=not args.no_fold,
+                       ran={row[0] for row in rows})
     peak_mm = MFMA_BF16_PEAK_TFLOPS if cfg.dtype == "bf16" else VEC_F32_PEAK_TFLOPS
     pieces = []
     for site, kern, n, ms in sorted(rows, key=lambda r: -r[3]):
