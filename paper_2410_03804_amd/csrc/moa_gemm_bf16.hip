@@ -182,14 +182,14 @@ static GemmPlan plan_gemm(int64_t R, int K, const int *n_seg, int nseg, int epi,
         ntot += n_seg[s];
         if (n_seg[s] % 64) most_splits = 1;        // the pass over the sums takes features in 64s
     }
-    if (nseg > 4) most_splits = 1;                 // and four matrices
+    if (nseg > LIN_FEW) most_splits = 1;           // and four matrices
     if (in_order || same_sums || R > 192) most_splits = 1;
     else if (R > 64 && most_splits > 4) most_splits = 4;       // eight pay off where the sums are few (64 x 4096 x 1024: 9.7 against 10.5 us)
     float best_us = 3.4e38f;
     const float stream_us = 6.f + 2.f * (float)K * (float)ntot / 5.8e6f;
     for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
         const GemmTile &t = kTiles[i];
-        if (in_order ? t.wk > 1 : ((R <= 16 ? t.bm != 16 : R <= 32 ? t.bm != 32 : t.bm < 64) || K % (64 * t.wk) != 0 || (same_sums && t.wk != 2))) continue;
+        if (in_order ? t.wk > 1 : ((R <= 16 ? t.bm != 16 : R <= 32 ? t.bm != 32 : t.bm < 64) || K % (64 * t.wk) != 0 || (same_sums && t.wk != 2) || (nseg > LIN_FEW && t.wk > 2))) continue;
         const int64_t row_tiles = (R + t.bm - 1) / t.bm;
         int64_t tiles = 0;
         for (int s = 0; s < nseg; ++s) tiles += (n_seg[s] + t.bn - 1) / t.bn;
@@ -273,11 +273,15 @@ static hipError_t launch_tile(const LinArgs &a, const GemmPlan &p, hipStream_t s
     static bool raised[sizeof(kTiles) / sizeof(kTiles[0])][16] = {};
     switch (p.tile) {
 #define MOA_GEMM_LAUNCH(id, WR, WF, MR, NF, SX, SW, WK, US1, USM, US2)                                                               \
-    case id:                                                                                                                         \
-        e = raise_lds_limit_once(raised[id], (const void *)k_linear_bf16<WR, WF, MR, NF, SX, SW, WK, SEGS>, t.lds);                  \
-        if (e != hipSuccess) return e;                                                                                               \
-        prof_begin(K_LIN_BF16 + 64 * (id + 1), stream);                                                                              \
-        MOA_KLAUNCH((k_linear_bf16<WR, WF, MR, NF, SX, SW, WK, SEGS>), dim3((unsigned)blocks), dim3(t.threads), t.lds, stream, ga);  \
+    case id:                                                                                                                             \
+        if constexpr (SEGS == LIN_FEW || WK <= 2) {                                                                                      \
+            e = raise_lds_limit_once(raised[id], (const void *)k_linear_bf16<WR, WF, MR, NF, SX, SW, WK, SEGS>, t.lds);                  \
+            if (e != hipSuccess) return e;                                                                                               \
+            prof_begin(K_LIN_BF16 + 64 * (id + 1), stream);                                                                              \
+            MOA_KLAUNCH((k_linear_bf16<WR, WF, MR, NF, SX, SW, WK, SEGS>), dim3((unsigned)blocks), dim3(t.threads), t.lds, stream, ga);  \
+        } else {                                                                                                                         \
+            return hipErrorInvalidValue;         /* the plan gives more than LIN_FEW matrices no such tile */                            \
+        }                                                                                                                                \
         break;
         MOA_GEMM_TILES(MOA_GEMM_LAUNCH)
     }
