@@ -1598,13 +1598,8 @@ static bool grouped_takes_sa(const moa_step_args_t *args, const moa_step_args_t 
     const moa_shape_t *sa = args->sa_shape;
     if (!args->sa_wq || !args->sa_wk || !args->sa_wv || !args->sa_wo || sa->head_dim != a->shape->head_dim) return false;
     if (attn_ws_bytes(sa, args->B, args->M, args->sa_P_cap) > L.scratch) return false;
-    const SaMem m(args);
-    if (!m.aligned || !apart_from_integers(a, m)) return false;
     if (bf->first > (LIN_SEGS - 3) / 3) bf->first = (LIN_SEGS - 3) / 3;
-    for (int l = 0; l < bf->first; ++l) {
-        const LayerMem v(a, l);
-        if (!v.aligned || any_meet(v.writes, m.reads) || any_meet(v.writes, m.writes) || any_meet(v.reads, m.writes)) return false;
-    }
+    if (!sa_apart(args, bf->first)) return false;
     const AttnBufs sb = attn_carve(sa, a->B, a->M, scr, L.scratch);
     LinArgs alone = {};
     alone.X = a->sa_emb;

@@ -94,6 +94,18 @@ inline bool apart_from_integers(const moa_step_args_t *a, const SaMem &m)
     return !any_meet(m.writes, reads) && !any_meet(m.writes, writes) && !any_meet(m.reads, writes) && !any_meet(m.writes, mask) && !any_meet(m.reads, mask);
 }
 
+// whether the layer's projections can go into a launch with the integer work and those of the first `layers` verification layers
+inline bool sa_apart(const moa_step_args_t *a, int layers)
+{
+    const SaMem m(a);
+    if (!m.aligned || !apart_from_integers(a, m)) return false;
+    for (int l = 0; l < layers; ++l) {
+        const LayerMem v(a, l);
+        if (!v.aligned || any_meet(v.writes, m.reads) || any_meet(v.writes, m.writes) || any_meet(v.reads, m.writes)) return false;
+    }
+    return true;
+}
+
 // what the rest of a step -- the LSA, the memory, the cross-attention, the integer work -- reads and writes
 inline bool apart_from_rest(const moa_step_args_t *a, const LayerMem &m)
 {

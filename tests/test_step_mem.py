@@ -10,7 +10,10 @@ CSRC = Path(__file__).resolve().parent.parent / "paper_2410_03804_amd" / "csrc"
 LAYER = ("x", "wq", "wk", "wv", "wo", "kcache", "vcache", "out", "ktree", "vtree")
 REST_READS = ("parent", "tok", "tgt", "tok_off", "prefix_len", "lsa_hs", "lsa_wq", "lsa_wk", "lsa_wv", "lsa_wo", "lsa_w_packed", "ca_wk", "ca_wv",
               "ca_wk_lsa_wo", "ca_wv_lsa_wo", "ca_xq", "ca_wq", "ca_wo")
+SA = ("emb", "wq", "wk", "wv", "wo", "kcache", "vcache", "out", "k_draft", "v_draft")
+INT_READS, INT_WRITES = ("parent", "tok", "tgt", "tok_off"), ("depth", "path", "n_path", "bonus", "ca_len", "dev_status")
 REST_WRITES = ("mask", "depth", "path", "n_path", "bonus", "lsa_out", "ca_len", "ca_k", "ca_v", "ca_out", "dev_status")
+SP, SHQ, SHKV = 70, 6, 1                                                 # the Self-Attention layer's cache capacity and heads
 S = dict(L=4, d=256, H=4, Hkv=2, dh=64, din=128, Hl=2, Hkvl=2)          # bf16
 B, M, P, CP, T = 2, 19, 50, 60, 7
 
@@ -27,6 +30,12 @@ def sizes():
     return n
 
 
+def sa_sizes():
+    es, e, ekv, d, R = 2, SHQ * S["dh"], SHKV * S["dh"], S["d"], B * M
+    return dict(emb=R * d * es, wq=e * d * es, wk=ekv * d * es, wv=ekv * d * es, wo=e * d * es, kcache=B * SP * ekv * es, vcache=B * SP * ekv * es,
+                out=R * d * es, k_draft=R * ekv * es, v_draft=R * ekv * es)
+
+
 @pytest.fixture(scope="module")
 def run(tmp_path_factory):
     d = tmp_path_factory.mktemp("step_mem")
@@ -40,6 +49,14 @@ def run(tmp_path_factory):
     src += "".join(f"    a.{name} = (decltype(a.{name}))rest[{i}];\n" for i, name in enumerate(rest))
     src += "".join(f"    a.{arrays[name]} = (decltype(a.{arrays[name]}))layers[{i}];\n" for i, name in enumerate(LAYER))
     src += "    return moa::verify_run(&a, l0, most, with_rest);\n}\n" \
+           "extern \"C\" int sa(char **rest, char ***layers, int n, char **own)\n{\n" \
+           f'    moa_shape_t s = {{{S["L"]}, {S["d"]}, {S["H"]}, {S["Hkv"]}, {S["dh"]}, {S["din"]}, {S["Hl"]}, {S["Hkvl"]}, MOA_BF16}}, o = s;\n' \
+           f"    o.n_q_heads = {SHQ}; o.n_kv_heads = {SHKV};\n" \
+           f"    moa_step_args_t a = {{}};\n    a.shape = &s; a.sa_shape = &o; a.B = {B}; a.M = a.Mq = {M}; a.P_cap = {P}; a.sa_P_cap = {SP}; a.n_verify_layers = n;\n" \
+           + "".join(f"    a.{name} = (decltype(a.{name}))rest[{i}];\n" for i, name in enumerate(rest)) \
+           + "".join(f"    a.{arrays[name]} = (decltype(a.{arrays[name]}))layers[{i}];\n" for i, name in enumerate(LAYER)) \
+           + "".join(f"    a.sa_{name} = (decltype(a.sa_{name}))own[{i}];\n" for i, name in enumerate(SA)) \
+           + "    return moa::sa_apart(&a, n);\n}\n" \
            'extern "C" int carve(int most, size_t qa, size_t core, char *spare, size_t ns, char *idle, size_t ni, size_t *out)\n{\n' \
            "    moa::VerifyMem m[4] = {};\n    const int n = moa::carve_verify(m, most, qa, core, spare, ns, idle, ni);\n" \
            "    for (int i = 1; i < n; ++i, out += 4) out[0] = (size_t)m[i].q, out[1] = (size_t)m[i].h, out[2] = (size_t)m[i].core, out[3] = m[i].core_bytes;\n" \
@@ -63,7 +80,12 @@ def run(tmp_path_factory):
         z = C.c_size_t
         n = so.carve(most, z(qa), z(core), C.c_void_p(spare), z(spare_bytes), C.c_void_p(idle), z(idle_bytes), out)
         return [tuple(out[4 * i:4 * i + 4]) for i in range(n - 1)]
-    call.carve = carve
+    def sa(rest_at, layers_at, own_at):
+        n = len(layers_at)
+        cols = [(C.c_void_p * n)(*[la[k] for la in layers_at]) for k in LAYER]
+        return bool(so.sa((C.c_void_p * len(rest))(*[rest_at[k] for k in rest]), (C.c_void_p * len(LAYER))(*[C.addressof(c) for c in cols]), n,
+                          (C.c_void_p * len(SA))(*[own_at[k] for k in SA])))
+    call.carve, call.sa = carve, sa
     return call
 
 
@@ -159,3 +181,32 @@ def test_buffers_lie_apart_in_what_they_are_carved_from(run, core):
     assert {n for n, _, _ in seen} == {0, 1, 2, 3}
     if core:
         assert {(3, True, False), (3, True, True), (3, False, True)} <= seen
+
+
+@pytest.mark.parametrize("seed", range(3))
+def test_self_attention_joins_only_apart_from_the_integer_work_and_the_layers(run, seed):
+    """One or two of its buffers moved onto or to the edge of a buffer of the step, a layer or its own: the rule and the definition, byte
+    ranges of what is read and written pairwise, agree.  (What lies behind the first launch of a step may meet anything of the layer's.)"""
+    rng, n, own_n = random.Random(seed), sizes(), sa_sizes()
+    meet = lambda a, b: any(p < y and x < q for p, q in a for x, y in b)
+    joined = 0
+    for _ in range(400):
+        rest, layers = layout(rng, rng.randint(1, 3))
+        at, own = 1 << 28, {}
+        for k in SA:
+            own[k], at = at, at + (own_n[k] + 15) // 16 * 16
+        for _ in range(rng.randint(0, 2)):
+            key, (src, other) = rng.choice(SA), rng.choice([(rest, rng.choice(REST_READS + REST_WRITES)), (rng.choice(layers), rng.choice(LAYER))])
+            end = src[other] + (n[other] + 15) // 16 * 16
+            own[key] = rng.choice([src[other], end, src[other] - (own_n[key] + 15) // 16 * 16, max(end - 16, src[other]), own[key] + 8])
+        span = lambda where, size, keys: [(where[k], where[k] + size[k]) for k in keys]
+        reads, writes = span(own, own_n, SA[:7]), span(own, own_n, SA[7:])
+        mask = span(rest, n, ("mask",))
+        want = not any(own[k] % 16 for k in SA) and not meet(writes, span(rest, n, INT_READS + INT_WRITES) + mask) and \
+            not meet(reads, span(rest, n, INT_WRITES) + mask)
+        for la in layers:
+            lr, lw = span(la, n, LAYER[:7]), span(la, n, LAYER[7:])
+            want = want and not meet(lw, reads + writes) and not meet(lr, writes)
+        assert run.sa(rest, layers, own) == want, (rest, layers, own)
+        joined += want
+    assert 100 < joined < 300
