@@ -165,8 +165,10 @@ struct GemmPlan { int tile, splits; };
 // The tile, and into how many slices K is cut, by an estimate of the time: rounds of workgroups over 256 compute units at
 // the measured time per k tile, or the weights at 5.8 TB/s, whichever is longer; slices cost a pass over their sums.  An XCD
 // gets whole feature tiles, so a round is full when its share of them fills its 32 compute units (1600 x 8192 x 9216 in
-// 256 x 256: 252 workgroups, 35 of them on seven XCDs each, 355 us against 232 in 256 x 128).  Against the best tile of each
-// of 693 measured calls (33 shapes, weights from memory) the choice is 1.3 % slower on average.  What it comes to: up to 16
+// 256 x 256: 252 workgroups, 35 of them on seven XCDs each, 355 us against 232 in 256 x 128).  Against the best tile and slices
+// of each of 689 measured calls (33 shapes, 1 .. 4096 rows, weights from memory) the choice is 1.7 % slower on average, 0.7 % above 192
+// rows, 4.9 % at 17 to 32 and 29 % at worst (180 x 10240 x 8192); the times of the 64-row tiles and larger were measured with
+// 32x32x16 instructions, those of the others are kept for their order of sums.  What it comes to: up to 16
 // rows the 16-row tiles, up to 32 the 32-row ones; up to some hundred the 64-row ones; with more, the largest tile that still gives every compute
 // unit one (1024 x 4096: 256 x 160 for 10240 features, 77.6 us against 98 - 108 with the tiles next to it, 256 x 128 for
 // 8192); slices only for a long K with few features (60 x 14336 x 4096: four, 30 us against 52).  A pass of its own behind

@@ -658,7 +658,7 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk(LsaFusedArgs a)
     lsa_pk_tile<DH, NB, TT, false>(a, at.unit, at.tile * TT);
 }
 // The first `wide_tiles` tiles take five tokens (160 rows), those behind them TT (where the line lies: lsa_fused_plan).  160
-// rows bring a weight tile to more of them (62 us a round against 50 for 128), and their parked tile fills the LDS
+// rows bring a weight tile to more of them (63 us a round against 51 for 128), and their parked tile fills the LDS
 // like a dense one's; ten (token, head) units on eight wavefronts cost the second pass.
 template <int DH, int TT>
 __global__ __launch_bounds__(512) void k_lsa_fused_pk_wide(LsaFusedArgs a)
@@ -675,9 +675,10 @@ __global__ __launch_bounds__(512) void k_lsa_fused_pk_wide(LsaFusedArgs a)
 // The same with the rows of TT tokens one behind another in 160 (five blocks of 32), for layer counts that leave much of
 // their last block empty: 80 layers in 96 rows waste a sixth of the matrix work, two tokens in 160 nothing, and a weight
 // tile serves 160 rows.  The accumulators take 160 registers, so one weight tile is in registers instead of two, and the parked tile
-// fills the LDS to the last byte.  240 tokens x 80 layers (d_in 2048): 255 us; a token per workgroup takes 1.44 times as long,
-// projection and attention as kernels of their own 1.28 times.  1.6 us per k tile at 160 rows, with the MFMA pipe busy for 63 % of
-// the SIMDs' time, and 17 us in front and behind, 6 of which were saved by giving a unit's query blocks to two wavefronts.
+// fills the LDS to the last byte.  240 tokens x 80 layers (d_in 2048): 253 - 257 us; a token per workgroup takes 370 - 375,
+// projection and attention as kernels of their own 257 + 55.  That is four rounds of 64 us: 1.7 per k tile at 160 rows, with the MFMA
+// pipe busy for 65 % of the SIMDs' time, and 10 in front and behind (one round, 64 tokens: 39, 66 and 120 us at d_in 1024, 2048, 4096),
+// from which giving a unit's query blocks to two wavefronts had taken 6.
 template <int DH, int NB, int TT>
 __global__ __launch_bounds__(512) void k_lsa_fused_pk_dense(LsaFusedArgs a)
 {

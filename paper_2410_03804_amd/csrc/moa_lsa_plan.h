@@ -55,7 +55,7 @@ inline LsaFusedPlan lsa_fused_plan(bool packed, int64_t T, int L, int d_in, int 
         return plan;
     }
     if (nb == 2) return {big_ok && us(T, 2, 4) < us(T, 1, 2) ? 2 : 1, false, 0};
-    // two tokens in 160 rows take 68 us a round where one in 96 takes 50, as much as 3.4 blocks: as soon as that saves a round
+    // two tokens in 160 rows take 66 us a round where one in 96 takes 48, as much as 3.4 blocks: as soon as that saves a round
     // (6 or 8 units: 78 tokens in two rounds 136 us with the output projection, in three 151)
     const bool dense = packed && big_ok && lsa_dense_layers(L) && us(T, 2, 5) < us(T, 1, 3.4);
     return {dense ? 2 : 1, dense, 0};
