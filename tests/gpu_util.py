@@ -45,18 +45,18 @@ def status_word():
 
 
 def launches_of(call):
-    """The names of the kernels that a call launches, one for each launch, as the library's profiler prints them; the call has finished."""
+    """(site, kernel) of each launch that a call makes, as the library's profiler prints them; the call has finished."""
     moa.profile_enable(True)
     try:
         call()
         torch.cuda.synchronize()
-        return [kernel for _, kernel, n, _ in moa.profile_collect() for _ in range(n)]
+        return [(site, kernel) for site, kernel, n, _ in moa.profile_collect() for _ in range(n)]
     finally:
         moa.profile_enable(False)
 
 
 def kernels_of(call):
-    return set(launches_of(call))
+    return {kernel for _, kernel in launches_of(call)}
 
 
 def mask_u64(mask_t):
