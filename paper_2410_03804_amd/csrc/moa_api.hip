@@ -156,8 +156,9 @@ GroupLayout group_layout(const moa_shape_t *s, int B, int M, int P_cap, int ca_P
     GroupLayout L;
     L.len_bytes = align256((size_t)B * sizeof(int32_t));
     L.qa = align256((size_t)B * M * s->n_q_heads * s->head_dim * esize(s->dtype));
-    const int cap = P_cap > ca_P_cap ? P_cap : ca_P_cap;
-    L.attn_each = align256(attn_workspace_bytes(s->dtype, B, M, s->n_q_heads, s->n_kv_heads, s->head_dim, cap, upto));
+    // (a smaller capacity can need more than a larger one, and a core may be cut by its own)
+    L.attn_each = align256(max2(attn_workspace_bytes(s->dtype, B, M, s->n_q_heads, s->n_kv_heads, s->head_dim, P_cap, upto),
+                                attn_workspace_bytes(s->dtype, B, M, s->n_q_heads, s->n_kv_heads, s->head_dim, ca_P_cap, upto)));
     size_t n = 2 * L.attn_each;                                       // (the grouped projections cut no K)
     n = max2(n, attn_ws_bytes(s, B, M, P_cap, upto));                       // verification layers after the first
     n = max2(n, attn_ws_bytes(s, B, M, ca_P_cap, upto));

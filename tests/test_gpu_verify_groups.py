@@ -193,3 +193,29 @@ def test_self_attention_in_a_step_gives_what_the_call_alone_gives(G, case):
         for i, (a, b) in enumerate(zip(alone + outs["sequential"][3:], out)):
             assert torch.equal(a, b), (name, i)
     assert ("sa.qkv_proj" in sites["grouped"]) == (case != "bf16"), sites
+
+
+def test_the_smaller_capacity_may_need_more_scratch(G):
+    """The cross-attention over the whole of 8192 keys, two verification layers in slices of 8065, which take more scratch than slices of
+    8192 would: no core falls back to the kernel that needs none, and the results are those of one stage after another."""
+    from paper_2410_03804_amd.workload import DeviceStep
+    c = mi.Config(name="VSc", index=39, dtype="bf16", B=4, P_min=7000, P_max=7937, M=128, D=6, max_branch=4, L=4, d=512, H=11, Hkv=1, dh=128, d_lsa_in=256,
+                  rms_norm=True)
+    work = mi.step_workload(c, n_verify_layers=2)
+    assert work["P_cap"] == 8065
+    for k in ("ca_k", "ca_v"):
+        old = work[k]
+        work[k] = np.zeros((c.B, c.Hkv, 8192, c.dh), dtype=old.dtype)
+        work[k][:, :, :old.shape[2]] = old
+    work["ca_P_cap"] = 8192
+    outs = {}
+    for name, schedule in SCHEDULES.items():
+        print(f"[case] capacities 8192 and 8065 {name}", flush=True)
+        step = DeviceStep(work, fold=False)
+        launched = G.launches_of(lambda: step.run(schedule=schedule))
+        kernels = {kernel for site, kernel in launched if "core" in site}
+        assert "k_attn_generic" not in kernels and any(k.startswith("k_attn_fused") for k in kernels) and "k_attn_merge<128>" in kernels, (name, kernels)
+        assert step.dev_status.item() == 0
+        outs[name] = [t.clone() for t in (*step.v_out, step.ca_out)]
+    for out in outs.values():
+        assert all(torch.equal(a, b) for a, b in zip(outs["sequential"], out))
