@@ -7,6 +7,12 @@
 #include <Python.h>
 
 static PyObject *tensor_type, *s_is_cuda, *s_is_contiguous, *s_dtype, *s_numel, *s_data_ptr;
+static PyObject *is_contiguous, *numel, *data_ptr;     /* torch.Tensor's own, for what is no subclass of it */
+
+static PyObject *call(PyObject *t, int plain, PyObject *method, PyObject *name)
+{
+    return plain ? PyObject_CallFunctionObjArgs(method, t, NULL) : PyObject_CallMethodObjArgs(t, name, NULL);
+}
 
 /* 1, 0, or -1 with an exception */
 static int truth(PyObject *o)
@@ -24,13 +30,14 @@ static PyObject *dev(PyObject *self, PyObject *const *args, Py_ssize_t n)
     if (n != 4) return PyErr_Format(PyExc_TypeError, "dev: 4 arguments expected, not %zd", n);
     PyObject *t = args[0], *name = args[3];
     if (t == Py_None) Py_RETURN_NONE;
-    if ((PyObject *)Py_TYPE(t) != tensor_type) {
+    const int plain = (PyObject *)Py_TYPE(t) == tensor_type;
+    if (!plain) {
         const int is = PyObject_IsInstance(t, tensor_type);
         if (is < 0) return NULL;
         if (!is) return PyErr_Format(PyExc_TypeError, "%S: expected a torch tensor", name);
     }
     int ok = truth(PyObject_GetAttr(t, s_is_cuda));
-    if (ok > 0) ok = truth(PyObject_CallMethodObjArgs(t, s_is_contiguous, NULL));
+    if (ok > 0) ok = truth(call(t, plain, is_contiguous, s_is_contiguous));
     if (ok < 0) return NULL;
     if (!ok) return PyErr_Format(PyExc_ValueError, "%S: must be a contiguous CUDA tensor", name);
     PyObject *dtype = PyObject_GetAttr(t, s_dtype);
@@ -44,13 +51,13 @@ static PyObject *dev(PyObject *self, PyObject *const *args, Py_ssize_t n)
         }
     }
     Py_DECREF(dtype);
-    PyObject *have = PyObject_CallMethodObjArgs(t, s_numel, NULL);
+    PyObject *have = call(t, plain, numel, s_numel);
     if (!have) return NULL;
     const int less = PyObject_RichCompareBool(have, args[2], Py_LT);
     if (less > 0) PyErr_Format(PyExc_ValueError, "%S: %S elements, the call touches %S", name, have, args[2]);
     Py_DECREF(have);
     if (less) return NULL;
-    return PyObject_CallMethodObjArgs(t, s_data_ptr, NULL);
+    return call(t, plain, data_ptr, s_data_ptr);
 }
 
 static PyMethodDef methods[] = {
@@ -66,11 +73,16 @@ PyMODINIT_FUNC PyInit__argcheck(void)
     if (!torch) return NULL;
     tensor_type = PyObject_GetAttrString(torch, "Tensor");
     Py_DECREF(torch);
+    if (!tensor_type) return NULL;
+    is_contiguous = PyObject_GetAttrString(tensor_type, "is_contiguous");
+    numel = PyObject_GetAttrString(tensor_type, "numel");
+    data_ptr = PyObject_GetAttrString(tensor_type, "data_ptr");
+    if (!is_contiguous || !numel || !data_ptr) return NULL;
     s_is_cuda = PyUnicode_InternFromString("is_cuda");
     s_is_contiguous = PyUnicode_InternFromString("is_contiguous");
     s_dtype = PyUnicode_InternFromString("dtype");
     s_numel = PyUnicode_InternFromString("numel");
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
-    if (!tensor_type || !s_is_cuda || !s_is_contiguous || !s_dtype || !s_numel || !s_data_ptr) return NULL;
+    if (!s_is_cuda || !s_is_contiguous || !s_dtype || !s_numel || !s_data_ptr) return NULL;
     return PyModule_Create(&module);
 }
